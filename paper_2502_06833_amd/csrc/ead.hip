@@ -85,36 +85,70 @@ struct PlanArgs {
 // Rows of one forward pass of model m: for every sequence that m serves, the positions
 // m has not consumed yet (one in steady decoding, more right after a switch).
 // lm_mode 0: no logits; 1: last row of sequences whose chunk reaches the end; 2: every row.
-__global__ __launch_bounds__(256) void k_plan(PlanArgs a) {
+//
+// One workgroup.  Its first wave takes 64 sequences at a time, a lane each: their state is read at once, and
+// running sums over the lanes give every sequence its first row (cut at the pass's budget) and its place
+// among the logit rows; then one thread per row looks up its sequence (one thread walking 64 sequences took
+// 44 us).
+constexpr int kPlanThreads = 256;
+
+__device__ __forceinline__ int wave_scan(int v) {       // inclusive sum over the lanes
+    const int lane = threadIdx.x & 63;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const int u = __shfl_up(v, o, kWave);
+        if (lane >= o) v += u;
+    }
+    return v;
+}
+
+__global__ __launch_bounds__(kPlanThreads) void k_plan(PlanArgs a) {
     extern __shared__ int sm[];
-    int *s_off = sm, *s_n = sm + a.batch, *s_have = sm + 2 * a.batch;
+    __shared__ int s_rows;
+    int *s_off = sm, *s_have = sm + a.batch;
     const int tid = threadIdx.x;
-    if (tid == 0) {
-        int off = 0, nlm = 0;
-        for (int b = 0; b < a.batch; ++b) {
-            const bool allowed = !a.use_allow || ((a.allow[b >> 6] >> (b & 63)) & 1ull);
-            const bool active = allowed && !a.s.done[b] && (a.ignore_model || a.s.model[b] == a.m) &&
-                                (a.step < 0 || a.s.last_step[b] != a.step) &&
-                                (a.ignore_model || a.s.ngen[b] < a.s.goal[b]);
-            const int target = a.s.len[b] - a.limit_off, have = a.s.kvlen[a.m * a.s.max_batch + b];
-            int n = active ? max(0, target - have) : 0;
-            n = min(n, a.budget - off);
-            s_off[b] = off; s_n[b] = n; s_have[b] = have;
-            if (a.lm_mode == 1 && n > 0 && have + n == target) { a.p.lm_row[nlm] = off + n - 1; a.p.lm_seq[nlm] = b; ++nlm; }
-            off += n;
+    if (tid < 64) {
+        int base = 0, nlm = 0;               // rows and logit rows of the sequences before these
+        for (int b0 = 0; b0 < a.batch; b0 += 64) {
+            const int b = b0 + tid;
+            int want = 0, have = 0;
+            if (b < a.batch) {
+                const bool allowed = !a.use_allow || ((a.allow[b >> 6] >> (b & 63)) & 1ull);
+                // everything the test may read is requested at once
+                const int done = a.s.done[b], model = a.s.model[b], last = a.s.last_step[b], ngen = a.s.ngen[b], goal = a.s.goal[b], len = a.s.len[b];
+                have = a.s.kvlen[a.m * a.s.max_batch + b];
+                const bool active = allowed & !done & (a.ignore_model | (model == a.m)) & ((a.step < 0) | (last != a.step)) &
+                                    (a.ignore_model | (ngen < goal));
+                want = active ? max(0, len - a.limit_off - have) : 0;
+            }
+            const int incl = base + wave_scan(want);
+            const int off = min(incl - want, a.budget), n = min(incl, a.budget) - off;
+            // sequences whose chunk reaches the end, counted by lane
+            const unsigned long long whole = __ballot(a.lm_mode == 1 && n > 0 && n == want);
+            if (b < a.batch) {
+                s_off[b] = off; s_have[b] = have;
+                if (n > 0) a.s.kvlen[a.m * a.s.max_batch + b] = have + n;
+                if ((whole >> tid) & 1ull) {
+                    const int place = nlm + __popcll(whole & ((1ull << tid) - 1ull));
+                    a.p.lm_row[place] = off + n - 1; a.p.lm_seq[place] = b;
+                }
+            }
+            base = __shfl(incl, 63, kWave); nlm += __popcll(whole);
         }
-        a.p.hdr[0] = off;
-        a.p.hdr[1] = a.lm_mode == 2 ? off : nlm;
+        const int rows = min(base, a.budget);
+        if (tid == 0) { s_rows = rows; a.p.hdr[0] = rows; a.p.hdr[1] = a.lm_mode == 2 ? rows : nlm; }
     }
     __syncthreads();
-    for (int b = 0; b < a.batch; ++b) {
-        const int off = s_off[b], n = s_n[b], have = s_have[b];
-        for (int j = tid; j < n; j += 256) {
-            a.p.row_seq[off + j] = b; a.p.row_pos[off + j] = have + j;
-            if (a.lm_mode == 2) { a.p.lm_row[off + j] = off + j; a.p.lm_seq[off + j] = b; }
+    const int rows = s_rows;
+    for (int r = tid; r < rows; r += kPlanThreads) {
+        int lo = 0, hi = a.batch - 1;                    // the last sequence whose first row is at or before r
+        while (lo < hi) {
+            const int mid = (lo + hi + 1) >> 1;
+            if (s_off[mid] <= r) lo = mid; else hi = mid - 1;
         }
+        a.p.row_seq[r] = lo; a.p.row_pos[r] = s_have[lo] + r - s_off[lo];
+        if (a.lm_mode == 2) { a.p.lm_row[r] = r; a.p.lm_seq[r] = lo; }
     }
-    for (int b = tid; b < a.batch; b += 256) a.s.kvlen[a.m * a.s.max_batch + b] = s_have[b] + s_n[b];
 }
 
 template <typename WT>
@@ -900,13 +934,13 @@ void launch_plan(ead_handle *h, int m, int budget, int limit_off, int lm_mode, b
         for (int b = 0; b < h->batch; ++b) if ((*rows)[b] > 0) pa.allow[b >> 6] |= 1ull << (b & 63);
     }
     ProfScope ps(h, PK_PLAN, m, 0.0);
-    hipLaunchKernelGGL(k_plan, dim3(1), dim3(256), 3 * h->batch * sizeof(int), h->stream, pa);
+    hipLaunchKernelGGL(k_plan, dim3(1), dim3(kPlanThreads), 2 * h->batch * sizeof(int), h->stream, pa);
 }
 
 void launch_finalize(ead_handle *h, int m, int n_lm, bool score) {
     FinArgs fa = make_fin(h, m, score);
     ProfScope ps(h, PK_FINALIZE, m, 0.0);
-    hipLaunchKernelGGL(k_lm_finalize, dim3(n_lm), dim3(64), 0, h->stream, fa);
+    hipLaunchKernelGGL(k_lm_finalize, dim3(n_lm), dim3(kFinThreads), 0, h->stream, fa);
 }
 
 void account_pass(ead_handle *h, int m, const std::vector<int> &rows, bool with_lm) {
@@ -1473,7 +1507,7 @@ ead_status ead_create(const ead_model_desc *small_model, const ead_model_desc *l
         h->Tmax = (int)std::min<long>(std::max<long>(MB, 1024), std::max<long>(total, MB));
         h->Tmax = (h->Tmax + 15) & ~15;
         h->items_max = std::max(h->Tmax, 2048);
-        h->lm_grid = 1024;
+        h->lm_grid = kFinThreads * kFinVecs;       // partials per row, all of them requested at once by k_lm_finalize
         h->score_rows = 160;         // rows per teacher-forced pass (two 128-row sweeps at most)
         SeqState &s = h->s;
         s.max_batch = MB; s.max_seq = MS; s.cap = MS;

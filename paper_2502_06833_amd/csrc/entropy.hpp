@@ -32,6 +32,16 @@ __device__ __forceinline__ EntStat merge_partials(const EntPartial *p, int n) {
 // ---------------------------------------------------------------------------------------
 struct GateCfg { int w; float tau; int d_min; };
 
+// The switch rule (Eq. 4 / Algorithm 1) on a window mean; updates *model and *c.
+__device__ __forceinline__ void gate_switch(float Hbar, const GateCfg &cfg, int *model, int *c) {
+    int cc = *c + 1, mm = *model;
+    if (cc >= cfg.d_min) {
+        if (mm == 0 && Hbar > cfg.tau) { mm = 1; cc = 0; }
+        else if (mm == 1 && Hbar <= cfg.tau) { mm = 0; cc = 0; }
+    }
+    *model = mm; *c = cc;
+}
+
 // n = entropies recorded before this one.  Returns the window mean; updates *model and *c.
 __device__ __forceinline__ float gate_update(float *ring, int n, float H, const GateCfg &cfg,
                                              int *model, int *c) {
@@ -40,12 +50,7 @@ __device__ __forceinline__ float gate_update(float *ring, int n, float H, const 
     float s = 0.f;
     for (int q = 0; q < cnt; ++q) s = s + ring[(n + 1 - cnt + q) % cfg.w];
     const float Hbar = s / (float)cnt;
-    int cc = *c + 1, mm = *model;
-    if (cc >= cfg.d_min) {
-        if (mm == 0 && Hbar > cfg.tau) { mm = 1; cc = 0; }
-        else if (mm == 1 && Hbar <= cfg.tau) { mm = 0; cc = 0; }
-    }
-    *model = mm; *c = cc;
+    gate_switch(Hbar, cfg, model, c);
     return Hbar;
 }
 
@@ -88,11 +93,7 @@ __device__ __forceinline__ void gate_row_apply(const GateStepArgs &a, int r, con
             const size_t o = (size_t)s * a.rows + r;
             if (a.model_id_out) a.model_id_out[o] = (uint8_t)model;
             const float hb = s_hb[s];
-            ++c;
-            if (c >= a.cfg.d_min) {
-                if (model == 0 && hb > a.cfg.tau) { model = 1; c = 0; }
-                else if (model == 1 && hb <= a.cfg.tau) { model = 0; c = 0; }
-            }
+            gate_switch(hb, a.cfg, &model, &c);
             if (a.Hbar_out) a.Hbar_out[o] = hb;
             if (a.next_out) a.next_out[o] = (uint8_t)model;
         }

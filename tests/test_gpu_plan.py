@@ -1,0 +1,34 @@
+"""GPU: the row plan and the finalisation kernel where their per-sequence work wraps around (more than 64
+sequences, more prompt positions than a pass takes, windows longer than a workgroup), against the oracle."""
+import numpy as np
+import pytest
+
+import oracle
+import synth_inputs as si
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("batch,w,n,hi", [(64, 5, 14, 40), (65, 5, 14, 40), (130, 3, 14, 24), (1, 300, 290, 8)])
+def test_wide_batches_and_long_windows_follow_the_oracle(batch, w, n, hi):
+    import paper_2502_06833_amd as ead
+    ss, sl = si.TINY_S, si.TINY_L
+    Ws, Wl = si.model_weights_torch(ss, 0, "cuda"), si.model_weights_torch(sl, 0, "cuda")
+    os_ = oracle.Model(ss, {k: v.float().cpu().numpy() for k, v in Ws.items()})
+    ol = oracle.Model(sl, {k: v.float().cpu().numpy() for k, v in Wl.items()})
+    prompts = [si.prompt_np(0, f"plan{b}", 1 + (b * 7) % hi, ss.vocab) for b in range(batch)]
+    probe = oracle.generate(os_, ol, prompts[batch // 2], n, w, 1e30)
+    tau = float(np.percentile(probe["Hbar"], 50))
+    e = ead.EAD(ss, Ws, sl, Wl, window=w, tau=tau, d_min=4, max_batch=batch, max_seq=max(32, hi + n))
+    # every row along the oracle's trajectory: fp32 sums of at most 1024 terms in another order (1e-4 nats as for
+    # the fp32 pair elsewhere)
+    rows = range(batch) if batch == 1 else sorted({0, 1, 62, 63, batch - 2, batch - 1, batch // 3})
+    refs = {b: oracle.generate(os_, ol, prompts[b], n, w, tau, d_min=4) for b in rows}
+    tok = np.stack([refs[b]["tokens"] if b in refs else refs[0]["tokens"] for b in range(batch)])
+    mid = np.stack([refs[b]["model_id"] if b in refs else refs[0]["model_id"] for b in range(batch)])
+    rp = e.replay(prompts, tok, mid)
+    for b in rows:
+        assert np.abs(rp["H"][b] - refs[b]["H"]).max() < 1e-4, b
+        assert np.abs(rp["Hbar"][b] - refs[b]["Hbar"]).max() < 1e-4, b
+        assert (rp["argmax"][b] == refs[b]["tokens"]).all(), b
+    e.close()
