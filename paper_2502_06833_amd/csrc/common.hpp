@@ -243,12 +243,16 @@ __device__ __forceinline__ Philox4 philox4x32_10(uint32_t c0, uint32_t c1, uint3
     return Philox4{c0, c1, c2, c3};
 }
 
+__device__ __forceinline__ float gumbel_of(uint32_t word) {
+    const float u = (float)(2u * (word >> 9) + 1u) * (1.0f / 16777216.0f);
+    return -logf(-logf(u));
+}
+
 __device__ __forceinline__ float gumbel_noise(uint32_t k0, uint32_t k1, int seq, int token_index, int i) {
     const Philox4 r = philox4x32_10((uint32_t)i >> 2, (uint32_t)token_index, (uint32_t)seq, 0u, k0, k1);
     const int lane = i & 3;
     const uint32_t word = lane == 0 ? r.x : (lane == 1 ? r.y : (lane == 2 ? r.z : r.w));
-    const float u = (float)(2u * (word >> 9) + 1u) * (1.0f / 16777216.0f);
-    return -logf(-logf(u));
+    return gumbel_of(word);
 }
 
 }  // namespace ead

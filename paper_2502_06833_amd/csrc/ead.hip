@@ -214,6 +214,7 @@ struct ead_handle {
     ead_params prm;
     hipStream_t stream;
     int Tmax, items_max, lm_grid, score_rows, n_cu = 256;
+    int lm_n_part = 0;                   // LM-head partials per row of the pass enqueued last (forward_pass -> launch_finalize)
     size_t lds_per_block = 65536;        // most LDS one workgroup may ask for on this device
     SeqState s; Plan plan; GateCfg cfg;
     // scratch
@@ -452,45 +453,6 @@ ead_status build_model(ead_handle *h, const ead_model_desc *src, Model *m, int m
 // ======================================================================================
 // one forward pass of one model over the rows of the current plan
 // ======================================================================================
-template <typename WT, int EPI>
-void launch_valu(ead_handle *h, int mi, LinArgs<WT> &a, int T, int grid) {
-    ProfScope ps(h, PK_FMA_QKV + EPI, mi, (double)a.Np * a.K * sizeof(WT));
-    const int KC = a.K / 32;
-    const size_t budget = 60 * 1024;
-    int TC = 4;
-    while (TC > 1 && ((size_t)TC * a.K * 4 + 8 * TC * 16 * 4 > budget || TC / 2 >= T)) TC >>= 1;
-    const bool wide = std::is_same<WT, bf16_t>::value && KC >= 64;
-    const int NW = wide ? 8 : 4;
-    const size_t lds = (size_t)TC * a.K * 4 + (size_t)NW * TC * 16 * 4;
-#define EAD_LV(TC_, NW_) hipLaunchKernelGGL((k_linear_valu<WT, TC_, NW_, EPI>), dim3(grid), dim3(NW_ * 64), lds, h->stream, a)
-    if constexpr (std::is_same<WT, bf16_t>::value) {
-        if (wide) { if (TC == 4) EAD_LV(4, 8); else if (TC == 2) EAD_LV(2, 8); else EAD_LV(1, 8); }
-        else { if (TC == 4) EAD_LV(4, 4); else if (TC == 2) EAD_LV(2, 4); else EAD_LV(1, 4); }
-    } else {
-        if (TC == 4) EAD_LV(4, 4); else if (TC == 2) EAD_LV(2, 4); else EAD_LV(1, 4);
-    }
-#undef EAD_LV
-}
-
-// T: the host's count of token rows.  The shape of the matrix and ceil(T / 16) pick the kernel:
-//  * large matrices, more than 32 rows (QKV and residual projections: more than 16): k_linear_mfma_ls, 64 to 128
-//    rows per sweep, eight (gate/up: seven) row blocks per workgroup; where that gives fewer workgroups than
-//    compute units, K is split over workgroups and k_sk_merge adds the slabs.  k_linear_mfma_wt is the
-//    fallback should the device not grant the LDS k_linear_mfma_ls asks for;
-//  * passes of 32 token blocks or more (prefill): no split of K; every matrix takes one workgroup per
-//    (row-block group, sweep), the large ones in 128 x 256 tiles (k_linear_mfma_gemm) where those fill the chip;
-//  * large matrices at fewer rows, and the LM head: k_linear_mfma with four waves
-//    of four row blocks each (an activation tile is fetched once for four weight tiles) where
-//    there are many row blocks, else with K split over KS workgroups per group of four row blocks
-//    so that the chip still gets about two workgroups per compute unit (the last to arrive adds
-//    the slabs), or eight waves that split K inside a workgroup of two row blocks (QKV);
-//  * small matrices are latency-bound: one row block per four-wave workgroup, as many
-//    workgroups as possible.
-// NT token blocks per sweep follow T; the ring depth D follows the register budget.
-constexpr float kSmallLaneMin = 0.3f;                  // grouped schedule, two lanes: see decode_grouped
-constexpr int kSplitKGroups = 4096;                     // arrival counters
-constexpr size_t kSplitKFloats = (size_t)8 << 20;      // partial sums: KS slabs of (padded Np) x 128 floats at most
-
 // Kernels that ask for more than 64 KB of dynamic LDS have to say so once.
 std::mutex g_lds_attr_mutex;
 bool allow_big_lds(const void *kernel, size_t bytes) {
@@ -502,6 +464,48 @@ bool allow_big_lds(const void *kernel, size_t bytes) {
     return true;
 }
 
+template <typename WT, int EPI>
+void launch_valu(ead_handle *h, int mi, LinArgs<WT> &a, int T, int grid) {
+    ProfScope ps(h, PK_FMA_QKV + EPI, mi, (double)a.Np * a.K * sizeof(WT));
+    const int KC = a.K / 32;
+    const size_t budget = 60 * 1024;
+    int TC = 4;
+    while (TC > 1 && ((size_t)TC * a.K * 4 + 8 * TC * 16 * 4 > budget || TC / 2 >= T)) TC >>= 1;
+    const bool wide = std::is_same<WT, bf16_t>::value && KC >= 64;
+    const int NW = wide ? 8 : 4;
+    size_t lds = (size_t)TC * a.K * 4 + (size_t)NW * TC * 16 * 4;
+    if constexpr (std::is_same<WT, bf16_t>::value) {
+        // two rows of a long K (the down projections): one workgroup per compute unit with both rows in LDS beats two
+        // with a row each, which both stream the matrix (14336 x 4096: 23.7 against 37.7 us, one row 22.2)
+        const size_t two = 2 * ((size_t)a.K * 4 + (size_t)NW * 16 * 4);
+        constexpr size_t most = 130 * 1024;         // two rows of the longest K (15360)
+        if (wide && T == 2 && TC == 1 && two <= most && most <= h->lds_per_block && allow_big_lds((const void *)k_linear_valu<WT, 2, 8, EPI>, most)) { TC = 2; lds = two; }
+    }
+    // the groups of TC rows of a pass go side by side: a matrix is small, or its second reader finds it in L2
+    const dim3 grid2(grid, (T + TC - 1) / TC);
+#define EAD_LV(TC_, NW_) hipLaunchKernelGGL((k_linear_valu<WT, TC_, NW_, EPI>), grid2, dim3(NW_ * 64), lds, h->stream, a)
+    if constexpr (std::is_same<WT, bf16_t>::value) {
+        if (wide) { if (TC == 4) EAD_LV(4, 8); else if (TC == 2) EAD_LV(2, 8); else EAD_LV(1, 8); }
+        else { if (TC == 4) EAD_LV(4, 4); else if (TC == 2) EAD_LV(2, 4); else EAD_LV(1, 4); }
+    } else {
+        if (TC == 4) EAD_LV(4, 4); else if (TC == 2) EAD_LV(2, 4); else EAD_LV(1, 4);
+    }
+#undef EAD_LV
+}
+
+// T: the host's count of token rows.  The shape of the matrix and ceil(T / 16) pick the kernel:
+//  * up to 32 rows: launch_narrow (k_linear_mfma; see there);
+//  * 33 to 128 rows: gate/up, and the QKV and residual projections of large matrices with many or long row blocks, through
+//    k_linear_mfma_ls, 64 to 128 rows per sweep; where that gives fewer workgroups than compute units, K is split over
+//    workgroups and k_sk_merge adds the slabs.  k_linear_mfma_wt is the fallback should the device not grant the LDS
+//    k_linear_mfma_ls asks for.  The others stay with launch_narrow, 64 rows per sweep, the sweeps side by side;
+//  * passes of 32 token blocks or more (prefill): no split of K; every matrix takes one workgroup per
+//    (row-block group, sweep), the large ones in 128 x 256 tiles (k_linear_mfma_gemm) where those fill the chip.
+// The LM head has a function of its own (launch_lm).
+constexpr float kSmallLaneMin = 0.3f;                  // grouped schedule, two lanes: see decode_grouped
+constexpr int kSplitKGroups = 4096;                     // arrival counters
+constexpr size_t kSplitKFloats = (size_t)8 << 20;      // partial sums: KS slabs of (padded Np) x 128 floats at most
+
 template <int EPI, bool SK, int NW, int RG>
 bool launch_ls(ead_handle *h, const LinArgs<bf16_t> &a, int grid) {
     const void *kern = (const void *)k_linear_mfma_ls<EPI, SK, NW, RG>;
@@ -511,84 +515,140 @@ bool launch_ls(ead_handle *h, const LinArgs<bf16_t> &a, int grid) {
     return true;
 }
 
+// Passes of up to 32 rows, and longer ones through matrices that k_linear_mfma_ls does not serve better: k_linear_mfma, a
+// workgroup of few waves per R row blocks.  These passes are bound by the weight stream and, below some 30 MB of
+// weights, by how evenly the workgroups fall on the compute units, so R and the split of K follow the number of row
+// blocks (measured on rotating weights at 16 rows; before: one rule by matrix size):
+//  * gate/up: many row blocks, no split.  More than four per compute unit: two waves and two row blocks a workgroup, so that
+//    the workgroups are many and all resident (14336 x 4096 gate/up: 54.0 -> 40.7 us = 5.8 TB/s; 13824 x 5120: 50.1 -> 49.1;
+//    at 32 rows, with four row blocks: 51.7 -> 46.9).  Fewer: four waves and two row blocks (8192 x 2048: 17.9 -> 13.6 us).
+//  * others: one row block a workgroup while that is at most one workgroup per compute unit (4096 x 4096: 15.1 -> 8.3 us,
+//    2048 x 2048: 7.5 -> 5.2), else two (5120 x 5120: 18.8 -> 13.1; 320 workgroups of one block: 15.5), and K split over
+//    workgroups only where half the chip would idle and a slab keeps more than 32 k tiles (896 x 4864: 8.0 -> 6.6).
+//  * long K (256 k tiles and more) with half a row block per compute unit and more: two or four row blocks and the K split
+//    that brings one workgroup per compute unit (4096 x 14336: 27.9 -> 21.5 us, 5120 x 13824: 29.5 -> 26.1).
+// Two waves a workgroup where it has enough tiles for both (6144 x 4096 with two row blocks: 12.1 -> 11.5 us).
+struct NarrowPlan { int R, KS; };
+NarrowPlan narrow_plan(int NB, int KC, int n_cu, bool may_split) {
+    if (may_split && KC >= 256 && 2 * NB >= n_cu) {
+        const int R = NB > n_cu ? 4 : 2, KS = std::min(kSplitKMax, n_cu / ((NB + R - 1) / R));
+        if (KS > 1) return {R, KS};
+    }
+    const int R = NB <= n_cu ? 1 : 2, NG = (NB + R - 1) / R;
+    int KS = 1;
+    while (may_split && KS < kSplitKMax && (KS + 1) * NG <= n_cu && KC / (KS + 1) > 32) ++KS;
+    return {R, KS};
+}
+
 template <int EPI>
-void launch_mfma(ead_handle *h, int mi, LinArgs<bf16_t> &a, int T, int grid_cap = 0) {
+void launch_narrow(ead_handle *h, LinArgs<bf16_t> &a, int T) {
+    const int NB = a.Np / 16, KC = a.K / 32, TB = (T + 15) / 16;
+    const int NT = TB <= 1 ? 1 : (TB == 2 ? 2 : 4), sweeps = (TB + NT - 1) / NT;
+    int R, KS = 1;
+#define EAD_LM(NW_, R_, NT_, D_, SK_) hipLaunchKernelGGL((k_linear_mfma<NW_, R_, NT_, D_, EPI, SK_>), dim3((NB + R - 1) / R * KS, sweeps), dim3(NW_ * 64), 0, h->stream, a)
+    if constexpr (EPI == EPI_SWIGLU) {
+        const bool many = NB > 4 * h->n_cu;
+        R = many && NT == 2 ? 4 : 2;
+        if (NT == 1) { if (many) EAD_LM(2, 2, 1, 8, false); else EAD_LM(4, 2, 1, 4, false); }
+        else if (NT == 2) { if (many) EAD_LM(2, 4, 2, 4, false); else EAD_LM(4, 2, 2, 4, false); }
+        else EAD_LM(4, 2, 4, 4, false);
+    } else {
+        // (the rotary / cache-append epilogue is too heavy to be left to one workgroup per group)
+        NarrowPlan np = narrow_plan(NB, KC, h->n_cu, EPI == EPI_RES);
+        const auto fits = [&]() { const int NG = (NB + np.R - 1) / np.R; return (size_t)sweeps * np.KS * NG * np.R * NT * 256 <= kSplitKFloats && (long)sweeps * NG <= kSplitKGroups; };
+        while (np.KS > 1 && !fits()) --np.KS;
+        if (np.KS == 1 && np.R == 4) np.R = 2;
+        R = np.R; KS = np.KS;
+        a.KS = KS; a.sk_part = h->sk_part; a.sk_tickets = h->sk_tickets;
+        if constexpr (EPI == EPI_RES) {
+            if (KS > 1) {
+                switch (R * 10 + NT) {
+                    case 11: EAD_LM(4, 1, 1, 4, true); break; case 12: EAD_LM(4, 1, 2, 4, true); break; case 14: EAD_LM(4, 1, 4, 4, true); break;
+                    case 21: EAD_LM(4, 2, 1, 4, true); break; case 22: EAD_LM(4, 2, 2, 4, true); break; case 24: EAD_LM(4, 2, 4, 4, true); break;
+                    case 41: EAD_LM(2, 4, 1, 6, true); break; case 42: EAD_LM(2, 4, 2, 4, true); break; default: EAD_LM(2, 4, 4, 3, true); break;
+                }
+                return;
+            }
+        }
+        switch (R * 10 + NT) {
+            case 11: EAD_LM(4, 1, 1, 4, false); break; case 12: EAD_LM(4, 1, 2, 4, false); break; case 14: EAD_LM(4, 1, 4, 4, false); break;
+            case 21: EAD_LM(2, 2, 1, 8, false); break; case 22: EAD_LM(4, 2, 2, 4, false); break; default: EAD_LM(4, 2, 4, 4, false); break;
+        }
+    }
+#undef EAD_LM
+}
+
+// The LM head: writes one partial per (row, workgroup) and returns their number per row.  Up to 16 rows through
+// k_linear_mfma, two waves and two row blocks per workgroup (128256 x 4096: 212 -> 162 us = 6.5 TB/s, 151936 x 5120:
+// 255 -> 238), at 17 to 32 rows with four row blocks while K is long (203 -> 175); otherwise, and where a row block
+// is so short that filling and draining the pipeline per block counts (K < 1280: 50.9 against 57.3 us at 151936 x 896),
+// through k_lm_ls, 128 rows per sweep (64 rows: 350 -> 257 us at 151936 x 5120, 122 -> 52 at 151936 x 896; 128 rows:
+// 699 -> 300).
+int launch_lm(ead_handle *h, int mi, LinArgs<bf16_t> &a, int T) {
+    ProfScope ps(h, PK_MFMA_LOGITS, mi, (double)a.Np * a.K * 2.0);
+    const int NB = a.Np / 16, KC = a.K / 32, TB = (T + 15) / 16;
+    if (!((TB == 1 && KC >= 40) || (TB == 2 && KC > 64)) && kLmLdsBytes <= h->lds_per_block) {
+        const int grid = std::min(NB, h->n_cu);
+        bool ok = true;
+        for (a.tb_base = 0; ok && a.tb_base < TB; a.tb_base += 8) {
+#define EAD_LL(NW_) case NW_: ok = allow_big_lds((const void *)k_lm_ls<NW_>, kLmLdsBytes); \
+                              if (ok) hipLaunchKernelGGL((k_lm_ls<NW_>), dim3(grid), dim3((NW_ + kLsProducers) * 64), kLmLdsBytes, h->stream, a); break
+            switch (std::min(TB - a.tb_base, 8)) { EAD_LL(1); EAD_LL(2); EAD_LL(3); EAD_LL(4); EAD_LL(5); EAD_LL(6); EAD_LL(7); EAD_LL(8); }
+#undef EAD_LL
+        }
+        if (ok) return grid;
+    }
+    const int R = TB == 1 ? 2 : 4, grid = std::min((NB + R - 1) / R, 2 * h->n_cu);
+    if (TB == 1) hipLaunchKernelGGL((k_linear_mfma<2, 2, 1, 8, EPI_LOGITS, false>), dim3(grid), dim3(128), 0, h->stream, a);
+    else if (TB == 2) hipLaunchKernelGGL((k_linear_mfma<2, 4, 2, 4, EPI_LOGITS, false>), dim3(grid), dim3(128), 0, h->stream, a);
+    else hipLaunchKernelGGL((k_linear_mfma<4, 4, 4, 3, EPI_LOGITS, false>), dim3(grid), dim3(256), 0, h->stream, a);      // no LDS for k_lm_ls
+    return grid;
+}
+
+template <int EPI>
+void launch_mfma(ead_handle *h, int mi, LinArgs<bf16_t> &a, int T) {
     ProfScope ps(h, PK_MFMA_QKV + EPI, mi, (double)a.Np * a.K * 2.0);
     const int NB = a.Np / 16, TB = (T + 15) / 16;
     const bool big = (double)a.Np * a.K * 2.0 >= 24e6;
-    const int NT = TB <= 1 ? 1 : (TB == 2 ? 2 : 4);
-    int cfg = !big ? 1 : (NB >= 4 * 256 ? 4 : 2);       // 1: (4 waves, R=1)  4: (4, R=4)  2: (8 waves, R=2)  5: (4, R=4, split K)
-    // 3: (4 waves, R=2) for matrices below that size with many row blocks, from 33 rows up: with one row block per
-    // workgroup every workgroup fetches all activation tiles for 16 output rows (gate/up of a narrow model:
-    // 139 MB of activation reads beside 17 MB of weights)
-    if constexpr (EPI == EPI_SWIGLU) { if (!big && NB >= 2 * h->n_cu && TB >= 3) cfg = 3; }
-    const int rpw = cfg == 3 ? 2 : cfg;                  // row blocks per workgroup
-    int grid = (NB + rpw - 1) / rpw;
-    if constexpr (EPI != EPI_LOGITS) {
-        // more than 32 rows: 64 to 128 rows per sweep, weight tiles shared through LDS.  Matrices with few
-        // row blocks are split along K over workgroups; a second kernel adds the slabs in order and
-        // runs the epilogue.  Passes of two or three sweeps (teacher-forced scoring) take one launch pair per
-        // sweep, or one workgroup per (group, sweep) where K is not split; longer ones (prefill) see below.
-        // (17-32 rows: measured better for the split-K matrices, 32 against 34 us, not for gate/up, 72 against 69)
-        if ((big && (TB > 2 || (TB == 2 && EPI != EPI_SWIGLU))) || TB >= 4 * kWideTok) {
-            // token blocks per sweep: four up to 64 rows; the pass's own five to eight for 65-128 rows, one
-            // wave per block; eight for the sweeps of longer passes
-            const bool multi = TB > kWideTok;
-            const int NG = (NB + 7) / 8, nt = TB <= 4 ? 4 : (multi ? kWideTok : TB);
-            // passes of four sweeps or more: one workgroup per (group, sweep) for every matrix.  Cost of a
-            // launch in cycles per k tile: rounds of workgroups over the compute units times the time of a k
-            // step (measured: about 260 + 64 rg cycles with rg row blocks x 128 rows, about 1150 for the
-            // 128 x 256 tiles, which move twice the rows per step but are bound by what a compute unit
-            // can fetch); the 128 x 256 tiles win where their groups still fill the chip
-            const bool longpass = TB >= 4 * kWideTok;
-            int rg_long = 8;
-            if (longpass) {
-                const int sw = (TB + kWideTok - 1) / kWideTok, n_cu = h->n_cu;
-                auto cost_of = [&](int r) { return (((long)((NB + r - 1) / r) * sw + n_cu - 1) / n_cu) * (260 + 64 * r); };
-                long cost = -1;
-                if (EPI != EPI_QKV && cfg == 4) { rg_long = (NB + 6) / 7 <= n_cu ? 7 : 8; cost = cost_of(rg_long); }
-                else for (int r = 8; r >= 5; --r) if (cost < 0 || cost_of(r) < cost) { cost = cost_of(r); rg_long = r; }
-                const int sg = (TB + kGemmTok - 1) / kGemmTok;
-                const long cost_gemm = (((long)NG * sg + n_cu - 1) / n_cu) * 1150;
-                const void *kern = (const void *)k_linear_mfma_gemm<EPI>;
-                if (big && cost_gemm < cost && kGemmLdsBytes <= h->lds_per_block && allow_big_lds(kern, kGemmLdsBytes)) {
-                    a.sweeps = sg;
-                    hipLaunchKernelGGL((k_linear_mfma_gemm<EPI>), dim3((NG + 7) / 8 * 8 * sg), dim3(640), kGemmLdsBytes, h->stream, a);
-                    return;
-                }
-            }
-            if constexpr (EPI != EPI_QKV) if (cfg == 4) {
-                // seven row blocks per workgroup where that still fits one workgroup per compute unit
-                // (1728 row blocks: 247 workgroups instead of 216 on 256 units)
-                const int rg = (NB + 6) / 7 <= h->n_cu ? 7 : 8, ng = (NB + rg - 1) / rg;
-                a.sweeps = (TB + nt - 1) / nt;
-                const int grid_wt = a.sweeps > 1 ? (ng + 7) / 8 * 8 * a.sweeps : ng;
-#define EAD_WT(TPW_, NW_) do { if (rg == 7) hipLaunchKernelGGL((k_linear_mfma_wt<6, EPI, false, TPW_, 7, NW_>), dim3(grid_wt), dim3(NW_ * 64), 0, h->stream, a); \
-                               else hipLaunchKernelGGL((k_linear_mfma_wt<6, EPI, false, TPW_, 8, NW_>), dim3(grid_wt), dim3(NW_ * 64), 0, h->stream, a); } while (0)
-#define EAD_LS(NW_) (rg == 7 ? launch_ls<EPI, false, NW_, 7>(h, a, grid_wt) : launch_ls<EPI, false, NW_, 8>(h, a, grid_wt))
-                if (multi) { if (!EAD_LS(8)) EAD_WT(2, 4); }
-                else switch (nt) {      // weight tiles straight into LDS by fetching waves; the register-ring kernel where LDS does not allow it
-                    case 4: if (!EAD_LS(4)) EAD_WT(1, 4); break; case 5: if (!EAD_LS(5)) EAD_WT(1, 5); break;
-                    case 6: if (!EAD_LS(6)) EAD_WT(1, 6); break; case 7: if (!EAD_LS(7)) EAD_WT(1, 7); break;
-                    default: if (!EAD_LS(8)) EAD_WT(1, 8); break; }
-#undef EAD_LS
-#undef EAD_WT
+    // more than 32 rows: 64 to 128 rows per sweep, weight tiles shared through LDS.  Matrices with few
+    // row blocks are split along K over workgroups; a second kernel adds the slabs in order and
+    // runs the epilogue.  Passes of two or three sweeps (teacher-forced scoring) take one launch pair per
+    // sweep, or one workgroup per (group, sweep) where K is not split; longer ones (prefill) see below.
+    // Gate/up goes this way from 128 row blocks (9728 x 896 at 64 rows: 10.8 us against 12.3; 16384 x 2048: 19.8 against
+    // 24.8 with seven row blocks a workgroup).  Residual projections of up to 64 rows and under 40 MB, and QKV
+    // projections of up to 64 rows, don't: the second launch costs more than it saves (4096 x 4096: 13.1 against 15.3 us;
+    // 5120 x 5120: 18.7 against 18.0).
+    const bool longpass = TB >= 4 * kWideTok, multi = TB > kWideTok;
+    const bool wide = TB > 2 && (EPI == EPI_SWIGLU ? NB >= 128 : big && (TB > 4 || (EPI == EPI_RES && (long)NB * (a.K / 32) >= 40000)));
+    if (wide || longpass) {
+        // token blocks per sweep: four up to 64 rows; the pass's own five to eight for 65-128 rows, one
+        // wave per block; eight for the sweeps of longer passes
+        const int NG = (NB + 7) / 8, nt = TB <= 4 ? 4 : (multi ? kWideTok : TB);
+        const int sw = (TB + nt - 1) / nt, n_cu = h->n_cu;
+        // row blocks per workgroup without a split of K: the fewest that still make one round of workgroups over the
+        // compute units; of longer passes the cheapest.  Cost of a launch in cycles per k tile: rounds of workgroups over
+        // the compute units times the time of a k step (measured: about 260 + 64 rg cycles with rg row blocks x 128
+        // rows, about 1150 for the 128 x 256 tiles, which move twice the rows per step but are bound by what a
+        // compute unit can fetch); the 128 x 256 tiles win where their groups still fill the chip
+        auto cost_of = [&](int r) { return (((long)((NB + r - 1) / r) * sw + n_cu - 1) / n_cu) * (260 + 64 * r); };
+        int rg = 8;
+        if (!multi) { while (rg > 4 && (NB + rg - 2) / (rg - 1) <= n_cu) --rg; }
+        else for (int r = 7; r >= 5; --r) if (cost_of(r) < cost_of(rg)) rg = r;
+        if (longpass) {
+            const int sg = (TB + kGemmTok - 1) / kGemmTok;
+            const long cost_gemm = (((long)NG * sg + n_cu - 1) / n_cu) * 1150;
+            const void *kern = (const void *)k_linear_mfma_gemm<EPI>;
+            if (big && cost_gemm < cost_of(rg) && kGemmLdsBytes <= h->lds_per_block && allow_big_lds(kern, kGemmLdsBytes)) {
+                a.sweeps = sg;
+                hipLaunchKernelGGL((k_linear_mfma_gemm<EPI>), dim3((NG + 7) / 8 * 8 * sg), dim3(640), kGemmLdsBytes, h->stream, a);
                 return;
             }
-            // long passes of a matrix with few row blocks, or of a small matrix: no split of K -- a launch pair
-            // per sweep would stream the matrix from memory once per sweep
-            if (longpass) {
-                const int sw = (TB + nt - 1) / nt, rg = rg_long, ng = (NB + rg - 1) / rg, grid_sw = (ng + 7) / 8 * 8 * sw;
-                a.sweeps = sw;
-                const bool ok = rg == 5 ? launch_ls<EPI, false, 8, 5>(h, a, grid_sw) : rg == 6 ? launch_ls<EPI, false, 8, 6>(h, a, grid_sw)
-                              : rg == 7 ? launch_ls<EPI, false, 8, 7>(h, a, grid_sw) : launch_ls<EPI, false, 8, 8>(h, a, grid_sw);
-                if (ok) return;
-                a.sweeps = 0;
-            }
-            // one workgroup per compute unit at most: a second round would double the time
-            int KS = big ? std::min(kSplitKMax, std::max(1, h->n_cu / NG)) : 1;
-            while (KS > 1 && (a.K / 32) / KS < 16) --KS;
-            if (KS > 1 && (size_t)KS * NG * 8 * nt * 256 <= kSplitKFloats) {
+        }
+        // one workgroup per compute unit at most: a second round would double the time
+        int KS = EPI != EPI_SWIGLU && big && !longpass ? std::min(kSplitKMax, std::max(1, n_cu / NG)) : 1;
+        while (KS > 1 && (a.K / 32) / KS < 16) --KS;
+        if (KS > 1 && (size_t)KS * NG * 8 * nt * 256 <= kSplitKFloats) {
+            if constexpr (EPI != EPI_SWIGLU) {
                 a.KS = KS; a.sk_part = h->sk_part;
 #define EAD_SK(TPW_, NW_) do { if (TPW_ != 1 || !launch_ls<EPI, true, NW_, 8>(h, a, NG * KS)) \
                                    hipLaunchKernelGGL((k_linear_mfma_wt<6, EPI, true, TPW_, 8, NW_>), dim3(NG * KS), dim3(NW_ * 64), 0, h->stream, a); \
@@ -602,43 +662,29 @@ void launch_mfma(ead_handle *h, int mi, LinArgs<bf16_t> &a, int T, int grid_cap 
                 return;
             }
         }
-    }
-    // (the rotary / cache-append epilogue is too heavy to be left to one workgroup per group)
-    if (cfg == 2 && TB <= 4 && EPI != EPI_LOGITS && EPI != EPI_QKV) {
-        const int NG = (NB + 3) / 4;
-        int KS = std::min(kSplitKMax, std::max(1, (2 * h->n_cu + NG / 2) / NG));
-        while (KS > 1 && (a.K / 32) / KS < 16) --KS;                   // a slab keeps at least 16 k tiles
-        if (KS > 1 && (size_t)KS * NG * 4 * NT * 256 <= kSplitKFloats && NG <= kSplitKGroups) {
-            cfg = 5; a.KS = KS; a.sk_part = h->sk_part; a.sk_tickets = h->sk_tickets; grid = NG * KS;
+        // no split of K (a launch pair per sweep would stream the matrix from memory once per sweep): one workgroup per
+        // (group, sweep)
+        const int ng = (NB + rg - 1) / rg;
+        a.sweeps = sw;
+        const int grid = sw > 1 ? (ng + 7) / 8 * 8 * sw : ng;
+        bool ok = false;
+#define EAD_LS(NW_) do { switch (rg) { case 4: ok = launch_ls<EPI, false, NW_, 4>(h, a, grid); break; case 5: ok = launch_ls<EPI, false, NW_, 5>(h, a, grid); break; \
+                                       case 6: ok = launch_ls<EPI, false, NW_, 6>(h, a, grid); break; case 7: ok = launch_ls<EPI, false, NW_, 7>(h, a, grid); break; \
+                                       default: ok = launch_ls<EPI, false, NW_, 8>(h, a, grid); break; } } while (0)
+        if constexpr (EPI == EPI_SWIGLU) {
+            switch (nt) { case 4: EAD_LS(4); break; case 5: EAD_LS(5); break; case 6: EAD_LS(6); break; case 7: EAD_LS(7); break; default: EAD_LS(8); break; }
+        } else if (nt == 8) EAD_LS(8);
+#undef EAD_LS
+        if (ok) return;
+        // the register-ring kernel where LDS does not allow it (eight row blocks a workgroup)
+        if (EPI == EPI_SWIGLU || nt == 8) {
+            a.sweeps = (TB + 7) / 8;
+            hipLaunchKernelGGL((k_linear_mfma_wt<6, EPI, false, 2, 8, 4>), dim3(a.sweeps > 1 ? (NG + 7) / 8 * 8 * a.sweeps : NG), dim3(256), 0, h->stream, a);
+            return;
         }
+        a.sweeps = 0;
     }
-    // small matrices with few row blocks and a long K (the down projection of a narrow model: 56 row blocks,
-    // 152 k tiles) leave most of the chip idle with one workgroup per row block: K is split over workgroups here
-    // too, the last to arrive adds the slabs
-    if constexpr (EPI == EPI_RES) {
-        if (cfg == 1 && TB <= 4 && NB <= h->n_cu) {
-            int KS = std::min(kSplitKMax, std::max(1, 2 * h->n_cu / NB));
-            while (KS > 1 && (a.K / 32) / KS < 16) --KS;
-            if (KS > 1 && (size_t)KS * NB * NT * 256 <= kSplitKFloats && NB <= kSplitKGroups) {
-                cfg = 6; a.KS = KS; a.sk_part = h->sk_part; a.sk_tickets = h->sk_tickets; grid = NB * KS;
-            }
-        }
-    }
-    if (grid_cap > 0) grid = grid_cap;      // LM head: the number of partials per row is fixed
-#define EAD_LM(NW_, R_, NT_, D_, SK_) hipLaunchKernelGGL((k_linear_mfma<NW_, R_, NT_, D_, EPI, SK_>), dim3(grid), dim3(NW_ * 64), 0, h->stream, a)
-    switch (cfg * 10 + NT) {
-        case 11: EAD_LM(4, 1, 1, 8, false); break; case 12: EAD_LM(4, 1, 2, 6, false); break; case 14: EAD_LM(4, 1, 4, 4, false); break;
-        case 21: EAD_LM(8, 2, 1, 8, false); break; case 22: EAD_LM(8, 2, 2, 6, false); break; case 24: EAD_LM(8, 2, 4, 3, false); break;
-        case 34: if constexpr (EPI == EPI_SWIGLU) EAD_LM(4, 2, 4, 4, false); break;
-        case 41: EAD_LM(4, 4, 1, 6, false); break; case 42: EAD_LM(4, 4, 2, 4, false); break; case 44: EAD_LM(4, 4, 4, 3, false); break;
-        case 51: if constexpr (EPI != EPI_LOGITS && EPI != EPI_QKV) EAD_LM(4, 4, 1, 6, true); break;
-        case 52: if constexpr (EPI != EPI_LOGITS && EPI != EPI_QKV) EAD_LM(4, 4, 2, 4, true); break;
-        case 54: if constexpr (EPI != EPI_LOGITS && EPI != EPI_QKV) EAD_LM(4, 4, 4, 3, true); break;
-        case 61: if constexpr (EPI == EPI_RES) EAD_LM(4, 1, 1, 8, true); break;
-        case 62: if constexpr (EPI == EPI_RES) EAD_LM(4, 1, 2, 6, true); break;
-        default: if constexpr (EPI == EPI_RES) EAD_LM(4, 1, 4, 4, true); break;
-    }
-#undef EAD_LM
+    launch_narrow<EPI>(h, a, T);
 }
 
 template <typename KT, int HD>
@@ -769,11 +815,12 @@ ead_status forward_pass(ead_handle *h, int mi, int T, int n_lm, int ctx_max, boo
                 PackArgs pa{h->x, d, cnt + 1, h->plan.lm_row, m.g_final, m.eps, h->xp_a, d};
                 { ProfScope ps(h, PK_PACK_ACT, mi, 0.0); hipLaunchKernelGGL(k_pack_act, dim3((n_lm + 15) & ~15), dim3(256), 0, st, pa); }
                 g.xp = h->xp_a;
-                launch_mfma<EPI_LOGITS>(h, mi, g, n_lm, grid);
+                h->lm_n_part = launch_lm(h, mi, g, n_lm);
             }
         } else {
             g.x = h->x; g.ldx = d; g.gain = m.g_final; g.eps = m.eps;
             launch_valu<WT, EPI_LOGITS>(h, mi, g, n_lm, grid);
+            h->lm_n_part = grid;
         }
     }
     HIP_TRY(h, hipGetLastError());
@@ -855,7 +902,7 @@ size_t fused_lds_bytes(const Model &m) {
 FinArgs make_fin(ead_handle *h, int m, bool score) {
     FinArgs fa{};
     fa.s = h->s; fa.p = h->plan; fa.cfg = h->cfg; fa.partials = h->lm_part;
-    fa.n_part = std::min(h->mdl[m].V / 16, h->lm_grid); fa.unit = h->prm.unit;
+    fa.n_part = h->lm_n_part; fa.unit = h->prm.unit;
     fa.score_mode = score ? 1 : 0; fa.sc_H = h->sc_H; fa.sc_arg = h->sc_arg;
     fa.model_id = m; fa.max_new = h->max_new; fa.eos_id = h->prm.eos_id; fa.replay = h->replay; fa.n_new = h->n_new;
     fa.force_model = h->force_model; fa.step = h->step;

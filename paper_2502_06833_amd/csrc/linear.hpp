@@ -49,7 +49,7 @@ struct LinArgs {
     float samp_inv_t; uint32_t samp_k0, samp_k1;
     const int *samp_seq, *samp_ngen;
     // MFMA path with K split over KS workgroups per row-block group
-    int tb_base;            // k_linear_mfma_wt with split K, k_sk_merge: first token block of the sweep this launch takes
+    int tb_base;            // k_linear_mfma_wt with split K, k_sk_merge, k_lm_ls: first token block of the sweep this launch takes
     int sweeps;             // without split K: > 1 = one workgroup per (row-block group, sweep of 128 rows; k_linear_mfma_gemm: 256)
     int KS;
     float *sk_part;         // [KS][groups][R][NT][256] partial sums
@@ -198,7 +198,8 @@ __global__ __launch_bounds__(NW * 64) void k_linear_valu(LinArgs<WT> a) {
     Vec8<WT> cur[U];
     if ((int)blockIdx.x < NB) load_group<WT, U>(cur, a.W + tile_offset(blockIdx.x, kc0, KC) + lane * 8, kc0, kc1);
 
-    for (int t0 = 0; t0 < T; t0 += TC) {
+    const int tstep = TC * (int)gridDim.y;                // blockIdx.y: one of the groups of TC rows of a pass
+    for (int t0 = (int)blockIdx.y * TC; t0 < T; t0 += tstep) {
         // ---- stage (and normalise) TC activation rows ----
         for (int tc = 0; tc < TC; ++tc) {
             const int t = t0 + tc;
@@ -250,7 +251,7 @@ __global__ __launch_bounds__(NW * 64) void k_linear_valu(LinArgs<WT> a) {
                 if (kc + U < kc1) load_group<WT, U>(nxt, wp + (size_t)U * 512, kc + U, kc1);
                 else {
                     int nrb = rb + gridDim.x;
-                    if (nrb >= NB && t0 + TC < T) nrb = blockIdx.x;
+                    if (nrb >= NB && t0 + tstep < T) nrb = blockIdx.x;
                     if (nrb < NB) load_group<WT, U>(nxt, a.W + tile_offset(nrb, kc0, KC) + lane * 8, kc0, kc1);
                     else {
 #pragma unroll
@@ -328,15 +329,22 @@ __global__ __launch_bounds__(NW * 64) void k_linear_mfma(LinArgs<bf16_t> a) {
     const int T = *a.count;
     const int TB = (T + 15) >> 4;
     if (TB == 0) return;
-    // SK: workgroup (g, ks) takes slab ks of K for row-block group g, and TB <= NT
+    // SK: workgroup (g, ks) takes slab ks of K for row-block group g, and TB <= NT gridDim.y
     const int KS = SK ? a.KS : 1;
     const int ks = SK ? (int)blockIdx.x % KS : 0;
     const int slab0 = (ks * KC) / KS, slab1 = ((ks + 1) * KC) / KS;
     const int kc0 = slab0 + (wave * (slab1 - slab0)) / NW, kc1 = slab0 + ((wave + 1) * (slab1 - slab0)) / NW;
     const int nsteps = kc1 - kc0;
-    const int c = (tid >> 4) & 15, j = tid & 15;        // this thread's token column and weight row in the epilogue
+    float *part = SK ? a.sk_part + (size_t)blockIdx.y * KS * NG * R * NT * 256 : nullptr;      // this sweep's partial sums and counters
+    int *tickets = SK ? a.sk_tickets + (size_t)blockIdx.y * NG : nullptr;
+    // this thread's i-th element in the epilogue: number e of the sweep's NT blocks of 16 x 16, token block e >> 8, token column
+    // (e >> 4) & 15 (the same for all i from four waves up), weight row j
+    const int j = tid & 15;
+    auto elem = [&](int i) __attribute__((always_inline)) { return tid + i * NW * 64; };
+    auto column = [&](int i) __attribute__((always_inline)) { return (elem(i) >> 4) & 15; };
 
-    for (int tb0 = 0; tb0 < TB; tb0 += NT) {
+    // blockIdx.y: one of the pass's sweeps of NT token blocks
+    for (int tb0 = (int)blockIdx.y * NT; tb0 < TB; tb0 += NT * (int)gridDim.y) {
         EntStat st[NE];
 #pragma unroll
         for (int i = 0; i < NE; ++i) st[i].init();
@@ -395,7 +403,7 @@ __global__ __launch_bounds__(NW * 64) void k_linear_mfma(LinArgs<bf16_t> a) {
                 for (int r = 0; r < R; ++r)
 #pragma unroll
                     for (int i = 0; i < NE; ++i) {
-                        const int b = (tid + i * NW * 64) >> 8, t = (tb0 + b) * 16 + c, rb = g * R + r;
+                        const int b = elem(i) >> 8, t = (tb0 + b) * 16 + column(i), rb = g * R + r;
                         pre[r][i] = epi_prefetch<bf16_t, EPI>(a, rb * 16 + j, t, b < NT && rb < NB && tb0 + b < TB && t < T);
                     }
             }
@@ -410,14 +418,14 @@ __global__ __launch_bounds__(NW * 64) void k_linear_mfma(LinArgs<bf16_t> a) {
                 const int rb = g * R + r;
 #pragma unroll
                 for (int i = 0; i < NE; ++i) {
-                    const int b = (tid + i * NW * 64) >> 8;          // uniform within a wave
+                    const int b = elem(i) >> 8;          // uniform within a wave
                     if (b < NT) {
                         float v = 0.f;
 #pragma unroll
-                        for (int w = 0; w < NW; ++w) v += red[w][b][c + 16 * (j >> 2)][j & 3];
-                        const int t = (tb0 + b) * 16 + c;
+                        for (int w = 0; w < NW; ++w) v += red[w][b][column(i) + 16 * (j >> 2)][j & 3];
+                        const int t = (tb0 + b) * 16 + column(i);
                         if constexpr (SK)
-                            st_coherent(a.sk_part + ((((size_t)ks * NG + g) * R + r) * NT + b) * 256 + (tid & 255), v);
+                            st_coherent(part + ((((size_t)ks * NG + g) * R + r) * NT + b) * 256 + (elem(i) & 255), v);
                         else
                             epilogue<bf16_t, EPI>(a, rb * 16 + j, t, v, rb < NB && tb0 + b < TB && t < T, st[i], pre[r][i]);
                     }
@@ -430,17 +438,17 @@ __global__ __launch_bounds__(NW * 64) void k_linear_mfma(LinArgs<bf16_t> a) {
                 // is left at zero for the next launch.
                 wait_stores();
                 __syncthreads();
-                if (tid == 0) s_ticket = __hip_atomic_fetch_add(a.sk_tickets + g, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                if (tid == 0) s_ticket = __hip_atomic_fetch_add(tickets + g, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 __syncthreads();
                 if (s_ticket == KS - 1) {
-                    if (tid == 0) st_coherent(a.sk_tickets + g, 0);
+                    if (tid == 0) st_coherent(tickets + g, 0);
                     // all slabs of all the group's elements, and what the epilogues read, are
                     // requested before the first sum
 #pragma unroll
                     for (int r = 0; r < R; ++r)
 #pragma unroll
                         for (int i = 0; i < NE; ++i) {
-                            const int b = (tid + i * NW * 64) >> 8, t = (tb0 + b) * 16 + c, rb = g * R + r;
+                            const int b = elem(i) >> 8, t = (tb0 + b) * 16 + column(i), rb = g * R + r;
                             pre[r][i] = epi_prefetch<bf16_t, EPI>(a, rb * 16 + j, t, b < NT && rb < NB && tb0 + b < TB && t < T);
                         }
                     float pv[R][NE][kSplitKMax];
@@ -448,22 +456,22 @@ __global__ __launch_bounds__(NW * 64) void k_linear_mfma(LinArgs<bf16_t> a) {
                     for (int r = 0; r < R; ++r)
 #pragma unroll
                         for (int i = 0; i < NE; ++i) {
-                            const int b = min((tid + i * NW * 64) >> 8, NT - 1);
+                            const int b = min(elem(i) >> 8, NT - 1);
 #pragma unroll
                             for (int q = 0; q < kSplitKMax; ++q)
-                                pv[r][i][q] = ld_coherent(a.sk_part + ((((size_t)min(q, KS - 1) * NG + g) * R + r) * NT + b) * 256 + (tid & 255));
+                                pv[r][i][q] = ld_coherent(part + ((((size_t)min(q, KS - 1) * NG + g) * R + r) * NT + b) * 256 + (elem(i) & 255));
                         }
 #pragma unroll
                     for (int r = 0; r < R; ++r) {
                         const int rb = g * R + r;
 #pragma unroll
                         for (int i = 0; i < NE; ++i) {
-                            const int b = (tid + i * NW * 64) >> 8;
+                            const int b = elem(i) >> 8;
                             if (b < NT) {
                                 float v = 0.f;
 #pragma unroll
                                 for (int q = 0; q < kSplitKMax; ++q) v += q < KS ? pv[r][i][q] : 0.f;
-                                const int t = (tb0 + b) * 16 + c;
+                                const int t = (tb0 + b) * 16 + column(i);
                                 epilogue<bf16_t, EPI>(a, rb * 16 + j, t, v, rb < NB && tb0 + b < TB && t < T, st[i], pre[r][i]);
                             }
                         }
@@ -474,9 +482,9 @@ __global__ __launch_bounds__(NW * 64) void k_linear_mfma(LinArgs<bf16_t> a) {
         if constexpr (EPI == EPI_LOGITS) {
 #pragma unroll
             for (int i = 0; i < NE; ++i) {
-                const int b = (tid + i * NW * 64) >> 8;
+                const int b = elem(i) >> 8;
                 if (b < NT) {
-                    const int t = (tb0 + b) * 16 + c;
+                    const int t = (tb0 + b) * 16 + column(i);
                     logits_flush<bf16_t>(a, t, tb0 + b < TB && t < T, st[i]);
                 }
             }
@@ -662,13 +670,18 @@ __global__ __launch_bounds__(NW * 64) void k_linear_mfma_wt(LinArgs<bf16_t> a) {
 constexpr int kLsDepth = 14;                 // k steps of weight tiles LDS holds (8 KB each)
 constexpr int kLsProducers = 2;              // fetching waves; each has 4 (kLsDepth - 1) loads of 1 KB in flight (the counter holds 63)
 constexpr size_t kLsLdsBytes(int nw) { return (size_t)kLsDepth * 8 * 1024 + (size_t)nw * 64 * 4 * sizeof(float); }
+// The ring of a kernel with rg row blocks per workgroup: up to four take slots of half the size, and twice as many steps fit.
+constexpr int ls_slot_tiles(int rg) { return rg <= 4 ? 4 : 8; }
+constexpr int ls_depth(int rg) { return kLsDepth * 8 / ls_slot_tiles(rg); }
 
 template <int EPI, bool SK, int NW, int RG>
 __global__ __launch_bounds__((NW + kLsProducers) * 64) void k_linear_mfma_ls(LinArgs<bf16_t> a) {
-    static_assert(RG >= 5 && RG <= 8 && NW >= 4 && NW <= 8, "a producer wave fetches four of the step's eight tile slots");
+    static_assert(RG >= 3 && RG <= 8 && NW >= 2 && NW <= 8, "two producer waves share a step's four or eight tile slots");
+    constexpr int SLOT = ls_slot_tiles(RG), PL = SLOT / 2, DEPTH = ls_depth(RG);      // tiles per slot, loads per producer wave and step, k steps in the ring
+    static_assert(PL * (DEPTH - 1) <= 63, "the load counter holds 63");
     constexpr int DA = 6;                              // ring of activation fragments per multiplying wave
     extern __shared__ __attribute__((aligned(16))) unsigned char ls_smem[];
-    bf16_t (*s_w)[8][512] = reinterpret_cast<bf16_t (*)[8][512]>(ls_smem);                       // [kLsDepth][8][512]
+    bf16_t (*s_w)[SLOT][512] = reinterpret_cast<bf16_t (*)[SLOT][512]>(ls_smem);                 // [DEPTH][SLOT][512]
     float (*s_t)[64][4] = reinterpret_cast<float (*)[64][4]>(ls_smem + (size_t)kLsDepth * 8 * 1024);   // [NW][64][4]
     const int K = a.K, KCfull = K >> 5, NB = a.Np >> 4, NG = (NB + RG - 1) / RG;
     const int tid = threadIdx.x, lane = tid & 63;
@@ -690,29 +703,29 @@ __global__ __launch_bounds__((NW + kLsProducers) * 64) void k_linear_mfma_ls(Lin
     auto kstep = [&](int j) __attribute__((always_inline)) { return min(j, KC - 1); };      // past the end: the last step again
 
     if (wave >= NW) {
-        // ---- fetching wave p: tile slots p, p + 2, p + 4, p + 6 of every step (slots past RG repeat the last row block) ----
+        // ---- fetching wave p: tile slots p, p + 2, .. of every step (slots past RG repeat the last row block) ----
         const int p = wave - NW;
-        const bf16_t *wp[4];
+        const bf16_t *wp[PL];
 #pragma unroll
-        for (int q = 0; q < 4; ++q)
+        for (int q = 0; q < PL; ++q)
             wp[q] = a.W + tile_offset(min(g * RG + min(p + 2 * q, RG - 1), NB - 1), kbase, KCfull) + lane * 8;
         auto issue = [&](int j) __attribute__((always_inline)) {      // step j (past the end: the last step again, never read)
             const size_t off = (size_t)kstep(j) * 512;
-            bf16_t (*slot)[512] = s_w[j % kLsDepth];
+            bf16_t (*slot)[512] = s_w[j % DEPTH];
 #pragma unroll
-            for (int q = 0; q < 4; ++q)
+            for (int q = 0; q < PL; ++q)
                 __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(wp[q] + off),
                                                  (__attribute__((address_space(3))) void *)&slot[p + 2 * q][0], 16, 0, 0);
         };
-        for (int j = 0; j < kLsDepth - 1; ++j) issue(j);
-        asm volatile("s_waitcnt vmcnt(%0)" ::"n"(4 * (kLsDepth - 2)) : "memory");      // step 0 has landed
+        for (int j = 0; j < DEPTH - 1; ++j) issue(j);
+        asm volatile("s_waitcnt vmcnt(%0)" ::"n"(PL * (DEPTH - 2)) : "memory");      // step 0 has landed
         __builtin_amdgcn_s_barrier();                 // the bare barrier: this wave has nothing else to wait for
         for (int i = 0; i < KC; ++i) {
             // the multiplying waves read a step's tiles one step ahead of using them: step i + 1 has to
-            // have landed; steps i + 2 .. i + kLsDepth - 2 may still be on their way
-            asm volatile("s_waitcnt vmcnt(%0)" ::"n"(4 * (kLsDepth - 3)) : "memory");
+            // have landed; steps i + 2 .. i + DEPTH - 2 may still be on their way
+            asm volatile("s_waitcnt vmcnt(%0)" ::"n"(PL * (DEPTH - 3)) : "memory");
             __builtin_amdgcn_s_barrier();
-            issue(i + kLsDepth - 1);                  // into the slot of step i - 1, which every wave has read by now
+            issue(i + DEPTH - 1);                  // into the slot of step i - 1, which every wave has read by now
         }
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");    // nothing may land in LDS after the workgroup has gone
         return;
@@ -745,7 +758,7 @@ __global__ __launch_bounds__((NW + kLsProducers) * 64) void k_linear_mfma_ls(Lin
             const int i = i0 + s;
             if (i < KC) {                                  // uniform over the workgroup
                 __syncthreads();
-                bf16_t (*nxt)[512] = s_w[(i + 1) % kLsDepth];      // past the last step: a slot nobody uses
+                bf16_t (*nxt)[512] = s_w[(i + 1) % DEPTH];      // past the last step: a slot nobody uses
 #pragma unroll
                 for (int j = 0; j < RG; ++j) fw[(s + 1) & 1][j] = *reinterpret_cast<const u32x4_t *>(&nxt[j][lane * 8]);
                 __builtin_amdgcn_sched_barrier(0);
@@ -776,6 +789,187 @@ __global__ __launch_bounds__((NW + kLsProducers) * 64) void k_linear_mfma_ls(Lin
                 st_coherent(dst + 128, acc[j][2]); st_coherent(dst + 192, acc[j][3]);
             }
         }
+    }
+}
+
+// ------------------------------------------------------------------------------------
+// The LM head of passes of several rows: the weight stream of k_linear_mfma_ls, one workgroup per compute unit that
+// walks its share of the row blocks (ranges of equal length, eight blocks at a time) without the stream ever
+// stopping -- the fetching waves run 13 k steps ahead across the groups of row blocks, so the ring fills while the
+// multiplying waves fold a group's logits into the statistics.  A multiplying wave owns one token block; a lane
+// holds 4 consecutive vocabulary entries x 8 row blocks of one token, takes their maximum first and moves its sums
+// once per group, and keeps its statistics in registers to the end: no exchange between waves, one partial per
+// (token, workgroup).  A perturbed score's noise comes four to a generator call, since a lane's entries are
+// exactly the four words of one counter.
+// What bounds it: the weight stream from memory (every byte once).
+// ------------------------------------------------------------------------------------
+constexpr int kLmRows = 8;                            // row blocks per group
+constexpr size_t kLmLdsBytes = (size_t)kLsDepth * kLmRows * 1024;
+
+// the 4 x kLmRows logits a lane holds after a group: first vocabulary entry p0 + 16 j of row block j (`have` of them valid)
+__device__ __forceinline__ void lm_fold(const LinArgs<bf16_t> &a, const f32x4_t (&acc)[kLmRows], int p0, int have, int t, bool valid,
+                                        int seq, int tok, EntStat &st) {
+    if (!valid) return;
+    if (a.logits) {
+#pragma unroll
+        for (int j = 0; j < kLmRows; ++j)
+            if (j < have) *reinterpret_cast<float4 *>(a.logits + (size_t)t * a.Np + p0 + 16 * j) = make_float4(acc[j][0], acc[j][1], acc[j][2], acc[j][3]);
+    }
+    if (a.samp_inv_t > 0.f) {
+#pragma unroll
+        for (int j = 0; j < kLmRows; ++j) {
+            if (j >= have) continue;
+            const int p = p0 + 16 * j;                // a multiple of 4: the four entries share one counter
+            const Philox4 r = philox4x32_10((uint32_t)p >> 2, (uint32_t)tok, (uint32_t)seq, 0u, a.samp_k0, a.samp_k1);
+            const uint32_t w[4] = {r.x, r.y, r.z, r.w};
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const float sc = fmaf(acc[j][e], a.samp_inv_t, gumbel_of(w[e]));
+                if (sc > st.gs) { st.gs = sc; st.gidx = p + e; }        // entries come in rising order
+            }
+        }
+    }
+    float mx = -INFINITY;
+#pragma unroll
+    for (int j = 0; j < kLmRows; ++j)
+        if (j < have) mx = fmaxf(mx, fmaxf(fmaxf(acc[j][0], acc[j][1]), fmaxf(acc[j][2], acc[j][3])));
+    if (st.Z == 0.f || mx > st.m) {
+        int idx = 0x7FFFFFFF;
+#pragma unroll
+        for (int j = kLmRows - 1; j >= 0; --j)
+#pragma unroll
+            for (int e = 3; e >= 0; --e) if (j < have && acc[j][e] == mx) idx = p0 + 16 * j + e;
+        if (st.Z != 0.f) {
+            const float d = st.m - mx, x = __expf(d);
+            st.S = x * (st.S + d * st.Z); st.Z *= x;
+        }
+        st.m = mx; st.idx = idx;
+    }
+#pragma unroll
+    for (int j = 0; j < kLmRows; ++j)
+        if (j < have) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const float d = acc[j][e] - st.m, x = __expf(d);
+                st.S += x * d; st.Z += x;
+            }
+        }
+}
+
+template <int NW>
+__global__ __launch_bounds__((NW + kLsProducers) * 64) void k_lm_ls(LinArgs<bf16_t> a) {
+    static_assert(NW >= 1 && NW <= 8 && kLmRows == 8, "a producer wave fetches four of the step's eight tile slots");
+    constexpr int DA = 6;                              // ring of activation fragments per multiplying wave
+    extern __shared__ __attribute__((aligned(16))) unsigned char ls_smem[];
+    bf16_t (*s_w)[kLmRows][512] = reinterpret_cast<bf16_t (*)[kLmRows][512]>(ls_smem);        // [kLsDepth]
+    const int KC = a.K >> 5, NB = a.Np >> 4;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int T = *a.count;
+    const int TB = (T + 15) >> 4;
+    const int rb0 = (int)(((long)blockIdx.x * NB) / gridDim.x), rb1 = (int)(((long)(blockIdx.x + 1) * NB) / gridDim.x);
+    if (a.tb_base >= TB || rb0 >= rb1) return;          // the grid is at most NB, so every range holds a row block
+    const int groups = (rb1 - rb0 + kLmRows - 1) / kLmRows, total = groups * KC;      // k steps of the whole range
+
+    if (wave >= NW) {
+        // ---- fetching wave p: tile slots p, p + 2, p + 4, p + 6 of every step (slots past the range repeat its last row block) ----
+        const int p = wave - NW;
+        const bf16_t *wp[4];
+        int g = 0, k = 0, slot = 0;                    // next step to request
+        auto point = [&]() __attribute__((always_inline)) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) wp[q] = a.W + tile_offset(min(rb0 + g * kLmRows + p + 2 * q, rb1 - 1), 0, KC) + lane * 8;
+        };
+        point();
+        auto issue = [&]() __attribute__((always_inline)) {      // past the range: its last step again, never read
+            const size_t off = (size_t)k * 512;
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(wp[q] + off),
+                                                 (__attribute__((address_space(3))) void *)&s_w[slot][p + 2 * q][0], 16, 0, 0);
+            slot = slot + 1 == kLsDepth ? 0 : slot + 1;
+            if (k + 1 < KC) ++k;
+            else if (g + 1 < groups) { k = 0; ++g; point(); }
+        };
+        for (int j = 0; j < kLsDepth - 1; ++j) issue();
+        asm volatile("s_waitcnt vmcnt(%0)" ::"n"(4 * (kLsDepth - 2)) : "memory");      // step 0 has landed
+        __builtin_amdgcn_s_barrier();
+        for (int i = 0; i < total; ++i) {
+            asm volatile("s_waitcnt vmcnt(%0)" ::"n"(4 * (kLsDepth - 3)) : "memory");  // step i + 1 has landed
+            __builtin_amdgcn_s_barrier();
+            issue();                                   // into the slot of step i - 1, which every wave has read by now
+        }
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");    // nothing may land in LDS after the workgroup has gone
+        return;
+    }
+
+    // ---- multiplying wave: token block a.tb_base + wave, the range's row blocks in groups of eight ----
+    const int tb = a.tb_base + wave, t = tb * 16 + (lane & 15);
+    const bool valid = tb < TB && t < T;
+    int seq = 0, tok = 0;
+    if (a.samp_inv_t > 0.f && valid) { seq = a.samp_seq[t]; tok = a.samp_ngen[seq]; }
+    const bf16_t *bp = a.xp + act_tile_offset(min(tb, TB - 1), 0, TB) + lane * 8;
+    Vec8<bf16_t> ba[DA];
+    auto issue = [&](int s, int k) __attribute__((always_inline)) { ba[s].load(bp + (size_t)min(k, KC - 1) * 512 * TB); };
+#pragma unroll
+    for (int s = 0; s < DA; ++s) {
+        issue(s, s);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    EntStat st; st.init();
+    static_assert(DA % 2 == 0, "the two fragment sets alternate with the unrolled ring slots");
+    u32x4_t fw[2][kLmRows];
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < kLmRows; ++j) fw[0][j] = *reinterpret_cast<const u32x4_t *>(&s_w[0][j][lane * 8]);
+    int slot = 0;                                      // of the step being multiplied
+    for (int g = 0; g < groups; ++g) {
+        f32x4_t acc[kLmRows];
+#pragma unroll
+        for (int j = 0; j < kLmRows; ++j) acc[j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+        for (int i0 = 0; i0 < KC; i0 += DA) {
+#pragma unroll
+            for (int s = 0; s < DA; ++s) {
+                const int i = i0 + s;
+                if (i < KC) {                          // uniform over the workgroup
+                    __syncthreads();
+                    slot = slot + 1 == kLsDepth ? 0 : slot + 1;      // past the last step: a slot nobody uses
+#pragma unroll
+                    for (int j = 0; j < kLmRows; ++j) fw[(s + 1) & 1][j] = *reinterpret_cast<const u32x4_t *>(&s_w[slot][j][lane * 8]);
+                    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                    for (int j = 0; j < kLmRows; ++j)
+                        acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(
+                            __builtin_bit_cast(f16x8_t, fw[s & 1][j]), __builtin_bit_cast(f16x8_t, ba[s].raw), acc[j], 0, 0, 0);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+                issue(s, i + DA);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+        // the next group starts again at activation fragment 0 and at the even fragment set; what it needs is
+        // requested before this group's logits are folded
+#pragma unroll
+        for (int s = 0; s < DA; ++s) issue(s, s);
+        if (KC & 1) {
+#pragma unroll
+            for (int j = 0; j < kLmRows; ++j) fw[0][j] = fw[1][j];
+        }
+        const int first = rb0 + g * kLmRows;
+        lm_fold(a, acc, first * 16 + 4 * (lane >> 4), min(kLmRows, rb1 - first), t, valid, seq, tok, st);
+    }
+    // the four lanes of a token
+#pragma unroll
+    for (int o = 16; o < 64; o <<= 1) {
+        EntStat q;
+        q.m = __shfl_xor(st.m, o, kWave); q.Z = __shfl_xor(st.Z, o, kWave);
+        q.S = __shfl_xor(st.S, o, kWave); q.idx = __shfl_xor(st.idx, o, kWave);
+        q.gs = __shfl_xor(st.gs, o, kWave); q.gidx = __shfl_xor(st.gidx, o, kWave);
+        st.merge(q);
+    }
+    if (valid && lane < 16) {
+        EntPartial e; e.m = st.m; e.Z = st.Z; e.S = st.S; e.idx = st.idx; e.gs = st.gs; e.gidx = st.gidx;
+        a.partials[(size_t)t * gridDim.x + blockIdx.x] = e;
     }
 }
 

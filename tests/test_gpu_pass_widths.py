@@ -1,0 +1,69 @@
+"""GPU: passes of every width class (1-2, 3-16, 17-32, 33-64, 65-128 rows and beyond) through models whose row-block counts
+and depths of K leave remainders in every kernel's split, against the oracle."""
+import numpy as np
+import pytest
+
+import oracle
+import synth_inputs as si
+from gpu_helpers import TOL_H, TOL_LOGIT, check_logits, make_pair
+
+pytestmark = pytest.mark.gpu
+
+# odd numbers of k tiles (11 and 13), row blocks that divide evenly by nothing (vocabulary: 513), fewer row blocks than
+# compute units; 40 k tiles and a long K that is split (258 tiles); half a row block per compute unit at a long K (2048 x 8192)
+ODD = si.ModelShape("odd-k", 2, 352, 11, 11, 416, 8208, 1e-5, 1e4)
+LONG = si.ModelShape("long-k", 1, 1280, 10, 2, 8256, 8208, 1e-5, 1e4)
+HALF = si.ModelShape("half-chip", 1, 2048, 16, 4, 8192, 1040, 1e-5, 1e4)
+WIDE = si.ModelShape("wide-ffn", 1, 256, 4, 2, 15328, 1040, 1e-5, 1e4)          # 1916 row blocks in gate/up
+WIDTHS = (1, 2, 3, 16, 17, 32, 33, 64, 70, 128, 131)
+
+
+@pytest.mark.parametrize("small,large", [(ODD, LONG), (WIDE, HALF)], ids=lambda s: s.name)
+def test_score_at_every_pass_width(small, large):
+    """Logits within 2e-2 of the row maximum, entropy within 1e-2 nats (the tolerances of all bf16 parity tests)."""
+    import paper_2502_06833_amd as ead
+    Ws, Wl, os_, ol = make_pair(small, large, lm_sigma=1.5)
+    e = ead.EAD(small, Ws, large, Wl, window=5, tau=0.0, d_min=4, max_batch=1, max_seq=160)
+    toks = si.prompt_np(0, "widths", max(WIDTHS), small.vocab)
+    for which, om in ((0, os_), (1, ol)):
+        ref = om.forward_dense(toks)                     # causal: a shorter passage is a prefix
+        Hr, ar = oracle.entropy_rows(ref)
+        top = np.sort(ref, axis=1)[:, -2:]
+        clear = top[:, 1] - top[:, 0] > 2 * TOL_LOGIT * np.abs(ref).max(axis=1)
+        for T in WIDTHS:
+            print(f"score model {which} width {T}", flush=True)
+            out = e.score(which, toks[:T])
+            check_logits(out["logits"], ref[:T], TOL_LOGIT)
+            assert np.abs(out["H"] - Hr[:T]).max() < TOL_H
+            assert (out["argmax"] == ar[:T])[clear[:T]].all()
+            assert np.abs(oracle.entropy_rows(out["logits"])[0] - out["H"]).max() < 1e-4      # statistics against the logits they fold
+            assert (out["logits"].argmax(1) == out["argmax"]).all()
+    e.close()
+
+
+@pytest.mark.parametrize("batch", [3, 20, 40])
+def test_sampled_choice_of_wide_passes(batch):
+    """The sampled token of every row of a pass, where the two best perturbed scores are clearly apart."""
+    import paper_2502_06833_amd as ead
+    other = si.ModelShape("other", 1, 512, 4, 4, 512, ODD.vocab, 1e-5, 1e4)
+    Ws, Wl, os_, ol = make_pair(ODD, other, lm_sigma=1.5)
+    temperature, n = 0.8, 3
+    prompts = [si.prompt_np(0, f"w{b}", 4 + b % 5, ODD.vocab) for b in range(batch)]
+    forced = np.stack([si.prompt_np(1, f"w{b}", n, ODD.vocab) for b in range(batch)])
+    mid = np.zeros((batch, n), np.uint8)
+    mid[1::2, 1:] = 1
+    e = ead.EAD(ODD, Ws, other, Wl, window=5, tau=0.0, d_min=2, max_batch=batch, max_seq=32)
+    e.set_sampling(temperature, 77)
+    rp = e.replay(prompts, forced, mid)
+    checked = 0
+    for b in range(batch):
+        seq = np.concatenate([prompts[b], forced[b]])
+        for i in range(n):
+            lg = (ol if mid[b, i] else os_).forward_dense(seq[:len(prompts[b]) + i])[-1]
+            sc = lg / temperature + oracle.gumbel(77, b, i, ODD.vocab)
+            two = np.sort(sc)[-2:]
+            if two[1] - two[0] > 2 * TOL_LOGIT * np.abs(lg).max() / temperature:
+                checked += 1
+                assert rp["choice"][b, i] == int(sc.argmax()), (b, i)
+    assert checked >= batch                              # a third of the positions at least
+    e.close()
