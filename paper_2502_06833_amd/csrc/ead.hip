@@ -213,7 +213,7 @@ struct ead_handle {
     Model mdl[2];
     ead_params prm;
     hipStream_t stream;
-    int Tmax, items_max, lm_grid, score_rows, n_cu = 256;
+    int Tmax, Tprefill, items_max, lm_grid, score_rows, n_cu = 256;      // Tmax, Tprefill: most rows of a decode pass, of a prompt pass
     int lm_n_part = 0;                   // LM-head partials per row of the pass enqueued last (forward_pass -> launch_finalize)
     size_t lds_per_block = 65536;        // most LDS one workgroup may ask for on this device
     SeqState s; Plan plan; GateCfg cfg;
@@ -499,8 +499,9 @@ void launch_valu(ead_handle *h, int mi, LinArgs<WT> &a, int T, int grid) {
 //    k_linear_mfma_ls, 64 to 128 rows per sweep; where that gives fewer workgroups than compute units, K is split over
 //    workgroups and k_sk_merge adds the slabs.  k_linear_mfma_wt is the fallback should the device not grant the LDS
 //    k_linear_mfma_ls asks for.  The others stay with launch_narrow, 64 rows per sweep, the sweeps side by side;
-//  * passes of 32 token blocks or more (prefill): no split of K; every matrix takes one workgroup per
-//    (row-block group, sweep), the large ones in 128 x 256 tiles (k_linear_mfma_gemm) where those fill the chip.
+//  * more than 128 rows (prefill, scoring): no split of K but for two sweeps of a long K; one workgroup per (row-block
+//    group, sweep), in 256 x 256 tiles (k_linear_mfma_tile) or 128 x 256 ones (k_linear_mfma_gemm) where those fill the
+//    chip; small matrices other than gate/up go this way from 32 token blocks.
 // The LM head has a function of its own (launch_lm).
 constexpr float kSmallLaneMin = 0.3f;                  // grouped schedule, two lanes: see decode_grouped
 constexpr int kSplitKGroups = 4096;                     // arrival counters
@@ -509,7 +510,7 @@ constexpr size_t kSplitKFloats = (size_t)8 << 20;      // partial sums: KS slabs
 template <int EPI, bool SK, int NW, int RG>
 bool launch_ls(ead_handle *h, const LinArgs<bf16_t> &a, int grid) {
     const void *kern = (const void *)k_linear_mfma_ls<EPI, SK, NW, RG>;
-    const size_t lds = kLsLdsBytes(NW);
+    const size_t lds = kLsLdsBytes;
     if (lds > h->lds_per_block || !allow_big_lds(kern, lds)) return false;
     hipLaunchKernelGGL((k_linear_mfma_ls<EPI, SK, NW, RG>), dim3(grid), dim3((NW + kLsProducers) * 64), lds, h->stream, a);
     return true;
@@ -527,7 +528,8 @@ bool launch_ls(ead_handle *h, const LinArgs<bf16_t> &a, int grid) {
 //    workgroups only where half the chip would idle and a slab keeps more than 32 k tiles (896 x 4864: 8.0 -> 6.6).
 //  * long K (256 k tiles and more) with half a row block per compute unit and more: two or four row blocks and the K split
 //    that brings one workgroup per compute unit (4096 x 14336: 27.9 -> 21.5 us, 5120 x 13824: 29.5 -> 26.1).
-// Two waves a workgroup where it has enough tiles for both (6144 x 4096 with two row blocks: 12.1 -> 11.5 us).
+// Two waves a workgroup where it has enough tiles for both (6144 x 4096 with two row blocks: 12.1 -> 11.5 us; 3072 wide and 17 to
+// 32 rows: 12.2 with four waves, 14.5 with two).
 struct NarrowPlan { int R, KS; };
 NarrowPlan narrow_plan(int NB, int KC, int n_cu, bool may_split) {
     if (may_split && KC >= 256 && 2 * NB >= n_cu) {
@@ -572,7 +574,9 @@ void launch_narrow(ead_handle *h, LinArgs<bf16_t> &a, int T) {
         }
         switch (R * 10 + NT) {
             case 11: EAD_LM(4, 1, 1, 4, false); break; case 12: EAD_LM(4, 1, 2, 4, false); break; case 14: EAD_LM(4, 1, 4, 4, false); break;
-            case 21: EAD_LM(2, 2, 1, 8, false); break; case 22: EAD_LM(4, 2, 2, 4, false); break; default: EAD_LM(4, 2, 4, 4, false); break;
+            case 21: EAD_LM(2, 2, 1, 8, false); break;
+            case 22: if (KC >= 128) EAD_LM(2, 2, 2, 6, false); else EAD_LM(4, 2, 2, 4, false); break;
+            default: EAD_LM(4, 2, 4, 4, false); break;
         }
     }
 #undef EAD_LM
@@ -612,14 +616,15 @@ void launch_mfma(ead_handle *h, int mi, LinArgs<bf16_t> &a, int T) {
     const bool big = (double)a.Np * a.K * 2.0 >= 24e6;
     // more than 32 rows: 64 to 128 rows per sweep, weight tiles shared through LDS.  Matrices with few
     // row blocks are split along K over workgroups; a second kernel adds the slabs in order and
-    // runs the epilogue.  Passes of two or three sweeps (teacher-forced scoring) take one launch pair per
-    // sweep, or one workgroup per (group, sweep) where K is not split; longer ones (prefill) see below.
-    // Gate/up goes this way from 128 row blocks (9728 x 896 at 64 rows: 10.8 us against 12.3; 16384 x 2048: 19.8 against
-    // 24.8 with seven row blocks a workgroup).  Residual projections of up to 64 rows and under 40 MB, and QKV
-    // projections of up to 64 rows, don't: the second launch costs more than it saves (4096 x 4096: 13.1 against 15.3 us;
-    // 5120 x 5120: 18.7 against 18.0).
+    // runs the epilogue.  Gate/up goes this way from 128 row blocks (9728 x 896 at 64 rows: 8.4 us against 12.3; 16384 x
+    // 2048: 18.0 against 24.8 with seven row blocks a workgroup).  Residual and QKV projections of up to 64 rows and
+    // under 40 MB don't: the second launch costs more than it saves (4096 x 4096: 13.1 against 15.3 us; 5120 x 5120: 18.7
+    // against 18.0, 7168 x 5120 with the QKV epilogue: 28 against 23).  Small matrices do from two sweeps
+    // (QKV) or three (3072 x 2048 at 300 rows: 26 us in sweeps of 64, 18 this way at 512).
     const bool longpass = TB >= 4 * kWideTok, multi = TB > kWideTok;
-    const bool wide = TB > 2 && (EPI == EPI_SWIGLU ? NB >= 128 : big && (TB > 4 || (EPI == EPI_RES && (long)NB * (a.K / 32) >= 40000)));
+    const long tiles = (long)NB * (a.K / 32);
+    const bool wide = TB > 2 && (EPI == EPI_SWIGLU ? NB >= 128 : (big && (TB > 4 || tiles >= 40000)) ||
+                                                                 (NB >= 128 && TB > (EPI == EPI_QKV ? 1 : 2) * kWideTok));
     if (wide || longpass) {
         // token blocks per sweep: four up to 64 rows; the pass's own five to eight for 65-128 rows, one
         // wave per block; eight for the sweeps of longer passes
@@ -628,24 +633,34 @@ void launch_mfma(ead_handle *h, int mi, LinArgs<bf16_t> &a, int T) {
         // row blocks per workgroup without a split of K: the fewest that still make one round of workgroups over the
         // compute units; of longer passes the cheapest.  Cost of a launch in cycles per k tile: rounds of workgroups over
         // the compute units times the time of a k step (measured: about 260 + 64 rg cycles with rg row blocks x 128
-        // rows, about 1150 for the 128 x 256 tiles, which move twice the rows per step but are bound by what a
-        // compute unit can fetch); the 128 x 256 tiles win where their groups still fill the chip
+        // rows, about 1150 for the 128 x 256 tiles and 1750 for the 256 x 256 ones); the tiles win where their groups still fill the chip.
+        // cost_tile: 256 x 256 tiles.  (Gate/up 28672 x 4096 at 300 rows: 113 us in tiles, 126 in sweeps; at 1024: 209 against 260
+        // in 128 x 256 tiles = 1150 Tflop/s; 4096 x 14336 at 3584: 365 against 435.  9728 x 896 at 512: 28 against 24 in sweeps.)
         auto cost_of = [&](int r) { return (((long)((NB + r - 1) / r) * sw + n_cu - 1) / n_cu) * (260 + 64 * r); };
         int rg = 8;
         if (!multi) { while (rg > 4 && (NB + rg - 2) / (rg - 1) <= n_cu) --rg; }
-        else for (int r = 7; r >= 5; --r) if (cost_of(r) < cost_of(rg)) rg = r;
-        if (longpass) {
-            const int sg = (TB + kGemmTok - 1) / kGemmTok;
-            const long cost_gemm = (((long)NG * sg + n_cu - 1) / n_cu) * 1150;
-            const void *kern = (const void *)k_linear_mfma_gemm<EPI>;
-            if (big && cost_gemm < cost_of(rg) && kGemmLdsBytes <= h->lds_per_block && allow_big_lds(kern, kGemmLdsBytes)) {
+        else for (int r = 7; r >= 4; --r) if (cost_of(r) < cost_of(rg)) rg = r;
+        // two sweeps of a long K are still cheaper with K split (14336 x 4096 at 200 rows: 63 against 87 us); from three on the
+        // launch pairs per sweep, which stream the matrix once each, are not (4096 x 4096 at 300 rows: 58 against 32)
+        const bool split = EPI != EPI_SWIGLU && big && (!multi || (sw == 2 && a.K >= 256 * 32));
+        if (multi && !split) {
+            const int sg = (TB + kGemmTok - 1) / kGemmTok, NG16 = (NB + kTileBlocks - 1) / kTileBlocks;
+            const long cost_gemm = (((long)NG * sg + n_cu - 1) / n_cu) * 1150, cost_tile = (((long)NG16 * sg + n_cu - 1) / n_cu) * 1750;
+            const void *gemm = (const void *)k_linear_mfma_gemm<EPI>, *tile = (const void *)k_linear_mfma_tile<EPI>;
+            if (cost_tile < cost_gemm && cost_tile < cost_of(rg) && kTileLdsBytes <= h->lds_per_block && allow_big_lds(tile, kTileLdsBytes)) {
+                const int bands = (sg + kTileBand - 1) / kTileBand;
+                a.sweeps = (sg + bands - 1) / bands;
+                hipLaunchKernelGGL((k_linear_mfma_tile<EPI>), dim3((NG16 + 7) / 8 * a.sweeps * bands * 8), dim3(512), kTileLdsBytes, h->stream, a);
+                return;
+            }
+            if (cost_gemm < cost_of(rg) && kGemmLdsBytes <= h->lds_per_block && allow_big_lds(gemm, kGemmLdsBytes)) {
                 a.sweeps = sg;
                 hipLaunchKernelGGL((k_linear_mfma_gemm<EPI>), dim3((NG + 7) / 8 * 8 * sg), dim3(640), kGemmLdsBytes, h->stream, a);
                 return;
             }
         }
         // one workgroup per compute unit at most: a second round would double the time
-        int KS = EPI != EPI_SWIGLU && big && !longpass ? std::min(kSplitKMax, std::max(1, n_cu / NG)) : 1;
+        int KS = split ? std::min(kSplitKMax, std::max(1, n_cu / NG)) : 1;
         while (KS > 1 && (a.K / 32) / KS < 16) --KS;
         if (KS > 1 && (size_t)KS * NG * 8 * nt * 256 <= kSplitKFloats) {
             if constexpr (EPI != EPI_SWIGLU) {
@@ -738,7 +753,7 @@ ead_status forward_pass(ead_handle *h, int mi, int T, int n_lm, int ctx_max, boo
     int chunk = T <= 2 ? 128 : 512;
     while ((long)T * m.KV * ((ctx_max + chunk - 1) / chunk) > 1024 && chunk < 65536) chunk <<= 1;
     while ((ctx_max + chunk - 1) / chunk > kAttnMaxSplits) chunk <<= 1;
-    while ((long)T * ((ctx_max + chunk - 1) / chunk) > h->items_max) chunk <<= 1;
+    while (ctx_max > chunk && (long)T * ((ctx_max + chunk - 1) / chunk) > h->items_max) chunk <<= 1;      // a single split leaves no partials
     // the matrix-core kernel (many rows) is bound by the latency of its short chains of loads, two
     // workgroups per compute unit at a time: fewer, longer workgroups
     if (is_bf16 && m.layers[0].vtcache && T > 2 && (long)T * m.KV * ((ctx_max + chunk - 1) / chunk) > 64)
@@ -1062,12 +1077,16 @@ ead_status begin_impl(ead_handle *h, const int32_t *toks, const int32_t *lens, i
     TRY(reset_run_state(h, max_new, 0));           // waits for the stream: tok may leave scope
     // both models consume every prompt token but the last
     std::vector<int> rows; std::vector<char> complete;
+    long left = 0;
+    for (int b = 0; b < batch; ++b) left += lens[b] - 1;
+    const int n_pass = (int)std::max<long>(1, (left + h->Tprefill - 1) / h->Tprefill);      // passes of about equal length
+    const int budget = std::min(h->Tprefill, ((int)((left + n_pass - 1) / n_pass) + 255) & ~255);
     for (int m = 0; m < 2; ++m) {
         for (;;) {
             int n_lm, ctx_max;
-            const int T = host_plan(h, m, h->Tmax, 1, 0, true, -1, &n_lm, &ctx_max, &rows, &complete);
+            const int T = host_plan(h, m, budget, 1, 0, true, -1, &n_lm, &ctx_max, &rows, &complete);
             if (T == 0) break;
-            launch_plan(h, m, h->Tmax, 1, 0, true, -1);
+            launch_plan(h, m, budget, 1, 0, true, -1);
             TRY(run_pass(h, m, T, 0, ctx_max, false, rows));
             for (int b = 0; b < batch; ++b) h->hs[b].kvlen[m] += rows[b];
         }
@@ -1553,6 +1572,10 @@ ead_status ead_create(const ead_model_desc *small_model, const ead_model_desc *l
         const long total = (long)MB * MS;
         h->Tmax = (int)std::min<long>(std::max<long>(MB, 1024), std::max<long>(total, MB));
         h->Tmax = (h->Tmax + 15) & ~15;
+        // prompt passes run on lane 0 alone and take up to 4096 rows: the 128 x 256 tiles of a 1024-row pass fill the chip to
+        // 62-84 %, those of 4096 rows to 83-96 %, and a narrow model's launches of 5-10 us carry four times the work
+        h->Tprefill = ((int)std::min<long>(std::max(h->Tmax, 4096), std::max<long>(total, MB)) + 15) & ~15;
+        h->Tprefill = std::max(h->Tprefill, h->Tmax);
         h->items_max = std::max(h->Tmax, 2048);
         h->lm_grid = kFinThreads * kFinVecs;       // partials per row, all of them requested at once by k_lm_finalize
         h->score_rows = 160;         // rows per teacher-forced pass (two 128-row sweeps at most)
@@ -1568,32 +1591,34 @@ ead_status ead_create(const ead_model_desc *small_model, const ead_model_desc *l
         TRY(dmalloc(h, &s.forced_tok, (size_t)MB * MS)); TRY(dmalloc(h, &s.forced_mid, (size_t)MB * MS));
         const Model &a = h->mdl[0], &b = h->mdl[1];
         const size_t dmax = std::max(a.d, b.d), qmax = std::max(a.H * a.hd, b.H * b.hd), fmax_ = std::max(a.F, b.F);
-        const size_t T = h->Tmax;
+        const bool any_f32 = a.dtype == EAD_F32 || b.dtype == EAD_F32;
         // per-lane scratch: allocated twice when two passes may run side by side
-        auto alloc_lane = [&]() -> ead_status {
-            TRY(dmalloc(h, &h->plan.hdr, (size_t)4)); TRY(dmalloc(h, &h->plan.row_seq, (size_t)h->Tmax));
-            TRY(dmalloc(h, &h->plan.row_pos, (size_t)h->Tmax));
-            TRY(dmalloc(h, &h->plan.lm_row, (size_t)h->Tmax)); TRY(dmalloc(h, &h->plan.lm_seq, (size_t)h->Tmax));
-            TRY(dmalloc(h, &h->x, T * dmax)); TRY(dmalloc(h, &h->q, T * qmax)); TRY(dmalloc(h, &h->o, T * qmax));
-            TRY(dmalloc(h, &h->hbuf, T * fmax_));
+        auto alloc_lane = [&](size_t T) -> ead_status {
+            // what only the FMA path writes: passes of one or two rows of a bf16 model, any pass of a float32 one
+            const size_t Tf = any_f32 ? T : std::min<size_t>(T, 16);
+            TRY(dmalloc(h, &h->plan.hdr, (size_t)4)); TRY(dmalloc(h, &h->plan.row_seq, T));
+            TRY(dmalloc(h, &h->plan.row_pos, T));
+            TRY(dmalloc(h, &h->plan.lm_row, T)); TRY(dmalloc(h, &h->plan.lm_seq, T));
+            TRY(dmalloc(h, &h->x, T * dmax)); TRY(dmalloc(h, &h->q, T * qmax)); TRY(dmalloc(h, &h->o, Tf * qmax));
+            TRY(dmalloc(h, &h->hbuf, Tf * fmax_));
             TRY(dmalloc(h, &h->xp_a, T * dmax)); TRY(dmalloc(h, &h->xp_o, T * qmax)); TRY(dmalloc(h, &h->xp_h, T * fmax_));
             HIP_TRY(h, hipMemsetAsync(h->xp_a, 0, T * dmax * 2, h->stream));
             HIP_TRY(h, hipMemsetAsync(h->xp_o, 0, T * qmax * 2, h->stream));
             HIP_TRY(h, hipMemsetAsync(h->xp_h, 0, T * fmax_ * 2, h->stream));
             TRY(dmalloc(h, &h->part_o, (size_t)h->items_max * qmax)); TRY(dmalloc(h, &h->part_ml, (size_t)h->items_max * std::max(a.H, b.H)));
-            TRY(dmalloc(h, &h->tickets, (size_t)h->Tmax * std::max(a.H, b.H)));
+            TRY(dmalloc(h, &h->tickets, T * std::max(a.H, b.H)));
             TRY(dmalloc(h, &h->sk_part, kSplitKFloats)); TRY(dmalloc(h, &h->sk_tickets, (size_t)kSplitKGroups));
             HIP_TRY(h, hipMemsetAsync(h->sk_tickets, 0, kSplitKGroups * sizeof(int), h->stream));
-            HIP_TRY(h, hipMemsetAsync(h->tickets, 0, (size_t)h->Tmax * std::max(a.H, b.H) * sizeof(int), h->stream));
+            HIP_TRY(h, hipMemsetAsync(h->tickets, 0, T * std::max(a.H, b.H) * sizeof(int), h->stream));
             TRY(dmalloc(h, &h->lm_part, std::max((size_t)std::max<size_t>(MB, h->score_rows) * h->lm_grid, (size_t)256 * kFusedRbChunk)));
             return EAD_OK;
         };
         h->two_lanes = (MB > 1 && MB <= 64 * kAllowWords) ? 1 : 0;
-        TRY(alloc_lane());
+        TRY(alloc_lane(h->Tprefill));
         save_lane(h, 0);
         h->lanes[0].stream = h->stream;
         if (h->two_lanes) {
-            TRY(alloc_lane());
+            TRY(alloc_lane(h->Tmax));
             save_lane(h, 1);
             HIP_TRY(h, hipStreamCreateWithFlags(&h->lane1_stream, hipStreamNonBlocking));   // default priority
             h->lanes[1].stream = h->lane1_stream;

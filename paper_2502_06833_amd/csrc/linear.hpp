@@ -50,7 +50,7 @@ struct LinArgs {
     const int *samp_seq, *samp_ngen;
     // MFMA path with K split over KS workgroups per row-block group
     int tb_base;            // k_linear_mfma_wt with split K, k_sk_merge, k_lm_ls: first token block of the sweep this launch takes
-    int sweeps;             // without split K: > 1 = one workgroup per (row-block group, sweep of 128 rows; k_linear_mfma_gemm: 256)
+    int sweeps;             // without split K: > 1 = one workgroup per (row-block group, sweep of 128 rows; k_linear_mfma_gemm: 256); k_linear_mfma_tile: sweeps of a band
     int KS;
     float *sk_part;         // [KS][groups][R][NT][256] partial sums
     int *sk_tickets;        // [groups] arrival counters, zero between launches
@@ -499,36 +499,82 @@ __global__ __launch_bounds__(NW * 64) void k_linear_mfma(LinArgs<bf16_t> a) {
 // wave needs all of them, so the four waves of a workgroup walk K together: each fetches a
 // quarter of the step's activation tiles (ring of DA steps, like its R weight tiles), the
 // quarters meet in LDS (two buffers, one barrier per step), and every wave multiplies its own
-// 16 R weight rows with all 128 token rows.  No sums cross waves; a wave turns its accumulators
-// to the epilogue's (token column, weight row) order through a private 1 KB of LDS.
+// 16 R weight rows with all 128 token rows.  No sums cross waves.
 // Each output element still accumulates its k tiles in ascending order.
 // ------------------------------------------------------------------------------------
-// One 16 x 16 block of results in the matrix cores' layout (lane L: weight rows 4*(L/16)..+3 of
-// token column L%16) -> the epilogue, which wants neighbouring lanes to hold neighbouring weight
-// rows of one token column.  s_tw: 1 KB of LDS owned by the calling wave.
+// ------------------------------------------------------------------------------------
+// The epilogues on the matrix cores' own output layout: lane L of a 16 x 16 block holds weight rows p .. p + 3
+// (p = first row of the block + 4 (L / 16)) of token L % 16, so both halves of a rotary pair or of a gate/up pair are
+// in the lane and a residual or a rotary table entry is one 16-byte load: no exchange between lanes.
+// ------------------------------------------------------------------------------------
+struct QuadTok { int pos, seq; };                      // EPI_QKV: of the lane's token
+
 template <int EPI>
-__device__ __forceinline__ void block_epilogue(const LinArgs<bf16_t> &a, float (*s_tw)[4], int rb, int tb, f32x4_t d,
-                                               bool ok, int T, int lane) {
-    EntStat st; st.init();            // unused by the epilogues this is built for
-    EpiPre pre[4];
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        const int e = k * 64 + lane, c = e >> 4, j = e & 15, t = tb * 16 + c;
-        pre[k] = epi_prefetch<bf16_t, EPI>(a, rb * 16 + j, t, ok && t < T);
+__device__ __forceinline__ QuadTok quad_token(const LinArgs<bf16_t> &a, int t, bool ok) {
+    QuadTok k{0, 0};
+    if constexpr (EPI == EPI_QKV) { if (ok) { k.pos = a.row_pos[t]; k.seq = a.row_seq[t]; } }
+    return k;
+}
+template <int EPI>
+__device__ __forceinline__ float4 quad_prefetch(const LinArgs<bf16_t> &a, int p, int t, bool ok, const QuadTok &k) {
+    float4 r = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (!ok) return r;
+    if constexpr (EPI == EPI_RES) r = *reinterpret_cast<const float4 *>(a.out + (size_t)t * a.ldo + p);
+    else if constexpr (EPI == EPI_QKV) {
+        const int NQ = a.n_heads * a.hd, NK = a.n_kv_heads * a.hd;
+        if (p < NQ + NK) r = *reinterpret_cast<const float4 *>(a.rope + (size_t)k.pos * (a.hd >> 1) + (((p < NQ ? p : p - NQ) & (a.hd - 1)) >> 1));
     }
-    *reinterpret_cast<float4 *>(&s_tw[lane][0]) = make_float4(d[0], d[1], d[2], d[3]);
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        const int e = k * 64 + lane, c = e >> 4, j = e & 15, t = tb * 16 + c;
-        const float v = s_tw[c + 16 * (j >> 2)][j & 3];
-        epilogue<bf16_t, EPI>(a, rb * 16 + j, t, v, ok && t < T, st, pre[k]);
+    return r;
+}
+template <int EPI>
+__device__ __forceinline__ void quad_epilogue(const LinArgs<bf16_t> &a, int p, int t, const f32x4_t &v, bool ok, const QuadTok &k, const float4 &pre) {
+    if (!ok) return;
+    if constexpr (EPI == EPI_RES) {
+        *reinterpret_cast<float4 *>(a.out + (size_t)t * a.ldo + p) = make_float4(pre.x + v[0], pre.y + v[1], pre.z + v[2], pre.w + v[3]);
+    } else if constexpr (EPI == EPI_SWIGLU) {
+        const int i = p >> 1;                          // even: the two outputs are neighbours in a tile
+        const float h0 = v[0] / (1.f + __expf(-v[0])) * v[1], h1 = v[2] / (1.f + __expf(-v[2])) * v[3];
+        const size_t off = act_tile_offset(t >> 4, i >> 5, a.tbs) + (size_t)(((t & 15) + 16 * ((i & 31) >> 3)) * 8 + (i & 7));
+        *reinterpret_cast<uint32_t *>(a.out_tiles + off) = (uint32_t)f32_to_f16_sat(h0) | ((uint32_t)f32_to_f16_sat(h1) << 16);
+    } else {
+        const int hd = a.hd, sh = 31 - __clz(hd), NQ = a.n_heads * hd, NK = a.n_kv_heads * hd;      // hd: 32, 64 or 128
+        if (p < NQ + NK) {                             // rows (2i, 2i + 1) hold dims (i, i + hd/2): here pairs i and i + 1
+            const int pp = p < NQ ? p : p - NQ, head = pp >> sh, i = (pp & (hd - 1)) >> 1;
+            const float lo0 = v[0] * pre.x - v[1] * pre.y, hi0 = v[0] * pre.y + v[1] * pre.x;
+            const float lo1 = v[2] * pre.z - v[3] * pre.w, hi1 = v[2] * pre.w + v[3] * pre.z;
+            if (p < NQ) {
+                float *q = a.out + (size_t)t * a.ldo + head * hd + i;
+                *reinterpret_cast<float2 *>(q) = make_float2(lo0, lo1);
+                *reinterpret_cast<float2 *>(q + (hd >> 1)) = make_float2(hi0, hi1);
+            } else {
+                bf16_t *c = a.kcache + (((size_t)k.seq * a.n_kv_heads + head) * a.max_seq + k.pos) * hd + i;
+                *reinterpret_cast<uint32_t *>(c) = (uint32_t)f32_to_bf16(lo0) | ((uint32_t)f32_to_bf16(lo1) << 16);
+                *reinterpret_cast<uint32_t *>(c + (hd >> 1)) = (uint32_t)f32_to_bf16(hi0) | ((uint32_t)f32_to_bf16(hi1) << 16);
+            }
+        } else {
+            const int pp = p - NQ - NK, head = pp >> sh, dim = pp & (hd - 1);
+            const size_t row = (size_t)k.seq * a.n_kv_heads + head;
+            const uint16_t b0 = f32_to_bf16(v[0]), b1 = f32_to_bf16(v[1]), b2 = f32_to_bf16(v[2]), b3 = f32_to_bf16(v[3]);
+            *reinterpret_cast<uint2 *>(a.vcache + (row * a.max_seq + k.pos) * hd + dim) = make_uint2((uint32_t)b0 | ((uint32_t)b1 << 16), (uint32_t)b2 | ((uint32_t)b3 << 16));
+            if (a.vtcache) {
+                bf16_t *vt = a.vtcache + row * hd * a.max_seq + vt_offset(dim, k.pos, a.max_seq);      // dims are 32 elements apart
+                vt[0].u = b0; vt[32].u = b1; vt[64].u = b2; vt[96].u = b3;
+            }
+        }
     }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// All blocks of a wave that share a token block: first row block rb of `n` (those below NB count), token block tb.
+template <int EPI, int N>
+__device__ __forceinline__ void quad_blocks(const LinArgs<bf16_t> &a, const f32x4_t *const (&v)[N], int rb, int NB, int tb, int T, int lane, bool ok) {
+    const int t = tb * 16 + (lane & 15), p = rb * 16 + 4 * (lane >> 4);
+    ok = ok && t < T;
+    const QuadTok k = quad_token<EPI>(a, t, ok);
+    float4 pre[N];
+#pragma unroll
+    for (int j = 0; j < N; ++j) pre[j] = quad_prefetch<EPI>(a, p + 16 * j, t, ok && rb + j < NB, k);
+#pragma unroll
+    for (int j = 0; j < N; ++j) quad_epilogue<EPI>(a, p + 16 * j, t, *v[j], ok && rb + j < NB, k, pre[j]);
 }
 
 constexpr int kWideTok = 8;          // token blocks (of 16 rows) per sweep
@@ -549,7 +595,6 @@ __global__ __launch_bounds__(NW * 64) void k_linear_mfma_wt(LinArgs<bf16_t> a) {
     constexpr int NT = NW * TPW;                       // token blocks per sweep (TPW per wave); RG row blocks per workgroup
     constexpr int WPT = (RG + NW - 1) / NW;            // weight tiles a wave fetches per step: tiles wave, wave + NW
     __shared__ __attribute__((aligned(16))) bf16_t s_w[2][8][512];
-    __shared__ __attribute__((aligned(16))) float s_t[NW][64][4];
     const int K = a.K, KCfull = K >> 5, NB = a.Np >> 4, NG = (NB + RG - 1) / RG;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -627,12 +672,13 @@ __global__ __launch_bounds__(NW * 64) void k_linear_mfma_wt(LinArgs<bf16_t> a) {
         }
         if constexpr (!SK) {
 #pragma unroll
-            for (int j = 0; j < RG; ++j)
+            for (int q = 0; q < TPW; ++q) {
+                const f32x4_t *v[RG];
 #pragma unroll
-                for (int q = 0; q < TPW; ++q) {
-                    const int rb = g * RG + j, tb = tb0 + wave * TPW + q;
-                    block_epilogue<EPI>(a, s_t[wave], rb, tb, acc[j][q], rb < NB && tb < TB, T, lane);
-                }
+                for (int j = 0; j < RG; ++j) v[j] = &acc[j][q];
+                const int tb = tb0 + wave * TPW + q;
+                quad_blocks<EPI, RG>(a, v, g * RG, NB, tb, T, lane, tb < TB);
+            }
         } else {
             const size_t slab = (size_t)NG * RG * NT * 256;                // floats per slab
 #pragma unroll
@@ -669,7 +715,7 @@ __global__ __launch_bounds__(NW * 64) void k_linear_mfma_wt(LinArgs<bf16_t> a) {
 // ------------------------------------------------------------------------------------
 constexpr int kLsDepth = 14;                 // k steps of weight tiles LDS holds (8 KB each)
 constexpr int kLsProducers = 2;              // fetching waves; each has 4 (kLsDepth - 1) loads of 1 KB in flight (the counter holds 63)
-constexpr size_t kLsLdsBytes(int nw) { return (size_t)kLsDepth * 8 * 1024 + (size_t)nw * 64 * 4 * sizeof(float); }
+constexpr size_t kLsLdsBytes = (size_t)kLsDepth * 8 * 1024;
 // The ring of a kernel with rg row blocks per workgroup: up to four take slots of half the size, and twice as many steps fit.
 constexpr int ls_slot_tiles(int rg) { return rg <= 4 ? 4 : 8; }
 constexpr int ls_depth(int rg) { return kLsDepth * 8 / ls_slot_tiles(rg); }
@@ -682,7 +728,6 @@ __global__ __launch_bounds__((NW + kLsProducers) * 64) void k_linear_mfma_ls(Lin
     constexpr int DA = 6;                              // ring of activation fragments per multiplying wave
     extern __shared__ __attribute__((aligned(16))) unsigned char ls_smem[];
     bf16_t (*s_w)[SLOT][512] = reinterpret_cast<bf16_t (*)[SLOT][512]>(ls_smem);                 // [DEPTH][SLOT][512]
-    float (*s_t)[64][4] = reinterpret_cast<float (*)[64][4]>(ls_smem + (size_t)kLsDepth * 8 * 1024);   // [NW][64][4]
     const int K = a.K, KCfull = K >> 5, NB = a.Np >> 4, NG = (NB + RG - 1) / RG;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -773,11 +818,10 @@ __global__ __launch_bounds__((NW + kLsProducers) * 64) void k_linear_mfma_ls(Lin
         }
     }
     if constexpr (!SK) {
+        const f32x4_t *v[RG];
 #pragma unroll
-        for (int j = 0; j < RG; ++j) {
-            const int rb = g * RG + j, tb = tb0 + wave;
-            block_epilogue<EPI>(a, s_t[wave], rb, tb, acc[j], rb < NB && tb < TB, T, lane);
-        }
+        for (int j = 0; j < RG; ++j) v[j] = &acc[j];
+        quad_blocks<EPI, RG>(a, v, g * RG, NB, tb0 + wave, T, lane, tb0 + wave < TB);
     } else {
         const size_t slab = (size_t)NG * RG * NW * 256;                // floats per slab
 #pragma unroll
@@ -987,7 +1031,7 @@ __global__ __launch_bounds__((NW + kLsProducers) * 64) void k_lm_ls(LinArgs<bf16
 constexpr int kGemmDepth = 6;                        // k steps of tiles LDS holds
 constexpr int kGemmRows = 8, kGemmTok = 16;          // row blocks and token blocks per workgroup
 constexpr int kGemmTiles = kGemmRows + kGemmTok;     // 1 KB tiles per k step; each fetching wave brings half of them
-constexpr size_t kGemmLdsBytes = (size_t)kGemmDepth * kGemmTiles * 1024 + (size_t)8 * 64 * 4 * sizeof(float);
+constexpr size_t kGemmLdsBytes = (size_t)kGemmDepth * kGemmTiles * 1024;
 
 template <int EPI>
 __global__ __launch_bounds__(640) void k_linear_mfma_gemm(LinArgs<bf16_t> a) {
@@ -995,7 +1039,6 @@ __global__ __launch_bounds__(640) void k_linear_mfma_gemm(LinArgs<bf16_t> a) {
     static_assert(PL * (kGemmDepth - 1) <= 63, "the load counter holds 63");
     extern __shared__ __attribute__((aligned(16))) unsigned char ls_smem[];
     bf16_t (*s_w)[kGemmTiles][512] = reinterpret_cast<bf16_t (*)[kGemmTiles][512]>(ls_smem);    // [kGemmDepth]: weight tiles, then activation tiles
-    float (*s_t)[64][4] = reinterpret_cast<float (*)[64][4]>(ls_smem + (size_t)kGemmDepth * kGemmTiles * 1024);
     const int KC = a.K >> 5, NB = a.Np >> 4, NG = (NB + kGemmRows - 1) / kGemmRows;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -1075,25 +1118,137 @@ __global__ __launch_bounds__(640) void k_linear_mfma_gemm(LinArgs<bf16_t> a) {
         }
     }
 #pragma unroll
-    for (int j = 0; j < 4; ++j)
+    for (int b = 0; b < 4; ++b) {
+        const f32x4_t *v[4] = {&acc[0][b], &acc[1][b], &acc[2][b], &acc[3][b]};
+        const int tb = tb0 + 4 * wt + b;
+        quad_blocks<EPI, 4>(a, v, g * kGemmRows + 4 * wr, NB, tb, T, lane, tb < TB);
+    }
+}
+
+// ------------------------------------------------------------------------------------
+// Long passes, 256 x 256 tiles: 16 row blocks x 16 token blocks per workgroup, eight waves of 8 x 4 blocks (128 accumulator
+// registers; 12 KB of LDS reads per 32 products, where the 4 x 4 blocks of k_linear_mfma_gemm read 16 KB and the
+// LDS port bounds them).  No separate fetching waves -- two waves per SIMD may use 256 registers each, three would not --
+// so every wave requests four of the step's 32 tiles (16 of weights, 16 of activations, 32 KB) straight into a ring
+// of five steps.  The requests are written in assembly: they have no output register, and the compiler, which would
+// otherwise let every LDS read wait for all of them, is told by the counter waits here instead.
+//
+// Step i: wait until this wave's tiles of step i + 1 have landed, meet the other waves (theirs have, too, and all have
+// read step i - 1), request step i + 4 into the slot of step i - 1, read the fragments of step i + 1, multiply step i.
+// Every output element adds its k tiles in ascending order, as in the other kernels without a split of K.
+// ------------------------------------------------------------------------------------
+constexpr int kTileDepth = 5, kTileBlocks = 16;        // k steps in LDS; row blocks and token blocks per workgroup
+constexpr size_t kTileLdsBytes = (size_t)kTileDepth * 2 * kTileBlocks * 1024;
+constexpr int kTileBand = 6;                           // most sweeps that run side by side, see launch
+
+constexpr int kWaitLdsReads = 0xC07F;                  // s_waitcnt lgkmcnt(0), the other counters at their maximum
+
+// 16 bytes per lane from base + voff (base uniform over the wave) to LDS at lds + 16 lane.  Nothing else in the
+// kernels that call this uses M0.
+__device__ __forceinline__ void request_tile(const bf16_t *base, uint32_t voff, uint32_t lds) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(voff), "s"(base) : "memory");
+}
+
+template <int EPI>
+__global__ __launch_bounds__(512, 2) void k_linear_mfma_tile(LinArgs<bf16_t> a) {
+    constexpr int NWV = 8, WB = 4, PL = 4;             // waves; token blocks of a wave; its requests per step
+    extern __shared__ __attribute__((aligned(16))) unsigned char ls_smem[];
+    bf16_t (*s_w)[2 * kTileBlocks][512] = reinterpret_cast<bf16_t (*)[2 * kTileBlocks][512]>(ls_smem);       // [kTileDepth]: weight tiles, activation tiles
+    const int KC = a.K >> 5, NB = a.Np >> 4, NG = (NB + kTileBlocks - 1) / kTileBlocks;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int T = *a.count;
+    const int TB = (T + 15) >> 4;
+    // workgroup id -> (group of row blocks, sweep of tokens): XCD id % 8 takes every eighth group; on it the sweeps of a band run
+    // side by side for one group after the other, so that what runs at a time shares weights and activations in L2
+    const int GX = (NG + 7) >> 3, q = (int)blockIdx.x >> 3, per = GX * a.sweeps, band = q / per, in = q % per;
+    const int g = (in / a.sweeps) * 8 + ((int)blockIdx.x & 7), tb0 = (band * a.sweeps + in % a.sweeps) * kTileBlocks;
+    if (g >= NG || tb0 >= TB) return;
+
+    // this wave's four tiles of a step: weight tiles wave, wave + 8, activation tiles wave, wave + 8
+    const bf16_t *src[PL];
 #pragma unroll
-        for (int b = 0; b < 4; ++b) {
-            const int rb = g * kGemmRows + 4 * wr + j, tb = tb0 + 4 * wt + b;
-            block_epilogue<EPI>(a, s_t[wave], rb, tb, acc[j][b], rb < NB && tb < TB, T, lane);
+    for (int j = 0; j < PL / 2; ++j) {
+        src[j] = a.W + tile_offset(min(g * kTileBlocks + wave + NWV * j, NB - 1), 0, KC);
+        src[PL / 2 + j] = a.xp + act_tile_offset(min(tb0 + wave + NWV * j, TB - 1), 0, TB);
+    }
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char *)ls_smem + (uint32_t)wave * 1024, voff = (uint32_t)lane * 16;
+    const size_t xstep = (size_t)TB * 512;
+    int next = 0, nslot = 0;                            // step to request next and its slot; past the end the last step again, never read
+    auto request = [&]() __attribute__((always_inline)) {
+        const uint32_t l = lds0 + (uint32_t)nslot * (2 * kTileBlocks * 1024);
+#pragma unroll
+        for (int j = 0; j < PL; ++j) request_tile(src[j], voff, l + (uint32_t)j * NWV * 1024);
+        nslot = nslot + 1 == kTileDepth ? 0 : nslot + 1;
+        if (++next < KC) {
+#pragma unroll
+            for (int j = 0; j < PL / 2; ++j) { src[j] += 512; src[PL / 2 + j] += xstep; }
         }
+    };
+    const int wr = wave & 1, wt = wave >> 1;            // row blocks 8 wr .. + 7 of the group, token blocks 4 wt .. + 3 of the sweep
+    f32x4_t acc[8][WB];
+#pragma unroll
+    for (int j = 0; j < 8; ++j)
+#pragma unroll
+        for (int b = 0; b < WB; ++b) acc[j][b] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    u32x4_t fw[2][8], fx[2][WB];
+    auto fetch = [&](int set, int slot) __attribute__((always_inline)) {
+#pragma unroll
+        for (int b = 0; b < WB; ++b) fx[set][b] = *reinterpret_cast<const u32x4_t *>(&s_w[slot][kTileBlocks + WB * wt + b][lane * 8]);
+#pragma unroll
+        for (int j = 0; j < 8; ++j) fw[set][j] = *reinterpret_cast<const u32x4_t *>(&s_w[slot][8 * wr + j][lane * 8]);
+    };
+    for (int j = 0; j < kTileDepth - 1; ++j) request();
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(PL * (kTileDepth - 2)) : "memory");      // step 0 has landed
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    fetch(0, 0);
+    int slot = 0;
+    for (int i0 = 0; i0 < KC; i0 += 2) {
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+            if (i0 + s < KC) {                          // uniform over the workgroup
+                asm volatile("s_waitcnt vmcnt(%0)" ::"n"(PL * (kTileDepth - 3)) : "memory");
+                // step i's fragments, requested a step ago, are here: said before the next ones are requested, or the
+                // compiler waits for those as well before the first product
+                __builtin_amdgcn_s_waitcnt(kWaitLdsReads);
+                __builtin_amdgcn_s_barrier();
+                request();
+                slot = slot + 1 == kTileDepth ? 0 : slot + 1;
+                fetch(s ^ 1, slot);                     // past the last step: a slot nobody uses
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int j = 0; j < 8; ++j)
+#pragma unroll
+                    for (int b = 0; b < WB; ++b)
+                        acc[j][b] = __builtin_amdgcn_mfma_f32_16x16x32_f16(
+                            __builtin_bit_cast(f16x8_t, fw[s][j]), __builtin_bit_cast(f16x8_t, fx[s][b]), acc[j][b], 0, 0, 0);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");    // nothing may land in LDS after the workgroup has gone
+#pragma unroll
+    for (int b = 0; b < WB; ++b) {
+        const f32x4_t *v[8] = {&acc[0][b], &acc[1][b], &acc[2][b], &acc[3][b], &acc[4][b], &acc[5][b], &acc[6][b], &acc[7][b]};
+        const int tb = tb0 + WB * wt + b;
+        quad_blocks<EPI, 8>(a, v, g * kTileBlocks + 8 * wr, NB, tb, T, lane, tb < TB);
+    }
 }
 
 // Sum of the K slabs that k_linear_mfma_wt<..., SK = true, TPW> left in memory, in slab order, then
 // the epilogue.  One wave per 16 x 16 block; grid = ceil(row blocks * NT / 4) workgroups, NT = 4 TPW.
 template <int EPI, int NT = kWideTok>
 __global__ __launch_bounds__(256) void k_sk_merge(LinArgs<bf16_t> a, int NGR /* row blocks incl. padding */) {
-    __shared__ __attribute__((aligned(16))) float s_t[4][64][4];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int NB = a.Np >> 4, T = *a.count, TB = (T + 15) >> 4, KS = a.KS;
     const int blk = blockIdx.x * 4 + wave, rb = blk / NT, b = blk % NT;
     if (rb >= NB || a.tb_base + b >= TB) return;
     const size_t slab = (size_t)NGR * NT * 256;
     const float *src = a.sk_part + ((size_t)rb * NT + b) * 256 + lane;
+    const int t = (a.tb_base + b) * 16 + (lane & 15), p = rb * 16 + 4 * (lane >> 4);
+    const QuadTok k = quad_token<EPI>(a, t, t < T);
+    const float4 pre = quad_prefetch<EPI>(a, p, t, t < T, k);
     float pv[kSplitKMax][4];
 #pragma unroll
     for (int q = 0; q < kSplitKMax; ++q) {
@@ -1104,7 +1259,7 @@ __global__ __launch_bounds__(256) void k_sk_merge(LinArgs<bf16_t> a, int NGR /* 
 #pragma unroll
     for (int q = 0; q < kSplitKMax; ++q)
         if (q < KS) { d[0] += pv[q][0]; d[1] += pv[q][1]; d[2] += pv[q][2]; d[3] += pv[q][3]; }
-    block_epilogue<EPI>(a, s_t[wave], rb, a.tb_base + b, d, true, T, lane);
+    quad_epilogue<EPI>(a, p, t, d, t < T, k, pre);
 }
 
 // ------------------------------------------------------------------------------------
