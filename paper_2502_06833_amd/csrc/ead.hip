@@ -165,6 +165,38 @@ __global__ __launch_bounds__(256) void k_embed(const WT *embed, const int *token
     }
 }
 
+// ---- a run's state and results without a copy call per array or row (each is 5-15 us of host time) -----------
+// Algorithm 1's initialisation for every sequence; the prompts' lengths come from pinned host memory.
+struct ResetArgs { SeqState s; const int *prompt_len; int batch, kv_fill, model, max_new; };
+
+__global__ __launch_bounds__(256) void k_reset_run(ResetArgs a) {
+    const int b = blockIdx.x * 256 + threadIdx.x, MB = a.s.max_batch;
+    if (b == 0) *a.s.err = 0;
+    if (b >= MB) return;
+    const int len = b < a.batch ? a.prompt_len[b] : 0, kv = a.kv_fill && b < a.batch ? len - 1 : 0;
+    a.s.len[b] = len; a.s.kvlen[b] = kv; a.s.kvlen[MB + b] = kv;
+    a.s.model[b] = b < a.batch ? a.model : 0;
+    a.s.c[b] = 0; a.s.ngen[b] = 0; a.s.done[b] = 0; a.s.last_step[b] = -1; a.s.goal[b] = a.max_new;
+}
+
+// What sequences first .. first + gridDim.x - 1 have generated, into pinned host memory (rows of `cap` entries).
+struct FetchArgs { SeqState s; int first; int *n, *tok; float *H, *Hbar; uint8_t *mid, *dec; };
+
+__global__ __launch_bounds__(256) void k_fetch(FetchArgs a) {
+    const int r = blockIdx.x, b = a.first + r, n = a.s.ngen[b];
+    const size_t src = (size_t)b * a.s.cap, dst = (size_t)r * a.s.cap;
+    if (threadIdx.x == 0) a.n[r] = n;
+    for (int i = threadIdx.x; i < n; i += 256) {
+        a.tok[dst + i] = a.s.out_tok[src + i]; a.H[dst + i] = a.s.out_H[src + i]; a.Hbar[dst + i] = a.s.out_Hbar[src + i];
+        a.mid[dst + i] = a.s.out_mid[src + i]; a.dec[dst + i] = a.s.out_dec[src + i];
+    }
+}
+
+// the flags a decode call ends by looking at, into pinned host memory
+__global__ void k_status(const int *err, const int *abort_flag, int *out) {
+    if (threadIdx.x == 0) { out[0] = *err; out[1] = *abort_flag; }
+}
+
 // entropy-only finalisation for ead_entropy_argmax
 __global__ __launch_bounds__(64) void k_entropy_finalize(const EntPartial *partials, int n_part, int rows, int unit,
                                                          float *H, int *argmax) {
@@ -221,7 +253,9 @@ struct ead_handle {
     float *x, *q, *o, *hbuf; bf16_t *xp_a, *xp_o, *xp_h;
     float *sk_part; int *sk_tickets;     // split-K partial sums of the MFMA path
     float *part_o; float2 *part_ml; int *tickets; EntPartial *lm_part; float *logits_dump; float *sc_H; int *sc_arg;
-    int *h_model, *h_done;   // pinned
+    int *h_model = nullptr, *h_plen = nullptr, *h_status = nullptr;   // pinned: forced ids of a replay; prompt lengths; flags (k_status)
+    char *h_fetch = nullptr; int fetch_rows = 0;                       // pinned: results of up to fetch_rows sequences (k_fetch)
+    std::vector<int> h_tokens;           // the prompts as they are copied to the device
     LaneSet lanes[2]; int cur_lane = 0, two_lanes = 0; hipStream_t lane1_stream = nullptr;
     // fused single-row decode
     float *att_o; float2 *att_ml; unsigned *bar_mem; int *abort_flag; unsigned bar_epoch = 0; int fused_on = 0, fused_grid = 0;
@@ -1037,25 +1071,18 @@ ead_status reset_run_state(ead_handle *h, int max_new, int kv_fill) {
     const int MB = h->s.max_batch, batch = h->batch;
     h->max_new = max_new; h->began = 0; h->step = 0; h->sched_phase = 0;
     h->hs.assign(batch, HostSeq{});
-    std::vector<int> len(MB, 0), zeros(MB * 2, 0), kv(MB * 2, 0), model(MB, 0), neg(MB, -1), goal(MB, max_new);
+    const int model = h->force_model >= 0 ? h->force_model : (h->replay ? -1 : 0);
+    HIP_TRY(h, hipStreamSynchronize(st));          // an earlier run's k_reset_run has read its prompt lengths
     for (int b = 0; b < batch; ++b) {
         HostSeq &s = h->hs[b];
-        s.len = len[b] = h->prompt_len[b];
-        s.kvlen[0] = s.kvlen[1] = kv[b] = kv[MB + b] = kv_fill ? h->prompt_len[b] - 1 : 0;
+        s.len = h->h_plen[b] = h->prompt_len[b];
+        s.kvlen[0] = s.kvlen[1] = kv_fill ? h->prompt_len[b] - 1 : 0;
         s.c = 0; s.ngen = 0; s.done = 0; s.last_step = -1; s.goal = max_new;
-        s.model = h->force_model >= 0 ? h->force_model : (h->replay ? -1 : 0);
-        model[b] = std::max(s.model, 0);
+        s.model = model;
     }
-    HIP_TRY(h, hipMemcpyAsync(h->s.len, len.data(), MB * sizeof(int), hipMemcpyHostToDevice, st));
-    HIP_TRY(h, hipMemcpyAsync(h->s.kvlen, kv.data(), 2 * MB * sizeof(int), hipMemcpyHostToDevice, st));
-    HIP_TRY(h, hipMemcpyAsync(h->s.model, model.data(), MB * sizeof(int), hipMemcpyHostToDevice, st));
-    HIP_TRY(h, hipMemcpyAsync(h->s.c, zeros.data(), MB * sizeof(int), hipMemcpyHostToDevice, st));
-    HIP_TRY(h, hipMemcpyAsync(h->s.ngen, zeros.data(), MB * sizeof(int), hipMemcpyHostToDevice, st));
-    HIP_TRY(h, hipMemcpyAsync(h->s.done, zeros.data(), MB * sizeof(int), hipMemcpyHostToDevice, st));
-    HIP_TRY(h, hipMemcpyAsync(h->s.last_step, neg.data(), MB * sizeof(int), hipMemcpyHostToDevice, st));
-    HIP_TRY(h, hipMemcpyAsync(h->s.goal, goal.data(), MB * sizeof(int), hipMemcpyHostToDevice, st));
-    HIP_TRY(h, hipMemcpyAsync(h->s.err, zeros.data(), sizeof(int), hipMemcpyHostToDevice, st));
-    HIP_TRY(h, hipStreamSynchronize(st));          // the staging vectors leave scope
+    ResetArgs ra{h->s, h->h_plen, batch, kv_fill, std::max(model, 0), max_new};
+    hipLaunchKernelGGL(k_reset_run, dim3((MB + 255) / 256), dim3(256), 0, st, ra);
+    HIP_TRY(h, hipGetLastError());
     return EAD_OK;
 }
 
@@ -1067,14 +1094,14 @@ ead_status begin_impl(ead_handle *h, const int32_t *toks, const int32_t *lens, i
     const int MS = h->s.max_seq;
     h->batch = batch; h->prefilled = 0;
     h->prompt_len.assign(lens, lens + batch);
-    std::vector<int> tok((size_t)batch * MS, 0);
+    TRY(reset_run_state(h, max_new, 0));           // waits for the stream: h_tokens is not being read
+    h->h_tokens.assign((size_t)batch * MS, 0);
     size_t off = 0;
     for (int b = 0; b < batch; ++b) {
-        memcpy(&tok[(size_t)b * MS], toks + off, sizeof(int) * lens[b]);
+        memcpy(&h->h_tokens[(size_t)b * MS], toks + off, sizeof(int) * lens[b]);
         off += lens[b];
     }
-    HIP_TRY(h, hipMemcpyAsync(h->s.tokens, tok.data(), tok.size() * sizeof(int), hipMemcpyHostToDevice, st));
-    TRY(reset_run_state(h, max_new, 0));           // waits for the stream: tok may leave scope
+    HIP_TRY(h, hipMemcpyAsync(h->s.tokens, h->h_tokens.data(), h->h_tokens.size() * sizeof(int), hipMemcpyHostToDevice, st));
     // both models consume every prompt token but the last
     std::vector<int> rows; std::vector<char> complete;
     long left = 0;
@@ -1353,9 +1380,10 @@ ead_status decode_impl(ead_handle *h, int n_steps, long budget = -1, int lead = 
         h->step++;
     }
     if (h->two_lanes) HIP_TRY(h, hipStreamSynchronize(h->lanes[1].stream));
+    hipLaunchKernelGGL(k_status, dim3(1), dim3(64), 0, st, h->s.err, h->abort_flag, h->h_status);
+    HIP_TRY(h, hipGetLastError());
     HIP_TRY(h, hipStreamSynchronize(st));
-    int err = 0, aborted = 0;
-    HIP_TRY(h, hipMemcpy(&aborted, h->abort_flag, sizeof(int), hipMemcpyDeviceToHost));
+    const int err = h->h_status[0], aborted = h->h_status[1];
     if (aborted) {
         // a grid barrier gave up: drop the fused path for this handle and start its counters afresh
         h->fused_on = 0; h->bar_epoch = 0; h->began = 0;
@@ -1363,7 +1391,6 @@ ead_status decode_impl(ead_handle *h, int n_steps, long budget = -1, int lead = 
         HIP_TRY(h, hipMemset(h->abort_flag, 0, sizeof(int)));
         return fail(h, EAD_ERR_DEVICE, "fused decode kernel abandoned a grid barrier; fused path disabled, run again");
     }
-    HIP_TRY(h, hipMemcpy(&err, h->s.err, sizeof(int), hipMemcpyDeviceToHost));
     if (err) return fail(h, EAD_ERR_NONFINITE, "a non-finite entropy was produced (non-finite logits)");
     return EAD_OK;
 }
@@ -1371,20 +1398,27 @@ ead_status decode_impl(ead_handle *h, int n_steps, long budget = -1, int lead = 
 ead_status fetch_impl(ead_handle *h, int stride, int32_t *tok, uint8_t *mid, float *H, float *Hbar, uint8_t *dec,
                       int32_t *lens) {
     if (!h->began) return fail(h, EAD_ERR_STATE, "nothing to fetch: call ead_begin first");
-    HIP_TRY(h, hipStreamSynchronize(h->stream));
-    const int cap = h->s.cap;
-    std::vector<int> ngen(h->batch);
-    HIP_TRY(h, hipMemcpy(ngen.data(), h->s.ngen, h->batch * sizeof(int), hipMemcpyDeviceToHost));
-    for (int b = 0; b < h->batch; ++b) {
-        const int n = ngen[b];
-        if (n > stride) return fail(h, EAD_ERR_INVALID_ARG, "stride %d smaller than %d generated tokens", stride, n);
-        if (lens) lens[b] = n;
-        if (!n) continue;
-        if (tok) HIP_TRY(h, hipMemcpy(tok + (size_t)b * stride, h->s.out_tok + (size_t)b * cap, n * sizeof(int), hipMemcpyDeviceToHost));
-        if (mid) HIP_TRY(h, hipMemcpy(mid + (size_t)b * stride, h->s.out_mid + (size_t)b * cap, n, hipMemcpyDeviceToHost));
-        if (H) HIP_TRY(h, hipMemcpy(H + (size_t)b * stride, h->s.out_H + (size_t)b * cap, n * sizeof(float), hipMemcpyDeviceToHost));
-        if (Hbar) HIP_TRY(h, hipMemcpy(Hbar + (size_t)b * stride, h->s.out_Hbar + (size_t)b * cap, n * sizeof(float), hipMemcpyDeviceToHost));
-        if (dec) HIP_TRY(h, hipMemcpy(dec + (size_t)b * stride, h->s.out_dec + (size_t)b * cap, n, hipMemcpyDeviceToHost));
+    const size_t cap = h->s.cap;
+    for (int b0 = 0; b0 < h->batch; b0 += h->fetch_rows) {
+        const int rows = std::min(h->fetch_rows, h->batch - b0);
+        FetchArgs fa{};
+        fa.s = h->s; fa.first = b0;
+        fa.n = (int *)h->h_fetch; fa.tok = fa.n + h->fetch_rows; fa.H = (float *)(fa.tok + h->fetch_rows * cap); fa.Hbar = fa.H + h->fetch_rows * cap;
+        fa.mid = (uint8_t *)(fa.Hbar + h->fetch_rows * cap); fa.dec = fa.mid + h->fetch_rows * cap;
+        hipLaunchKernelGGL(k_fetch, dim3(rows), dim3(256), 0, h->stream, fa);
+        HIP_TRY(h, hipGetLastError());
+        HIP_TRY(h, hipStreamSynchronize(h->stream));
+        for (int r = 0; r < rows; ++r) {
+            const size_t n = (size_t)fa.n[r], src = r * cap, dst = (size_t)(b0 + r) * stride;
+            if ((long)n > stride) return fail(h, EAD_ERR_INVALID_ARG, "stride %d smaller than %d generated tokens", stride, (int)n);
+            if (lens) lens[b0 + r] = (int)n;
+            if (!n) continue;
+            if (tok) memcpy(tok + dst, fa.tok + src, n * sizeof(int));
+            if (mid) memcpy(mid + dst, fa.mid + src, n);
+            if (H) memcpy(H + dst, fa.H + src, n * sizeof(float));
+            if (Hbar) memcpy(Hbar + dst, fa.Hbar + src, n * sizeof(float));
+            if (dec) memcpy(dec + dst, fa.dec + src, n);
+        }
     }
     return EAD_OK;
 }
@@ -1534,7 +1568,9 @@ void ead_destroy(ead_handle *h) {
     }
     for (void *p : h->allocs) (void)hipFree(p);
     if (h->h_model) (void)hipHostFree(h->h_model);
-    if (h->h_done) (void)hipHostFree(h->h_done);
+    if (h->h_plen) (void)hipHostFree(h->h_plen);
+    if (h->h_status) (void)hipHostFree(h->h_status);
+    if (h->h_fetch) (void)hipHostFree(h->h_fetch);
     prof_collect(h);
     for (hipEvent_t e : h->ev_pool) (void)hipEventDestroy(e);
     delete h;
@@ -1662,7 +1698,11 @@ ead_status ead_create(const ead_model_desc *small_model, const ead_model_desc *l
             }
         }
         HIP_TRY(h, hipHostMalloc((void **)&h->h_model, std::max<size_t>((size_t)MB * MS, 64) * sizeof(int), hipHostMallocDefault));
-        HIP_TRY(h, hipHostMalloc((void **)&h->h_done, std::max<size_t>(MB, 64) * sizeof(int), hipHostMallocDefault));
+        HIP_TRY(h, hipHostMalloc((void **)&h->h_plen, std::max<size_t>(MB, 64) * sizeof(int), hipHostMallocDefault));
+        HIP_TRY(h, hipHostMalloc((void **)&h->h_status, 64 * sizeof(int), hipHostMallocDefault));
+        // results of a fetch: a row's 14 bytes per token and its count, at most about 4 MB (longer batches take several rounds)
+        h->fetch_rows = (int)std::min<long>(MB, std::max<long>(1, (4l << 20) / (14l * MS)));
+        HIP_TRY(h, hipHostMalloc((void **)&h->h_fetch, (size_t)h->fetch_rows * (14 * (size_t)MS + sizeof(int)), hipHostMallocDefault));
         HIP_TRY(h, hipStreamSynchronize(h->stream));
         HIP_TRY(h, hipGetLastError());
         return EAD_OK;
@@ -1709,6 +1749,7 @@ ead_status ead_rewind(ead_handle *h, int32_t max_new_tokens) {
     HIP_TRY(h, hipStreamSynchronize(h->stream));
     h->replay = 0; h->n_new = 0;
     TRY(reset_run_state(h, max_new_tokens, 1));
+    HIP_TRY(h, hipStreamSynchronize(h->stream));   // the other lane starts from this state too
     memset(&h->stats, 0, sizeof h->stats);
     h->began = 1;
     return EAD_OK;

@@ -32,3 +32,20 @@ def test_wide_batches_and_long_windows_follow_the_oracle(batch, w, n, hi):
         assert np.abs(rp["Hbar"][b] - refs[b]["Hbar"]).max() < 1e-4, b
         assert (rp["argmax"][b] == refs[b]["tokens"]).all(), b
     e.close()
+
+
+def test_results_of_a_batch_that_takes_several_fetch_rounds():
+    """40 sequences of up to 8192 tokens exceed the staging buffer of one round (36 rows): same results as with room for
+    64 tokens, bit for bit."""
+    import paper_2502_06833_amd as ead
+    ss, sl = si.TINY_S, si.TINY_L
+    Ws, Wl = si.model_weights_torch(ss, 0, "cuda"), si.model_weights_torch(sl, 0, "cuda")
+    prompts = [si.prompt_np(0, f"fetch{b}", 1 + b % 9, ss.vocab) for b in range(40)]
+    got = []
+    for room in (64, 8192):
+        e = ead.EAD(ss, Ws, sl, Wl, window=5, tau=6.2, d_min=2, max_batch=40, max_seq=room)
+        got.append(e.generate(prompts, 11))
+        e.close()
+    for k in got[0]:
+        assert (got[0][k] == got[1][k]).all(), k
+    assert (got[0]["lens"] == 11).all()
