@@ -165,6 +165,14 @@ __global__ __launch_bounds__(256) void k_embed(const WT *embed, const int *token
     }
 }
 
+// a gate's state as at its creation, and its counters at zero (one launch where five memsets took 20 us of host time)
+__global__ __launch_bounds__(256) void k_gate_reset(GateState s, int *row_tickets, int *pair_tickets, int rows, int w, int n_pairs) {
+    const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
+    if (i < (size_t)rows * w) s.ring[i] = 0.f;
+    if (i < (size_t)rows) { s.n[i] = 0; s.c[i] = 0; s.model[i] = 0; row_tickets[i] = 0; }
+    if (i < (size_t)n_pairs) pair_tickets[i] = 0;
+}
+
 // ---- a run's state and results without a copy call per array or row (each is 5-15 us of host time) -----------
 // Algorithm 1's initialisation for every sequence; the prompts' lengths come from pinned host memory.
 struct ResetArgs { SeqState s; const int *prompt_len; int batch, kv_fill, model, max_new; };
@@ -1430,6 +1438,7 @@ ead_status fetch_impl(ead_handle *h, int stride, int32_t *tok, uint8_t *mid, flo
 constexpr int kEntMaxRows = 4096, kEntMaxChunks = 64;
 constexpr int kEntStaticPartials = 16384;              // rows * chunks a call of ead_entropy_argmax_static may need
 constexpr int kEntMaxDevices = 16;
+constexpr size_t kEntFoldBytes = (size_t)4 << 20;      // largest input of ead_entropy_argmax that takes one launch
 
 static __device__ __align__(256) unsigned char scratch[(size_t)kEntStaticPartials * sizeof(EntPartial)];
 
@@ -1438,6 +1447,8 @@ struct EntDevice {                // per device, set up once by the first call o
     int resident = 1024;          // workgroups of k_entropy_partial the chip holds at once
     EntPartial *static_part = nullptr;     // device address of `scratch` on this device
     EntPartial *heap_part = nullptr;       // ead_entropy_argmax's buffer, allocated on first use
+    unsigned long long *heap_words = nullptr;      // and its arrival words, [kEntMaxRows], zero at first (k_entropy_partial)
+    unsigned long long calls = 0;          // numbers the calls that use them
 };
 EntDevice g_ent_dev[kEntMaxDevices];
 std::mutex g_ent_mutex;
@@ -1466,15 +1477,23 @@ ead_status entropy_device(EntDevice **out) {
     return EAD_OK;
 }
 
-ead_status entropy_heap_scratch(EntDevice *d, EntPartial **out) {
+// *call: a number of its own for this call, shifted past the count (k_entropy_partial)
+ead_status entropy_heap_scratch(EntDevice *d, EntPartial **out, unsigned long long *call) {
     std::lock_guard<std::mutex> lock(g_ent_mutex);
     if (!d->heap_part) {
         void *p = nullptr;
-        if (hipMalloc(&p, sizeof(EntPartial) * (size_t)kEntMaxRows * kEntMaxChunks) != hipSuccess)
+        const size_t bytes = sizeof(EntPartial) * (size_t)kEntMaxRows * kEntMaxChunks;      // a multiple of 8
+        if (hipMalloc(&p, bytes + sizeof(unsigned long long) * kEntMaxRows) != hipSuccess)
             return fail(nullptr, EAD_ERR_OOM, "scratch allocation failed");
-        d->heap_part = (EntPartial *)p;
+        unsigned long long *words = (unsigned long long *)((char *)p + bytes);
+        if (hipMemset(words, 0, sizeof(unsigned long long) * kEntMaxRows) != hipSuccess || hipDeviceSynchronize() != hipSuccess) {
+            (void)hipGetLastError(); (void)hipFree(p);
+            return fail(nullptr, EAD_ERR_DEVICE, "clearing the scratch failed");
+        }
+        d->heap_part = (EntPartial *)p; d->heap_words = words;
     }
     *out = d->heap_part;
+    *call = ++d->calls << kEntCountBits;
     return EAD_OK;
 }
 
@@ -1503,6 +1522,17 @@ void launch_entropy_partial(const void *const *step_logits, int steps, int rows,
     hipLaunchKernelGGL((k_entropy_partial<T>), dim3(std::min(a.items, resident)), dim3(256), 0, st, a);
 }
 
+template <typename T>
+void launch_entropy_folded(const void *logits, int rows, int V, EntPartial *part, const EntDevice *d, unsigned long long call, int unit,
+                           float *H, int *argmax, hipStream_t st) {
+    EntArgs<T> a{};
+    entropy_split(rows, V, &a.chunks, &a.vec_per_item);
+    a.step_logits[0] = (const T *)logits;
+    a.V = V; a.rows = rows; a.items = rows * a.chunks; a.partials = part;
+    a.words = d->heap_words; a.call = call; a.unit = unit; a.H = H; a.argmax = argmax;
+    hipLaunchKernelGGL((k_entropy_partial<T, true>), dim3(std::min(a.items, d->resident)), dim3(256), 0, st, a);
+}
+
 ead_status entropy_check(const void *const *step_logits, int steps, int dtype, int rows, int vocab) {
     if (steps < 1 || steps > kGateMaxSteps || (long)steps * rows > kEntMaxRows)
         return fail(nullptr, EAD_ERR_INVALID_ARG, "too many steps for one launch");
@@ -1524,17 +1554,27 @@ void entropy_launch(const void *const *step_logits, int steps, int dtype, int ro
     else launch_entropy_partial<float>(step_logits, steps, rows, vocab, part, resident, st);
 }
 
+// Pieces a row is given to workgroups in (1: a workgroup takes whole rows), by rows and vocabulary alone.  From about 24 rows
+// the rows of a launch's 16 steps fill the chip by themselves; below, pieces of 512 vectors and more, 64 at most.
+int entropy_row_parts(int rows, int V) {
+    const int nvec = V / 8;
+    if (rows > 24 || nvec < 1024) return 1;
+    const int least = (nvec + 2047) / 2048;                       // at most 8 vectors per thread and piece
+    return std::max(std::max(least, 2), std::min(std::min(kEntMaxChunks, 256 / rows), nvec / 512));
+}
+
 template <typename T>
 void launch_entropy_rows(const void *const *step_logits, int steps, int rows, int V, int resident, hipStream_t st,
-                         const GateStepArgs &gate, float *pair_H, int *row_tickets) {
+                         const GateStepArgs &gate, float *pair_H, int *row_tickets, EntPartial *partials, int *pair_tickets) {
     const int nvec = V / 8;
     EntRowArgs<T> a{};
     for (int z = 0; z < steps; ++z) a.step_logits[z] = (const T *)step_logits[z];
     a.V = V; a.rows = rows; a.steps = steps;
-    a.chunks = std::max(1, (nvec + 2047) / 2048);                 // pieces of at most 8 vectors per thread
+    a.parts = entropy_row_parts(rows, V); a.partials = partials; a.pair_tickets = pair_tickets;
+    a.chunks = a.parts > 1 ? a.parts : std::max(1, (nvec + 2047) / 2048);      // pieces of at most 8 vectors per thread
     a.vec_per_item = (std::max(nvec, 1) + a.chunks - 1) / a.chunks;
     a.pair_H = pair_H; a.row_tickets = row_tickets; a.gate = gate;
-    hipLaunchKernelGGL((k_entropy_rows<T>), dim3(std::min(steps * rows, resident)), dim3(256), 0, st, a);
+    hipLaunchKernelGGL((k_entropy_rows<T>), dim3(std::min(steps * rows * a.parts, resident)), dim3(256), 0, st, a);
 }
 
 }  // namespace
@@ -1544,7 +1584,8 @@ struct ead_gate {
     EntPartial *part = nullptr;   // partials of this gate's entropy passes: (steps per launch) x rows x kEntMaxChunks
     float *pair_H = nullptr;      // small windows (one launch per group of steps): entropies handed between workgroups
     int *row_tickets = nullptr;   //   and the arrival counters per row, zero between launches
-    int resident = 1024;
+    int *pair_tickets = nullptr;  //   and per (step, row) where a row's pieces go to several workgroups
+    int resident = 1024, n_pairs = 0;
     std::vector<void *> allocs;
 };
 
@@ -1960,13 +2001,23 @@ ead_status entropy_argmax_impl(const void *logits_dev, int32_t dtype, int32_t ro
     EntDevice *d = nullptr;
     TRY(entropy_device(&d));
     EntPartial *part = nullptr;
+    unsigned long long call = 0;
     if (use_static) {
         if ((long)rows * chunks > kEntStaticPartials)
             return fail(nullptr, EAD_ERR_INVALID_ARG, "rows * chunks = %d * %d exceeds the %d partials of the static scratch array",
                         rows, chunks, kEntStaticPartials);
         part = d->static_part;
     } else {
-        TRY(entropy_heap_scratch(d, &part));
+        TRY(entropy_heap_scratch(d, &part, &call));
+    }
+    // Small inputs take one launch: the call is bound by the host then (128256 bf16 logits: 10.2 us against 13.0), and the
+    // last workgroup's chain of counter and partials, 3-4 us, is hidden.  It is not behind a kernel of 8 us and more (97 x 50264
+    // float32: 14.6 us against 12.9).  Always two for the entry point that has no counters, only the static array.
+    if (!use_static && (size_t)rows * vocab * (dtype == EAD_BF16 ? 2 : 4) <= kEntFoldBytes) {
+        if (dtype == EAD_BF16) launch_entropy_folded<bf16_t>(logits_dev, rows, vocab, part, d, call, unit, H_dev, argmax_dev, st);
+        else launch_entropy_folded<float>(logits_dev, rows, vocab, part, d, call, unit, H_dev, argmax_dev, st);
+        if (hipGetLastError() != hipSuccess) return fail(nullptr, EAD_ERR_DEVICE, "kernel launch failed");
+        return EAD_OK;
     }
     entropy_launch(&logits_dev, 1, dtype, rows, vocab, st, part, d->resident);
     hipLaunchKernelGGL(k_entropy_finalize, dim3(rows), dim3(64), 0, st, part, chunks, rows, unit, H_dev, argmax_dev);
@@ -1997,26 +2048,25 @@ ead_status ead_gate_create(int32_t rows, int32_t window, float tau, int32_t d_mi
     { const ead_status rc = entropy_device(&d); if (rc != EAD_OK) { delete g; return rc; } }
     g->resident = d->resident;
     const size_t steps_per_launch = std::max(1, std::min(kGateMaxSteps, kEntMaxRows / rows));
-    void *p[7] = {nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr};
-    const size_t sz[7] = {(size_t)rows * window * 4, (size_t)rows * 4, (size_t)rows * 4, (size_t)rows * 4,
-                          steps_per_launch * rows * kEntMaxChunks * sizeof(EntPartial), steps_per_launch * rows * 4, (size_t)rows * 4};
-    for (int i = 0; i < 7; ++i) {
+    void *p[8] = {nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr};
+    const size_t sz[8] = {(size_t)rows * window * 4, (size_t)rows * 4, (size_t)rows * 4, (size_t)rows * 4,
+                          steps_per_launch * rows * kEntMaxChunks * sizeof(EntPartial), steps_per_launch * rows * 4, (size_t)rows * 4, steps_per_launch * rows * 4};
+    for (int i = 0; i < 8; ++i) {
         if (hipMalloc(&p[i], sz[i]) != hipSuccess) { for (int j = 0; j < i; ++j) (void)hipFree(p[j]); delete g; return fail(nullptr, EAD_ERR_OOM, "hipMalloc failed"); }
         g->allocs.push_back(p[i]);
     }
     g->st.ring = (float *)p[0]; g->st.n = (int *)p[1]; g->st.c = (int *)p[2]; g->st.model = (int *)p[3];
     g->part = (EntPartial *)p[4]; g->pair_H = (float *)p[5]; g->row_tickets = (int *)p[6];
+    g->pair_tickets = (int *)p[7]; g->n_pairs = (int)(steps_per_launch * rows);
     *out = g;
     return ead_gate_reset(g);
 }
 
 ead_status ead_gate_reset(ead_gate *g) {
     if (!g) return EAD_ERR_INVALID_ARG;
-    (void)hipMemsetAsync(g->st.ring, 0, (size_t)g->rows * g->cfg.w * 4, g->stream);
-    (void)hipMemsetAsync(g->st.n, 0, (size_t)g->rows * 4, g->stream);
-    (void)hipMemsetAsync(g->st.c, 0, (size_t)g->rows * 4, g->stream);
-    (void)hipMemsetAsync(g->st.model, 0, (size_t)g->rows * 4, g->stream);
-    (void)hipMemsetAsync(g->row_tickets, 0, (size_t)g->rows * 4, g->stream);
+    const size_t n = std::max((size_t)g->rows * g->cfg.w, (size_t)g->n_pairs);
+    hipLaunchKernelGGL(k_gate_reset, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, g->stream, g->st, g->row_tickets, g->pair_tickets, g->rows,
+                       g->cfg.w, g->n_pairs);
     return hipGetLastError() == hipSuccess ? EAD_OK : EAD_ERR_DEVICE;
 }
 
@@ -2048,8 +2098,8 @@ ead_status gate_steps(ead_gate *g, const void *const *ptrs, int ns, int dtype, i
     a.H_out = H_dev; a.argmax_out = argmax_dev;
     a.model_id_out = model_id_dev; a.Hbar_out = window_mean_dev; a.next_out = next_model_dev;
     if (g->cfg.w <= kGateFoldWindow) {
-        if (dtype == EAD_BF16) launch_entropy_rows<bf16_t>(ptrs, ns, g->rows, vocab, g->resident, g->stream, a, g->pair_H, g->row_tickets);
-        else launch_entropy_rows<float>(ptrs, ns, g->rows, vocab, g->resident, g->stream, a, g->pair_H, g->row_tickets);
+        if (dtype == EAD_BF16) launch_entropy_rows<bf16_t>(ptrs, ns, g->rows, vocab, g->resident, g->stream, a, g->pair_H, g->row_tickets, g->part, g->pair_tickets);
+        else launch_entropy_rows<float>(ptrs, ns, g->rows, vocab, g->resident, g->stream, a, g->pair_H, g->row_tickets, g->part, g->pair_tickets);
     } else {
         int chunks = 0, per = 0;
         entropy_split(g->rows, vocab, &chunks, &per);

@@ -26,6 +26,20 @@ __device__ __forceinline__ EntStat merge_partials(const EntPartial *p, int n) {
     return wave_merge(st);
 }
 
+// The same for partials that other workgroups of this kernel have just written through to memory.
+__device__ __forceinline__ void put_partial(EntPartial *d, const EntStat &s) {
+    st_coherent(&d->m, s.m); st_coherent(&d->Z, s.Z); st_coherent(&d->S, s.S); st_coherent(&d->idx, s.idx);
+}
+__device__ __forceinline__ EntStat merge_partials_coherent(const EntPartial *p, int n) {
+    EntStat st; st.init();
+    for (int i = threadIdx.x & 63; i < n; i += 64) {
+        EntStat q; q.m = ld_coherent(&p[i].m); q.Z = ld_coherent(&p[i].Z); q.S = ld_coherent(&p[i].S); q.idx = ld_coherent(&p[i].idx);
+        q.gs = -INFINITY; q.gidx = 0x7FFFFFFF;
+        st.merge(q);
+    }
+    return wave_merge(st);
+}
+
 // ---------------------------------------------------------------------------------------
 // Rolling window + switch rule for one sequence.  Ring buffer of w entropies; the mean is
 // re-summed oldest to newest in fp32 every step (no running sum), as the definition reads.
@@ -130,7 +144,14 @@ struct EntArgs {
     const T *step_logits[kGateMaxSteps];      // one [rows, V] matrix per step of the launch
     int V, rows, chunks, vec_per_item, items; // items = steps * rows * chunks
     EntPartial *partials;                     // [items]
+    // FOLD (one step): the workgroup that finishes a row's last chunk merges its partials and writes the results, which
+    // saves the second launch.  Its arrival is counted in a word per row, zero between calls, that also holds the
+    // number of the call (count in the low kEntCountBits): a call first raises the word to its own number, so a count
+    // left behind by calls that overlapped never counts for a later one.
+    unsigned long long *words, call;          // [rows]; call number << kEntCountBits
+    int unit; float *H; int *argmax;
 };
+constexpr int kEntCountBits = 24;
 
 constexpr float kLog2e = 1.4426950408889634f, kLn2 = 0.6931471805599453f;
 constexpr float kEntNone = -1e30f;            // running maximum before any logit was seen
@@ -198,10 +219,11 @@ __device__ __forceinline__ void ent_take4(const Vec8<T> (&s)[4], EntRun<T> &r, c
     }
 }
 
-template <typename T>
+template <typename T, bool FOLD = false>
 __global__ __launch_bounds__(256) void k_entropy_partial(EntArgs<T> a) {
     __shared__ float s_max[4];
     __shared__ EntPartial s_fin[4];
+    __shared__ int s_last;
     const int tid = threadIdx.x;
     int item = blockIdx.x;                  // uniform: kept in scalar registers
     if (item >= a.items) return;
@@ -257,7 +279,24 @@ __global__ __launch_bounds__(256) void k_entropy_partial(EntArgs<T> a) {
             e.S = (((s_fin[0].S + s_fin[1].S) + s_fin[2].S) + s_fin[3].S) * kLn2;
             e.idx = min(min(s_fin[0].idx, s_fin[1].idx), min(s_fin[2].idx, s_fin[3].idx));
             e.gs = -INFINITY; e.gidx = 0x7FFFFFFF;          // no sampling on materialised logits
-            a.partials[item] = e;
+            if constexpr (FOLD) {
+                EntStat st; st.m = e.m; st.Z = e.Z; st.S = e.S; st.idx = e.idx; st.gs = e.gs; st.gidx = e.gidx;
+                put_partial(a.partials + item, st);
+                wait_stores();
+                unsigned long long *w = a.words + item / a.chunks;
+                __hip_atomic_fetch_max(w, a.call, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                const bool last = __hip_atomic_fetch_add(w, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == a.call + (unsigned long long)(a.chunks - 1);
+                if (last) __hip_atomic_store(w, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                s_last = last;
+            } else a.partials[item] = e;
+        }
+        if constexpr (FOLD) {
+            __syncthreads();
+            if (s_last && tid < 64) {
+                const int row = item / a.chunks;
+                const EntStat st = merge_partials_coherent(a.partials + (size_t)row * a.chunks, a.chunks);
+                if (tid == 0) { a.H[row] = entropy_from(st, a.unit); if (a.argmax) a.argmax[row] = st.idx; }
+            }
         }
         item = __builtin_amdgcn_readfirstlane(nitem); it = nit;
         return !more;
@@ -277,6 +316,10 @@ __global__ __launch_bounds__(256) void k_entropy_partial(EntArgs<T> a) {
 // and leaves the row's entropy and arg max.  The workgroup that does so for the last of a row's steps
 // in this launch (arrival counter per row, left at zero) reads the row's entropies back and takes its
 // window and switch rule through the steps in order.  One launch per up to kGateMaxSteps steps.
+// With few rows a workgroup per (row, step) leaves most of the chip idle (two rows x 3 steps of 151936 logits: six
+// workgroups, 35 us); `parts` > 1 gives every piece of a row a workgroup, which leaves a partial, and the last to
+// arrive at the row's step merges them.  The split follows rows and vocabulary alone, so that a step's result does
+// not depend on how many steps share a launch.
 // ---------------------------------------------------------------------------------------
 constexpr int kGateFoldWindow = 64;     // largest window this kernel serves (its LDS copy of the ring)
 
@@ -286,6 +329,8 @@ struct EntRowArgs {
     int V, rows, steps, chunks, vec_per_item; // a row is walked in `chunks` pieces of vec_per_item vectors (<= 8 per thread)
     float *pair_H;                            // [steps * rows]: the entropies, handed between workgroups (written through)
     int *row_tickets;                         // [rows] arrival counters, zero between launches
+    int parts;                                // 1, or = chunks: a workgroup per piece
+    EntPartial *partials; int *pair_tickets;  // parts > 1: [steps * rows * parts], [steps * rows] counters, zero between launches
     GateStepArgs gate;                        // state, configuration and outputs (partials unused)
 };
 
@@ -302,12 +347,15 @@ __device__ __forceinline__ EntItem<T> ent_row_item(const EntRowArgs<T> &a, int p
 template <typename T>
 __global__ __launch_bounds__(256) void k_entropy_rows(EntRowArgs<T> a) {
     __shared__ float s_max[4], s_Z[4], s_S[4];
-    __shared__ int s_idx[4], s_last_row;
+    __shared__ int s_idx[4], s_last_row, s_last_part;
     __shared__ float s_H[kGateMaxSteps], s_hb[kGateMaxSteps], s_ring[kGateFoldWindow];
     const int tid = threadIdx.x, pairs = a.steps * a.rows;
-    int pair = blockIdx.x, chunk = 0;       // uniform: kept in scalar registers
+    // uniform, kept in scalar registers.  parts = 1: (pair, chunk) walks whole rows; else blockIdx.x and its successors number
+    // the pieces of all rows
+    const bool split = a.parts > 1;
+    int item = blockIdx.x, pair = split ? item / a.parts : item, chunk = split ? item % a.parts : 0;
     if (pair >= pairs) return;
-    EntItem<T> it = ent_row_item(a, pair, 0);
+    EntItem<T> it = ent_row_item(a, pair, chunk);
     Vec8<T> A[4], B[4], C[4];
     ent_load4(A, it, 0);
     EntRun<T> r; r.m = kEntNone; r.Z = 0.f; r.S2 = 0.f; r.bestv = 0; r.best.zero();
@@ -316,8 +364,9 @@ __global__ __launch_bounds__(256) void k_entropy_rows(EntRowArgs<T> a) {
     // next row).  Returns true after the last piece.
     auto one_piece = [&](Vec8<T> (&first)[4], Vec8<T> (&next)[4]) __attribute__((always_inline)) -> bool {
         ent_load4(B, it, 4);
-        const bool row_done = chunk + 1 == a.chunks;
-        const int npair = row_done ? pair + (int)gridDim.x : pair, nchunk = row_done ? 0 : chunk + 1;
+        const bool row_done = split || chunk + 1 == a.chunks;
+        const int nitem = row_done ? item + (int)gridDim.x : item;
+        const int npair = split ? nitem / a.parts : nitem, nchunk = split ? nitem % a.parts : (row_done ? 0 : chunk + 1);
         const bool more = npair < pairs;
         const EntItem<T> nit = ent_row_item(a, more ? npair : pair, more ? nchunk : chunk);
         __builtin_amdgcn_sched_barrier(0);
@@ -351,12 +400,27 @@ __global__ __launch_bounds__(256) void k_entropy_rows(EntRowArgs<T> a) {
             if ((tid & 63) == 0) { s_Z[tid >> 6] = Z; s_S[tid >> 6] = S2; s_idx[tid >> 6] = idx; }
             __syncthreads();
             const int row = pair % a.rows;
+            EntStat st; st.init();
             if (tid == 0) {
-                EntStat st; st.init();
                 st.m = gmx > kEntNone ? gmx : -INFINITY;
                 st.Z = ((s_Z[0] + s_Z[1]) + s_Z[2]) + s_Z[3];
                 st.S = (((s_S[0] + s_S[1]) + s_S[2]) + s_S[3]) * kLn2;
                 st.idx = min(min(s_idx[0], s_idx[1]), min(s_idx[2], s_idx[3]));
+            }
+            bool whole = true;                  // st holds the whole row's statistics
+            if (split) {
+                if (tid == 0) {
+                    put_partial(a.partials + item, st);
+                    wait_stores();
+                    const int t = __hip_atomic_fetch_add(a.pair_tickets + pair, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    s_last_part = t == a.parts - 1 ? 1 : 0;
+                    if (t == a.parts - 1) st_coherent(a.pair_tickets + pair, 0);
+                }
+                __syncthreads();
+                whole = s_last_part != 0;
+                if (whole && tid < 64) st = merge_partials_coherent(a.partials + (size_t)pair * a.parts, a.parts);
+            }
+            if (tid == 0 && whole) {
                 const float H = entropy_from(st, a.gate.unit);
                 if (a.gate.H_out) a.gate.H_out[pair] = H;
                 if (a.gate.argmax_out) a.gate.argmax_out[pair] = st.idx;
@@ -368,14 +432,14 @@ __global__ __launch_bounds__(256) void k_entropy_rows(EntRowArgs<T> a) {
                 if (t == a.steps - 1) st_coherent(a.row_tickets + row, 0);
             }
             __syncthreads();
-            if (s_last_row) {
+            if (whole && s_last_row) {
                 if (tid < a.steps) s_H[tid] = ld_coherent(a.pair_H + (size_t)tid * a.rows + row);
                 __syncthreads();
                 gate_row_apply(a.gate, row, s_H, s_ring, s_hb);      // ends with a barrier
             }
             r.m = kEntNone; r.Z = 0.f; r.S2 = 0.f; r.bestv = 0; r.best.zero();
         }
-        pair = __builtin_amdgcn_readfirstlane(npair); chunk = __builtin_amdgcn_readfirstlane(nchunk); it = nit;
+        item = __builtin_amdgcn_readfirstlane(nitem); pair = __builtin_amdgcn_readfirstlane(npair); chunk = __builtin_amdgcn_readfirstlane(nchunk); it = nit;
         return !more;
     };
     for (;;) {

@@ -139,3 +139,63 @@ def test_multi_step_run_matches_single_steps():
     assert np.abs(Hn[2] - Hr).max() < TOL_H and (am[2].cpu().numpy() == ar).all()
     assert 0 < midn.mean() < 1
     g1.close(); g2.close()
+
+
+@pytest.mark.parametrize("rows,steps,V", [(1, 1, 8192), (1, 17, 151936), (2, 3, 32000), (3, 20, 128256), (24, 5, 8200), (25, 5, 8200), (7, 4, 8184)])
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+def test_gate_with_rows_split_over_workgroups(rows, steps, V, dtype):
+    """Few rows: a row's pieces go to several workgroups.  Entropies against float64 (fp32 sums of up to 151936 terms by at
+    most 256 threads: 1e-5 nats), the same bits step by step as in one call, window and model as gate_trace gives them."""
+    ead = _ead()
+    tensors = [si.logits_torch(s, f"split{V}", rows, V, dtype, "cuda") for s in range(min(steps, 4))]
+    tau = math.log(V) - 2.0
+    g, one = ead.Gate(rows, 5, tau, 2), ead.Gate(rows, 5, tau, 2)
+    for _ in range(2):                                       # counters are back at zero after a call
+        g.reset()
+        H, am, mid, hb = (t.cpu().numpy() for t in g.run_logits(tensors, steps))
+        for s in range(steps):
+            x = tensors[s % len(tensors)].double()
+            lp = torch.log_softmax(x, -1)
+            assert np.abs(H[s] - (-(lp.exp() * lp).sum(-1)).cpu().numpy()).max() < 1e-5 * math.log(V), s
+            assert (am[s] == x.argmax(-1).cpu().numpy()).all(), s
+        for r in range(rows):
+            ref_hb, ref_id = oracle.gate_trace(H[:, r], 5, 2, tau)
+            assert (hb[:, r] == ref_hb).all() and (mid[:, r] == ref_id).all(), r
+    one.reset()
+    for s in range(steps):
+        h1, a1, m1, b1, _ = one.step_logits(tensors[s % len(tensors)])
+        assert (h1.cpu().numpy() == H[s]).all() and (a1.cpu().numpy() == am[s]).all()
+        assert (m1.cpu().numpy() == mid[s]).all() and (b1.cpu().numpy() == hb[s]).all()
+    g.close(); one.close()
+
+
+def test_entropy_calls_in_a_row_and_under_capture():
+    """One launch per call, counters zero between calls: growing and shrinking inputs back to back, two streams in turn, and
+    a captured call replayed between eager ones."""
+    ead = _ead()
+    xs = [si.logits_torch(i, "row", r, V, dt, "cuda") for i, (r, V, dt) in enumerate(
+        [(1, 128256, torch.bfloat16), (97, 50264, torch.float32), (3, 8, torch.float32), (600, 4096, torch.bfloat16), (1, 151936, torch.float32)])]
+    ref = [ead.entropy_argmax(x, static=x.shape[0] < 500) for x in xs]
+    ref = [(h.clone(), a.clone()) for h, a in ref]
+    other = torch.cuda.Stream()
+    for rnd in range(3):
+        for x, (h, a) in zip(xs, ref):
+            h1, a1 = ead.entropy_argmax(x)
+            assert torch.equal(h1, h) and torch.equal(a1, a)
+            torch.cuda.synchronize()
+            with torch.cuda.stream(other):
+                h2, a2 = ead.entropy_argmax(x)
+            torch.cuda.synchronize()
+            assert torch.equal(h2, h) and torch.equal(a2, a)
+    out = (torch.zeros(97, device="cuda"), torch.zeros(97, dtype=torch.int32, device="cuda"))
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        ead.entropy_argmax(xs[1], out=out)
+    for rnd in range(4):
+        out[0].zero_(); out[1].zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out[0], ref[1][0]) and torch.equal(out[1], ref[1][1])
+        h1, a1 = ead.entropy_argmax(xs[0])
+        torch.cuda.synchronize()
+        assert torch.equal(h1, ref[0][0])
