@@ -1559,11 +1559,12 @@ void entropy_launch(const void *const *step_logits, int steps, int dtype, int ro
     else launch_entropy_partial<float>(step_logits, steps, rows, vocab, part, resident, st);
 }
 
-// Pieces a row is given to workgroups in (1: a workgroup takes whole rows), by rows and vocabulary alone.  From about 24 rows
-// the rows of a launch's 16 steps fill the chip by themselves; below, pieces of 512 vectors and more, 64 at most.
+// Pieces a row is given to workgroups in (1: a workgroup takes whole rows), by rows and vocabulary alone.  One or two rows:
+// pieces of 512 vectors and more, 64 at most (2 rows x 151936: 3 steps 31 -> 16 us, 40 steps 76 -> 71).  From more rows on the
+// pieces' merges cost more over 16 steps than the fuller chip gives (8 rows x 151936, 40 steps: 75 whole, 132 in pieces).
 int entropy_row_parts(int rows, int V) {
     const int nvec = V / 8;
-    if (rows > 24 || nvec < 1024) return 1;
+    if (rows > 2 || nvec < 1024) return 1;
     const int least = (nvec + 2047) / 2048;                       // at most 8 vectors per thread and piece
     return std::max(std::max(least, 2), std::min(std::min(kEntMaxChunks, 256 / rows), nvec / 512));
 }
