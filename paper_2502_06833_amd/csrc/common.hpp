@@ -189,13 +189,20 @@ __host__ __device__ __forceinline__ size_t vt_offset(int dim, int pos, int max_s
 // ---- online soft-max statistics for the entropy (Eq. 1-2) ------------------------------
 // For a set of logits: m = max, Z = sum exp(l-m), S = sum exp(l-m)(l-m), plus the arg max
 // (lowest index on ties).  H = ln Z - S/Z.  merge() combines two disjoint sets.
+constexpr int kNoIndex = 0x7FFFFFFF;
+
+// What a maximum is looked for by where its index is found afterwards by comparing with it: NaN counts as -inf.  A set that
+// holds nothing but NaN then still has entries of the largest rank, and an index inside the vocabulary: the next
+// pass reads that token's embedding before the host learns that the entropy was not finite.
+__device__ __forceinline__ float rank_of(float v) { return v == v ? v : -INFINITY; }
+
 struct EntStat {
     float m, Z, S;
     int idx;
     // sampling (Algorithm 1's y ~ softmax(l / T)): running maximum of the perturbed scores
     // l_i / T + g_i and where it is (lowest index on ties); unused when decoding greedily
     float gs; int gidx;
-    __device__ __forceinline__ void init() { m = -INFINITY; Z = 0.f; S = 0.f; idx = 0x7FFFFFFF; gs = -INFINITY; gidx = 0x7FFFFFFF; }
+    __device__ __forceinline__ void init() { m = -INFINITY; Z = 0.f; S = 0.f; idx = kNoIndex; gs = -INFINITY; gidx = kNoIndex; }
     __device__ __forceinline__ void merge(const EntStat &o) {
         if (o.Z == 0.f) return;                      // empty set
         if (Z == 0.f) { *this = o; return; }

@@ -878,7 +878,7 @@ __device__ __forceinline__ void lm_fold(const LinArgs<bf16_t> &a, const f32x4_t 
     for (int j = 0; j < kLmRows; ++j)
         if (j < have) mx = fmaxf(mx, fmaxf(fmaxf(acc[j][0], acc[j][1]), fmaxf(acc[j][2], acc[j][3])));
     if (st.Z == 0.f || mx > st.m) {
-        int idx = 0x7FFFFFFF;
+        int idx = p0;                                 // of a group of NaN alone: its first entry
 #pragma unroll
         for (int j = kLmRows - 1; j >= 0; --j)
 #pragma unroll

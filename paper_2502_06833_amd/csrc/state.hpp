@@ -106,13 +106,13 @@ __global__ __launch_bounds__(kFinThreads) void k_lm_finalize(FinArgs a) {
         m = wave_max(m);
         if (a.sampling) gs = wave_max(gs);
         float Z = 0.f, S = 0.f;
-        int idx = 0x7FFFFFFF, gidx = 0x7FFFFFFF;
+        int idx = kNoIndex, gidx = kNoIndex;
 #pragma unroll
         for (int v = 0; v < kFinVecs; ++v)
             if (e[v].Z != 0.f) {
                 const float d = e[v].m - m, x = __expf(d);
                 Z += x * e[v].Z; S += x * (e[v].S + d * e[v].Z);
-                if (e[v].m == m) idx = min(idx, e[v].idx);
+                if (rank_of(e[v].m) == m) idx = min(idx, e[v].idx);      // m is the largest rank: fmaxf drops NaN
                 if (e[v].gs == gs) gidx = min(gidx, e[v].gidx);
             }
         Z = wave_sum(Z); S = wave_sum(S);
@@ -131,6 +131,7 @@ __global__ __launch_bounds__(kFinThreads) void k_lm_finalize(FinArgs a) {
         EntStat t; t.m = s_m[v]; t.Z = s_Z[v]; t.S = s_S[v]; t.idx = s_idx[v]; t.gs = s_gs[v]; t.gidx = s_gidx[v];
         st.merge(t);
     }
+    if (st.gidx == kNoIndex) st.gidx = st.idx;           // no perturbed score above -inf (NaN, or an overflow of l / T): the arg max
     const float H = entropy_from(st, a.unit);
     if (a.score_mode) {
         const int pos = a.p.row_pos[a.p.lm_row[i]];

@@ -1,0 +1,47 @@
+// Kernels of the library compiled for the CPU (tests/host_hip stands in for the HIP headers), with a C interface for
+// tests/test_host_kernels.py: what they do with inputs that must not reach a GPU before they are known to be handled.
+#include <hip/hip_runtime.h>
+#undef HOST_SHARED
+#define HOST_SHARED
+#include "linear.hpp"
+#undef HOST_SHARED
+#define HOST_SHARED static
+#include "state.hpp"
+
+using namespace ead;
+
+extern "C" {
+
+// k_lm_finalize over `rows` sequences of n_part partials each: the token appended, its entropy, and the error flag.
+void host_finalize(const EntPartial *partials, int rows, int n_part, int sampling, int *tok, float *H, int *err) {
+    std::vector<int> zero(rows, 0), len(rows, 0), seq(rows), out[5];
+    for (auto &v : out) v.assign(rows, 0);
+    std::vector<float> ring(rows * 5, 0.f), hb(rows);
+    std::vector<uint8_t> mid(rows), dec(rows);
+    for (int r = 0; r < rows; ++r) seq[r] = r;
+    int hdr[4] = {rows, rows, 0, 0};
+    FinArgs a{};
+    a.s.tokens = tok; a.s.len = len.data(); a.s.model = out[0].data(); a.s.c = out[1].data(); a.s.ngen = zero.data();
+    a.s.done = out[2].data(); a.s.last_step = out[3].data(); a.s.ring = ring.data(); a.s.out_tok = out[4].data(); a.s.out_mid = mid.data();
+    a.s.out_H = H; a.s.out_Hbar = hb.data(); a.s.out_dec = dec.data(); a.s.err = err; a.s.max_batch = rows; a.s.max_seq = 1; a.s.cap = 1;
+    a.p.hdr = hdr; a.p.lm_seq = seq.data();
+    a.cfg = GateCfg{5, 0.f, 1};
+    a.partials = partials; a.n_part = n_part; a.max_new = 2; a.eos_id = -1; a.force_model = -1; a.sampling = sampling;
+    *err = 0;
+    host_launch((unsigned)rows, kFinThreads, [=] { k_lm_finalize(a); });
+}
+
+// lm_fold over `groups` groups of 8 row blocks, as the lane that holds rows 0..3 of every block; inv_t 0: greedy.
+void host_fold(const float *logits /* [groups][8][4] */, int groups, int last_have, float inv_t, EntPartial *out) {
+    LinArgs<bf16_t> a{};
+    a.samp_inv_t = inv_t;
+    EntStat st; st.init();
+    for (int g = 0; g < groups; ++g) {
+        f32x4_t acc[kLmRows];
+        for (int j = 0; j < kLmRows; ++j) for (int e = 0; e < 4; ++e) acc[j][e] = logits[(g * kLmRows + j) * 4 + e];
+        lm_fold(a, acc, g * kLmRows * 16, g + 1 == groups ? last_have : kLmRows, 0, true, 0, 0, st);
+    }
+    out->m = st.m; out->Z = st.Z; out->S = st.S; out->idx = st.idx; out->gs = st.gs; out->gidx = st.gidx;
+}
+
+}  // extern "C"

@@ -1,0 +1,95 @@
+"""CPU: kernels of the library compiled for the host (tests/host_kernels.cpp), on inputs that are shown to be handled before
+a GPU sees them: logits that are not finite must leave a token inside the vocabulary."""
+import ctypes as C
+import os
+import subprocess
+
+import numpy as np
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+CLANG = "/opt/rocm/llvm/bin/clang++"
+PARTIAL = np.dtype([("m", "f4"), ("Z", "f4"), ("S", "f4"), ("idx", "i4"), ("gs", "f4"), ("gidx", "i4")])
+NONE = 0x7FFFFFFF
+
+
+@pytest.fixture(scope="module")
+def host(tmp_path_factory):
+    so = str(tmp_path_factory.mktemp("host") / "host_kernels.so")
+    subprocess.run([CLANG, "-x", "c++", "-std=c++17", "-O1", "-fPIC", "-shared", "-w", "-I", os.path.join(HERE, "host_hip"),
+                    "-I", os.path.join(os.path.dirname(HERE), "paper_2502_06833_amd", "csrc"),
+                    os.path.join(HERE, "host_kernels.cpp"), "-o", so, "-lpthread"], check=True)
+    return C.CDLL(so)
+
+
+def _finalize(host, parts, sampling):
+    rows, n = parts.shape
+    tok, H, err = np.full(rows, -1, np.int32), np.zeros(rows, np.float32), np.zeros(1, np.int32)
+    host.host_finalize(parts.ctypes.data_as(C.c_void_p), rows, n, int(sampling), tok.ctypes.data_as(C.c_void_p),
+                       H.ctypes.data_as(C.c_void_p), err.ctypes.data_as(C.c_void_p))
+    return tok, H, int(err[0])
+
+
+def _partials(n, rng):
+    p = np.zeros((1, n), PARTIAL)
+    p["m"] = rng.integers(0, 5, n); p["Z"] = 1 + rng.random(n); p["S"] = -rng.random(n); p["idx"] = 16 * np.arange(n) + rng.integers(0, 16, n)
+    p["gs"] = rng.integers(0, 5, n); p["gidx"] = 16 * np.arange(n) + rng.integers(0, 16, n)
+    return p
+
+
+@pytest.mark.parametrize("n", [1, 37, 64, 65, 256, 512, 1024])
+@pytest.mark.parametrize("sampling", [False, True])
+def test_finalize_picks_a_token_of_the_vocabulary(host, n, sampling):
+    p = _partials(n, np.random.default_rng(n))
+    key, idx = ("gs", "gidx") if sampling else ("m", "idx")
+    tok, H, err = _finalize(host, p, sampling)                       # finite: the lowest index of the largest value
+    assert tok[0] == p[idx][0][p[key][0] == p[key].max()].min() and np.isfinite(H[0]) and err == 0
+    for bad in (np.ones(n, bool), np.arange(n) < 64, np.arange(n) >= 64, np.arange(n) % 3 != 1):
+        q = p.copy()
+        for k in ("m", "Z", "S"):
+            q[k][0][bad] = np.nan
+        q["gs"][0][bad] = -np.inf                                    # a NaN score never beats the running maximum
+        q["gidx"][0][bad] = NONE
+        tok, H, err = _finalize(host, q, sampling)
+        good = ~bad
+        if good.any():
+            assert tok[0] == q[idx][0][good][q[key][0][good] == q[key][0][good].max()].min()
+        else:
+            assert tok[0] == q["idx"].min()
+        if bad.any():
+            assert np.isnan(H[0]) and err == 1
+
+
+def test_finalize_without_a_perturbed_score_takes_the_arg_max(host):
+    """l / T can overflow to -inf in every entry while the logits are finite."""
+    p = _partials(100, np.random.default_rng(0))
+    p["gs"] = -np.inf; p["gidx"] = NONE
+    tok, H, err = _finalize(host, p, True)
+    assert tok[0] == p["idx"][0][p["m"][0] == p["m"].max()].min() and np.isfinite(H[0]) and err == 0
+
+
+@pytest.mark.parametrize("groups,have", [(1, 8), (1, 1), (3, 5)])
+def test_lm_fold_keeps_an_index_of_the_vocabulary(host, groups, have):
+    rng = np.random.default_rng(groups)
+    blocks = (groups - 1) * 8 + have
+    base = rng.normal(size=(groups * 8, 4)).astype(np.float32)
+    place = 16 * np.arange(groups * 8)[:, None] + np.arange(4)
+    for bad in ("none", "all", "first group", "scattered", "-inf"):
+        x = base.copy()
+        if bad == "all":
+            x[:] = np.nan
+        elif bad == "first group":
+            x[:8] = np.nan
+        elif bad == "scattered":
+            x[rng.random(x.shape) < 0.5] = np.nan
+        elif bad == "-inf":
+            x[:] = -np.inf
+        out = np.zeros(1, PARTIAL)
+        host.host_fold(x.ctypes.data_as(C.c_void_p), groups, have, C.c_float(0.0), out.ctypes.data_as(C.c_void_p))
+        v, where = x[:blocks].ravel(), place[:blocks].ravel()
+        finite = v[np.isfinite(v)]
+        if len(finite):
+            assert out["idx"][0] == where[v == finite.max()].min(), bad
+        else:
+            assert out["idx"][0] in where, bad
+        assert bool(np.isfinite(out["Z"][0])) == (bad == "none" or bool(np.isfinite(v).all())), bad
