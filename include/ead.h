@@ -213,7 +213,9 @@ ead_status ead_replay(ead_handle *h, const int32_t *prompt_tokens, const int32_t
  * Limits: 1 <= rows <= 4096, vocab a multiple of 8 and at most 1048576.
  * The per-chunk statistics go through a 6 MB buffer per device that the first call on that
  * device allocates and the process keeps; all calls on a device share it, so calls whose
- * work overlaps on the GPU (different streams) race: issue them on one stream or wait in between. */
+ * work overlaps on the GPU (different streams) race: issue them on one stream or wait in between.
+ * Calls that raced may leave wrong values in their outputs or not write them at all; later calls, and
+ * calls a graph has captured, are not affected. */
 ead_status ead_entropy_argmax(const void *logits_dev, int32_t dtype, int32_t rows, int32_t vocab,
                               int32_t unit, float *H_dev, int32_t *argmax_dev, void *hip_stream);
 /* The same computation for callers that cannot allocate device memory (code under HIP graph

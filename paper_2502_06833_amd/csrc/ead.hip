@@ -1446,13 +1446,15 @@ constexpr int kEntMaxDevices = 16;
 constexpr size_t kEntFoldBytes = (size_t)4 << 20;      // largest input of ead_entropy_argmax that takes one launch
 
 static __device__ __align__(256) unsigned char scratch[(size_t)kEntStaticPartials * sizeof(EntPartial)];
+// arrival words of the one-launch form (k_entropy_partial): zero when the library is loaded, so that no call has to clear them
+static __device__ unsigned long long arrivals[kEntMaxRows];
 
 struct EntDevice {                // per device, set up once by the first call on it
     bool ready = false;
     int resident = 1024;          // workgroups of k_entropy_partial the chip holds at once
     EntPartial *static_part = nullptr;     // device address of `scratch` on this device
     EntPartial *heap_part = nullptr;       // ead_entropy_argmax's buffer, allocated on first use
-    unsigned long long *heap_words = nullptr;      // and its arrival words, [kEntMaxRows], zero at first (k_entropy_partial)
+    unsigned long long *words = nullptr;   // device address of `arrivals` on this device
     unsigned long long calls = 0;          // numbers the calls that use them
 };
 EntDevice g_ent_dev[kEntMaxDevices];
@@ -1471,6 +1473,9 @@ ead_status entropy_device(EntDevice **out) {
         const hipError_t e = hipGetSymbolAddress(&p, HIP_SYMBOL(scratch));
         if (e != hipSuccess || !p) return fail(nullptr, EAD_ERR_DEVICE, "hipGetSymbolAddress(scratch): %s", hipGetErrorString(e));
         d.static_part = (EntPartial *)p;
+        const hipError_t e2 = hipGetSymbolAddress(&p, HIP_SYMBOL(arrivals));
+        if (e2 != hipSuccess || !p) return fail(nullptr, EAD_ERR_DEVICE, "hipGetSymbolAddress(arrivals): %s", hipGetErrorString(e2));
+        d.words = (unsigned long long *)p;
         int per_cu = 0;
         hipDeviceProp_t prop;
         if (hipGetDeviceProperties(&prop, dev) == hipSuccess &&
@@ -1482,24 +1487,26 @@ ead_status entropy_device(EntDevice **out) {
     return EAD_OK;
 }
 
-// *call: a number of its own for this call, shifted past the count (k_entropy_partial)
+// ead_entropy_argmax's buffer; *call: a number of its own for this call, shifted past the count (k_entropy_partial)
 ead_status entropy_heap_scratch(EntDevice *d, EntPartial **out, unsigned long long *call) {
     std::lock_guard<std::mutex> lock(g_ent_mutex);
     if (!d->heap_part) {
         void *p = nullptr;
-        const size_t bytes = sizeof(EntPartial) * (size_t)kEntMaxRows * kEntMaxChunks;      // a multiple of 8
-        if (hipMalloc(&p, bytes + sizeof(unsigned long long) * kEntMaxRows) != hipSuccess)
+        if (hipMalloc(&p, sizeof(EntPartial) * (size_t)kEntMaxRows * kEntMaxChunks) != hipSuccess)
             return fail(nullptr, EAD_ERR_OOM, "scratch allocation failed");
-        unsigned long long *words = (unsigned long long *)((char *)p + bytes);
-        if (hipMemset(words, 0, sizeof(unsigned long long) * kEntMaxRows) != hipSuccess || hipDeviceSynchronize() != hipSuccess) {
-            (void)hipGetLastError(); (void)hipFree(p);
-            return fail(nullptr, EAD_ERR_DEVICE, "clearing the scratch failed");
-        }
-        d->heap_part = (EntPartial *)p; d->heap_words = words;
+        d->heap_part = (EntPartial *)p;
     }
     *out = d->heap_part;
     *call = ++d->calls << kEntCountBits;
     return EAD_OK;
+}
+
+// A launch that a graph records keeps the number it was recorded with, so it must not use the arrival words: a later
+// eager call that overlapped another one may have left a higher number there.
+bool stream_records(hipStream_t st) {
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(st, &status) != hipSuccess) { (void)hipGetLastError(); return true; }
+    return status != hipStreamCaptureStatusNone;
 }
 
 // The split of a row into work items depends on (rows, V) alone, so a step's result does not depend on
@@ -1534,7 +1541,7 @@ void launch_entropy_folded(const void *logits, int rows, int V, EntPartial *part
     entropy_split(rows, V, &a.chunks, &a.vec_per_item);
     a.step_logits[0] = (const T *)logits;
     a.V = V; a.rows = rows; a.items = rows * a.chunks; a.partials = part;
-    a.words = d->heap_words; a.call = call; a.unit = unit; a.H = H; a.argmax = argmax;
+    a.words = d->words; a.call = call; a.unit = unit; a.H = H; a.argmax = argmax;
     hipLaunchKernelGGL((k_entropy_partial<T, true>), dim3(std::min(a.items, d->resident)), dim3(256), 0, st, a);
 }
 
@@ -2018,8 +2025,9 @@ ead_status entropy_argmax_impl(const void *logits_dev, int32_t dtype, int32_t ro
     }
     // Small inputs take one launch: the call is bound by the host then (128256 bf16 logits: 10.2 us against 13.0), and the
     // last workgroup's chain of counter and partials, 3-4 us, is hidden.  It is not behind a kernel of 8 us and more (97 x 50264
-    // float32: 14.6 us against 12.9).  Always two for the entry point that has no counters, only the static array.
-    if (!use_static && (size_t)rows * vocab * (dtype == EAD_BF16 ? 2 : 4) <= kEntFoldBytes) {
+    // float32: 14.6 us against 12.9).  Always two under capture (stream_records) and for the entry point that shares its
+    // array with captured calls.
+    if (!use_static && (size_t)rows * vocab * (dtype == EAD_BF16 ? 2 : 4) <= kEntFoldBytes && !stream_records(st)) {
         if (dtype == EAD_BF16) launch_entropy_folded<bf16_t>(logits_dev, rows, vocab, part, d, call, unit, H_dev, argmax_dev, st);
         else launch_entropy_folded<float>(logits_dev, rows, vocab, part, d, call, unit, H_dev, argmax_dev, st);
         if (hipGetLastError() != hipSuccess) return fail(nullptr, EAD_ERR_DEVICE, "kernel launch failed");

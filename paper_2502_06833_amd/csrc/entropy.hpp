@@ -146,8 +146,9 @@ struct EntArgs {
     EntPartial *partials;                     // [items]
     // FOLD (one step): the workgroup that finishes a row's last chunk merges its partials and writes the results, which
     // saves the second launch.  Its arrival is counted in a word per row, zero between calls, that also holds the
-    // number of the call (count in the low kEntCountBits): a call first raises the word to its own number, so a count
-    // left behind by calls that overlapped never counts for a later one.
+    // number of the call (count in the low kEntCountBits): a call first raises the word to its own number, so what calls
+    // that overlapped have left there (a count, or a number between theirs) does not count for one with a higher number.
+    // Numbers rise from launch to launch, which a launch replayed by a graph would not: those take the two-launch form.
     unsigned long long *words, call;          // [rows]; call number << kEntCountBits
     int unit; float *H; int *argmax;
 };
