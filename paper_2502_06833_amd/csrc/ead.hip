@@ -21,6 +21,7 @@
 #include "common.hpp"
 #include "entropy.hpp"
 #include "linear.hpp"
+#include "rules.hpp"
 #include "state.hpp"
 #include "fused.hpp"
 #include "stream.hpp"
@@ -1440,10 +1441,9 @@ ead_status fetch_impl(ead_handle *h, int stride, int32_t *tok, uint8_t *mid, flo
 // ead_entropy_argmax: a per-device buffer that the first call on a device allocates (kept until the
 // process ends).  A gate owns a buffer of its own.  ead_entropy_argmax_static: the file-scope device
 // array below, for callers that must not allocate.
-constexpr int kEntMaxRows = 4096, kEntMaxChunks = 64;
+constexpr int kEntMaxRows = 4096;
 constexpr int kEntStaticPartials = 16384;              // rows * chunks a call of ead_entropy_argmax_static may need
 constexpr int kEntMaxDevices = 16;
-constexpr size_t kEntFoldBytes = (size_t)4 << 20;      // largest input of ead_entropy_argmax that takes one launch
 
 static __device__ __align__(256) unsigned char scratch[(size_t)kEntStaticPartials * sizeof(EntPartial)];
 // arrival words of the one-launch form (k_entropy_partial): zero when the library is loaded, so that no call has to clear them
@@ -1507,19 +1507,6 @@ bool stream_records(hipStream_t st) {
     hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(st, &status) != hipSuccess) { (void)hipGetLastError(); return true; }
     return status != hipStreamCaptureStatusNone;
-}
-
-// The split of a row into work items depends on (rows, V) alone, so a step's result does not depend on
-// how many steps share a launch, nor on which entry point asked for it.  Long chunks (up to 8 vectors
-// per thread) amortise the per-workgroup merge; shorter ones only when the rows of one step would
-// otherwise give too few workgroups to fill the chip.
-void entropy_split(int rows, int V, int *chunks_out, int *per_out) {
-    const int nvec = V / 8;
-    int chunks = std::max(1, (nvec + 2047) / 2048);
-    while ((long)chunks * rows < 512 && chunks < kEntMaxChunks && nvec / (chunks * 2) >= 256) chunks *= 2;
-    int per = (std::max(nvec, 1) + chunks - 1) / chunks;
-    while (per > 8 * 256) { ++chunks; per = (nvec + chunks - 1) / chunks; }
-    *chunks_out = chunks; *per_out = per;
 }
 
 template <typename T>
@@ -2023,11 +2010,9 @@ ead_status entropy_argmax_impl(const void *logits_dev, int32_t dtype, int32_t ro
     } else {
         TRY(entropy_heap_scratch(d, &part, &call));
     }
-    // Small inputs take one launch: the call is bound by the host then (128256 bf16 logits: 10.2 us against 13.0), and the
-    // last workgroup's chain of counter and partials, 3-4 us, is hidden.  It is not behind a kernel of 8 us and more (97 x 50264
-    // float32: 14.6 us against 12.9).  Always two under capture (stream_records) and for the entry point that shares its
-    // array with captured calls.
-    if (!use_static && (size_t)rows * vocab * (dtype == EAD_BF16 ? 2 : 4) <= kEntFoldBytes && !stream_records(st)) {
+    // One launch where the counting of arrivals costs less than a second launch (entropy_folds).  Always two under capture
+    // (stream_records) and for the entry point that shares its array with captured calls.
+    if (!use_static && entropy_folds(rows, chunks, (size_t)rows * vocab * (dtype == EAD_BF16 ? 2 : 4)) && !stream_records(st)) {
         if (dtype == EAD_BF16) launch_entropy_folded<bf16_t>(logits_dev, rows, vocab, part, d, call, unit, H_dev, argmax_dev, st);
         else launch_entropy_folded<float>(logits_dev, rows, vocab, part, d, call, unit, H_dev, argmax_dev, st);
         if (hipGetLastError() != hipSuccess) return fail(nullptr, EAD_ERR_DEVICE, "kernel launch failed");

@@ -6,6 +6,7 @@
 #include "linear.hpp"
 #undef HOST_SHARED
 #define HOST_SHARED static
+#include "rules.hpp"
 #include "state.hpp"
 
 using namespace ead;
@@ -42,6 +43,13 @@ void host_fold(const float *logits /* [groups][8][4] */, int groups, int last_ha
         lm_fold(a, acc, g * kLmRows * 16, g + 1 == groups ? last_have : kLmRows, 0, true, 0, 0, st);
     }
     out->m = st.m; out->Z = st.Z; out->S = st.S; out->idx = st.idx; out->gs = st.gs; out->gidx = st.gidx;
+}
+
+// 1 if ead_entropy_argmax takes one launch for [rows, V] logits of `size` bytes each
+int host_entropy_folds(int rows, int V, int size) {
+    int chunks, per;
+    entropy_split(rows, V, &chunks, &per);
+    return entropy_folds(rows, chunks, (size_t)rows * V * size);
 }
 
 }  // extern "C"

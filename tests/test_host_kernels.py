@@ -1,5 +1,6 @@
 """CPU: kernels of the library compiled for the host (tests/host_kernels.cpp), on inputs that are shown to be handled before
-a GPU sees them: logits that are not finite must leave a token inside the vocabulary."""
+a GPU sees them: logits that are not finite must leave a token inside the vocabulary.  Also the rules of dispatch, at sizes
+where the other side was measured slower."""
 import ctypes as C
 import os
 import subprocess
@@ -93,3 +94,11 @@ def test_lm_fold_keeps_an_index_of_the_vocabulary(host, groups, have):
         else:
             assert out["idx"][0] in where, bad
         assert bool(np.isfinite(out["Z"][0])) == (bad == "none" or bool(np.isfinite(v).all())), bad
+
+
+@pytest.mark.parametrize("rows,V,size,one", [
+    (1, 8, 2, 1), (1, 262144, 2, 1), (3, 151936, 2, 1), (16, 50264, 4, 1), (64, 32000, 2, 1), (600, 512, 2, 1),
+    (24, 50264, 2, 0), (7, 128256, 2, 0), (13, 151936, 2, 0), (4, 262144, 2, 0), (2000, 512, 2, 0), (4096, 64, 4, 0),      # in one launch: 6-47 % slower
+    (97, 50264, 4, 0)])
+def test_small_entropy_calls_take_one_launch_where_that_is_faster(host, rows, V, size, one):
+    assert host.host_entropy_folds(rows, V, size) == one
