@@ -1553,28 +1553,20 @@ void entropy_launch(const void *const *step_logits, int steps, int dtype, int ro
     else launch_entropy_partial<float>(step_logits, steps, rows, vocab, part, resident, st);
 }
 
-// Pieces a row is given to workgroups in (1: a workgroup takes whole rows), by rows and vocabulary alone.  One or two rows:
-// pieces of 512 vectors and more, 64 at most (2 rows x 151936: 3 steps 31 -> 16 us, 40 steps 76 -> 71).  From more rows on the
-// pieces' merges cost more over 16 steps than the fuller chip gives (8 rows x 151936, 40 steps: 75 whole, 132 in pieces).
-int entropy_row_parts(int rows, int V) {
-    const int nvec = V / 8;
-    if (rows > 2 || nvec < 1024) return 1;
-    const int least = (nvec + 2047) / 2048;                       // at most 8 vectors per thread and piece
-    return std::max(std::max(least, 2), std::min(std::min(kEntMaxChunks, 256 / rows), nvec / 512));
-}
-
 template <typename T>
 void launch_entropy_rows(const void *const *step_logits, int steps, int rows, int V, int resident, hipStream_t st,
                          const GateStepArgs &gate, float *pair_H, int *row_tickets, EntPartial *partials, int *pair_tickets) {
-    const int nvec = V / 8;
-    EntRowArgs<T> a{};
+    const int nvec = V / 8, parts = entropy_row_parts(rows, V);
+    EntPieceArgs<T> a{};
     for (int z = 0; z < steps; ++z) a.step_logits[z] = (const T *)step_logits[z];
     a.V = V; a.rows = rows; a.steps = steps;
-    a.parts = entropy_row_parts(rows, V); a.partials = partials; a.pair_tickets = pair_tickets;
-    a.chunks = a.parts > 1 ? a.parts : std::max(1, (nvec + 2047) / 2048);      // pieces of at most 8 vectors per thread
+    a.parts = parts; a.partials = partials; a.pair_tickets = pair_tickets;
+    a.chunks = parts > 1 ? parts : std::max(1, (nvec + 2047) / 2048);      // pieces of at most 8 vectors per thread
     a.vec_per_item = (std::max(nvec, 1) + a.chunks - 1) / a.chunks;
     a.pair_H = pair_H; a.row_tickets = row_tickets; a.gate = gate;
-    hipLaunchKernelGGL((k_entropy_rows<T>), dim3(std::min(steps * rows * a.parts, resident)), dim3(256), 0, st, a);
+    const dim3 grid(std::min(steps * rows * parts, resident));
+    if (parts > 1) hipLaunchKernelGGL((k_entropy_rows<T, true>), grid, dim3(256), 0, st, a);
+    else hipLaunchKernelGGL((k_entropy_rows<T, false>), grid, dim3(256), 0, st, static_cast<const EntRowArgs<T> &>(a));
 }
 
 }  // namespace

@@ -3,6 +3,7 @@
 #pragma once
 #include "common.hpp"
 #include "linear.hpp"
+#include <type_traits>
 
 namespace ead {
 
@@ -317,10 +318,9 @@ __global__ __launch_bounds__(256) void k_entropy_partial(EntArgs<T> a) {
 // and leaves the row's entropy and arg max.  The workgroup that does so for the last of a row's steps
 // in this launch (arrival counter per row, left at zero) reads the row's entropies back and takes its
 // window and switch rule through the steps in order.  One launch per up to kGateMaxSteps steps.
-// With few rows a workgroup per (row, step) leaves most of the chip idle (two rows x 3 steps of 151936 logits: six
-// workgroups, 35 us); `parts` > 1 gives every piece of a row a workgroup, which leaves a partial, and the last to
-// arrive at the row's step merges them.  The split follows rows and vocabulary alone, so that a step's result does
-// not depend on how many steps share a launch.
+// With few rows a workgroup per (row, step) leaves most of the chip idle (two rows x 3 steps: six workgroups); `parts` > 1
+// gives every piece of a row a workgroup (SPLIT: its indexes and arguments cost whole rows 0.5 us a launch), which leaves a
+// partial, and the last to arrive at the row's step merges them (entropy_row_parts: which rows, and what it measured).
 // ---------------------------------------------------------------------------------------
 constexpr int kGateFoldWindow = 64;     // largest window this kernel serves (its LDS copy of the ring)
 
@@ -330,10 +330,14 @@ struct EntRowArgs {
     int V, rows, steps, chunks, vec_per_item; // a row is walked in `chunks` pieces of vec_per_item vectors (<= 8 per thread)
     float *pair_H;                            // [steps * rows]: the entropies, handed between workgroups (written through)
     int *row_tickets;                         // [rows] arrival counters, zero between launches
-    int parts;                                // 1, or = chunks: a workgroup per piece
-    EntPartial *partials; int *pair_tickets;  // parts > 1: [steps * rows * parts], [steps * rows] counters, zero between launches
     GateStepArgs gate;                        // state, configuration and outputs (partials unused)
 };
+template <typename T>
+struct EntPieceArgs : EntRowArgs<T> {         // a workgroup per piece: parts = chunks
+    int parts;
+    EntPartial *partials; int *pair_tickets;  // [steps * rows * parts], [steps * rows] counters, zero between launches
+};
+template <typename T, bool SPLIT> using EntRowsArgs = std::conditional_t<SPLIT, EntPieceArgs<T>, EntRowArgs<T>>;
 
 template <typename T>
 __device__ __forceinline__ EntItem<T> ent_row_item(const EntRowArgs<T> &a, int pair, int chunk) {
@@ -345,16 +349,16 @@ __device__ __forceinline__ EntItem<T> ent_row_item(const EntRowArgs<T> &a, int p
     return it;
 }
 
-template <typename T>
-__global__ __launch_bounds__(256) void k_entropy_rows(EntRowArgs<T> a) {
+template <typename T, bool SPLIT>
+__global__ __launch_bounds__(256) void k_entropy_rows(EntRowsArgs<T, SPLIT> a) {
     __shared__ float s_max[4], s_Z[4], s_S[4];
     __shared__ int s_idx[4], s_last_row, s_last_part;
     __shared__ float s_H[kGateMaxSteps], s_hb[kGateMaxSteps], s_ring[kGateFoldWindow];
     const int tid = threadIdx.x, pairs = a.steps * a.rows;
-    // uniform, kept in scalar registers.  parts = 1: (pair, chunk) walks whole rows; else blockIdx.x and its successors number
-    // the pieces of all rows
-    const bool split = a.parts > 1;
-    int item = blockIdx.x, pair = split ? item / a.parts : item, chunk = split ? item % a.parts : 0;
+    // uniform, kept in scalar registers.  (pair, chunk) walks whole rows; SPLIT: blockIdx.x and its successors number the
+    // pieces of all rows
+    int item = blockIdx.x, pair = item, chunk = 0;
+    if constexpr (SPLIT) { pair = item / a.parts; chunk = item % a.parts; }
     if (pair >= pairs) return;
     EntItem<T> it = ent_row_item(a, pair, chunk);
     Vec8<T> A[4], B[4], C[4];
@@ -365,9 +369,10 @@ __global__ __launch_bounds__(256) void k_entropy_rows(EntRowArgs<T> a) {
     // next row).  Returns true after the last piece.
     auto one_piece = [&](Vec8<T> (&first)[4], Vec8<T> (&next)[4]) __attribute__((always_inline)) -> bool {
         ent_load4(B, it, 4);
-        const bool row_done = split || chunk + 1 == a.chunks;
+        const bool row_done = SPLIT || chunk + 1 == a.chunks;
         const int nitem = row_done ? item + (int)gridDim.x : item;
-        const int npair = split ? nitem / a.parts : nitem, nchunk = split ? nitem % a.parts : (row_done ? 0 : chunk + 1);
+        int npair = nitem, nchunk = row_done ? 0 : chunk + 1;
+        if constexpr (SPLIT) { npair = nitem / a.parts; nchunk = nitem % a.parts; }
         const bool more = npair < pairs;
         const EntItem<T> nit = ent_row_item(a, more ? npair : pair, more ? nchunk : chunk);
         __builtin_amdgcn_sched_barrier(0);
@@ -409,7 +414,7 @@ __global__ __launch_bounds__(256) void k_entropy_rows(EntRowArgs<T> a) {
                 st.idx = min(min(s_idx[0], s_idx[1]), min(s_idx[2], s_idx[3]));
             }
             bool whole = true;                  // st holds the whole row's statistics
-            if (split) {
+            if constexpr (SPLIT) {
                 if (tid == 0) {
                     put_partial(a.partials + item, st);
                     wait_stores();

@@ -31,4 +31,16 @@ inline bool entropy_folds(int rows, int chunks, size_t bytes) {
     return bytes <= ((size_t)4 << 20) && (long)rows * chunks <= 600 && (long)rows * chunks * chunks <= 4800;
 }
 
+// Pieces a row is given to workgroups in by k_entropy_rows (1: a workgroup takes whole rows, 2048 vectors at a time), by rows
+// and vocabulary alone, so that a step's result does not depend on how many steps share a launch.  One or two rows of
+// more than three times 2048 vectors: eight pieces (more where 2048 vectors ask for it), which keep 16 steps of two rows
+// at about one workgroup per compute unit
+// (2 rows x 151936: one step 19.5 -> 9.9 us, 64 steps 90 -> 58; 37 pieces: 10.4 and 105).  Shorter rows are through
+// before a piece's partial and counter are (1 x 32000: whole 7.3 and 45 us, in pieces 9.6 and 50).  From more rows on the pieces'
+// merges cost more over 16 steps than the fuller chip gives (8 rows x 151936, 40 steps: 75 whole, 132 in pieces).
+inline int entropy_row_parts(int rows, int V) {
+    const int nvec = V / 8, least = (nvec + 2047) / 2048;         // at most 8 vectors per thread and piece
+    return rows > 2 || nvec <= 3 * 2048 ? 1 : std::max(least, 8);
+}
+
 }  // namespace ead

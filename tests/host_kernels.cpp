@@ -52,4 +52,6 @@ int host_entropy_folds(int rows, int V, int size) {
     return entropy_folds(rows, chunks, (size_t)rows * V * size);
 }
 
+int host_entropy_row_parts(int rows, int V) { return entropy_row_parts(rows, V); }
+
 }  // extern "C"

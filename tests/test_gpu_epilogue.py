@@ -141,13 +141,18 @@ def test_multi_step_run_matches_single_steps():
     g1.close(); g2.close()
 
 
-@pytest.mark.parametrize("rows,steps,V", [(1, 1, 8192), (1, 17, 151936), (2, 3, 32000), (3, 20, 128256), (24, 5, 8200), (25, 5, 8200), (7, 4, 8184)])
+@pytest.mark.parametrize("rows,steps,V", [(1, 1, 49152), (1, 1, 49160), (1, 17, 151936), (2, 40, 151936), (2, 5, 50264), (2, 16, 1048576),
+                                          (3, 20, 128256), (25, 5, 8200), (7, 4, 8184)])
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
 def test_gate_with_rows_split_over_workgroups(rows, steps, V, dtype):
-    """Few rows: a row's pieces go to several workgroups.  Entropies against float64 (fp32 sums of up to 151936 terms by at
-    most 256 threads: 1e-5 nats), the same bits step by step as in one call, window and model as gate_trace gives them."""
+    """One or two rows of more than 49152 entries: a row's pieces go to several workgroups (1048576 entries: more pieces than workgroups,
+    so that one takes pieces of several rows); the others are the neighbours that walk whole rows.  Every second tensor has
+    a run of -inf that covers whole pieces.  Entropies against float64 within 1e-5 ln V nats (fp32 sums of at most 64 terms
+    a thread, then trees), the same bits step by step as in one call, window and model as gate_trace gives them."""
     ead = _ead()
     tensors = [si.logits_torch(s, f"split{V}", rows, V, dtype, "cuda") for s in range(min(steps, 4))]
+    for x in tensors[1::2]:
+        x[:, V // 8: V // 2] = -math.inf
     tau = math.log(V) - 2.0
     g, one = ead.Gate(rows, 5, tau, 2), ead.Gate(rows, 5, tau, 2)
     for _ in range(2):                                       # counters are back at zero after a call
@@ -155,8 +160,8 @@ def test_gate_with_rows_split_over_workgroups(rows, steps, V, dtype):
         H, am, mid, hb = (t.cpu().numpy() for t in g.run_logits(tensors, steps))
         for s in range(steps):
             x = tensors[s % len(tensors)].double()
-            lp = torch.log_softmax(x, -1)
-            assert np.abs(H[s] - (-(lp.exp() * lp).sum(-1)).cpu().numpy()).max() < 1e-5 * math.log(V), s
+            ref = torch.special.entr(x.softmax(-1)).sum(-1)
+            assert np.abs(H[s] - ref.cpu().numpy()).max() < 1e-5 * math.log(V), s
             assert (am[s] == x.argmax(-1).cpu().numpy()).all(), s
         for r in range(rows):
             ref_hb, ref_id = oracle.gate_trace(H[:, r], 5, 2, tau)

@@ -102,3 +102,8 @@ def test_lm_fold_keeps_an_index_of_the_vocabulary(host, groups, have):
     (97, 50264, 4, 0)])
 def test_small_entropy_calls_take_one_launch_where_that_is_faster(host, rows, V, size, one):
     assert host.host_entropy_folds(rows, V, size) == one
+
+
+@pytest.mark.parametrize("rows,V,parts", [(1, 8192, 1), (2, 32000, 1), (1, 49152, 1), (1, 49160, 8), (2, 131072, 8), (2, 151936, 10), (3, 151936, 1), (1, 1048576, 64)])
+def test_gate_rows_go_to_workgroups_in_pieces_where_that_is_faster(host, rows, V, parts):
+    assert host.host_entropy_row_parts(rows, V) == parts
