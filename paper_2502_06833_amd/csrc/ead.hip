@@ -789,23 +789,7 @@ ead_status forward_pass(ead_handle *h, int mi, int T, int n_lm, int ctx_max, boo
                            h->plan.row_pos, h->s.max_seq, d, h->x);
     }
     const double attn_bytes = keys_read * 2.0 * NK * sizeof(WT);
-    // attention split: a workgroup (8 waves) takes at least 512 keys; more splits only while
-    // that helps to fill the chip, never more than 16 (the last one merges them all), bounded scratch
-    // (a decode step of one or two rows is a chain of latencies: splits of 128 keys, one workgroup per
-    // query head and split, spread it over more compute units: +3 % tokens/s at batch 1 against 512)
-    // From about 96 (row, KV head) pairs the matrix-core kernel takes contexts of up to 2048 keys whole: there are enough workgroups,
-    // and a launch with splits pays 4-8 us for the partials' way through memory and for the workgroups of short rows
-    // that find nothing to do (contexts 128-1050: 64 rows of the 0.5B shape 13.2 -> 10.2 us, 32 rows of the 14B shape 31.0 ->
-    // 23.0, 20 rows of the 8B shape at 40-700 keys 17.5 -> 14.1; below, 8 rows of the 14B shape: 14.8 against 17.0 whole).
-    const bool whole_rows = is_bf16 && m.layers[0].vtcache && (long)T * m.KV >= 3 * h->n_cu / 8;
-    int chunk = T <= 2 ? 128 : (whole_rows ? 2048 : 512);
-    while ((long)T * m.KV * ((ctx_max + chunk - 1) / chunk) > 1024 && chunk < 65536) chunk <<= 1;
-    while ((ctx_max + chunk - 1) / chunk > kAttnMaxSplits) chunk <<= 1;
-    while (ctx_max > chunk && (long)T * ((ctx_max + chunk - 1) / chunk) > h->items_max) chunk <<= 1;      // a single split leaves no partials
-    // the matrix-core kernel (many rows) is bound by the latency of its short chains of loads, two
-    // workgroups per compute unit at a time: fewer, longer workgroups
-    if (is_bf16 && m.layers[0].vtcache && T > 2 && (long)T * m.KV * ((ctx_max + chunk - 1) / chunk) > 64)
-        while ((long)T * m.KV * ((ctx_max + chunk - 1) / chunk) > 2 * h->n_cu && chunk < 65536) chunk <<= 1;
+    const int chunk = attention_chunk(T, m.KV, hd, ctx_max, is_bf16 && m.layers[0].vtcache, h->n_cu, kAttnMaxSplits, h->items_max);
     const int max_splits = (ctx_max + chunk - 1) / chunk;
 
     for (int l = 0; l < m.L; ++l) {

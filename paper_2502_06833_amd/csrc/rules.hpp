@@ -43,4 +43,37 @@ inline int entropy_row_parts(int rows, int V) {
     return rows > 2 || nvec <= 3 * 2048 ? 1 : std::max(least, 8);
 }
 
+// Keys per split of a pass's attention.  A workgroup takes at least 512 keys; more splits only while that helps to fill the
+// chip, never more than max_splits (the last one merges them all), bounded scratch (items: rows x splits).  A decode
+// step of one or two rows is a chain of latencies: splits of 128 keys, one workgroup per query head and split, spread it
+// over more compute units (+3 % tokens/s at batch 1 against 512).
+//
+// The matrix-core kernel (mfma) from 3/8 of a (row, KV head) pair per compute unit: there are workgroups enough, and a
+// launch with splits pays 4-8 us for the partials' way through memory and for workgroups that find nothing to do.
+//  * pairs for at most half the units: whole up to 896 keys (head dims below 128: 1664), then two splits, one workgroup per unit
+//    (us whole, in 2, 3 and 4 splits at 96 pairs of 5 query heads of 128, every row at 1000 keys 18.8, 18.5, 22.7, 21.3; 1600:
+//    30.5, 23.9, 29.6, 26.8; 2000: 33.3, 28.5, 35.4, 31.4; 4000: 59.9, 49.0, 57.1, 53.8; 6000: 81.2, 59.1, 78.0, 68.2; 128
+//    pairs, 2000 keys: 34.5, 33.7, 38.4, 34.4; rows of 250-2000 keys 34.5, 29.6, 32.3, 30.9; heads of 64, 96 pairs:
+//    2000 keys 17.4, 15.5, 18.9, 16.9; 128 pairs of 7 heads of 64: 1500 keys 14.7 whole, 16.1 in two);
+//  * more pairs: whole up to 2048 keys, since two splits are more workgroups than units (160 pairs, 2000 keys 38.2, 47.9, 41.4, 48.1;
+//    256 pairs 53.4, 57.4, 66.7, 66.1; 64 rows of the 0.5B shape at 128-1050 keys 10.2 whole, 13.2 split).
+// Beyond that, and with fewer pairs (8 rows of the 14B shape at 128-1050 keys: 14.8 against 17.0 whole): the splits that keep
+// two workgroups per unit.  The kernel is bound by the latency of its short chains of loads: fewer, longer workgroups.
+inline int attention_chunk(int T, int KV, int hd, int ctx_max, bool mfma, int n_cu, int max_splits, long items) {
+    const long pairs = (long)T * KV;
+    const auto splits = [&](int chunk) { return (ctx_max + chunk - 1) / chunk; };
+    int chunk = T <= 2 ? 128 : 512;
+    if (mfma && pairs >= 3 * n_cu / 8) {
+        if (2 * pairs <= n_cu && ctx_max > (hd >= 128 ? 896 : 1664)) {
+            if (ctx_max <= 6144) chunk = ((ctx_max + 1) / 2 + 31) & ~31;      // whole blocks of 32 keys
+        } else if (ctx_max <= 2048) chunk = 2048;
+    }
+    while (pairs * splits(chunk) > 1024 && chunk < 65536) chunk <<= 1;
+    while (splits(chunk) > max_splits) chunk <<= 1;
+    while (ctx_max > chunk && (long)T * splits(chunk) > items) chunk <<= 1;   // a single split leaves no partials
+    if (mfma && T > 2 && pairs * splits(chunk) > 64)
+        while (pairs * splits(chunk) > 2 * n_cu && chunk < 65536) chunk <<= 1;
+    return chunk;
+}
+
 }  // namespace ead

@@ -54,4 +54,6 @@ int host_entropy_folds(int rows, int V, int size) {
 
 int host_entropy_row_parts(int rows, int V) { return entropy_row_parts(rows, V); }
 
+int host_attention_chunk(int T, int KV, int hd, int ctx, int mfma, long items) { return attention_chunk(T, KV, hd, ctx, mfma != 0, 256, 16, items); }
+
 }  // extern "C"

@@ -94,3 +94,22 @@ def test_head_layouts_at_the_ends_of_the_range(heads, kv_heads):
     assert err.max() < TOL_LOGIT
     assert np.abs(out["H"] - Hr).max() < TOL_H
     e.close()
+
+
+@pytest.mark.parametrize("heads,kv_heads,hd,rows,lens", [(8, 8, 128, 12, (1003, 897, 30, 520)), (8, 4, 32, 24, (1750, 1409, 733, 60)),
+                                                         (16, 8, 64, 16, (1700, 31, 1000, 851))])
+def test_decode_rows_in_two_key_splits(heads, kv_heads, hd, rows, lens):
+    """96 to 128 (row, KV head) pairs at contexts beyond 896 (head dims below 128: 1664) keys: two splits of an odd number
+    of key blocks, short rows that reach only the first."""
+    import paper_2502_06833_amd as ead
+    shape = si.ModelShape(f"two-{heads}-{kv_heads}-{hd}", 1, heads * hd, heads, kv_heads, 256, 512, 1e-5, 1e4, bf16=True)
+    W = si.model_weights_torch(shape, 1, "cuda", 0.05)
+    om = oracle.Model(shape, {k: v.float().cpu().numpy() for k, v in W.items()})
+    e = ead.EAD(shape, W, shape, W, window=5, tau=0.0, d_min=4, max_batch=rows, max_seq=max(lens) + 8)
+    seqs = [si.prompt_np(7, f"two{n}", n + 4, shape.vocab) for n in lens]
+    refs = [oracle.entropy_rows(om.forward_dense(q[:-1]))[0][n - 1:] for q, n in zip(seqs, lens)]
+    which = [b % len(lens) for b in range(rows)]
+    rp = e.replay([seqs[i][:lens[i]] for i in which], np.stack([seqs[i][lens[i]:] for i in which]), np.zeros((rows, 4), np.uint8))
+    for b, i in enumerate(which):
+        assert np.abs(rp["H"][b] - refs[i]).max() < TOL_H, (b, lens[i])
+    e.close()

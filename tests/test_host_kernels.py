@@ -107,3 +107,26 @@ def test_small_entropy_calls_take_one_launch_where_that_is_faster(host, rows, V,
 @pytest.mark.parametrize("rows,V,parts", [(1, 8192, 1), (2, 32000, 1), (1, 49152, 1), (1, 49160, 8), (2, 131072, 8), (2, 151936, 10), (3, 151936, 1), (1, 1048576, 64)])
 def test_gate_rows_go_to_workgroups_in_pieces_where_that_is_faster(host, rows, V, parts):
     assert host.host_entropy_row_parts(rows, V) == parts
+
+
+@pytest.mark.parametrize("T,KV,hd,ctx,splits", [
+    (12, 8, 128, 700, 1), (12, 8, 128, 1000, 2), (12, 8, 128, 2000, 2), (16, 8, 128, 2000, 2), (16, 8, 128, 4000, 2), (12, 8, 128, 6000, 2),
+    (12, 8, 64, 1000, 1), (12, 8, 64, 2000, 2), (64, 2, 64, 1050, 1), (64, 2, 64, 2000, 2),
+    (18, 8, 128, 2000, 1), (32, 8, 128, 2000, 1), (18, 8, 128, 3000, 3), (20, 8, 128, 3000, 3), (32, 8, 128, 3000, 2),
+    (8, 8, 128, 1050, 3), (1, 8, 128, 500, 4)])
+def test_attention_splits_follow_the_measured_best(host, T, KV, hd, ctx, splits):
+    """Among them the passes that one workgroup per context (12-16 rows at 1000 keys and more) or two splits of 2048 keys
+    (18-20 rows at 3000) had made slower."""
+    chunk = host.host_attention_chunk(T, KV, hd, ctx, 1, C.c_long(2048))
+    assert -(-ctx // chunk) == splits and (splits == 1 or chunk % 32 == 0)
+
+
+def test_attention_splits_stay_within_the_scratch(host):
+    for T in (1, 2, 3, 12, 16, 17, 33, 100, 1024, 4096):
+        for KV in (1, 2, 8, 40):
+            for ctx in (1, 31, 128, 897, 1665, 2048, 2049, 6145, 70001):
+                for mfma in (0, 1):
+                    for hd in (32, 128):
+                        chunk = host.host_attention_chunk(T, KV, hd, ctx, mfma, C.c_long(2048))
+                        splits = -(-ctx // chunk)
+                        assert splits == 1 or (splits <= 16 and T * splits <= 2048 and chunk % 32 == 0), (T, KV, ctx, mfma, hd)
