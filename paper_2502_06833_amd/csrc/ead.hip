@@ -600,6 +600,7 @@ void launch_narrow(ead_handle *h, LinArgs<bf16_t> &a, int T) {
     } else {
         // (the rotary / cache-append epilogue is too heavy to be left to one workgroup per group)
         NarrowPlan np = narrow_plan(NB, KC, h->n_cu, EPI == EPI_RES);
+        if (NT == 4 && np.R == 4) np.R = 2;            // 33 rows and more: such a matrix goes through k_linear_mfma_ls on 256 units
         const auto fits = [&]() { const int NG = (NB + np.R - 1) / np.R; return (size_t)sweeps * np.KS * NG * np.R * NT * 256 <= kSplitKFloats && (long)sweeps * NG <= kSplitKGroups; };
         while (np.KS > 1 && !fits()) --np.KS;
         if (np.KS == 1 && np.R == 4) np.R = 2;
@@ -610,7 +611,7 @@ void launch_narrow(ead_handle *h, LinArgs<bf16_t> &a, int T) {
                 switch (R * 10 + NT) {
                     case 11: EAD_LM(4, 1, 1, 4, true); break; case 12: EAD_LM(4, 1, 2, 4, true); break; case 14: EAD_LM(4, 1, 4, 4, true); break;
                     case 21: EAD_LM(4, 2, 1, 4, true); break; case 22: EAD_LM(4, 2, 2, 4, true); break; case 24: EAD_LM(4, 2, 4, 4, true); break;
-                    case 41: EAD_LM(2, 4, 1, 6, true); break; case 42: EAD_LM(2, 4, 2, 4, true); break; default: EAD_LM(2, 4, 4, 3, true); break;
+                    case 41: EAD_LM(2, 4, 1, 6, true); break; default: EAD_LM(2, 4, 2, 4, true); break;
                 }
                 return;
             }
@@ -625,7 +626,7 @@ void launch_narrow(ead_handle *h, LinArgs<bf16_t> &a, int T) {
 #undef EAD_LM
 }
 
-// The LM head: writes one partial per (row, workgroup) and returns their number per row.  Up to 16 rows through
+// The LM head: writes one partial per (row, workgroup) and returns their number per row (0: no LDS for k_lm_ls).  Up to 16 rows through
 // k_linear_mfma, two waves and two row blocks per workgroup (128256 x 4096: 212 -> 162 us = 6.5 TB/s, 151936 x 5120:
 // 255 -> 238), at 17 to 32 rows with four row blocks while K is long (203 -> 175); otherwise, and where a row block
 // is so short that filling and draining the pipeline per block counts (K < 1280: 50.9 against 57.3 us at 151936 x 896),
@@ -645,10 +646,11 @@ int launch_lm(ead_handle *h, int mi, LinArgs<bf16_t> &a, int T) {
         }
         if (ok) return grid;
     }
+    if (TB > 2) return 0;
+    a.tb_base = 0;
     const int R = TB == 1 ? 2 : 4, grid = std::min((NB + R - 1) / R, 2 * h->n_cu);
     if (TB == 1) hipLaunchKernelGGL((k_linear_mfma<2, 2, 1, 8, EPI_LOGITS, false>), dim3(grid), dim3(128), 0, h->stream, a);
-    else if (TB == 2) hipLaunchKernelGGL((k_linear_mfma<2, 4, 2, 4, EPI_LOGITS, false>), dim3(grid), dim3(128), 0, h->stream, a);
-    else hipLaunchKernelGGL((k_linear_mfma<4, 4, 4, 3, EPI_LOGITS, false>), dim3(grid), dim3(256), 0, h->stream, a);      // no LDS for k_lm_ls
+    else hipLaunchKernelGGL((k_linear_mfma<2, 4, 2, 4, EPI_LOGITS, false>), dim3(grid), dim3(128), 0, h->stream, a);
     return grid;
 }
 
@@ -863,6 +865,7 @@ ead_status forward_pass(ead_handle *h, int mi, int T, int n_lm, int ctx_max, boo
                 { ProfScope ps(h, PK_PACK_ACT, mi, 0.0); hipLaunchKernelGGL(k_pack_act, dim3((n_lm + 15) & ~15), dim3(256), 0, st, pa); }
                 g.xp = h->xp_a;
                 h->lm_n_part = launch_lm(h, mi, g, n_lm);
+                if (!h->lm_n_part) return fail(h, EAD_ERR_DEVICE, "the device does not grant %zu bytes of LDS to a workgroup", kLmLdsBytes);
             }
         } else {
             g.x = h->x; g.ldx = d; g.gain = m.g_final; g.eps = m.eps;
