@@ -175,32 +175,38 @@ def test_gate_with_rows_split_over_workgroups(rows, steps, V, dtype):
 
 
 def test_entropy_calls_in_a_row_and_under_capture():
-    """One launch per call, counters zero between calls: growing and shrinking inputs back to back, two streams in turn, and
-    a captured call replayed between eager ones."""
+    """Calls of one launch (one chunk a row; several rows of 16 and 40 chunks; 4 MiB exactly) and of two (above 4 MiB; many
+    arrivals; more items than the chip holds) back to back, so that every counter has to be back at zero, on two streams
+    in turn, and a captured call of a size that takes one launch when it is eager, replayed between eager ones."""
     ead = _ead()
-    xs = [si.logits_torch(i, "row", r, V, dt, "cuda") for i, (r, V, dt) in enumerate(
-        [(1, 128256, torch.bfloat16), (97, 50264, torch.float32), (3, 8, torch.float32), (600, 4096, torch.bfloat16), (1, 151936, torch.float32)])]
-    ref = [ead.entropy_argmax(x, static=x.shape[0] < 500) for x in xs]
+    one = [(1, 128256, torch.bfloat16), (3, 8, torch.float32), (1, 151936, torch.float32), (3, 151936, torch.bfloat16), (16, 50264, torch.float32),
+           (64, 16384, torch.float32), (600, 512, torch.bfloat16)]
+    two = [(97, 50264, torch.float32), (600, 4096, torch.bfloat16), (64, 16392, torch.float32), (13, 151936, torch.bfloat16), (2000, 512, torch.float32)]
+    xs = [si.logits_torch(i, "row", r, V, dt, "cuda") for i, (r, V, dt) in enumerate(one + two)]
+    ref = [ead.entropy_argmax(x, static=True) for x in xs]               # always two launches, no counters
     ref = [(h.clone(), a.clone()) for h, a in ref]
+    order = [i for pair in zip(range(len(one)), range(len(one), len(xs))) for i in pair] + list(range(len(xs)))
     other = torch.cuda.Stream()
     for rnd in range(3):
-        for x, (h, a) in zip(xs, ref):
-            h1, a1 = ead.entropy_argmax(x)
-            assert torch.equal(h1, h) and torch.equal(a1, a)
+        for i in order:
+            h1, a1 = ead.entropy_argmax(xs[i])
+            assert torch.equal(h1, ref[i][0]) and torch.equal(a1, ref[i][1]), i
             torch.cuda.synchronize()
             with torch.cuda.stream(other):
-                h2, a2 = ead.entropy_argmax(x)
+                h2, a2 = ead.entropy_argmax(xs[i])
             torch.cuda.synchronize()
-            assert torch.equal(h2, h) and torch.equal(a2, a)
-    out = (torch.zeros(97, device="cuda"), torch.zeros(97, dtype=torch.int32, device="cuda"))
+            assert torch.equal(h2, ref[i][0]) and torch.equal(a2, ref[i][1]), i
+    cap = 4                                                              # 16 x 50264 float32
+    out = (torch.zeros(16, device="cuda"), torch.zeros(16, dtype=torch.int32, device="cuda"))
     graph = torch.cuda.CUDAGraph()
     with torch.cuda.graph(graph):
-        ead.entropy_argmax(xs[1], out=out)
+        ead.entropy_argmax(xs[cap], out=out)
     for rnd in range(4):
         out[0].zero_(); out[1].zero_()
         graph.replay()
         torch.cuda.synchronize()
-        assert torch.equal(out[0], ref[1][0]) and torch.equal(out[1], ref[1][1])
-        h1, a1 = ead.entropy_argmax(xs[0])
-        torch.cuda.synchronize()
-        assert torch.equal(h1, ref[0][0])
+        assert torch.equal(out[0], ref[cap][0]) and torch.equal(out[1], ref[cap][1])
+        for i in (cap, 3):
+            h1, a1 = ead.entropy_argmax(xs[i])
+            torch.cuda.synchronize()
+            assert torch.equal(h1, ref[i][0]) and torch.equal(a1, ref[i][1])
