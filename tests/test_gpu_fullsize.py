@@ -250,8 +250,8 @@ def test_qwen_truncated_batch_with_ragged_prompts_and_catchups():
 
 def test_qwen_truncated_1024_row_prefill_against_oracle():
     """Qwen-shaped widths (2 layers each, gains 1 + N(0, 0.3^2)): a 1025-token prompt is prefilled in one pass of
-    1024 rows per model (four sweeps of the 128 x 256 tiles through the large matrices, eight 128-row sweeps through
-    the small model's; attention over up to 1024 keys in row groups); then
+    1024 rows per model (four sweeps of 256 x 256 tiles through the gate/up matrices, of 128 x 256 tiles through the
+    large model's others, eight 128-row sweeps through the small model's others; attention over up to 1024 keys in row groups); then
     Algorithm 1 runs along the oracle's own trajectory: ten small-model tokens, the large model's catch-up of
     eleven rows on top of its 1024 cached positions, two large-model tokens.  Entropies, window means and clear
     arg maxes of all twelve tokens against the oracle."""
@@ -277,9 +277,9 @@ def test_qwen_truncated_1024_row_prefill_against_oracle():
 
 def test_ragged_row_block_counts_in_a_1024_row_prefill_against_oracle():
     """Widths whose row-block counts are not multiples of what a workgroup takes (gate/up of the large model: 740
-    row blocks in groups of 8 through the 128 x 256 tiles; its down projection: 128 row blocks in groups of 5
-    through the 128-row sweeps; the small model's gate/up: 372 row blocks): the last group of every such launch
-    holds row blocks that do not exist.  A 1025-token prompt is prefilled in one pass of 1024 rows per model and
+    row blocks in groups of 16 through the 256 x 256 tiles; the small model's: 372 row blocks in groups of 8 through the 128 x 256
+    tiles): the last group of these launches holds row blocks that do not exist (128-row sweeps with such a group:
+    test_gpu_long_prefill.py).  A 1025-token prompt is prefilled in one pass of 1024 rows per model and
     Algorithm 1 then runs along the oracle's trajectory (ten small-model tokens, the large model's catch-up,
     two large-model tokens); entropies, window means and clear arg maxes against the oracle."""
     from gpu_helpers import check_replay_row, make_pair, trajectory_logit_stats
@@ -301,7 +301,7 @@ def test_ragged_row_block_counts_in_a_1024_row_prefill_against_oracle():
 
 def test_qwen_truncated_long_prefill_agrees_with_scoring():
     """Qwen-shaped widths (2 layers each): a 600-token prompt is prefilled in one pass of 599 rows
-    (38 token blocks: three sweeps of the 128 x 256 tiles or five 128-row sweeps per matrix, the last of them
+    (38 token blocks: three sweeps of the tiled kernels or five 128-row sweeps per matrix, the last of them
     partly empty; row groups of 2 and 3 in the attention); the entropies of the following tokens -- small
     model, then the large one after a 10-row catch-up -- equal those of scoring the same tokens in passes of
     160 rows (two sweeps, one launch pair per sweep where K is split)."""
