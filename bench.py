@@ -209,7 +209,7 @@ def linear_params(shape):
 
 def bench_prefill(args):
     """Prompt prefill of both models (ead_begin): every prompt position but the last through all layers of
-    the small and of the large model, in passes of up to 1024 rows; no LM head.  Reported against the dense
+    the small and of the large model, in passes of up to 4096 rows; no LM head.  Reported against the dense
     bf16 matrix-core peak with the algorithmic flops 2 * parameters * positions (the second product per
     weight tile, for the low parts of the activations, is not counted) plus the causal attention flops."""
     import torch

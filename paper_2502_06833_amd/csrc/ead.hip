@@ -1210,7 +1210,8 @@ ead_status after_tokens(ead_handle *h, const std::vector<char> &emitted, bool al
 // gathered -- the large model's weights are streamed once for many rows instead of once per
 // token position.  The large model starts running when at least `hi` of the unfinished rows
 // wait for it and keeps running until fewer than `lo` do (rows stay on it for at least d_min
-// tokens, so its passes come in bursts).  No row's arithmetic depends on the schedule.
+// tokens, so its passes come in bursts).  The schedule changes a row's arithmetic only through the width of the passes
+// its positions fall into (the order of sums in the linear layers, the splits of its attention).
 // budget < 0: every row produces up to n_tokens more tokens (per-sequence goals).  budget >= 0: the batch as a
 // whole produces at least `budget` more tokens; rows run freely, none more than `lead` tokens ahead of the
 // unfinished row that has produced the fewest, and no pass is started once the budget is met.

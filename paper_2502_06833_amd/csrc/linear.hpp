@@ -1,14 +1,17 @@
 // Weight-streaming linear layers: Y[T, N] = X[T, K] * W[N, K]^T with fused prologues
 // (RMSNorm) and epilogues (rotary + KV append, residual add, SwiGLU, entropy statistics).
 //
-// Two kernels share the tiled weight layout and the epilogues:
-//   k_linear_valu  plain FMA path for a handful of token rows (and for fp32 weights);
-//                  activations stay fp32, staged once per workgroup in LDS.
-//   k_linear_mfma  16x16x32 f16 MFMA path for two or more token rows (batched decode,
-//                  catch-up chunks, prompt prefill); activations are half-precision tiles.
-// In both, a workgroup owns 16-row blocks of W and its waves split K, so a wave reads
-// contiguous streams of 1 KB (2-byte) tiles; partial sums meet in LDS and are added in wave
-// order, so a row's result does not depend on how many rows are in flight.
+// Two paths share the tiled weight layout and the epilogues:
+//   k_linear_valu  plain FMAs for one or two token rows (and for fp32 weights); activations stay fp32,
+//                  staged once per workgroup in LDS.
+//   k_linear_mfma, k_linear_mfma_ls, k_lm_ls, k_linear_mfma_gemm, k_linear_mfma_tile (k_linear_mfma_wt: fallback)
+//                  16x16x32 f16 products for three rows and more (batched decode, catch-up chunks, prompts);
+//                  activations are half-precision tiles.  Which one takes a pass follows the matrix's shape and the
+//                  pass's number of token blocks (launch_mfma, launch_lm).
+// A workgroup owns 16-row blocks of W.  In k_linear_valu and k_linear_mfma its waves split K, so a wave reads contiguous
+// streams of 1 KB (2-byte) tiles; partial sums meet in LDS and are added in wave order.  All sums are taken in an order that
+// the matrix's shape and the number of token blocks fix: a row's result does not depend on what the other rows of
+// its pass hold, but passes of another width class may add in another order.
 #pragma once
 #include "common.hpp"
 
@@ -309,12 +312,12 @@ __global__ __launch_bounds__(NW * 64) void k_linear_valu(LinArgs<WT> a) {
 // Both operands are IEEE halves (common.hpp): the weights keep their bf16 values exactly, the
 // activations are rounded to 11 significant bits (with bf16-rounded activations the logits of a
 // full-depth model drift well past their tolerance; a bf16 hi + lo pair, which this path used
-// first, costs two products and twice the activation traffic per weight tile).  Every output
-// element accumulates its k tiles in ascending order and the waves' sums
-// are added in wave order, whatever R, NT and D are: a row's result does not depend
-// on how many rows share the pass (NW is fixed per matrix shape).  Matrices with few row
-// blocks and a long K are also split along K over KS workgroups per group (SK), whose sums
-// meet in memory; KS follows the matrix shape alone and the slabs are added in order.
+// first, costs two products and twice the activation traffic per weight tile).  Within a wave every
+// output element accumulates its k tiles in ascending order, whatever R, NT and D are, and the waves' sums
+// are added in wave order.  Matrices with few row blocks are also split along K over KS workgroups per
+// group (SK), whose sums meet in memory and are added in order of the slabs.  NW and KS follow the
+// matrix's shape and the number of token blocks (launch_narrow), so they change the order of a row's sums only
+// from one width class of passes to another.
 // ------------------------------------------------------------------------------------
 constexpr int kSplitKMax = 8;       // most K slabs per row-block group
 
@@ -492,16 +495,6 @@ __global__ __launch_bounds__(NW * 64) void k_linear_mfma(LinArgs<bf16_t> a) {
     }
 }
 
-// ------------------------------------------------------------------------------------
-// MFMA path for passes of more than 64 token rows (catch-up chunks of many rows, prompt
-// prefill): 128 token rows per sweep over the weights.  The activation tiles of a k step
-// (8 KB for 128 rows) no longer fit a wave's registers next to a fetch ring, and every
-// wave needs all of them, so the four waves of a workgroup walk K together: each fetches a
-// quarter of the step's activation tiles (ring of DA steps, like its R weight tiles), the
-// quarters meet in LDS (two buffers, one barrier per step), and every wave multiplies its own
-// 16 R weight rows with all 128 token rows.  No sums cross waves.
-// Each output element still accumulates its k tiles in ascending order.
-// ------------------------------------------------------------------------------------
 // ------------------------------------------------------------------------------------
 // The epilogues on the matrix cores' own output layout: lane L of a 16 x 16 block holds weight rows p .. p + 3
 // (p = first row of the block + 4 (L / 16)) of token L % 16, so both halves of a rotary pair or of a gate/up pair are
@@ -1018,8 +1011,8 @@ __global__ __launch_bounds__((NW + kLsProducers) * 64) void k_lm_ls(LinArgs<bf16
 }
 
 // ------------------------------------------------------------------------------------
-// Passes of about 500 rows and more (prompt prefill) through a large matrix.  With 128 rows per
-// workgroup every wave of k_linear_mfma_ls reads all of a step's weight tiles from LDS for one
+// Passes of more than 128 rows (prompt prefill, scoring) through matrices whose 128 x 256 tiles fill the chip (the
+// costs are compared in launch_mfma).  With 128 rows per workgroup every wave of k_linear_mfma_ls reads all of a step's weight tiles from LDS for one
 // token block: 8 KB of LDS reads per 8 products, which is LDS-bound at half the matrix cores'
 // rate, and every workgroup fetches its activation tiles itself.  Here a workgroup covers
 // 8 row blocks x 16 token blocks (128 output rows x 256 token rows); its two fetching waves bring
@@ -1143,8 +1136,9 @@ constexpr int kTileBand = 6;                           // most sweeps that run s
 
 constexpr int kWaitLdsReads = 0xC07F;                  // s_waitcnt lgkmcnt(0), the other counters at their maximum
 
-// 16 bytes per lane from base + voff (base uniform over the wave) to LDS at lds + 16 lane.  Nothing else in the
-// kernels that call this uses M0.
+// 16 bytes per lane from base + voff (base uniform over the wave) to LDS at lds + 16 lane.  M0 cannot be named as clobbered:
+// the compiler reserves it, keeps no value in it from one instruction to the next and sets it itself right before an
+// instruction of its own that reads it (the kernels that call this have none: LDS reads need no M0 here).
 __device__ __forceinline__ void request_tile(const bf16_t *base, uint32_t voff, uint32_t lds) {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(voff), "s"(base) : "memory");
 }
