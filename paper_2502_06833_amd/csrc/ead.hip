@@ -560,67 +560,40 @@ bool launch_ls(ead_handle *h, const LinArgs<bf16_t> &a, int grid) {
 }
 
 // Passes of up to 32 rows, and longer ones through matrices that k_linear_mfma_ls does not serve better: k_linear_mfma, a
-// workgroup of few waves per R row blocks.  These passes are bound by the weight stream and, below some 30 MB of
-// weights, by how evenly the workgroups fall on the compute units, so R and the split of K follow the number of row
-// blocks (measured on rotating weights at 16 rows; before: one rule by matrix size):
-//  * gate/up: many row blocks, no split.  More than four per compute unit: two waves and two row blocks a workgroup, so that
-//    the workgroups are many and all resident (14336 x 4096 gate/up: 54.0 -> 40.7 us = 5.8 TB/s; 13824 x 5120: 50.1 -> 49.1;
-//    at 32 rows, with four row blocks: 51.7 -> 46.9).  Fewer: four waves and two row blocks (8192 x 2048: 17.9 -> 13.6 us).
-//  * others: one row block a workgroup while that is at most one workgroup per compute unit (4096 x 4096: 15.1 -> 8.3 us,
-//    2048 x 2048: 7.5 -> 5.2), else two (5120 x 5120: 18.8 -> 13.1; 320 workgroups of one block: 15.5), and K split over
-//    workgroups only where half the chip would idle and a slab keeps more than 32 k tiles (896 x 4864: 8.0 -> 6.6).
-//  * long K (256 k tiles and more) with half a row block per compute unit and more: two or four row blocks and the K split
-//    that brings one workgroup per compute unit (4096 x 14336: 27.9 -> 21.5 us, 5120 x 13824: 29.5 -> 26.1).
-// Two waves a workgroup where it has enough tiles for both (6144 x 4096 with two row blocks: 12.1 -> 11.5 us; 3072 wide and 17 to
-// 32 rows: 12.2 with four waves, 14.5 with two).
-struct NarrowPlan { int R, KS; };
-NarrowPlan narrow_plan(int NB, int KC, int n_cu, bool may_split) {
-    if (may_split && KC >= 256 && 2 * NB >= n_cu) {
-        const int R = NB > n_cu ? 4 : 2, KS = std::min(kSplitKMax, n_cu / ((NB + R - 1) / R));
-        if (KS > 1) return {R, KS};
-    }
-    const int R = NB <= n_cu ? 1 : 2, NG = (NB + R - 1) / R;
-    int KS = 1;
-    while (may_split && KS < kSplitKMax && (KS + 1) * NG <= n_cu && KC / (KS + 1) > 32) ++KS;
-    return {R, KS};
-}
-
+// workgroup of few waves per R row blocks and NT token blocks (narrow_plan in rules.hpp says how many of each, and how many slabs
+// of K).  Two waves a workgroup where row blocks are many, so that the workgroups are many and all resident: gate/up of up to 16
+// rows (28672 x 4096: 54.0 us with four waves and four row blocks, 40.7 with two and two, 40.2 with two and one; 9728 x 896:
+// 7.1 with four and two, 6.3 with two and one; but 16384 x 3072: 18.0 and 18.7), of 17 to 32 rows with four row blocks (51.7 -> 46.9).
 template <int EPI>
 void launch_narrow(ead_handle *h, LinArgs<bf16_t> &a, int T) {
-    const int NB = a.Np / 16, KC = a.K / 32, TB = (T + 15) / 16;
-    const int NT = TB <= 1 ? 1 : (TB == 2 ? 2 : 4), sweeps = (TB + NT - 1) / NT;
-    int R, KS = 1;
-#define EAD_LM(NW_, R_, NT_, D_, SK_) hipLaunchKernelGGL((k_linear_mfma<NW_, R_, NT_, D_, EPI, SK_>), dim3((NB + R - 1) / R * KS, sweeps), dim3(NW_ * 64), 0, h->stream, a)
+    const int NB = a.Np / 16, KC = a.K / 32, TB = (T + 15) / 16, n_cu = h->n_cu;
+    NarrowPlan p;
+#define EAD_LM(NW_, R_, NT_, D_, SK_) hipLaunchKernelGGL((k_linear_mfma<NW_, R_, NT_, D_, EPI, SK_>), dim3((NB + R_ - 1) / R_ * p.KS, (TB + NT_ - 1) / NT_), dim3(NW_ * 64), 0, h->stream, a)
     if constexpr (EPI == EPI_SWIGLU) {
-        const bool many = NB > 4 * h->n_cu;
-        R = many && NT == 2 ? 4 : 2;
-        if (NT == 1) { if (many) EAD_LM(2, 2, 1, 8, false); else EAD_LM(4, 2, 1, 4, false); }
-        else if (NT == 2) { if (many) EAD_LM(2, 4, 2, 4, false); else EAD_LM(4, 2, 2, 4, false); }
+        const bool many = NB > 4 * n_cu;
+        p.KS = 1;
+        if (TB <= 1) { if (many || KC < 96) EAD_LM(2, 1, 1, 8, false); else EAD_LM(4, 2, 1, 4, false); }
+        else if (TB == 2) { if (many) EAD_LM(2, 4, 2, 4, false); else EAD_LM(4, 2, 2, 4, false); }
         else EAD_LM(4, 2, 4, 4, false);
     } else {
         // (the rotary / cache-append epilogue is too heavy to be left to one workgroup per group)
-        NarrowPlan np = narrow_plan(NB, KC, h->n_cu, EPI == EPI_RES);
-        if (NT == 4 && np.R == 4) np.R = 2;            // 33 rows and more: such a matrix goes through k_linear_mfma_ls on 256 units
-        const auto fits = [&]() { const int NG = (NB + np.R - 1) / np.R; return (size_t)sweeps * np.KS * NG * np.R * NT * 256 <= kSplitKFloats && (long)sweeps * NG <= kSplitKGroups; };
-        while (np.KS > 1 && !fits()) --np.KS;
-        if (np.KS == 1 && np.R == 4) np.R = 2;
-        R = np.R; KS = np.KS;
-        a.KS = KS; a.sk_part = h->sk_part; a.sk_tickets = h->sk_tickets;
+        p = narrow_plan(NB, KC, TB, n_cu, EPI == EPI_RES, kSplitKFloats, kSplitKGroups);
+        a.KS = p.KS; a.sk_part = h->sk_part; a.sk_tickets = h->sk_tickets;
         if constexpr (EPI == EPI_RES) {
-            if (KS > 1) {
-                switch (R * 10 + NT) {
-                    case 11: EAD_LM(4, 1, 1, 4, true); break; case 12: EAD_LM(4, 1, 2, 4, true); break; case 14: EAD_LM(4, 1, 4, 4, true); break;
-                    case 21: EAD_LM(4, 2, 1, 4, true); break; case 22: EAD_LM(4, 2, 2, 4, true); break; case 24: EAD_LM(4, 2, 4, 4, true); break;
+            if (p.KS > 1) {
+                switch (p.R * 10 + p.NT) {
+                    case 11: EAD_LM(4, 1, 1, 4, true); break;
+                    case 21: EAD_LM(4, 2, 1, 4, true); break; case 22: EAD_LM(4, 2, 2, 4, true); break;
                     case 41: EAD_LM(2, 4, 1, 6, true); break; default: EAD_LM(2, 4, 2, 4, true); break;
                 }
                 return;
             }
         }
-        switch (R * 10 + NT) {
-            case 11: EAD_LM(4, 1, 1, 4, false); break; case 12: EAD_LM(4, 1, 2, 4, false); break; case 14: EAD_LM(4, 1, 4, 4, false); break;
-            case 21: EAD_LM(2, 2, 1, 8, false); break;
-            case 22: if (KC >= 128) EAD_LM(2, 2, 2, 6, false); else EAD_LM(4, 2, 2, 4, false); break;
-            default: EAD_LM(4, 2, 4, 4, false); break;
+        switch (p.R * 10 + p.NT) {
+            case 11: EAD_LM(4, 1, 1, 4, false); break; case 12: EAD_LM(4, 1, 2, 4, false); break;
+            case 21: if (TB == 1 && KC >= 128) EAD_LM(2, 2, 1, 8, false); else EAD_LM(4, 2, 1, 4, false); break;
+            case 22: if (TB == 2 && KC >= 128) EAD_LM(2, 2, 2, 6, false); else EAD_LM(4, 2, 2, 4, false); break; case 42: EAD_LM(4, 4, 2, 4, false); break;
+            case 44: EAD_LM(4, 4, 4, 3, false); break; default: EAD_LM(4, 2, 4, 4, false); break;
         }
     }
 #undef EAD_LM

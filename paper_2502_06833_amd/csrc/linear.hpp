@@ -14,6 +14,7 @@
 // its pass hold, but passes of another width class may add in another order.
 #pragma once
 #include "common.hpp"
+#include "rules.hpp"
 
 namespace ead {
 
@@ -319,8 +320,6 @@ __global__ __launch_bounds__(NW * 64) void k_linear_valu(LinArgs<WT> a) {
 // matrix's shape and the number of token blocks (launch_narrow), so they change the order of a row's sums only
 // from one width class of passes to another.
 // ------------------------------------------------------------------------------------
-constexpr int kSplitKMax = 8;       // most K slabs per row-block group
-
 template <int NW, int R, int NT, int D, int EPI, bool SK = false>
 __global__ __launch_bounds__(NW * 64) void k_linear_mfma(LinArgs<bf16_t> a) {
     constexpr int NE = (NT * 256 + NW * 64 - 1) / (NW * 64);     // epilogue elements per thread and row block

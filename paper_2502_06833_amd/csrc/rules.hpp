@@ -43,6 +43,60 @@ inline int entropy_row_parts(int rows, int V) {
     return rows > 2 || nvec <= 3 * 2048 ? 1 : std::max(least, 8);
 }
 
+// How k_linear_mfma takes a matrix of NB row blocks x KC k tiles (QKV and residual projections) in a pass of TB token blocks:
+// R row blocks and NT token blocks a workgroup, K split into KS slabs (may_split: residual projections).
+//
+// These passes are a weight stream and a chain of latencies, so what counts is that every compute unit has a workgroup and that a
+// workgroup has little to do: the smallest R x NT that is at most one workgroup per unit.  A matrix's second and
+// later token blocks find its tiles in L2.  Measured on rotating weights, us, with the former rule (all of up to 64 rows
+// in one workgroup, R by matrix size) -> now: 896 x 896 at 32, 64 and 128 rows 4.2 -> 3.5, 5.4 -> 3.5, 5.4 -> 4.1; 1152 x 896 at 64
+// rows 7.3 -> 5.0 (one block and one: 4.8); 896 x 4864 at 64: 9.8 -> 7.5; 2048 x 2048 at 32: 5.6 -> 4.8; 3072 x 2048 at 64: 9.9 ->
+// 8.5 (R = 1, NT = 2, 384 workgroups: 10.6); 4096 x 4096 at 64: 13.4 -> 12.0.  Of two R x NT of two, the one with more workgroups; of equally many
+// two row blocks (2048 x 2048 at 64 rows: 5.6 against 5.9), from 128 k tiles on two token blocks (896 x 4864 at 96: 9.7 against 11.0).
+// Eight blocks (3072 x 3072 at 160 rows: 20.8 -> 12.9) and sixteen (at 256: 23.8 -> 17.2) only where that leaves one round of
+// workgroups; a QKV projection of few k tiles takes two rounds of small ones instead (1152 x 896 at 320 rows 9.6 -> 8.3).
+//
+// K is split where units would idle and a slab keeps more than 32 k tiles (896 x 4864 at 16 rows: 8.0 -> 6.4; 2048 x 8192: 128
+// workgroups 10.7, two slabs 9.8).  Long K (256 k tiles and more) of 17 to 64 rows: two row blocks and two token blocks,
+// whose tiles are fetched half as often, and the slabs that fill the chip (2048 x 8192 at 64 rows 15.1 -> 14.0, 4096 x
+// 14336 at 32: 28.0 -> 24.5); of up to 16 rows and more than 3/4 of a row block per unit: two or four row blocks (4096 x 14336: 27.9 -> 21.5, 5120 x
+// 13824: 29.5 -> 26.1).
+constexpr int kSplitKMax = 8;       // most slabs of K per row-block group
+
+struct NarrowPlan { int R, NT, KS; };
+
+inline NarrowPlan narrow_plan(int NB, int KC, int TB, int n_cu, bool may_split, size_t most_floats, int most_groups) {
+    const auto groups = [&](int R, int NT) { return (long)((NB + R - 1) / R) * ((TB + NT - 1) / NT); };
+    const auto fits = [&](const NarrowPlan &p) {       // the slabs' sums and the counters have room
+        return (size_t)p.KS * groups(p.R, p.NT) * p.R * p.NT * 256 <= most_floats && groups(p.R, p.NT) <= most_groups;
+    };
+    if (may_split && KC >= 256 && TB <= 4) {
+        NarrowPlan p{0, 0, 1};
+        if (TB >= 2) p = NB > n_cu && TB == 2 ? NarrowPlan{4, 2, 1} : NarrowPlan{2, 2, 1};
+        else if (4 * NB > 3 * n_cu) p = NarrowPlan{NB > n_cu ? 4 : 2, 1, 1};
+        if (p.R) {
+            p.KS = std::min<long>(kSplitKMax, n_cu / groups(p.R, p.NT));
+            if (p.KS > 1 && fits(p)) return p;
+        }
+    }
+    NarrowPlan p{2, 1, 1};
+    const long one = groups(1, 1), rows2 = groups(2, 1), toks2 = groups(1, 2), rows4 = groups(4, 2), toks4 = groups(2, 4);
+    if (one <= n_cu || TB <= 1) p = NarrowPlan{one <= n_cu ? 1 : 2, 1, 1};
+    else if (std::min(rows2, toks2) <= n_cu) {
+        const bool toks = rows2 > n_cu || (toks2 <= n_cu && (toks2 > rows2 || (toks2 == rows2 && KC >= 128)));
+        p = toks ? NarrowPlan{1, 2, 1} : NarrowPlan{2, 1, 1};
+    } else if (groups(2, 2) <= n_cu) p = NarrowPlan{2, 2, 1};
+    else if (!may_split && KC < 32) p = NarrowPlan{1, 2, 1};
+    else if (toks4 <= n_cu || TB == 2) p = NarrowPlan{2, TB > 2 ? 4 : 2, 1};
+    else if (rows4 <= n_cu) p = NarrowPlan{4, 2, 1};
+    else p = groups(4, 4) <= n_cu ? NarrowPlan{4, 4, 1} : NarrowPlan{2, 4, 1};
+    if (may_split && (p.R == 1 || p.R == 2) && p.NT <= p.R) {
+        while (p.KS < kSplitKMax && (p.KS + 1) * groups(p.R, p.NT) <= n_cu && KC / (p.KS + 1) > 32) ++p.KS;
+        while (p.KS > 1 && !fits(p)) --p.KS;
+    }
+    return p;
+}
+
 // Keys per split of a pass's attention.  A workgroup takes at least 512 keys; more splits only while that helps to fill the
 // chip, never more than max_splits (the last one merges them all), bounded scratch (items: rows x splits).  A decode
 // step of one or two rows is a chain of latencies: splits of 128 keys, one workgroup per query head and split, spread it

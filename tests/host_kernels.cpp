@@ -56,4 +56,12 @@ int host_entropy_row_parts(int rows, int V) { return entropy_row_parts(rows, V);
 
 int host_attention_chunk(int T, int KV, int hd, int ctx, int mfma, long items) { return attention_chunk(T, KV, hd, ctx, mfma != 0, 256, 16, items); }
 
+// row blocks, token blocks and slabs of K a workgroup of k_linear_mfma takes, as R * 100 + NT * 10 + KS; 0 if scratch does not hold the slabs
+int host_narrow_plan(int NB, int KC, int TB, int split, long floats, int groups) {
+    const NarrowPlan p = narrow_plan(NB, KC, TB, 256, split != 0, (size_t)floats, groups);
+    const long g = (long)((NB + p.R - 1) / p.R) * ((TB + p.NT - 1) / p.NT);
+    if (p.KS > 1 && ((long)p.KS * g * p.R * p.NT * 256 > floats || g > groups || p.KS > KC)) return 0;
+    return p.R * 100 + p.NT * 10 + p.KS;
+}
+
 }  // extern "C"

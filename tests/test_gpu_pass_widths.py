@@ -41,6 +41,25 @@ def test_score_at_every_pass_width(small, large):
     e.close()
 
 
+def test_tiles_of_two_to_sixteen_blocks():
+    """Every R x NT of narrow_plan (rules.hpp) that the shapes above do not reach: 192 row blocks at 33 to 150 rows, scored, and at
+    200 as a prompt (four row blocks and four token blocks), whose first generated entropy hangs on it."""
+    import paper_2502_06833_amd as ead
+    small = si.ModelShape("mid-o", 1, 1056, 33, 11, 416, 1040, 1e-5, 1e4)          # 66 row blocks x 33 k tiles
+    large = si.ModelShape("wide-o", 1, 3072, 24, 8, 512, 1040, 1e-5, 1e4)
+    Ws, Wl, os_, ol = make_pair(small, large, lm_sigma=1.5)
+    e = ead.EAD(small, Ws, large, Wl, window=5, tau=0.0, d_min=4, max_batch=1, max_seq=224)
+    toks = si.prompt_np(0, "tiles", 201, small.vocab)
+    for which, om in ((0, os_), (1, ol)):
+        ref = om.forward_dense(toks)
+        for T in (33, 49, 65, 97, 150):
+            print(f"score model {which} width {T}", flush=True)
+            check_logits(e.score(which, toks[:T])["logits"], ref[:T], TOL_LOGIT)
+        out = e.replay([toks], np.array([[5]], np.int32), np.array([[which]], np.uint8))
+        assert abs(out["H"][0, 0] - oracle.entropy_rows(ref[-1:])[0][0]) < TOL_H
+    e.close()
+
+
 @pytest.mark.parametrize("batch", [3, 20, 40])
 def test_sampled_choice_of_wide_passes(batch):
     """The sampled token of every row of a pass, where the two best perturbed scores are clearly apart."""

@@ -130,3 +130,26 @@ def test_attention_splits_stay_within_the_scratch(host):
                         chunk = host.host_attention_chunk(T, KV, hd, ctx, mfma, C.c_long(2048))
                         splits = -(-ctx // chunk)
                         assert splits == 1 or (splits <= 16 and T * splits <= 2048 and chunk % 32 == 0), (T, KV, ctx, mfma, hd)
+
+
+@pytest.mark.parametrize("NB,KC,split,plans", [
+    (72, 28, 0, {1: 111, 2: 111, 3: 111, 4: 211, 12: 221, 20: 121}), (56, 28, 1, {1: 111, 4: 111, 6: 211, 10: 221, 31: 241}),
+    (56, 152, 1, {1: 114, 2: 112, 3: 111, 4: 111, 6: 121}), (128, 256, 1, {1: 112, 2: 224, 4: 222, 6: 221}),
+    (192, 96, 1, {1: 111, 2: 211, 4: 221, 8: 241, 10: 421, 16: 441}), (256, 448, 1, {1: 212, 2: 222, 4: 221}),
+    (320, 432, 1, {1: 413, 2: 423, 3: 241}), (448, 160, 0, {1: 211, 2: 221, 4: 241})])
+def test_narrow_passes_take_the_measured_best(host, NB, KC, split, plans):
+    for TB, plan in plans.items():
+        assert host.host_narrow_plan(NB, KC, TB, split, C.c_long(8 << 20), 4096) == plan, TB
+
+
+def test_narrow_plans_are_instantiated_and_stay_within_the_scratch(host):
+    plain = {11, 12, 21, 22, 24, 42, 44}                     # R, NT of the kernels launch_narrow knows without a split of K
+    slabs = {11, 21, 22, 41, 42}
+    for NB in (1, 2, 5, 16, 63, 64, 96, 128, 171, 192, 193, 256, 257, 320, 512, 513, 960):
+        for KC in (1, 4, 28, 33, 66, 128, 255, 256, 300, 448, 480):
+            for TB in (1, 2, 3, 4, 5, 8, 9, 16, 17, 31):
+                for split in (0, 1):
+                    for floats, groups in ((8 << 20, 4096), (1 << 16, 64)):
+                        r = host.host_narrow_plan(NB, KC, TB, split, C.c_long(floats), groups)
+                        assert r and r // 10 in (plain if r % 10 == 1 else slabs) and (split or r % 10 == 1), (NB, KC, TB, split)
+                        assert r % 10 <= 8
