@@ -60,6 +60,25 @@ def test_tiles_of_two_to_sixteen_blocks():
     e.close()
 
 
+@pytest.mark.parametrize("length", [64, 66, 171])
+def test_logits_of_many_pieces_arrive_in_their_place(length):
+    """Long logits reach the caller in pieces, by several threads (from 64 rows of this vocabulary on: a multiple of the piece,
+    a remainder, and two passes): every row's statistics, folded on the device, are those of the row's logits."""
+    import paper_2502_06833_amd as ead
+    shape = si.ModelShape("pieces", 1, 256, 4, 2, 416, 32768, 1e-5, 1e4)
+    Ws, Wl, os_, _ = make_pair(shape, si.ModelShape("other", 1, 128, 4, 4, 128, 32768, 1e-5, 1e4), lm_sigma=1.5)
+    e = ead.EAD(shape, Ws, si.ModelShape("other", 1, 128, 4, 4, 128, 32768, 1e-5, 1e4), Wl, window=5, tau=0.0, d_min=4, max_batch=1, max_seq=192)
+    toks = si.prompt_np(0, "pieces", length, shape.vocab)
+    first = e.score(0, toks)
+    again = e.score(0, toks)
+    for out in (first, again):
+        check_logits(out["logits"], os_.forward_dense(toks), TOL_LOGIT)
+        assert np.abs(oracle.entropy_rows(out["logits"])[0] - out["H"]).max() < 1e-4
+        assert (out["logits"].argmax(1) == out["argmax"]).all()
+    assert (first["logits"] == again["logits"]).all()
+    e.close()
+
+
 @pytest.mark.parametrize("batch", [3, 20, 40])
 def test_sampled_choice_of_wide_passes(batch):
     """The sampled token of every row of a pass, where the two best perturbed scores are clearly apart."""
