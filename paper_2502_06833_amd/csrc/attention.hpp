@@ -32,6 +32,7 @@ struct AttnArgs {
     // ones start first and the short ones fill in behind them instead of the other way round.
     int use_order;
     unsigned char order[128];
+    const int2 *groups;        // k_attn_prompt: (first row, rows) of a workgroup's rows (k_plan)
 };
 constexpr int kAttnOrderMax = 128;
 
@@ -502,5 +503,168 @@ __global__ __launch_bounds__(kAttnMfmaWaves * 64, 2) void k_attn_mfma(AttnArgs<b
     }
 }
 
+// ------------------------------------------------------------------------------------
+// Attention of prompt passes, where a sequence has many rows: the products of k_attn_mfma with K and V shared by a workgroup.
+// There a workgroup serves 16 / G rows and its waves split the keys, so every 16 / G rows read their sequence's K and V from L2
+// again: 3500 rows of 12 prompts of the 14B shape read 1.4 GB a layer, in 273 us.  Here each of a workgroup's waves has 16 / G rows of its
+// own (positions cut at multiples of all its waves' rows, so a row's column follows from its position alone) and all take the same
+// keys: a block of 32 keys, K as the fragments of the score product and V as tiles of the transposed copy, is requested straight into
+// LDS once for the workgroup, kPromptDepth - 1 blocks ahead.  No sums meet: a wave keeps its columns' maxima, sums and outputs from the
+// first key to the last and stores them.  Those 3500 rows: 99 us (0.5B shape 76 -> 33); with eight waves a workgroup 104 and 35.
+// What bounds it: with few workgroups the chain of a block (fragments, score products, maximum over lanes, exponentials, output products:
+// 0.5-0.7 us), with many the vector arithmetic between the products.  prompt_attention (rules.hpp) says which passes come here.
+// ------------------------------------------------------------------------------------
+constexpr int kPromptWaves = 4, kPromptDepth = 3;     // waves per workgroup; key blocks in LDS
+
+// two floats to bf16, rounded to nearest even (finite values), in one instruction
+__device__ __forceinline__ uint32_t pack_bf16(float a, float b) {
+    typedef float f32x2_t __attribute__((ext_vector_type(2)));
+    typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2_t{a, b}, bf16x2_t));
+}
+// eight floats as bf16 hi + lo
+__device__ __forceinline__ void split8(const float (&f)[8], bf16x8_t &hi, bf16x8_t &lo) {
+    u32x4_t h, l;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const uint32_t w = pack_bf16(f[2 * e], f[2 * e + 1]);
+        h[e] = w;
+        l[e] = pack_bf16(f[2 * e] - __uint_as_float(w << 16), f[2 * e + 1] - __uint_as_float(w & 0xFFFF0000u));
+    }
+    hi = __builtin_bit_cast(bf16x8_t, h); lo = __builtin_bit_cast(bf16x8_t, l);
+}
+
+template <int HD, int G>
+__global__ __launch_bounds__(kPromptWaves * 64, 2) void k_attn_prompt(AttnArgs<bf16_t> a) {
+    constexpr int NWV = kPromptWaves, RQ = 16 / G, SQ = NWV * RQ;        // rows per wave and per workgroup
+    constexpr int KC = HD / 32, HB = HD / 16, FR = 2 * KC + HB;           // fragments of a key block: K by (score tile, k step), V by output tile
+    constexpr int PL = (FR + NWV - 1) / NWV;                              // a wave's requests per block (past FR: the last fragment again)
+    __shared__ __attribute__((aligned(16))) bf16_t s_kv[kPromptDepth][FR][512];
+    const int2 grp = a.groups[gridDim.y - 1 - blockIdx.y];                // a sequence's later rows, which see more keys, first
+    const int kvh = blockIdx.x, t0 = grp.x, n = grp.y;
+    const int pos0 = a.row_pos[t0], seq = a.row_seq[t0];
+    const int tid = threadIdx.x, lane = tid & 63, col = lane & 15, lg = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int H = a.n_heads, nkeys = pos0 + n, nb = (nkeys + 31) >> 5;
+    const int first = pos0 - pos0 % SQ + wave * RQ;                       // position of the wave's first column
+    const int cr = col / G, cg = col % G, p = first + cr;
+    const bool col_ok = cr < RQ && p >= pos0 && p < pos0 + n;
+    const int lim = col_ok ? p : -1;                                      // last key the column may see
+    const int lo_lim = max(first, pos0), hi_lim = min(first + RQ, pos0 + n) - 1;      // of the wave's columns, if it has any
+    const bool busy = hi_lim >= lo_lim;
+    const int t = t0 + p - pos0;
+
+    // requests: base of the sequence's K and V for this head, uniform; a lane's place in fragment `f` of key block 0
+    const size_t base = ((size_t)seq * a.n_kv_heads + kvh) * (size_t)a.max_seq * HD;
+    const bf16_t *kbase = a.kcache + base, *vbase = a.vtcache + base;
+    const int krow = 8 * (col >> 2) + (col & 3);                          // row r of score tile 0 is key 8 (r / 4) + r % 4 of the block, of tile 1 that key + 4
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) bf16_t *)&s_kv[0][0][0];
+    int next = 0, nslot = 0;
+    auto request = [&]() __attribute__((always_inline)) {
+        const int kb = min(next, nb - 1) * 32;                            // past the end the last block again, never read
+#pragma unroll
+        for (int j = 0; j < PL; ++j) {
+            const int f = min(wave + NWV * j, FR - 1);                    // uniform
+            const uint32_t lds = lds0 + (uint32_t)(nslot * FR + f) * 1024;
+            if (f < 2 * KC) {
+                const int key = min(kb + krow + 4 * (f / KC), nkeys - 1);
+                request_tile(kbase, (uint32_t)(key * HD + (f % KC) * 32 + lg * 8) * 2, lds);
+            } else {
+                request_tile(vbase + ((size_t)(f - 2 * KC) * (a.max_seq >> 5) + (kb >> 5)) * 512, (uint32_t)(col * 32 + lg * 8) * 2, lds);
+            }
+        }
+        ++next; nslot = nslot + 1 == kPromptDepth ? 0 : nslot + 1;
+    };
+    // Q^T fragments: column col, hd elements kc*32 + lg*8 .. +8, scaled, as bf16 hi + lo
+    bf16x8_t qh[KC], ql[KC];
+#pragma unroll
+    for (int kc = 0; kc < KC; ++kc) {
+        float f[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+        if (col_ok) {
+            const float *qp = a.q + (size_t)t * H * HD + (size_t)(kvh * G + cg) * HD + kc * 32 + lg * 8;
+            const float4 x0 = *reinterpret_cast<const float4 *>(qp), x1 = *reinterpret_cast<const float4 *>(qp + 4);
+            f[0] = x0.x * a.scale; f[1] = x0.y * a.scale; f[2] = x0.z * a.scale; f[3] = x0.w * a.scale;
+            f[4] = x1.x * a.scale; f[5] = x1.y * a.scale; f[6] = x1.z * a.scale; f[7] = x1.w * a.scale;
+        }
+        split8(f, qh[kc], ql[kc]);
+    }
+#pragma unroll
+    for (int i = 0; i < kPromptDepth - 1; ++i) request();
+
+    f32x4_t acc[HB];
+#pragma unroll
+    for (int hb = 0; hb < HB; ++hb) acc[hb] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    float m = kNegBig, lsum = 0.f;
+    int slot = 0;
+    for (int i = 0; i < nb; ++i) {
+        asm volatile("s_waitcnt vmcnt(%0)" ::"n"(PL * (kPromptDepth - 2)) : "memory");      // this wave's part of block i has landed
+        __builtin_amdgcn_s_waitcnt(kWaitLdsReads);                         // and what it reads of block i - 1 has arrived
+        __builtin_amdgcn_s_barrier();                                      // the same holds for all waves
+        asm volatile("" ::: "memory");
+        request();                                                         // into the slot of block i - 1
+        const int kb = i * 32;
+        if (busy && kb <= hi_lim) {                                        // uniform over the wave
+            u32x4_t kf[2][KC], vf[HB];
+#pragma unroll
+            for (int ti = 0; ti < 2; ++ti)
+#pragma unroll
+                for (int kc = 0; kc < KC; ++kc) kf[ti][kc] = *reinterpret_cast<const u32x4_t *>(&s_kv[slot][ti * KC + kc][lane * 8]);
+#pragma unroll
+            for (int hb = 0; hb < HB; ++hb) vf[hb] = *reinterpret_cast<const u32x4_t *>(&s_kv[slot][2 * KC + hb][lane * 8]);
+            f32x4_t s0 = f32x4_t{0.f, 0.f, 0.f, 0.f}, s1 = s0;
+#pragma unroll
+            for (int kc = 0; kc < KC; ++kc) {
+                s0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, kf[0][kc]), ql[kc], s0, 0, 0, 0);
+                s1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, kf[1][kc]), ql[kc], s1, 0, 0, 0);
+            }
+#pragma unroll
+            for (int kc = 0; kc < KC; ++kc) {
+                s0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, kf[0][kc]), qh[kc], s0, 0, 0, 0);
+                s1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, kf[1][kc]), qh[kc], s1, 0, 0, 0);
+            }
+            // this lane: keys kb + 8 lg + e of column col
+            float sc[8] = {s0[0], s0[1], s0[2], s0[3], s1[0], s1[1], s1[2], s1[3]};
+            const bool whole = kb + 31 <= lo_lim;                          // uniform: every column of the wave sees the whole block
+            if (!whole) {
+#pragma unroll
+                for (int e = 0; e < 8; ++e) sc[e] = kb + 8 * lg + e <= lim ? sc[e] : -INFINITY;
+            }
+            float mc = fmaxf(fmaxf(fmaxf(sc[0], sc[1]), fmaxf(sc[2], sc[3])), fmaxf(fmaxf(sc[4], sc[5]), fmaxf(sc[6], sc[7])));
+            mc = fmaxf(mc, __shfl_xor(mc, 16, kWave));
+            mc = fmaxf(mc, __shfl_xor(mc, 32, kWave));
+            if (__any(mc > m)) {                                           // a column's maximum moves: all sums follow (by one where it does not)
+                const float mn = fmaxf(m, mc), corr = __expf(m - mn);
+                m = mn; lsum *= corr;
+#pragma unroll
+                for (int hb = 0; hb < HB; ++hb) { acc[hb][0] *= corr; acc[hb][1] *= corr; acc[hb][2] *= corr; acc[hb][3] *= corr; }
+            }
+            float pr[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) { pr[e] = __expf(sc[e] - m); lsum += pr[e]; }      // masked: exp(-inf) = 0
+            bf16x8_t ph, pl;
+            split8(pr, ph, pl);
+#pragma unroll
+            for (int hb = 0; hb < HB; ++hb) acc[hb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, vf[hb]), pl, acc[hb], 0, 0, 0);
+#pragma unroll
+            for (int hb = 0; hb < HB; ++hb) acc[hb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, vf[hb]), ph, acc[hb], 0, 0, 0);
+        }
+        slot = slot + 1 == kPromptDepth ? 0 : slot + 1;
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");                      // nothing may land in LDS after the workgroup has gone
+    lsum += __shfl_xor(lsum, 16, kWave);
+    lsum += __shfl_xor(lsum, 32, kWave);
+    if (!col_ok) return;
+    // acc[hb][j]: hd element hb*16 + 4 lg + j: four neighbours of the consuming product's tile
+    const int TB = (*a.count + 15) >> 4;
+#pragma unroll
+    for (int hb = 0; hb < HB; ++hb) {
+        const int c = (kvh * G + cg) * HD + hb * 16 + 4 * lg;
+        const size_t off = act_tile_offset(t >> 4, c >> 5, TB) + (size_t)(((t & 15) + 16 * ((c & 31) >> 3)) * 8 + (c & 7));
+        uint2 r;
+        r.x = (uint32_t)f32_to_f16_sat(acc[hb][0] / lsum) | ((uint32_t)f32_to_f16_sat(acc[hb][1] / lsum) << 16);
+        r.y = (uint32_t)f32_to_f16_sat(acc[hb][2] / lsum) | ((uint32_t)f32_to_f16_sat(acc[hb][3] / lsum) << 16);
+        *reinterpret_cast<uint2 *>(a.out_tiles + off) = r;
+    }
+}
 
 }  // namespace ead

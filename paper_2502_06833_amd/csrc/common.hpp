@@ -147,6 +147,16 @@ __device__ __forceinline__ void st_coherent(bf16_t *p, bf16_t v) {
 }
 __device__ __forceinline__ void wait_stores() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
+// ---- loads that write LDS themselves ----------------------------------------------------
+constexpr int kWaitLdsReads = 0xC07F;                  // s_waitcnt lgkmcnt(0), the other counters at their maximum
+
+// 16 bytes per lane from base + voff (base uniform over the wave) to LDS at lds + 16 lane.  M0 cannot be named as clobbered:
+// the compiler reserves it, keeps no value in it from one instruction to the next and sets it itself right before an
+// instruction of its own that reads it (the kernels that call this have none: LDS reads need no M0 here).
+__device__ __forceinline__ void request_tile(const bf16_t *base, uint32_t voff, uint32_t lds) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(voff), "s"(base) : "memory");
+}
+
 // ---- wave64 reductions -------------------------------------------------------------
 __device__ __forceinline__ float wave_sum(float v) {
 #pragma unroll

@@ -84,6 +84,8 @@ struct PlanArgs {
     // the state of ITS sequences while this plan is built.  The host names the sequences of this
     // pass (their state is at rest); all others are left out whatever their state reads.
     int use_allow; unsigned long long allow[kAllowWords];
+    // > 0: the rows are also listed as groups for k_attn_prompt, a sequence's rows cut at positions that are multiples of this
+    int group_rows;
 };
 
 // Rows of one forward pass of model m: for every sequence that m serves, the positions
@@ -109,10 +111,11 @@ __device__ __forceinline__ int wave_scan(int v) {       // inclusive sum over th
 __global__ __launch_bounds__(kPlanThreads) void k_plan(PlanArgs a) {
     extern __shared__ int sm[];
     __shared__ int s_rows;
-    int *s_off = sm, *s_have = sm + a.batch;
+    int *s_off = sm, *s_have = sm + a.batch, *s_group = sm + 2 * a.batch;      // s_group (a sequence's first group): only if there are groups
+    const int gr = a.group_rows;
     const int tid = threadIdx.x;
     if (tid < 64) {
-        int base = 0, nlm = 0;               // rows and logit rows of the sequences before these
+        int base = 0, nlm = 0, ngrp = 0;     // rows, logit rows and groups of the sequences before these
         for (int b0 = 0; b0 < a.batch; b0 += 64) {
             const int b = b0 + tid;
             int want = 0, have = 0;
@@ -137,6 +140,11 @@ __global__ __launch_bounds__(kPlanThreads) void k_plan(PlanArgs a) {
                     a.p.lm_row[place] = off + n - 1; a.p.lm_seq[place] = b;
                 }
             }
+            if (gr) {
+                const int mine = n > 0 ? (have + n - 1) / gr - have / gr + 1 : 0, upto = ngrp + wave_scan(mine);
+                if (b < a.batch) s_group[b] = upto - mine;
+                ngrp = __shfl(upto, 63, kWave);
+            }
             base = __shfl(incl, 63, kWave); nlm += __popcll(whole);
         }
         const int rows = min(base, a.budget);
@@ -150,7 +158,12 @@ __global__ __launch_bounds__(kPlanThreads) void k_plan(PlanArgs a) {
             const int mid = (lo + hi + 1) >> 1;
             if (s_off[mid] <= r) lo = mid; else hi = mid - 1;
         }
-        a.p.row_seq[r] = lo; a.p.row_pos[r] = s_have[lo] + r - s_off[lo];
+        const int pos = s_have[lo] + r - s_off[lo];
+        a.p.row_seq[r] = lo; a.p.row_pos[r] = pos;
+        if (gr && (r == s_off[lo] || pos % gr == 0)) {
+            const int end = lo + 1 < a.batch ? s_off[lo + 1] : rows;
+            a.p.groups[s_group[lo] + pos / gr - s_have[lo] / gr] = make_int2(r, min(gr - pos % gr, end - r));
+        }
         if (a.lm_mode == 2) { a.p.lm_row[r] = r; a.p.lm_seq[r] = lo; }
     }
 }
@@ -278,6 +291,7 @@ struct ead_handle {
     int prefilled = 0;                   // both caches hold the prompts of the last ead_begin and nothing has clobbered them
     std::vector<int> prompt_len;
     int sched_grouped = 0, sched_phase = 0; float sched_hi = 0.5f, sched_lo = 0.25f;
+    int group_rows = 0, n_groups = 0;    // host_plan -> launch_plan, forward_pass: the pass's groups for k_attn_prompt (0: none)
     unsigned char attn_order[kAttnOrderMax]; int attn_order_n = 0;      // run_pass -> forward_pass: rows by falling context
     float samp_temp = 0.f; uint64_t samp_seed = 0;        // temperature 0: greedy
     int scoring = 0;                                       // inside ead_score: logits of given tokens, nothing is sampled
@@ -731,6 +745,16 @@ void launch_attn(ead_handle *h, int mi, AttnArgs<KT> &a, int G, int T, double kv
     const bool per_head = T <= 2 || (long)T * a.n_kv_heads * a.max_splits <= 64;
     dim3 grid(a.max_splits, per_head ? a.n_heads : a.n_kv_heads, T);
     if constexpr (std::is_same<KT, bf16_t>::value) {
+        if (h->group_rows && a.out_tiles) {
+            ProfScope ps(h, PK_ATTN, mi, kv_bytes);
+            a.groups = h->plan.groups;
+            const dim3 gg(a.n_kv_heads, h->n_groups);
+#define EAD_LP_(G_) hipLaunchKernelGGL((k_attn_prompt<HD, G_>), gg, dim3(kPromptWaves * 64), 0, h->stream, a)
+            switch (G) { case 1: EAD_LP_(1); break; case 2: EAD_LP_(2); break; case 3: EAD_LP_(3); break; case 4: EAD_LP_(4); break;
+                         case 5: EAD_LP_(5); break; case 6: EAD_LP_(6); break; case 7: EAD_LP_(7); break; default: EAD_LP_(8); break; }
+#undef EAD_LP_
+            return;
+        }
         // many rows: scores and weighted sums on the matrix cores, rows of one sequence grouped
         if (!per_head && a.vtcache) {
             ProfScope ps(h, PK_ATTN, mi, kv_bytes);
@@ -975,6 +999,20 @@ ead_status fused_step(ead_handle *h, int mi, double keys) {
     return EAD_OK;
 }
 
+// Whether a pass's attention goes to k_attn_prompt, and in how many groups of rows (h->group_rows, h->n_groups).
+void plan_groups(ead_handle *h, int m, int T, int ctx, const std::vector<int> &rows) {
+    const Model &md = h->mdl[m];
+    h->group_rows = h->n_groups = 0;
+    if (md.dtype != EAD_BF16 || !md.layers[0].vtcache || h->batch > kGroupSeqs) return;
+    const int rq = 16 / (md.H / md.KV), gr = kPromptWaves * rq;
+    int seqs = 0, groups = 0, small = 0;
+    for (int b = 0; b < h->batch; ++b) {
+        const int have = h->hs[b].kvlen[m], last = have + rows[b] - 1;
+        if (rows[b]) { ++seqs; groups += last / gr - have / gr + 1; small += last / rq - have / rq + 1; }
+    }
+    if (prompt_attention(T, seqs, small, md.KV, ctx)) { h->group_rows = gr; h->n_groups = groups; }
+}
+
 // Host copy of k_plan: which rows the pass will hold.  Returns T; fills n_lm, ctx_max and,
 // per sequence, how many rows it got and whether its chunk reaches the end.
 int host_plan(ead_handle *h, int m, int budget, int limit_off, int lm_mode, bool ignore_model, int step, int *n_lm,
@@ -997,18 +1035,19 @@ int host_plan(ead_handle *h, int m, int budget, int limit_off, int lm_mode, bool
     }
     *n_lm = lm_mode == 2 ? off : nlm;
     *ctx_max = cm;
+    plan_groups(h, m, off, cm, *rows);
     return off;
 }
 
 void launch_plan(ead_handle *h, int m, int budget, int limit_off, int lm_mode, bool ignore_model, int step,
                  const std::vector<int> *rows = nullptr) {
-    PlanArgs pa{h->s, h->plan, h->batch, m, budget, limit_off, lm_mode, ignore_model ? 1 : 0, step, 0, {0}};
+    PlanArgs pa{h->s, h->plan, h->batch, m, budget, limit_off, lm_mode, ignore_model ? 1 : 0, step, 0, {0}, h->group_rows};
     if (rows && h->two_lanes) {          // name the sequences of this pass (see PlanArgs)
         pa.use_allow = 1;
         for (int b = 0; b < h->batch; ++b) if ((*rows)[b] > 0) pa.allow[b >> 6] |= 1ull << (b & 63);
     }
     ProfScope ps(h, PK_PLAN, m, 0.0);
-    hipLaunchKernelGGL(k_plan, dim3(1), dim3(kPlanThreads), 2 * h->batch * sizeof(int), h->stream, pa);
+    hipLaunchKernelGGL(k_plan, dim3(1), dim3(kPlanThreads), (h->group_rows ? 3 : 2) * h->batch * sizeof(int), h->stream, pa);
 }
 
 void launch_finalize(ead_handle *h, int m, int n_lm, bool score) {
@@ -1712,7 +1751,7 @@ ead_status ead_create(const ead_model_desc *small_model, const ead_model_desc *l
             // what only the FMA path writes: passes of one or two rows of a bf16 model, any pass of a float32 one
             const size_t Tf = any_f32 ? T : std::min<size_t>(T, 16);
             TRY(dmalloc(h, &h->plan.hdr, (size_t)4)); TRY(dmalloc(h, &h->plan.row_seq, T));
-            TRY(dmalloc(h, &h->plan.row_pos, T));
+            TRY(dmalloc(h, &h->plan.row_pos, T)); TRY(dmalloc(h, &h->plan.groups, T));
             TRY(dmalloc(h, &h->plan.lm_row, T)); TRY(dmalloc(h, &h->plan.lm_seq, T));
             TRY(dmalloc(h, &h->x, T * dmax)); TRY(dmalloc(h, &h->q, T * qmax)); TRY(dmalloc(h, &h->o, Tf * qmax));
             TRY(dmalloc(h, &h->hbuf, Tf * fmax_));

@@ -1133,15 +1133,6 @@ constexpr int kTileDepth = 5, kTileBlocks = 16;        // k steps in LDS; row bl
 constexpr size_t kTileLdsBytes = (size_t)kTileDepth * 2 * kTileBlocks * 1024;
 constexpr int kTileBand = 6;                           // most sweeps that run side by side, see launch
 
-constexpr int kWaitLdsReads = 0xC07F;                  // s_waitcnt lgkmcnt(0), the other counters at their maximum
-
-// 16 bytes per lane from base + voff (base uniform over the wave) to LDS at lds + 16 lane.  M0 cannot be named as clobbered:
-// the compiler reserves it, keeps no value in it from one instruction to the next and sets it itself right before an
-// instruction of its own that reads it (the kernels that call this have none: LDS reads need no M0 here).
-__device__ __forceinline__ void request_tile(const bf16_t *base, uint32_t voff, uint32_t lds) {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(voff), "s"(base) : "memory");
-}
-
 template <int EPI>
 __global__ __launch_bounds__(512, 2) void k_linear_mfma_tile(LinArgs<bf16_t> a) {
     constexpr int NWV = 8, WB = 4, PL = 4;             // waves; token blocks of a wave; its requests per step

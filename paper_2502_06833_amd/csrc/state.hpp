@@ -19,7 +19,7 @@ struct SeqState {
     int max_batch, max_seq, cap;
 };
 
-struct Plan { int *hdr; int *row_seq, *row_pos, *lm_row, *lm_seq; };
+struct Plan { int *hdr; int *row_seq, *row_pos, *lm_row, *lm_seq; int2 *groups; };      // groups: see PlanArgs::group_rows
 
 struct FinArgs {
     SeqState s; Plan p; GateCfg cfg;

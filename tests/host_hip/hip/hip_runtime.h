@@ -21,6 +21,7 @@
 struct dim3h { unsigned x = 0, y = 0, z = 0; };
 inline thread_local dim3h threadIdx, blockIdx, blockDim, gridDim;
 
+struct int2 { int x, y; };
 struct float2 { float x, y; };
 struct float4 { float x, y, z, w; };
 struct uint2 { uint32_t x, y; };

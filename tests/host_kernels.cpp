@@ -56,6 +56,8 @@ int host_entropy_row_parts(int rows, int V) { return entropy_row_parts(rows, V);
 
 int host_attention_chunk(int T, int KV, int hd, int ctx, int mfma, long items) { return attention_chunk(T, KV, hd, ctx, mfma != 0, 256, 16, items); }
 
+int host_prompt_attention(int T, int seqs, long groups, int KV, int ctx) { return prompt_attention(T, seqs, groups, KV, ctx); }
+
 // row blocks, token blocks and slabs of K a workgroup of k_linear_mfma takes, as R * 100 + NT * 10 + KS; 0 if scratch does not hold the slabs
 int host_narrow_plan(int NB, int KC, int TB, int split, long floats, int groups) {
     const NarrowPlan p = narrow_plan(NB, KC, TB, 256, split != 0, (size_t)floats, groups);

@@ -113,3 +113,28 @@ def test_decode_rows_in_two_key_splits(heads, kv_heads, hd, rows, lens):
     for b, i in enumerate(which):
         assert np.abs(rp["H"][b] - refs[i]).max() < TOL_H, (b, lens[i])
     e.close()
+
+
+@pytest.mark.parametrize("heads,kv,hd", [(8, 8, 32), (4, 2, 64), (6, 2, 128), (4, 1, 32), (5, 1, 128), (6, 1, 64), (7, 1, 64), (8, 1, 128), (4, 1, 128)])
+def test_prompt_attention_of_every_head_layout(heads, kv, hd):
+    """k_attn_prompt: rows cut at multiples of 8 (eight heads share K and V) to 64 positions, last key blocks and last groups partly
+    filled.  Scored in one pass of up to 160 rows from position 0; prompts of several lengths in one pass (first, middle and last
+    rows of a group), whose first generated entropy hangs on every cached key."""
+    import paper_2502_06833_amd as ead
+    shape = si.ModelShape(f"pa{heads}-{hd}", 2, heads * hd, heads, kv, 256, 512, 1e-5, 1e4, bf16=True)
+    tiny = si.ModelShape("pa-other", 1, 128, 4, 4, 128, 512, 1e-5, 1e4, bf16=True)
+    W, Wt = si.model_weights_torch(shape, 0, "cuda", 0.05), si.model_weights_torch(tiny, 0, "cuda", 0.05)
+    om = oracle.Model(shape, {k: v.float().cpu().numpy() for k, v in W.items()})
+    lens = (700, 33, 290, 2, 96, 511)
+    e = ead.EAD(shape, W, tiny, Wt, window=5, tau=0.0, d_min=4, max_batch=len(lens), max_seq=704)
+    toks = si.prompt_np(4, "pa", 160, 512)
+    ref = om.forward_dense(toks)
+    for T in (17, 33, 129, 160):
+        out = e.score(0, toks[:T])
+        assert (np.abs(out["logits"] - ref[:T]).max(axis=1) < TOL_LOGIT * np.abs(ref[:T]).max(axis=1)).all(), T
+    e.force_model(0)
+    prompts = [si.prompt_np(5, f"pa{n}", n, 512) for n in lens]
+    got = e.generate(prompts, 1)
+    for b, p in enumerate(prompts):
+        assert abs(got["H"][b, 0] - oracle.entropy_rows(om.forward_dense(p)[-1:])[0][0]) < TOL_H, lens[b]
+    e.close()

@@ -153,3 +153,11 @@ def test_narrow_plans_are_instantiated_and_stay_within_the_scratch(host):
                         r = host.host_narrow_plan(NB, KC, TB, split, C.c_long(floats), groups)
                         assert r and r // 10 in (plain if r % 10 == 1 else slabs) and (split or r % 10 == 1), (NB, KC, TB, split)
                         assert r % 10 <= 8
+
+
+@pytest.mark.parametrize("T,seqs,groups,KV,ctx,takes", [
+    (17, 1, 6, 8, 17, 1), (130, 1, 44, 8, 130, 1), (16, 4, 8, 8, 4, 0), (48, 12, 24, 8, 4, 1), (48, 48, 48, 8, 100, 0),
+    (64, 1, 22, 8, 264, 0), (130, 1, 44, 8, 330, 0), (130, 1, 44, 8, 310, 1), (160, 1, 55, 8, 2160, 1), (160, 1, 55, 8, 8160, 0), (500, 1, 168, 8, 8500, 1),
+    (64, 64, 64, 8, 1000, 0), (160, 1, 80, 2, 760, 0), (500, 1, 250, 2, 1100, 1)])
+def test_prompt_attention_takes_the_passes_it_is_faster_at(host, T, seqs, groups, KV, ctx, takes):
+    assert host.host_prompt_attention(T, seqs, C.c_long(groups), KV, ctx) == takes
