@@ -2080,9 +2080,10 @@ ead_status entropy_argmax_impl(const void *logits_dev, int32_t dtype, int32_t ro
     } else {
         TRY(entropy_heap_scratch(d, &part, &call));
     }
-    // One launch where the counting of arrivals costs less than a second launch (entropy_folds).  Always two under capture
+    // One launch where the counting of arrivals costs less than a second launch (entropy_folds, entropy_folds_large).  Always two under capture
     // (stream_records) and for the entry point that shares its array with captured calls.
-    if (!use_static && entropy_folds(rows, chunks, (size_t)rows * vocab * (dtype == EAD_BF16 ? 2 : 4)) && !stream_records(st)) {
+    const size_t bytes = (size_t)rows * vocab * (dtype == EAD_BF16 ? 2 : 4);
+    if (!use_static && (entropy_folds(rows, chunks, bytes) || entropy_folds_large(rows, chunks, bytes)) && !stream_records(st)) {
         if (dtype == EAD_BF16) launch_entropy_folded<bf16_t>(logits_dev, rows, vocab, part, d, call, unit, H_dev, argmax_dev, st);
         else launch_entropy_folded<float>(logits_dev, rows, vocab, part, d, call, unit, H_dev, argmax_dev, st);
         if (hipGetLastError() != hipSuccess) return fail(nullptr, EAD_ERR_DEVICE, "kernel launch failed");

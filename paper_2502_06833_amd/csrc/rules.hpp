@@ -10,11 +10,12 @@ constexpr int kEntMaxChunks = 64;                       // most pieces a row of 
 // The split of a row into work items depends on (rows, V) alone, so a step's result does not depend on
 // how many steps share a launch, nor on which entry point asked for it.  Long chunks (up to 8 vectors
 // per thread) amortise the per-workgroup merge; shorter ones only when the rows of one step would
-// otherwise give too few workgroups to fill the chip.
+// otherwise give too few workgroups to fill the chip: one per compute unit (with two, rows are cut finer than it pays: both launches
+// of 97 x 50264 float32 14.2 -> 12.5 us in a graph, 128 x 32000 12.0 -> 9.7, 40 x 128256 bf16 10.2 -> 9.3; nothing slower at 1-200 rows x 4096-128256).
 inline void entropy_split(int rows, int V, int *chunks_out, int *per_out) {
     const int nvec = V / 8;
     int chunks = std::max(1, (nvec + 2047) / 2048);
-    while ((long)chunks * rows < 512 && chunks < kEntMaxChunks && nvec / (chunks * 2) >= 256) chunks *= 2;
+    while ((long)chunks * rows < 256 && chunks < kEntMaxChunks && nvec / (chunks * 2) >= 256) chunks *= 2;
     int per = (std::max(nvec, 1) + chunks - 1) / chunks;
     while (per > 8 * 256) { ++chunks; per = (nvec + chunks - 1) / chunks; }
     *chunks_out = chunks; *per_out = per;
@@ -29,6 +30,13 @@ inline void entropy_split(int rows, int V, int *chunks_out, int *per_out) {
 // itself is the longer part.
 inline bool entropy_folds(int rows, int chunks, size_t bytes) {
     return bytes <= ((size_t)4 << 20) && (long)rows * chunks <= 600 && (long)rows * chunks * chunks <= 4800;
+}
+
+// The same for larger calls: up to 32 MB, at most 600 chunks, eight a row, the second launch still is the longer part (us in one launch
+// against two, float32: 97 x 50264 10.5 / 12.6, 128 x 50264 10.1 / 12.6, 64 x 128256 11.1 / 12.5, 256 x 32000 10.8 / 12.6; bf16: 64 x 128256 10.0 /
+// 12.5, 128 x 50264 10.1 / 12.5; but 776 chunks, 97 x 128256, 13.4 / 12.5).
+inline bool entropy_folds_large(int rows, int chunks, size_t bytes) {
+    return bytes <= ((size_t)32 << 20) && (long)rows * chunks <= 600 && chunks <= 8;
 }
 
 // Pieces a row is given to workgroups in by k_entropy_rows (1: a workgroup takes whole rows, 2048 vectors at a time), by rows

@@ -210,3 +210,23 @@ def test_entropy_calls_in_a_row_and_under_capture():
             h1, a1 = ead.entropy_argmax(xs[i])
             torch.cuda.synchronize()
             assert torch.equal(h1, ref[i][0]) and torch.equal(a1, ref[i][1])
+
+
+@pytest.mark.parametrize("rows,V,dtype", [(97, 50264, torch.float32), (64, 128256, torch.float32), (128, 50264, torch.bfloat16), (75, 65544, torch.bfloat16),
+                                          (256, 32000, torch.float32), (257, 32000, torch.float32), (600, 16376, torch.bfloat16), (600, 16392, torch.bfloat16)])
+def test_larger_calls_in_one_launch_equal_those_in_two(rows, V, dtype):
+    """Calls on both sides of the rule's edges (bytes, chunks): bit for bit what the entry point that always takes two launches gives,
+    on calls in a row, and the definition in 64 bits within 1e-5 nats (32-bit sums of at most 128256 terms)."""
+    import paper_2502_06833_amd as ead
+    g = torch.Generator(device="cuda")
+    g.manual_seed(rows * V)
+    for _ in range(3):
+        x = (torch.randn((rows, V), generator=g, device="cuda") * 3).to(dtype)
+        H, am = ead.entropy_argmax(x)
+        H2, am2 = ead.entropy_argmax(x, static=True)
+        assert torch.equal(H, H2) and torch.equal(am, am2)
+        d = x.double()
+        p = torch.softmax(d, -1)
+        ref = -(p * torch.log_softmax(d, -1)).sum(-1)
+        assert (H.double() - ref).abs().max() < 1e-5 * max(1.0, float(ref.max()))
+        assert torch.equal(am.long(), (x == x.max(-1, keepdim=True).values).int().argmax(-1))
