@@ -738,6 +738,29 @@ void launch_mfma(ead_handle *h, int mi, LinArgs<bf16_t> &a, int T) {
     launch_narrow<EPI>(h, a, T);
 }
 
+// Passes of more than 256 rows (a row per compute unit) give a row to a wave, where its pieces fit the registers.
+void launch_pack(ead_handle *h, int mi, const PackArgs &a) {
+    ProfScope ps(h, PK_PACK_ACT, mi, 0.0);
+    const int rows16 = (a.rows + 15) & ~15;
+    if (a.rows > h->n_cu && a.K <= 20 * 256) {
+        const dim3 grid(rows16 / 4);
+        if (a.K <= 4 * 256) hipLaunchKernelGGL(k_pack_rows<4>, grid, dim3(256), 0, h->stream, a);
+        else if (a.K <= 8 * 256) hipLaunchKernelGGL(k_pack_rows<8>, grid, dim3(256), 0, h->stream, a);
+        else if (a.K <= 12 * 256) hipLaunchKernelGGL(k_pack_rows<12>, grid, dim3(256), 0, h->stream, a);
+        else if (a.K <= 16 * 256) hipLaunchKernelGGL(k_pack_rows<16>, grid, dim3(256), 0, h->stream, a);
+        else hipLaunchKernelGGL(k_pack_rows<20>, grid, dim3(256), 0, h->stream, a);
+        return;
+    }
+    switch ((a.K + 1023) / 1024) {
+        case 1: hipLaunchKernelGGL(k_pack_act<1>, dim3(rows16), dim3(256), 0, h->stream, a); break;
+        case 2: hipLaunchKernelGGL(k_pack_act<2>, dim3(rows16), dim3(256), 0, h->stream, a); break;
+        case 3: hipLaunchKernelGGL(k_pack_act<3>, dim3(rows16), dim3(256), 0, h->stream, a); break;
+        case 4: hipLaunchKernelGGL(k_pack_act<4>, dim3(rows16), dim3(256), 0, h->stream, a); break;
+        case 5: hipLaunchKernelGGL(k_pack_act<5>, dim3(rows16), dim3(256), 0, h->stream, a); break;
+        default: hipLaunchKernelGGL(k_pack_act<kPackVecs>, dim3(rows16), dim3(256), 0, h->stream, a); break;
+    }
+}
+
 template <typename KT, int HD>
 void launch_attn(ead_handle *h, int mi, AttnArgs<KT> &a, int G, int T, double kv_bytes) {
     // few rows: one workgroup per query head (latency-bound, wants the lanes); many rows:
@@ -804,8 +827,7 @@ ead_status forward_pass(ead_handle *h, int mi, int T, int n_lm, int ctx_max, boo
         a.rope = m.rope; a.n_heads = m.H; a.n_kv_heads = m.KV; a.hd = hd; a.max_seq = h->s.max_seq;
         if (mfma) {
             if constexpr (is_bf16) {
-                PackArgs pa{h->x, d, cnt, nullptr, ly.g_attn, m.eps, h->xp_a, d};
-                { ProfScope ps(h, PK_PACK_ACT, mi, 0.0); hipLaunchKernelGGL(k_pack_act, dim3(T16), dim3(256), 0, st, pa); }
+                launch_pack(h, mi, PackArgs{h->x, d, T, nullptr, ly.g_attn, m.eps, h->xp_a, d});
                 a.xp = h->xp_a;
                 launch_mfma<EPI_QKV>(h, mi, a, T);
             }
@@ -834,8 +856,7 @@ ead_status forward_pass(ead_handle *h, int mi, int T, int n_lm, int ctx_max, boo
         c.W = (const WT *)ly.wgu; c.Np = 2 * F; c.K = d; c.count = cnt; c.ldo = F;
         if (mfma) {
             if constexpr (is_bf16) {
-                PackArgs pa{h->x, d, cnt, nullptr, ly.g_ffn, m.eps, h->xp_a, d};
-                { ProfScope ps(h, PK_PACK_ACT, mi, 0.0); hipLaunchKernelGGL(k_pack_act, dim3(T16), dim3(256), 0, st, pa); }
+                launch_pack(h, mi, PackArgs{h->x, d, T, nullptr, ly.g_ffn, m.eps, h->xp_a, d});
                 c.xp = h->xp_a; c.out_tiles = h->xp_h; c.tbs = T16 / 16;
                 launch_mfma<EPI_SWIGLU>(h, mi, c, T);
             }
@@ -862,8 +883,7 @@ ead_status forward_pass(ead_handle *h, int mi, int T, int n_lm, int ctx_max, boo
         const int grid = std::min(m.V / 16, h->lm_grid);
         if (is_bf16 && n_lm > 2) {
             if constexpr (is_bf16) {
-                PackArgs pa{h->x, d, cnt + 1, h->plan.lm_row, m.g_final, m.eps, h->xp_a, d};
-                { ProfScope ps(h, PK_PACK_ACT, mi, 0.0); hipLaunchKernelGGL(k_pack_act, dim3((n_lm + 15) & ~15), dim3(256), 0, st, pa); }
+                launch_pack(h, mi, PackArgs{h->x, d, n_lm, h->plan.lm_row, m.g_final, m.eps, h->xp_a, d});
                 g.xp = h->xp_a;
                 h->lm_n_part = launch_lm(h, mi, g, n_lm);
                 if (!h->lm_n_part) return fail(h, EAD_ERR_DEVICE, "the device does not grant %zu bytes of LDS to a workgroup", kLmLdsBytes);
@@ -1756,6 +1776,7 @@ ead_status ead_create(const ead_model_desc *small_model, const ead_model_desc *l
             TRY(dmalloc(h, &h->x, T * dmax)); TRY(dmalloc(h, &h->q, T * qmax)); TRY(dmalloc(h, &h->o, Tf * qmax));
             TRY(dmalloc(h, &h->hbuf, Tf * fmax_));
             TRY(dmalloc(h, &h->xp_a, T * dmax)); TRY(dmalloc(h, &h->xp_o, T * qmax)); TRY(dmalloc(h, &h->xp_h, T * fmax_));
+            HIP_TRY(h, hipMemsetAsync(h->plan.lm_row, 0, T * sizeof(int), h->stream));      // read by row number: never out of range
             HIP_TRY(h, hipMemsetAsync(h->xp_a, 0, T * dmax * 2, h->stream));
             HIP_TRY(h, hipMemsetAsync(h->xp_o, 0, T * qmax * 2, h->stream));
             HIP_TRY(h, hipMemsetAsync(h->xp_h, 0, T * fmax_ * 2, h->stream));

@@ -1247,61 +1247,82 @@ __global__ __launch_bounds__(256) void k_sk_merge(LinArgs<bf16_t> a, int NGR /* 
 }
 
 // ------------------------------------------------------------------------------------
-// fp32 activations -> half-precision activation tiles, optionally through RMSNorm.
-// One workgroup per token row; rows >= count (padding of the last 16-row block) are zeroed.
+// fp32 activations -> half-precision activation tiles, through RMSNorm.  Rows past `rows` (padding of the last 16-row
+// block) are zeroed.  Two launches a layer that do little else than be launched, so what counts is the chain of
+// latencies: the row's length is known when the kernel is compiled, so every load is requested at once and nothing branches, and the number of
+// rows comes with the launch (12 rows in a graph, us, an empty kernel taking 1.7: K = 896 2.9 -> 2.1, 2048 3.2 -> 2.3, 5120 4.0 ->
+// 2.8; before, one kernel for all lengths with 15 predicated pieces, and the count read from the plan).
 // ------------------------------------------------------------------------------------
 struct PackArgs {
     const float *x; int ldx;
-    const int *count; const int *rowmap;
+    int rows; const int *rowmap;         // rowmap, optional: row t is x[rowmap[t]]
     const float *gain; float eps;
     bf16_t *out; int K;
 };
 
-constexpr int kPackVecs = 15;        // 16-byte pieces of a row per thread: K <= 15 * 4 * 256
+constexpr int kPackVecs = 15;        // most 16-byte pieces of a row per thread of a workgroup: K <= 15 * 4 * 256
 
-__global__ __launch_bounds__(256) void k_pack_act(PackArgs a) {
-    __shared__ float s_ss[4];
-    const int T = *a.count;
-    const int t = blockIdx.x;
-    if (t >= ((T + 15) & ~15)) return;
-    const int K = a.K, tid = threadIdx.x, TB = (T + 15) >> 4;
-    const float *src = t < T ? a.x + (size_t)(a.rowmap ? a.rowmap[t] : t) * a.ldx : nullptr;
-    // the row is read once: thread tid keeps elements 4 tid + 1024 i .. + 3, i = 0, 1, ..; the gains are
-    // requested with it, so that one round trip to memory covers everything the row needs
-    float4 v[kPackVecs], g[kPackVecs];
+// pieces tid, tid + stride, .. (V of them) of row t, normalised, into their tiles; a piece past the row repeats its last one and is dropped
+template <int V>
+__device__ __forceinline__ void pack_load(const PackArgs &a, int t, int tid, int stride, float4 (&v)[V], float4 (&g)[V]) {
+    const float *src = a.x + (size_t)(a.rowmap ? a.rowmap[t] : t) * a.ldx;
 #pragma unroll
-    for (int i = 0; i < kPackVecs; ++i) {
-        const int k = tid * 4 + 1024 * i;
-        v[i] = make_float4(0.f, 0.f, 0.f, 0.f); g[i] = make_float4(1.f, 1.f, 1.f, 1.f);
-        if (k < K) {
-            if (src) v[i] = *reinterpret_cast<const float4 *>(src + k);
-            if (a.gain) g[i] = *reinterpret_cast<const float4 *>(a.gain + k);
-        }
+    for (int i = 0; i < V; ++i) v[i] = *reinterpret_cast<const float4 *>(src + min((tid + stride * i) * 4, a.K - 4));
+#pragma unroll
+    for (int i = 0; i < V; ++i) g[i] = *reinterpret_cast<const float4 *>(a.gain + min((tid + stride * i) * 4, a.K - 4));
+}
+template <int V>
+__device__ __forceinline__ float pack_squares(const PackArgs &a, int tid, int stride, const float4 (&v)[V]) {
+    float ss = 0.f;
+#pragma unroll
+    for (int i = 0; i < V; ++i) {
+        const float q = v[i].x * v[i].x + v[i].y * v[i].y + v[i].z * v[i].z + v[i].w * v[i].w;
+        ss += (tid + stride * i) * 4 < a.K ? q : 0.f;
     }
-    float inv = 1.f;
-    if (a.gain) {
-        float ss = 0.f;
+    return ss;
+}
+template <int V>
+__device__ __forceinline__ void pack_store(const PackArgs &a, int t, int tid, int stride, float inv, const float4 (&v)[V], const float4 (&g)[V]) {
+    const int TB = (a.rows + 15) >> 4;
+    const bool real = t < a.rows;
 #pragma unroll
-        for (int i = 0; i < kPackVecs; ++i) ss += v[i].x * v[i].x + v[i].y * v[i].y + v[i].z * v[i].z + v[i].w * v[i].w;
-        ss = wave_sum(ss);
-        if ((tid & 63) == 0) s_ss[tid >> 6] = ss;
-        __syncthreads();
-        inv = 1.0f / sqrtf((s_ss[0] + s_ss[1] + s_ss[2] + s_ss[3]) / (float)K + a.eps);
-    }
-#pragma unroll
-    for (int i = 0; i < kPackVecs; ++i) {
-        const int k = tid * 4 + 1024 * i;
-        if (k < K) {
-            float f[4] = {v[i].x, v[i].y, v[i].z, v[i].w};
-            if (a.gain) { f[0] *= inv * g[i].x; f[1] *= inv * g[i].y; f[2] *= inv * g[i].z; f[3] *= inv * g[i].w; }
+    for (int i = 0; i < V; ++i) {
+        const int k = (tid + stride * i) * 4;
+        if (k < a.K) {
+            const float f[4] = {v[i].x * (inv * g[i].x), v[i].y * (inv * g[i].y), v[i].z * (inv * g[i].z), v[i].w * (inv * g[i].w)};
             // four of the eight elements a lane of the consuming product holds: 8 bytes, side by side with the neighbouring thread's
             const size_t off = act_tile_offset(t >> 4, k >> 5, TB) + (size_t)(((t & 15) + 16 * ((k & 31) >> 3)) * 8 + (k & 7));
             uint2 r;
-            r.x = (uint32_t)f32_to_f16_sat(f[0]) | ((uint32_t)f32_to_f16_sat(f[1]) << 16);
-            r.y = (uint32_t)f32_to_f16_sat(f[2]) | ((uint32_t)f32_to_f16_sat(f[3]) << 16);
+            r.x = real ? (uint32_t)f32_to_f16_sat(f[0]) | ((uint32_t)f32_to_f16_sat(f[1]) << 16) : 0u;
+            r.y = real ? (uint32_t)f32_to_f16_sat(f[2]) | ((uint32_t)f32_to_f16_sat(f[3]) << 16) : 0u;
             *reinterpret_cast<uint2 *>(a.out + off) = r;
         }
     }
+}
+
+// A workgroup per row: V pieces per thread, K <= 1024 V.
+template <int V>
+__global__ __launch_bounds__(256) void k_pack_act(PackArgs a) {
+    __shared__ float s_ss[4];
+    const int t = blockIdx.x, tid = threadIdx.x;
+    float4 v[V], g[V];
+    pack_load<V>(a, min(t, a.rows - 1), tid, 256, v, g);
+    const float ss = wave_sum(pack_squares<V>(a, tid, 256, v));
+    if ((tid & 63) == 0) s_ss[tid >> 6] = ss;
+    __syncthreads();
+    const float inv = 1.0f / sqrtf((s_ss[0] + s_ss[1] + s_ss[2] + s_ss[3]) / (float)a.K + a.eps);
+    pack_store<V>(a, t, tid, 256, inv, v, g);
+}
+
+// Long passes: a wave per row, four rows per workgroup, V pieces per lane, K <= 256 V: nothing to wait for between waves (1024 rows,
+// us: K = 896 5.8 -> 2.7, 2048 7.6 -> 3.7, 5120 12.9 -> 7.7; at 96 rows a workgroup per row is the faster: K = 5120 3.4 against 4.3).
+template <int V>
+__global__ __launch_bounds__(256) void k_pack_rows(PackArgs a) {
+    const int t = blockIdx.x * 4 + (int)(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    float4 v[V], g[V];
+    pack_load<V>(a, min(t, a.rows - 1), lane, 64, v, g);
+    const float inv = 1.0f / sqrtf(wave_sum(pack_squares<V>(a, lane, 64, v)) / (float)a.K + a.eps);
+    pack_store<V>(a, t, lane, 64, inv, v, g);
 }
 
 }  // namespace ead
