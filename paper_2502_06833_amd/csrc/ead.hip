@@ -108,11 +108,12 @@ __device__ __forceinline__ int wave_scan(int v) {       // inclusive sum over th
     return v;
 }
 
+template <bool GROUPS>
 __global__ __launch_bounds__(kPlanThreads) void k_plan(PlanArgs a) {
     extern __shared__ int sm[];
     __shared__ int s_rows;
     int *s_off = sm, *s_have = sm + a.batch, *s_group = sm + 2 * a.batch;      // s_group (a sequence's first group): only if there are groups
-    const int gr = a.group_rows;
+    const int gr = GROUPS ? a.group_rows : 0;
     const int tid = threadIdx.x;
     if (tid < 64) {
         int base = 0, nlm = 0, ngrp = 0;     // rows, logit rows and groups of the sequences before these
@@ -140,7 +141,7 @@ __global__ __launch_bounds__(kPlanThreads) void k_plan(PlanArgs a) {
                     a.p.lm_row[place] = off + n - 1; a.p.lm_seq[place] = b;
                 }
             }
-            if (gr) {
+            if constexpr (GROUPS) {
                 const int mine = n > 0 ? (have + n - 1) / gr - have / gr + 1 : 0, upto = ngrp + wave_scan(mine);
                 if (b < a.batch) s_group[b] = upto - mine;
                 ngrp = __shfl(upto, 63, kWave);
@@ -160,7 +161,7 @@ __global__ __launch_bounds__(kPlanThreads) void k_plan(PlanArgs a) {
         }
         const int pos = s_have[lo] + r - s_off[lo];
         a.p.row_seq[r] = lo; a.p.row_pos[r] = pos;
-        if (gr && (r == s_off[lo] || pos % gr == 0)) {
+        if (GROUPS && (r == s_off[lo] || pos % gr == 0)) {
             const int end = lo + 1 < a.batch ? s_off[lo + 1] : rows;
             a.p.groups[s_group[lo] + pos / gr - s_have[lo] / gr] = make_int2(r, min(gr - pos % gr, end - r));
         }
@@ -525,9 +526,31 @@ bool allow_big_lds(const void *kernel, size_t bytes) {
     return true;
 }
 
+// One row of a bf16 model through k_linear_ring where it takes the matrix (ring_takes in rules.hpp): the workgroups launched, else 0.  Not
+// beside another lane's passes (four rows replayed by two models side by side took 1.3 % longer with it), and not for a sampled LM head, whose
+// epilogue calls the generator for every logit, which many workgroups per unit hide and one does not.
+template <int EPI>
+int launch_ring(ead_handle *h, const LinArgs<bf16_t> &a, int T) {
+    const int K = a.K, NB = a.Np / 16;
+    if (T != 1 || h->two_lanes || a.samp_inv_t > 0.f || !ring_takes(K, EPI == EPI_RES, EPI == EPI_LOGITS)) return 0;
+    const int grid = std::min(NB, EPI == EPI_SWIGLU && K < 2048 ? 2 * h->n_cu : h->n_cu);
+    const auto lds = [&](int nw) { return ((size_t)K + 32 + 2 * nw * 16) * sizeof(float); };
+#define EAD_LR(NW_, U_, D_, XV_) hipLaunchKernelGGL((k_linear_ring<NW_, EPI, U_, D_, XV_>), dim3(grid), dim3(NW_ * 64), lds(NW_), h->stream, a)
+    if constexpr (EPI == EPI_RES) EAD_LR(8, 8, 1, 4);
+    else if (K < 40 * 32) EAD_LR(4, 8, 1, 2);
+    else if (K <= 2048) EAD_LR(8, 4, 2, 1);
+    else EAD_LR(8, 4, 2, 2);
+#undef EAD_LR
+    return grid;
+}
+
+// returns the number of workgroups that each leave a partial per row (the LM head)
 template <typename WT, int EPI>
-void launch_valu(ead_handle *h, int mi, LinArgs<WT> &a, int T, int grid) {
+int launch_valu(ead_handle *h, int mi, LinArgs<WT> &a, int T, int grid) {
     ProfScope ps(h, PK_FMA_QKV + EPI, mi, (double)a.Np * a.K * sizeof(WT));
+    if constexpr (std::is_same<WT, bf16_t>::value) {
+        if (const int n = launch_ring<EPI>(h, a, T)) return n;
+    }
     const int KC = a.K / 32;
     const size_t budget = 60 * 1024;
     int TC = 4;
@@ -552,6 +575,7 @@ void launch_valu(ead_handle *h, int mi, LinArgs<WT> &a, int T, int grid) {
         if (TC == 4) EAD_LV(4, 4); else if (TC == 2) EAD_LV(2, 4); else EAD_LV(1, 4);
     }
 #undef EAD_LV
+    return grid;
 }
 
 // T: the host's count of token rows.  The shape of the matrix and ceil(T / 16) pick the kernel:
@@ -890,8 +914,7 @@ ead_status forward_pass(ead_handle *h, int mi, int T, int n_lm, int ctx_max, boo
             }
         } else {
             g.x = h->x; g.ldx = d; g.gain = m.g_final; g.eps = m.eps;
-            launch_valu<WT, EPI_LOGITS>(h, mi, g, n_lm, grid);
-            h->lm_n_part = grid;
+            h->lm_n_part = launch_valu<WT, EPI_LOGITS>(h, mi, g, n_lm, grid);
         }
     }
     HIP_TRY(h, hipGetLastError());
@@ -1067,7 +1090,8 @@ void launch_plan(ead_handle *h, int m, int budget, int limit_off, int lm_mode, b
         for (int b = 0; b < h->batch; ++b) if ((*rows)[b] > 0) pa.allow[b >> 6] |= 1ull << (b & 63);
     }
     ProfScope ps(h, PK_PLAN, m, 0.0);
-    hipLaunchKernelGGL(k_plan, dim3(1), dim3(kPlanThreads), (h->group_rows ? 3 : 2) * h->batch * sizeof(int), h->stream, pa);
+    if (h->group_rows) hipLaunchKernelGGL(k_plan<true>, dim3(1), dim3(kPlanThreads), 3 * h->batch * sizeof(int), h->stream, pa);
+    else hipLaunchKernelGGL(k_plan<false>, dim3(1), dim3(kPlanThreads), 2 * h->batch * sizeof(int), h->stream, pa);
 }
 
 void launch_finalize(ead_handle *h, int m, int n_lm, bool score) {

@@ -2,7 +2,7 @@
 // (RMSNorm) and epilogues (rotary + KV append, residual add, SwiGLU, entropy statistics).
 //
 // Two paths share the tiled weight layout and the epilogues:
-//   k_linear_valu  plain FMAs for one or two token rows (and for fp32 weights); activations stay fp32,
+//   k_linear_valu, k_linear_ring  plain FMAs for one or two token rows (and for fp32 weights); activations stay fp32,
 //                  staged once per workgroup in LDS.
 //   k_linear_mfma, k_linear_mfma_ls, k_lm_ls, k_linear_mfma_gemm, k_linear_mfma_tile (k_linear_mfma_wt: fallback)
 //                  16x16x32 f16 products for three rows and more (batched decode, catch-up chunks, prompts);
@@ -299,6 +299,122 @@ __global__ __launch_bounds__(NW * 64) void k_linear_valu(LinArgs<WT> a) {
         if constexpr (EPI == EPI_LOGITS) {
             if (tid < 16 * TC) logits_flush<WT>(a, t0 + (tid >> 4), t0 + (tid >> 4) < T, st);
         }
+    }
+}
+
+// ------------------------------------------------------------------------------------
+// One row of a bf16 model, where this is the faster form (launch_valu): QKV and gate/up of a short K, long residual projections, the LM head.
+// A wave needs only its own slice of the activations, so it requests the slice (XV vectors a lane) and its gains before its first weights,
+// leaves their product in LDS for itself alone, and the RMSNorm factor, which needs the whole row, is applied to the finished sums: the wait
+// for the row's sum of squares between two barriers goes.  Weights run through a ring of D groups of U tiles across the row blocks
+// of the workgroup, one barrier per row block.  (The activations must not be loaded in a loop: the compiler then waits for the
+// weights requested after them, which cost 1 us a launch.)  k_linear_valu -> this, us: QKV 3072 x 2048 6.0 -> 5.7, 2048 x 1536 6.1 -> 5.2;
+// down 2048 x 8192 9.9 -> 9.5, 3072 x 8192 12.2 -> 11.7; LM head 128256 x 2048 87 -> 82, 128256 x 3072 123 -> 116.
+// What bounds it: the weight stream, and in launches of some 10 MB the latencies.
+// ------------------------------------------------------------------------------------
+template <int NW, int EPI, int U, int D, int XV>
+__global__ __launch_bounds__(NW * 64) void k_linear_ring(LinArgs<bf16_t> a) {
+    extern __shared__ float smem[];
+    const int K = a.K, KC = K >> 5, NB = a.Np >> 4;
+    float *xs = smem;                                      // [K]: a wave's slice is written and read by the wave alone
+    float *zero = smem + K;                                // [32]: what tiles past a slice's end are multiplied with
+    float *red = zero + 32;                                // [2][NW][16]
+    __shared__ float s_ss[NW];
+    const int tid = threadIdx.x, lane = tid & 63, g8 = (lane >> 4) * 8;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const bool valid = tid < 16 && *a.count > 0;
+    const int kc0 = (wave * KC) / NW, kc1 = ((wave + 1) * KC) / NW;
+    const int ng = max(1, (kc1 - kc0 + U - 1) / U);        // groups of U tiles per row block
+    const int nrb = (NB - 1 - (int)blockIdx.x) / (int)gridDim.x + 1, total = nrb * ng;      // the grid is at most NB
+
+    const int ks = kc0 * 32 + lane * 4, ke = kc1 * 32;
+    const float *src = a.x + (size_t)(a.rowmap ? a.rowmap[0] : 0) * a.ldx;
+    float4 xv[XV], gv[XV];
+#pragma unroll
+    for (int i = 0; i < XV; ++i) xv[i] = *reinterpret_cast<const float4 *>(src + min(ks + 256 * i, K - 4));
+    if (a.gain) {
+#pragma unroll
+        for (int i = 0; i < XV; ++i) gv[i] = *reinterpret_cast<const float4 *>(a.gain + min(ks + 256 * i, K - 4));
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    Vec8<bf16_t> w[D][U];
+    int nj = 0, ngi = 0;                                   // next group to request; past the end the last row block's again, never used
+    const bf16_t *wbase = a.W + lane * 8;
+    auto request = [&](int s) __attribute__((always_inline)) {
+        const bf16_t *p = wbase + tile_offset((int)blockIdx.x + nj * (int)gridDim.x, 0, KC);
+#pragma unroll
+        for (int u = 0; u < U; ++u) w[s][u].load_stream(p + (size_t)min(kc0 + ngi * U + u, max(kc1 - 1, 0)) * 512);
+        if (++ngi == ng) { ngi = 0; if (nj + 1 < nrb) ++nj; }
+    };
+#pragma unroll
+    for (int s = 0; s < D; ++s) { request(s); __builtin_amdgcn_sched_barrier(0); }
+    float ss = 0.f;
+#pragma unroll
+    for (int i = 0; i < XV; ++i) {
+        const int k = ks + 256 * i;
+        if (k < ke) {
+            float4 v = xv[i];
+            if (a.gain) {
+                ss += v.x * v.x + v.y * v.y + v.z * v.z + v.w * v.w;
+                v.x *= gv[i].x; v.y *= gv[i].y; v.z *= gv[i].z; v.w *= gv[i].w;
+            }
+            *reinterpret_cast<float4 *>(xs + k) = v;
+        }
+    }
+    if (a.gain) { ss = wave_sum(ss); if (lane == 0) s_ss[wave] = ss; }
+    if (tid < 32) zero[tid] = 0.f;
+    __syncthreads();
+
+    EntStat st; st.init();
+    EpiPre pre;
+    float acc = 0.f, inv = 1.f;
+    int g = 0, rb = blockIdx.x, par = 0;
+    for (int i0 = 0; i0 < total; i0 += D) {
+#pragma unroll
+        for (int s = 0; s < D; ++s) {
+            if (i0 + s < total) {                          // uniform over the wave; every wave meets the others once per row block
+                if (g == 0) {
+                    pre = epi_prefetch<bf16_t, EPI>(a, rb * 16 + (tid & 15), 0, valid);
+                    acc = 0.f;
+                }
+                const int kb = kc0 + g * U;
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    float wf[8];
+                    w[s][u].unpack_w(wf);
+                    const float *xp = kb + u < kc1 ? xs + (kb + u) * 32 + g8 : zero + g8;
+                    const float4 x0 = *reinterpret_cast<const float4 *>(xp), x1 = *reinterpret_cast<const float4 *>(xp + 4);
+                    acc += wf[0] * x0.x + wf[1] * x0.y + wf[2] * x0.z + wf[3] * x0.w
+                         + wf[4] * x1.x + wf[5] * x1.y + wf[6] * x1.z + wf[7] * x1.w;
+                }
+                __builtin_amdgcn_sched_barrier(0);
+                request(s);
+                __builtin_amdgcn_sched_barrier(0);
+                if (++g == ng) {
+                    float *rd = red + (size_t)par * NW * 16;      // two sets: the next row block's sums may be written while these are read
+                    acc += __shfl_xor(acc, 16, kWave);
+                    acc += __shfl_xor(acc, 32, kWave);
+                    if (lane < 16) rd[wave * 16 + lane] = acc;
+                    __syncthreads();
+                    if (tid < 16) {
+                        if (a.gain && rb == (int)blockIdx.x) {
+                            float tot = 0.f;
+#pragma unroll
+                            for (int q = 0; q < NW; ++q) tot += s_ss[q];
+                            inv = 1.0f / sqrtf(tot / (float)K + a.eps);
+                        }
+                        float v = 0.f;
+#pragma unroll
+                        for (int q = 0; q < NW; ++q) v += rd[q * 16 + tid];
+                        epilogue<bf16_t, EPI>(a, rb * 16 + tid, 0, v * inv, valid, st, pre);
+                    }
+                    par ^= 1; g = 0; rb += gridDim.x;
+                }
+            }
+        }
+    }
+    if constexpr (EPI == EPI_LOGITS) {
+        if (tid < 16) logits_flush<bf16_t>(a, 0, valid, st);
     }
 }
 

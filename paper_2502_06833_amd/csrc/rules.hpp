@@ -138,6 +138,11 @@ inline int attention_chunk(int T, int KV, int hd, int ctx_max, bool mfma, int n_
     return chunk;
 }
 
+// Whether one row goes through k_linear_ring instead of k_linear_valu: short K where the wait for the row's norm shows (QKV and gate/up up to
+// 2048: 2048 x 1536 6.1 -> 5.2 us; but 5120 x 3072 10.2 -> 11.1, 6144 x 4096 11.5 -> 12.8), the LM head below 4096 (at 4096 156 against 158),
+// residual projections of 6145 to 8192 (3072 x 8192 12.2 -> 11.7; 2048 x 2048 4.9 -> 5.1, 896 x 4864 7.0 -> 8.0, 4096 x 14336 21.4 -> 21.8).
+inline bool ring_takes(int K, bool residual, bool lm) { return residual ? K > 6144 && K <= 8192 : K <= (lm ? 4064 : 2048); }
+
 // Whether a pass's attention goes to k_attn_prompt (rows of `seqs` sequences in workgroups of four waves that share K and V and take
 // all keys in turn) instead of k_attn_mfma (`groups` workgroups per KV head whose waves split the keys).  The first takes
 // 0.5 (head dims up to 64) to 0.7 us per 32 keys of the longest context whatever the number of rows, up to a workgroup per

@@ -58,6 +58,8 @@ int host_attention_chunk(int T, int KV, int hd, int ctx, int mfma, long items) {
 
 int host_prompt_attention(int T, int seqs, long groups, int KV, int ctx) { return prompt_attention(T, seqs, groups, KV, ctx); }
 
+int host_ring_takes(int K, int residual, int lm) { return ring_takes(K, residual != 0, lm != 0); }
+
 // row blocks, token blocks and slabs of K a workgroup of k_linear_mfma takes, as R * 100 + NT * 10 + KS; 0 if scratch does not hold the slabs
 int host_narrow_plan(int NB, int KC, int TB, int split, long floats, int groups) {
     const NarrowPlan p = narrow_plan(NB, KC, TB, 256, split != 0, (size_t)floats, groups);

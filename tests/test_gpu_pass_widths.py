@@ -42,7 +42,7 @@ def test_score_at_every_pass_width(small, large):
 
 
 def test_tiles_of_two_to_sixteen_blocks():
-    """Every R x NT of narrow_plan (rules.hpp) that the shapes above do not reach: 192 row blocks at 33 to 150 rows, scored, and at
+    """Every R x NT of narrow_plan (rules.hpp) that the shapes above do not reach: 192 row blocks at 33 to 150 rows (and one and two: K of 1056 and 3072), scored, and at
     200 as a prompt (four row blocks and four token blocks), whose first generated entropy hangs on it."""
     import paper_2502_06833_amd as ead
     small = si.ModelShape("mid-o", 1, 1056, 33, 11, 416, 1040, 1e-5, 1e4)          # 66 row blocks x 33 k tiles
@@ -52,7 +52,7 @@ def test_tiles_of_two_to_sixteen_blocks():
     toks = si.prompt_np(0, "tiles", 201, small.vocab)
     for which, om in ((0, os_), (1, ol)):
         ref = om.forward_dense(toks)
-        for T in (33, 49, 65, 97, 150):
+        for T in (1, 2, 33, 49, 65, 97, 150):
             print(f"score model {which} width {T}", flush=True)
             check_logits(e.score(which, toks[:T])["logits"], ref[:T], TOL_LOGIT)
         out = e.replay([toks], np.array([[5]], np.int32), np.array([[which]], np.uint8))

@@ -161,3 +161,9 @@ def test_narrow_plans_are_instantiated_and_stay_within_the_scratch(host):
     (64, 64, 64, 8, 1000, 0), (160, 1, 80, 2, 760, 0), (500, 1, 250, 2, 1100, 1)])
 def test_prompt_attention_takes_the_passes_it_is_faster_at(host, T, seqs, groups, KV, ctx, takes):
     assert host.host_prompt_attention(T, seqs, C.c_long(groups), KV, ctx) == takes
+
+
+@pytest.mark.parametrize("K,residual,lm,takes", [(2048, 0, 0, 1), (3072, 0, 0, 0), (2048, 1, 0, 0), (8192, 1, 0, 1), (14336, 1, 0, 0), (4864, 1, 0, 0),
+                                                 (3072, 0, 1, 1), (4096, 0, 1, 0), (32, 0, 0, 1)])
+def test_ring_kernel_takes_the_matrices_it_is_faster_at(host, K, residual, lm, takes):
+    assert host.host_ring_takes(K, residual, lm) == takes
