@@ -510,7 +510,7 @@ __global__ __launch_bounds__(kAttnMfmaWaves * 64, 2) void k_attn_mfma(AttnArgs<b
 // own (positions cut at multiples of all its waves' rows, so a row's column follows from its position alone) and all take the same
 // keys: a block of 32 keys, K as the fragments of the score product and V as tiles of the transposed copy, is requested straight into
 // LDS once for the workgroup, kPromptDepth - 1 blocks ahead.  No sums meet: a wave keeps its columns' maxima, sums and outputs from the
-// first key to the last and stores them.  Those 3500 rows: 99 us (0.5B shape 76 -> 33); with eight waves a workgroup 104 and 35.
+// first key to the last and stores them.  Those 3500 rows: 87 us (0.5B shape 76 -> 29); with eight waves a workgroup 104 and 35.
 // What bounds it: with few workgroups the chain of a block (fragments, score products, maximum over lanes, exponentials, output products:
 // 0.5-0.7 us), with many the vector arithmetic between the products.  prompt_attention (rules.hpp) says which passes come here.
 // ------------------------------------------------------------------------------------

@@ -604,7 +604,7 @@ bool launch_ls(ead_handle *h, const LinArgs<bf16_t> &a, int grid) {
 // Passes of up to 32 rows, and longer ones through matrices that k_linear_mfma_ls does not serve better: k_linear_mfma, a
 // workgroup of few waves per R row blocks and NT token blocks (narrow_plan in rules.hpp says how many of each, and how many slabs
 // of K).  Two waves a workgroup where row blocks are many, so that the workgroups are many and all resident: gate/up of up to 16
-// rows (28672 x 4096: 54.0 us with four waves and four row blocks, 40.7 with two and two, 40.2 with two and one; 9728 x 896:
+// rows (28672 x 4096: 44.8 us with four waves and two row blocks, 40.7 with two and two, 40.2 with two and one; 9728 x 896:
 // 7.1 with four and two, 6.3 with two and one; but 16384 x 3072: 18.0 and 18.7), of 17 to 32 rows with four row blocks (51.7 -> 46.9).
 template <int EPI>
 void launch_narrow(ead_handle *h, LinArgs<bf16_t> &a, int T) {
@@ -678,7 +678,7 @@ void launch_mfma(ead_handle *h, int mi, LinArgs<bf16_t> &a, int T) {
     // row blocks are split along K over workgroups; a second kernel adds the slabs in order and
     // runs the epilogue.  Gate/up goes this way from 128 row blocks (9728 x 896 at 64 rows: 8.4 us against 12.3; 16384 x
     // 2048: 18.0 against 24.8 with seven row blocks a workgroup).  Residual and QKV projections of up to 64 rows and
-    // under 40 MB don't: the second launch costs more than it saves (4096 x 4096: 13.1 against 15.3 us; 5120 x 5120: 18.7
+    // under 40 MB don't: the second launch costs more than it saves (4096 x 4096: 12.0 against 15.3 us; 5120 x 5120: 18.7
     // against 18.0, 7168 x 5120 with the QKV epilogue: 28 against 23).  Small matrices do from two sweeps
     // (QKV) or three (3072 x 2048 at 300 rows: 26 us in sweeps of 64, 18 this way at 512).
     const bool longpass = TB >= 4 * kWideTok, multi = TB > kWideTok;

@@ -57,17 +57,17 @@ inline int entropy_row_parts(int rows, int V) {
 // These passes are a weight stream and a chain of latencies, so what counts is that every compute unit has a workgroup and that a
 // workgroup has little to do: the smallest R x NT that is at most one workgroup per unit.  A matrix's second and
 // later token blocks find its tiles in L2.  Measured on rotating weights, us, with the former rule (all of up to 64 rows
-// in one workgroup, R by matrix size) -> now: 896 x 896 at 32, 64 and 128 rows 4.2 -> 3.5, 5.4 -> 3.5, 5.4 -> 4.1; 1152 x 896 at 64
-// rows 7.3 -> 5.0 (one block and one: 4.8); 896 x 4864 at 64: 9.8 -> 7.5; 2048 x 2048 at 32: 5.6 -> 4.8; 3072 x 2048 at 64: 9.9 ->
-// 8.5 (R = 1, NT = 2, 384 workgroups: 10.6); 4096 x 4096 at 64: 13.4 -> 12.0.  Of two R x NT of two, the one with more workgroups; of equally many
+// in one workgroup, R by matrix size) -> now: 896 x 896 at 32, 64 and 128 rows 4.3 -> 3.5, 5.7 -> 3.5, 5.6 -> 4.3; 1152 x 896 at 64
+// rows 7.2 -> 5.1 (one block and one: 4.9); 896 x 4864 at 64: 9.4 -> 7.6; 2048 x 2048 at 32: 6.0 -> 4.9; 3072 x 2048 at 64: 10.2 ->
+// 8.6 (R = 1, NT = 2, 384 workgroups: 10.8); 4096 x 4096 at 64: 13.4 -> 12.0.  Of two R x NT of two, the one with more workgroups; of equally many
 // two row blocks (2048 x 2048 at 64 rows: 5.6 against 5.9), from 128 k tiles on two token blocks (896 x 4864 at 96: 9.7 against 11.0).
-// Eight blocks (3072 x 3072 at 160 rows: 20.8 -> 12.9) and sixteen (at 256: 23.8 -> 17.2) only where that leaves one round of
+// Eight blocks (3072 x 3072 at 160 rows: 23.4 -> 12.9) and sixteen (at 256: 31.3 -> 17.2) only where that leaves one round of
 // workgroups; a QKV projection of few k tiles takes two rounds of small ones instead (1152 x 896 at 320 rows 9.6 -> 8.3).
 //
 // K is split where units would idle and a slab keeps more than 32 k tiles (896 x 4864 at 16 rows: 8.0 -> 6.4; 2048 x 8192: 128
-// workgroups 10.7, two slabs 9.8).  Long K (256 k tiles and more) of 17 to 64 rows: two row blocks and two token blocks,
-// whose tiles are fetched half as often, and the slabs that fill the chip (2048 x 8192 at 64 rows 15.1 -> 14.0, 4096 x
-// 14336 at 32: 28.0 -> 24.5); of up to 16 rows and more than 3/4 of a row block per unit: two or four row blocks (4096 x 14336: 27.9 -> 21.5, 5120 x
+// workgroups 11.8, two slabs 9.9, four of two row blocks 10.3).  Long K (256 k tiles and more) of 17 to 64 rows: two row blocks and two token blocks,
+// whose tiles are fetched half as often, and the slabs that fill the chip (2048 x 8192 at 64 rows 14.0, unsplit 15.0; 4096 x
+// 14336 at 32 24.5, unsplit 28.0); of up to 16 rows and more than 3/4 of a row block per unit: two or four row blocks (4096 x 14336: 27.9 -> 21.5, 5120 x
 // 13824: 29.5 -> 26.1).
 constexpr int kSplitKMax = 8;       // most slabs of K per row-block group
 
