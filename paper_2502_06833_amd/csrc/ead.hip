@@ -1498,14 +1498,15 @@ ead_status copy_out(ead_handle *h, void *dst, const void *src, size_t bytes) {
     hipStream_t st = h->stream;
     const int n = (int)((bytes + kCopyPiece - 1) / kCopyPiece);
     const int want = std::min({kCopyThreads, n / 2, (int)std::thread::hardware_concurrency()});
-    if (want >= 2 && !h->h_copy) {
-        if (hipHostMalloc((void **)&h->h_copy, kCopySlots * kCopyPiece, hipHostMallocDefault) != hipSuccess) { h->h_copy = nullptr; (void)hipGetLastError(); }
+    if (want >= 2 && h->copy_ev.size() < (size_t)kCopySlots) {
+        if (!h->h_copy && hipHostMalloc((void **)&h->h_copy, kCopySlots * kCopyPiece, hipHostMallocDefault) != hipSuccess) { h->h_copy = nullptr; (void)hipGetLastError(); }
+        hipEvent_t e;
         while (h->h_copy && h->copy_ev.size() < (size_t)kCopySlots) {
-            hipEvent_t e;
-            HIP_TRY(h, hipEventCreateWithFlags(&e, hipEventDisableTiming));
+            if (hipEventCreateWithFlags(&e, hipEventDisableTiming) != hipSuccess) { (void)hipGetLastError(); break; }
             h->copy_ev.push_back(e);
         }
     }
+    const bool pieces = want >= 2 && h->copy_ev.size() == (size_t)kCopySlots;      // else the runtime's copy
     struct Shared {                                    // pieces 0 .. landed - 1 are in their slots; `taken` of them have a thread; `left` counts a slot's pieces that have left it
         std::mutex m; std::condition_variable cv;
         int landed = 0, taken = 0, left[kCopySlots] = {0}; bool stop = false;
@@ -1526,7 +1527,7 @@ ead_status copy_out(ead_handle *h, void *dst, const void *src, size_t bytes) {
         }
     };
     std::vector<std::thread> threads;
-    if (want >= 2 && h->h_copy) {
+    if (pieces) {
         try {
             threads.reserve(want);
             while ((int)threads.size() < want) threads.emplace_back(bring);
