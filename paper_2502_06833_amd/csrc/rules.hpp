@@ -151,9 +151,13 @@ inline bool ring_takes(int K, bool residual, bool lm) { return residual ? K > 61
 // rows from key 200 on: 64 rows (176 workgroups) 10.6 / 11.1, 130 (352) 16.6 / 12.5; from 600: 64 rows 14.8 / 19.5, 130 rows 25.0 / 21.1, 11 rows each of
 // 12 sequences (384) 23.7 / 20.5, 4 rows each of 40 (640) 50.6 / 24.6; from 2000: 64 rows 29.7 / 49.5, 160 (440) 55.6 / 52.1, 500 rows (1344) 160.6 / 66.3; from 8000: 160 rows 177 /
 // 183, 500 rows 538 / 221.  Heads of 64, 7 per KV head, 2 KV heads: from 600 160 rows (160) 13.2 / 16.1, 500 rows (500) 27.2 / 21.7.
+//
+// Scoring stays with k_attn_mfma.  It returns logits, and the two kernels add a row's keys in another order: behind a few layers of half-precision
+// activations that is 9e-4 of the logits' norm (8 layers of the 14B shape, 101 rows; either kernel is 1.4e-3 from 64 bits), where a pass of 101 rows
+// with its logits takes 3.7 ms and the other kernel saves 0.03 of them.
 constexpr int kGroupSeqs = 1024;                        // most sequences of a batch whose passes k_plan lists in groups
-inline bool prompt_attention(int T, int seqs, long groups, int KV, int ctx) {
-    if (T < 17 || T < 4 * seqs) return false;
+inline bool prompt_attention(int T, int seqs, long groups, int KV, int ctx, bool scoring) {
+    if (scoring || T < 17 || T < 4 * seqs) return false;
     return ctx <= 160 || groups * KV >= (ctx <= 320 ? 256 : ctx <= 4096 ? 400 : 512);
 }
 

@@ -56,7 +56,9 @@ int host_entropy_row_parts(int rows, int V) { return entropy_row_parts(rows, V);
 
 int host_attention_chunk(int T, int KV, int hd, int ctx, int mfma, long items) { return attention_chunk(T, KV, hd, ctx, mfma != 0, 256, 16, items); }
 
-int host_prompt_attention(int T, int seqs, long groups, int KV, int ctx) { return prompt_attention(T, seqs, groups, KV, ctx); }
+int host_prompt_attention(int T, int seqs, long groups, int KV, int ctx) { return prompt_attention(T, seqs, groups, KV, ctx, false); }
+
+int host_score_prompt_attention(int T, long groups, int KV, int ctx) { return prompt_attention(T, 1, groups, KV, ctx, true); }
 
 int host_ring_takes(int K, int residual, int lm) { return ring_takes(K, residual != 0, lm != 0); }
 

@@ -10,6 +10,7 @@ import pytest
 
 import oracle
 import synth_inputs as si
+from gpu_helpers import make_pair
 
 pytestmark = pytest.mark.gpu
 
@@ -118,8 +119,8 @@ def test_decode_rows_in_two_key_splits(heads, kv_heads, hd, rows, lens):
 @pytest.mark.parametrize("heads,kv,hd", [(8, 8, 32), (4, 2, 64), (6, 2, 128), (4, 1, 32), (5, 1, 128), (6, 1, 64), (7, 1, 64), (8, 1, 128), (4, 1, 128)])
 def test_prompt_attention_of_every_head_layout(heads, kv, hd):
     """k_attn_prompt: rows cut at multiples of 8 (eight heads share K and V) to 64 positions, last key blocks and last groups partly
-    filled.  Scored in one pass of up to 160 rows from position 0; prompts of several lengths in one pass (first, middle and last
-    rows of a group), whose first generated entropy hangs on every cached key."""
+    filled.  Prompts of several lengths in one pass (first, middle and last rows of a group), whose first generated entropy hangs on
+    every cached key; and passes of the same rows scored, through k_attn_mfma."""
     import paper_2502_06833_amd as ead
     shape = si.ModelShape(f"pa{heads}-{hd}", 2, heads * hd, heads, kv, 256, 512, 1e-5, 1e4, bf16=True)
     tiny = si.ModelShape("pa-other", 1, 128, 4, 4, 128, 512, 1e-5, 1e4, bf16=True)
@@ -137,4 +138,31 @@ def test_prompt_attention_of_every_head_layout(heads, kv, hd):
     got = e.generate(prompts, 1)
     for b, p in enumerate(prompts):
         assert abs(got["H"][b, 0] - oracle.entropy_rows(om.forward_dense(p)[-1:])[0][0]) < TOL_H, lens[b]
+    e.close()
+
+
+@pytest.mark.parametrize("heads,kv,hd", [(8, 8, 32), (4, 2, 64), (6, 2, 128), (4, 1, 32), (5, 1, 128), (6, 1, 64), (7, 1, 64), (8, 1, 128)])
+def test_prompt_attention_from_inside_a_group(heads, kv, hd):
+    """k_attn_prompt in passes that start inside a group of rows (leading waves idle, leading columns of a wave masked) and end at each of
+    a group's rows: one model generates n tokens after a prompt of 45, then the other takes over and catches up n + 1 rows.  One layer, so
+    that the entropy there hangs on the pass's last row, whose attention is the only thing that scoring the same tokens does in another
+    kernel (k_attn_mfma).  The LM head of one row keeps float32 activations and that of a scoring pass rounds them to 11 bits, 2e-4 each over
+    512 logits of deviation 1.5: 5e-4 between the two seen, 1e-3 allowed; one wrong key moves them by 1e-2 and more in the median, the worst of a case by 0.09."""
+    import paper_2502_06833_amd as ead
+    shape = si.ModelShape(f"pc{heads}-{hd}", 1, heads * hd, heads, kv, 256, 512, 1e-5, 1e4, bf16=True)
+    tiny = si.ModelShape("pc-other", 1, 128, 4, 4, 128, 512, 1e-5, 1e4, bf16=True)
+    W, Wt, om, _ = make_pair(shape, tiny, lm_sigma=1.5)
+    e = ead.EAD(shape, W, tiny, Wt, window=5, tau=0.0, d_min=4, max_batch=1, max_seq=160)
+    toks = si.prompt_np(6, "inside", 160, 512)
+    ref = oracle.entropy_rows(om.forward_dense(toks))[0]
+    scored = e.score(0, toks)["H"]
+    worst = 0.0
+    for n in range(max(17, 65 // kv), min(max(17, 65 // kv) + 66, 114)):
+        mids = np.ones((1, n + 1), np.uint8)
+        mids[0, n] = 0
+        H = e.replay([toks[:45]], toks[None, 45:45 + n + 1], mids)["H"][0, n]
+        worst = max(worst, abs(H - scored[44 + n]))
+        assert abs(H - ref[44 + n]) < TOL_H, n
+    print(f"heads {heads} kv {kv} hd {hd}: {worst:.1e} from scoring", flush=True)
+    assert worst < 1e-3
     e.close()

@@ -163,6 +163,16 @@ def test_prompt_attention_takes_the_passes_it_is_faster_at(host, T, seqs, groups
     assert host.host_prompt_attention(T, seqs, C.c_long(groups), KV, ctx) == takes
 
 
+@pytest.mark.parametrize("G,KV", [(5, 8), (7, 2), (1, 32), (8, 1)])
+def test_scoring_keeps_its_attention_kernel(host, G, KV):
+    """Logits that a program compares from one version to the next: no scoring pass (up to 160 rows, any context) changes kernels."""
+    rq = 16 // G
+    for T in (17, 64, 101, 128, 160):
+        for pos in (0, 160, 1120, 4800):
+            groups = (pos + T - 1) // rq - pos // rq + 1
+            assert not host.host_score_prompt_attention(T, C.c_long(groups), KV, pos + T), (T, pos)
+
+
 @pytest.mark.parametrize("K,residual,lm,takes", [(2048, 0, 0, 1), (3072, 0, 0, 0), (2048, 1, 0, 0), (8192, 1, 0, 1), (14336, 1, 0, 0), (4864, 1, 0, 0),
                                                  (3072, 0, 1, 1), (4096, 0, 1, 0), (32, 0, 0, 1)])
 def test_ring_kernel_takes_the_matrices_it_is_faster_at(host, K, residual, lm, takes):
