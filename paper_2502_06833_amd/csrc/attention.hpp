@@ -510,29 +510,14 @@ __global__ __launch_bounds__(kAttnMfmaWaves * 64, 2) void k_attn_mfma(AttnArgs<b
 // own (positions cut at multiples of all its waves' rows, so a row's column follows from its position alone) and all take the same
 // keys: a block of 32 keys, K as the fragments of the score product and V as tiles of the transposed copy, is requested straight into
 // LDS once for the workgroup, kPromptDepth - 1 blocks ahead.  No sums meet: a wave keeps its columns' maxima, sums and outputs from the
-// first key to the last and stores them.  Those 3500 rows: 87 us (0.5B shape 76 -> 29); with eight waves a workgroup 104 and 35.
+// first key to the last and stores them.  12 x 290 rows from position 300 on: 274 -> 85 us (0.5B shape 95 -> 26); eight waves a workgroup were 5 % slower.
+// One chain of sums instead of four alone leaves it 1-4 % further from 64 bits than k_attn_mfma (four waves hold four maxima, whose
+// probabilities, ones, split without a rest), so the queries are held whole, in three terms: 1-6 % nearer at small scores, 2-6 times at
+// large ones (2e-6 to 3e-6 in all, 17-160 rows, up to 4000 keys), for 3-8 % of its time.
 // What bounds it: with few workgroups the chain of a block (fragments, score products, maximum over lanes, exponentials, output products:
-// 0.5-0.7 us), with many the vector arithmetic between the products.  prompt_attention (rules.hpp) says which passes come here.
+// 0.55-0.76 us), with many the vector arithmetic between the products.  prompt_attention (rules.hpp) says which passes come here.
 // ------------------------------------------------------------------------------------
 constexpr int kPromptWaves = 4, kPromptDepth = 3;     // waves per workgroup; key blocks in LDS
-
-// two floats to bf16, rounded to nearest even (finite values), in one instruction
-__device__ __forceinline__ uint32_t pack_bf16(float a, float b) {
-    typedef float f32x2_t __attribute__((ext_vector_type(2)));
-    typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
-    return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2_t{a, b}, bf16x2_t));
-}
-// eight floats as bf16 hi + lo
-__device__ __forceinline__ void split8(const float (&f)[8], bf16x8_t &hi, bf16x8_t &lo) {
-    u32x4_t h, l;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        const uint32_t w = pack_bf16(f[2 * e], f[2 * e + 1]);
-        h[e] = w;
-        l[e] = pack_bf16(f[2 * e] - __uint_as_float(w << 16), f[2 * e + 1] - __uint_as_float(w & 0xFFFF0000u));
-    }
-    hi = __builtin_bit_cast(bf16x8_t, h); lo = __builtin_bit_cast(bf16x8_t, l);
-}
 
 template <int HD, int G>
 __global__ __launch_bounds__(kPromptWaves * 64, 2) void k_attn_prompt(AttnArgs<bf16_t> a) {
@@ -575,8 +560,8 @@ __global__ __launch_bounds__(kPromptWaves * 64, 2) void k_attn_prompt(AttnArgs<b
         }
         ++next; nslot = nslot + 1 == kPromptDepth ? 0 : nslot + 1;
     };
-    // Q^T fragments: column col, hd elements kc*32 + lg*8 .. +8, scaled, as bf16 hi + lo
-    bf16x8_t qh[KC], ql[KC];
+    // Q^T fragments: column col, hd elements kc*32 + lg*8 .. +8, scaled, whole: three terms hold a float32's 24 bits
+    bf16x8_t qh[KC], ql[KC], qr[KC];
 #pragma unroll
     for (int kc = 0; kc < KC; ++kc) {
         float f[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
@@ -586,7 +571,7 @@ __global__ __launch_bounds__(kPromptWaves * 64, 2) void k_attn_prompt(AttnArgs<b
             f[0] = x0.x * a.scale; f[1] = x0.y * a.scale; f[2] = x0.z * a.scale; f[3] = x0.w * a.scale;
             f[4] = x1.x * a.scale; f[5] = x1.y * a.scale; f[6] = x1.z * a.scale; f[7] = x1.w * a.scale;
         }
-        split8(f, qh[kc], ql[kc]);
+        qh[kc] = take_bf16(f); ql[kc] = take_bf16(f); qr[kc] = take_bf16(f);
     }
 #pragma unroll
     for (int i = 0; i < kPromptDepth - 1; ++i) request();
@@ -612,6 +597,11 @@ __global__ __launch_bounds__(kPromptWaves * 64, 2) void k_attn_prompt(AttnArgs<b
 #pragma unroll
             for (int hb = 0; hb < HB; ++hb) vf[hb] = *reinterpret_cast<const u32x4_t *>(&s_kv[slot][2 * KC + hb][lane * 8]);
             f32x4_t s0 = f32x4_t{0.f, 0.f, 0.f, 0.f}, s1 = s0;
+#pragma unroll
+            for (int kc = 0; kc < KC; ++kc) {
+                s0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, kf[0][kc]), qr[kc], s0, 0, 0, 0);
+                s1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, kf[1][kc]), qr[kc], s1, 0, 0, 0);
+            }
 #pragma unroll
             for (int kc = 0; kc < KC; ++kc) {
                 s0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, kf[0][kc]), ql[kc], s0, 0, 0, 0);
@@ -641,8 +631,7 @@ __global__ __launch_bounds__(kPromptWaves * 64, 2) void k_attn_prompt(AttnArgs<b
             float pr[8];
 #pragma unroll
             for (int e = 0; e < 8; ++e) { pr[e] = __expf(sc[e] - m); lsum += pr[e]; }      // masked: exp(-inf) = 0
-            bf16x8_t ph, pl;
-            split8(pr, ph, pl);
+            const bf16x8_t ph = take_bf16(pr), pl = take_bf16(pr);
 #pragma unroll
             for (int hb = 0; hb < HB; ++hb) acc[hb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, vf[hb]), pl, acc[hb], 0, 0, 0);
 #pragma unroll

@@ -157,6 +157,25 @@ __device__ __forceinline__ void request_tile(const bf16_t *base, uint32_t voff, 
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(voff), "s"(base) : "memory");
 }
 
+// ---- bf16 terms of float32 values ---------------------------------------------------------
+// two floats to bf16, rounded to nearest even (finite values), in one instruction
+__device__ __forceinline__ uint32_t pack_bf16(float a, float b) {
+    typedef float f32x2_t __attribute__((ext_vector_type(2)));
+    typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2_t{a, b}, bf16x2_t));
+}
+// eight floats rounded to bf16; what is left of them stays in f (three terms hold a float32's 24 bits)
+__device__ __forceinline__ bf16x8_t take_bf16(float (&f)[8]) {
+    u32x4_t h;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const uint32_t w = pack_bf16(f[2 * e], f[2 * e + 1]);
+        h[e] = w;
+        f[2 * e] -= __uint_as_float(w << 16); f[2 * e + 1] -= __uint_as_float(w & 0xFFFF0000u);
+    }
+    return __builtin_bit_cast(bf16x8_t, h);
+}
+
 // ---- wave64 reductions -------------------------------------------------------------
 __device__ __forceinline__ float wave_sum(float v) {
 #pragma unroll

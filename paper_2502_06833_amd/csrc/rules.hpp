@@ -145,8 +145,9 @@ inline bool ring_takes(int K, bool residual, bool lm) { return residual ? K > 61
 
 // Whether a pass's attention goes to k_attn_prompt (rows of `seqs` sequences in workgroups of four waves that share K and V and take
 // all keys in turn) instead of k_attn_mfma (`groups` workgroups per KV head whose waves split the keys).  The first takes
-// 0.5 (head dims up to 64) to 0.7 us per 32 keys of the longest context whatever the number of rows, up to a workgroup per
-// unit; the second 0.4 us per 32 keys and round of workgroups.  us of the second against the first, heads of 128, 5 per KV head, 8 KV heads:
+// 0.55 (head dims up to 64) to 0.76 us per 32 keys of the longest context whatever the number of rows, up to a workgroup per
+// unit; the second 0.4 us per 32 keys and round of workgroups.  us of the second against the first (here with queries in two terms; the third adds
+// 3-8 %), heads of 128, 5 per KV head, 8 KV heads:
 // contexts up to 160: 17 rows 7.6 / 5.7, 130 rows 12.3 / 8.2, 4 rows each of 4 and 12 sequences 7.5 / 5.3 and 8.0 / 5.4;
 // rows from key 200 on: 64 rows (176 workgroups) 10.6 / 11.1, 130 (352) 16.6 / 12.5; from 600: 64 rows 14.8 / 19.5, 130 rows 25.0 / 21.1, 11 rows each of
 // 12 sequences (384) 23.7 / 20.5, 4 rows each of 40 (640) 50.6 / 24.6; from 2000: 64 rows 29.7 / 49.5, 160 (440) 55.6 / 52.1, 500 rows (1344) 160.6 / 66.3; from 8000: 160 rows 177 /

@@ -62,6 +62,16 @@ int host_score_prompt_attention(int T, long groups, int KV, int ctx) { return pr
 
 int host_ring_takes(int K, int residual, int lm) { return ring_takes(K, residual != 0, lm != 0); }
 
+// the first `terms` bf16 terms of eight floats, added up
+void host_bf16_terms(const float *in, int terms, double *sum) {
+    float f[8];
+    for (int e = 0; e < 8; ++e) { f[e] = in[e]; sum[e] = 0.0; }
+    for (int i = 0; i < terms; ++i) {
+        const u32x4_t w = __builtin_bit_cast(u32x4_t, take_bf16(f));
+        for (int e = 0; e < 8; ++e) sum[e] += __uint_as_float((e & 1 ? w[e / 2] >> 16 : w[e / 2] & 0xFFFFu) << 16);
+    }
+}
+
 // row blocks, token blocks and slabs of K a workgroup of k_linear_mfma takes, as R * 100 + NT * 10 + KS; 0 if scratch does not hold the slabs
 int host_narrow_plan(int NB, int KC, int TB, int split, long floats, int groups) {
     const NarrowPlan p = narrow_plan(NB, KC, TB, 256, split != 0, (size_t)floats, groups);

@@ -163,6 +163,20 @@ def test_prompt_attention_takes_the_passes_it_is_faster_at(host, T, seqs, groups
     assert host.host_prompt_attention(T, seqs, C.c_long(groups), KV, ctx) == takes
 
 
+def test_queries_in_three_terms_lose_nothing(host):
+    """k_attn_prompt's queries: three bf16 terms are the float32 value itself (two are within 2^-17 of it, which is seen in its sums)."""
+    rng = np.random.default_rng(0)
+    x = (rng.standard_normal(8000) * 10.0 ** rng.uniform(-8, 8, 8000)).astype(np.float32)
+    x[:8] = [0.0, 1.0, -1.0, 1.0 + 2.0 ** -23, 2.0 - 2.0 ** -23, -3.0000002, 65504.0, 1e-20]
+    out = np.zeros(8)
+    for i in range(0, x.size, 8):
+        v = np.ascontiguousarray(x[i:i + 8])
+        host.host_bf16_terms(v.ctypes.data_as(C.c_void_p), 3, out.ctypes.data_as(C.c_void_p))
+        assert (out == v).all()
+        host.host_bf16_terms(v.ctypes.data_as(C.c_void_p), 2, out.ctypes.data_as(C.c_void_p))
+        assert (np.abs(out - v) <= 2.0 ** -17 * np.abs(v)).all()
+
+
 @pytest.mark.parametrize("G,KV", [(5, 8), (7, 2), (1, 32), (8, 1)])
 def test_scoring_keeps_its_attention_kernel(host, G, KV):
     """Logits that a program compares from one version to the next: no scoring pass (up to 160 rows, any context) changes kernels."""
