@@ -789,7 +789,7 @@ template <typename KT, int HD>
 void launch_attn(ead_handle *h, int mi, AttnArgs<KT> &a, int G, int T, double kv_bytes) {
     // few rows: one workgroup per query head (latency-bound, wants the lanes); many rows:
     // one per KV head, so K and V are streamed once for the heads that share them
-    const bool per_head = T <= 2 || (long)T * a.n_kv_heads * a.max_splits <= 64;
+    const bool per_head = per_head_attention(T, a.n_kv_heads, a.max_splits);
     dim3 grid(a.max_splits, per_head ? a.n_heads : a.n_kv_heads, T);
     if constexpr (std::is_same<KT, bf16_t>::value) {
         if (h->group_rows && a.out_tiles) {

@@ -143,6 +143,10 @@ inline int attention_chunk(int T, int KV, int hd, int ctx_max, bool mfma, int n_
 // residual projections of 6145 to 8192 (3072 x 8192 12.2 -> 11.7; 2048 x 2048 4.9 -> 5.1, 896 x 4864 7.0 -> 8.0, 4096 x 14336 21.4 -> 21.8).
 inline bool ring_takes(int K, bool residual, bool lm) { return residual ? K > 6144 && K <= 8192 : K <= (lm ? 4064 : 2048); }
 
+// Whether a pass's attention goes to k_attn, a workgroup per (row, query head): few rows, which want the lanes.  All its products are
+// float32; the kernels of more rows split queries and probabilities into bf16 terms (1e-7 and 2e-6 from 64 bits).
+inline bool per_head_attention(int T, int KV, int splits) { return T <= 2 || (long)T * KV * splits <= 64; }
+
 // Whether a pass's attention goes to k_attn_prompt (rows of `seqs` sequences in workgroups of four waves that share K and V and take
 // all keys in turn) instead of k_attn_mfma (`groups` workgroups per KV head whose waves split the keys).  The first takes
 // 0.55 (head dims up to 64) to 0.76 us per 32 keys of the longest context whatever the number of rows, up to a workgroup per
@@ -158,7 +162,7 @@ inline bool ring_takes(int K, bool residual, bool lm) { return residual ? K > 61
 // with its logits takes 3.7 ms and the other kernel saves 0.03 of them.
 constexpr int kGroupSeqs = 1024;                        // most sequences of a batch whose passes k_plan lists in groups
 inline bool prompt_attention(int T, int seqs, long groups, int KV, int ctx, bool scoring) {
-    if (scoring || T < 17 || T < 4 * seqs) return false;
+    if (scoring || T < 17 || T < 4 * seqs || per_head_attention(T, KV, 1)) return false;
     return ctx <= 160 || groups * KV >= (ctx <= 320 ? 256 : ctx <= 4096 ? 400 : 512);
 }
 

@@ -177,6 +177,16 @@ def test_queries_in_three_terms_lose_nothing(host):
         assert (np.abs(out - v) <= 2.0 ** -17 * np.abs(v)).all()
 
 
+@pytest.mark.parametrize("KV,most", [(1, 64), (2, 32), (3, 21)])
+def test_passes_of_few_rows_and_heads_keep_float32_attention(host, KV, most):
+    """Up to 64 (row, KV head) pairs are k_attn's, whose queries and probabilities are float32, however short their contexts."""
+    for T in range(17, most + 2):
+        for G in (1, 2, 4, 7, 8):
+            for pos in (0, 40, 95):
+                groups = (pos + T - 1) // (16 // G) - pos // (16 // G) + 1
+                assert bool(host.host_prompt_attention(T, 1, C.c_long(groups), KV, pos + T)) == (T > most), (T, G, pos)
+
+
 @pytest.mark.parametrize("G,KV", [(5, 8), (7, 2), (1, 32), (8, 1)])
 def test_scoring_keeps_its_attention_kernel(host, G, KV):
     """Logits that a program compares from one version to the next: no scoring pass (up to 160 rows, any context) changes kernels."""
