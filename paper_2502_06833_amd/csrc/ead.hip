@@ -1997,6 +1997,7 @@ ead_status ead_score(ead_handle *h, int32_t which, const int32_t *tokens, int32_
     for (int i = 0; i < len; ++i)
         if (tokens[i] < 0 || tokens[i] >= m.V) return fail(h, EAD_ERR_INVALID_ARG, "token %d out of range", i);
     use_lane(h, 0);
+    if (h->two_lanes) HIP_TRY(h, hipStreamSynchronize(h->lanes[1].stream));      // a run that ended in an error may have left a pass there
     hipStream_t st = h->stream;
     h->began = 0; h->batch = 1; h->replay = 0; h->prefilled = 0;
     struct Scoring { ead_handle *h; Scoring(ead_handle *h_) : h(h_) { h->scoring = 1; } ~Scoring() { h->scoring = 0; } } scoring_guard(h);
