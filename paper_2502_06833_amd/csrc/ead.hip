@@ -532,7 +532,7 @@ bool allow_big_lds(const void *kernel, size_t bytes) {
 template <int EPI>
 int launch_ring(ead_handle *h, const LinArgs<bf16_t> &a, int T) {
     const int K = a.K, NB = a.Np / 16;
-    if (T != 1 || h->two_lanes || a.samp_inv_t > 0.f || !ring_takes(K, EPI == EPI_RES, EPI == EPI_LOGITS)) return 0;
+    if (T != 1 || h->two_lanes || a.samp_inv_t > 0.f || !ring_takes(K, NB, h->n_cu, (Epilogue)EPI)) return 0;
     const int grid = std::min(NB, EPI == EPI_SWIGLU && K < 2048 ? 2 * h->n_cu : h->n_cu);
     const auto lds = [&](int nw) { return ((size_t)K + 32 + 2 * nw * 16) * sizeof(float); };
 #define EAD_LR(NW_, U_, D_, XV_) hipLaunchKernelGGL((k_linear_ring<NW_, EPI, U_, D_, XV_>), dim3(grid), dim3(NW_ * 64), lds(NW_), h->stream, a)

@@ -18,8 +18,6 @@
 
 namespace ead {
 
-enum Epilogue { EPI_QKV = 0, EPI_RES = 1, EPI_SWIGLU = 2, EPI_LOGITS = 3 };
-
 struct EntPartial { float m, Z, S; int idx; float gs; int gidx; };
 
 template <typename WT>

@@ -5,6 +5,8 @@
 
 namespace ead {
 
+enum Epilogue { EPI_QKV = 0, EPI_RES = 1, EPI_SWIGLU = 2, EPI_LOGITS = 3 };      // what becomes of a linear layer's sums
+
 constexpr int kEntMaxChunks = 64;                       // most pieces a row of logits is cut into
 
 // The split of a row into work items depends on (rows, V) alone, so a step's result does not depend on
@@ -138,10 +140,30 @@ inline int attention_chunk(int T, int KV, int hd, int ctx_max, bool mfma, int n_
     return chunk;
 }
 
-// Whether one row goes through k_linear_ring instead of k_linear_valu: short K where the wait for the row's norm shows (QKV and gate/up up to
-// 2048: 2048 x 1536 6.1 -> 5.2 us; but 5120 x 3072 10.2 -> 11.1, 6144 x 4096 11.5 -> 12.8), the LM head below 4096 (at 4096 156 against 158),
-// residual projections of 6145 to 8192 (3072 x 8192 12.2 -> 11.7; 2048 x 2048 4.9 -> 5.1, 896 x 4864 7.0 -> 8.0, 4096 x 14336 21.4 -> 21.8).
-inline bool ring_takes(int K, bool residual, bool lm) { return residual ? K > 6144 && K <= 8192 : K <= (lm ? 4064 : 2048); }
+// Whether one row goes through k_linear_ring instead of k_linear_valu (NB row blocks x K).  The ring keeps one workgroup per compute unit (gate/up of
+// K < 2048: two) and gains the wait for the row's norm and the gaps between row blocks; it loses where its slices fill its groups badly
+// (below 1280 four waves take eight k tiles a group, from there on eight waves take four) or where the other form's many workgroups hide more.
+// us of k_linear_valu / ring, rotating weights, 256 units:
+//  * QKV: up to one row block per unit (1152 x 896 4.4 / 3.8, 3840 x 1280 6.5 / 5.4; but 4608 x 1536 7.2 / 7.5); K = 2048, where the other form
+//    has eight waves, too: up to 3/4 (3072 x 2048 6.1 / 5.8, 4096 x 2048 6.6 / 6.9).  Longer K 5120 x 3072 10.2 / 11.1.
+//  * gate/up below 1280: up to one row block per unit (4096 x 1024 4.9 / 4.1) or more than two (9856 x 896 7.0 / 6.3; between them 4160 x 384 4.2 / 4.4,
+//    8192 x 1024 6.1 / 6.4).  From 1280 on only 2048, whose slices are whole groups (8192 x 2048 9.2 / 8.7, 16384 x 2048 14.0 / 13.8; but 7680 x 1280
+//    7.1 / 8.5, 9216 x 1536 9.8 / 9.9, 15360 x 1920 13.1 / 14.4).
+//  * LM head: 1280 to 3776 (128256 x 1536 69 / 59, 128256 x 3072 129 / 116; 256000 x 3776 280 / 277, 256000 x 4064 302 / 308); 896 to 1024 (128256 x 1024 47 / 43;
+//    but x 1152 57 / 76, of which up to four row blocks per unit 16000 x 1152 13.9 / 13.3); shorter rows of few blocks (32768 x 640 14.6 / 13.2, 16000 x 384 9.2 / 8.3, 4096 x 64
+//    5.0 / 4.7; but 151936 x 512 35 / 47, 50304 x 640 18.2 / 18.7, 32000 x 384 12.3 / 13.0).
+//  * residual projections of 6144 to 8192, all that four vectors a lane hold, of up to 3/4 row block per unit (2048 x 8192 9.9 / 9.1, 3072 x 8192
+//    12.1 / 11.3, 1024 x 6144 7.7 / 7.35, 3072 x 6912 10.5 / 10.4; but 4096 x 7680 13.2 / 13.8, 2048 x 4864 7.6 / 7.8).
+inline bool ring_takes(int K, int NB, int n_cu, Epilogue epi) {
+    switch (epi) {
+        case EPI_QKV: return K <= 2048 && 4 * NB <= (K < 2048 ? 4 : 3) * n_cu;
+        case EPI_SWIGLU: return K < 1280 ? NB <= n_cu || NB > 2 * n_cu : K == 2048;
+        case EPI_RES: return K >= 6144 && K <= 8192 && 4 * NB <= 3 * n_cu;
+        default: break;
+    }
+    if (K >= 896) return K <= 1024 || (K < 1280 ? NB <= 4 * n_cu : K <= 3776);
+    return NB <= (K >= 640 ? 8 : K >= 128 ? 4 : 2) * n_cu;
+}
 
 // Whether a pass's attention goes to k_attn, a workgroup per (row, query head): few rows, which want the lanes.  All its products are
 // float32; the kernels of more rows split queries and probabilities into bf16 terms (1e-7 and 2e-6 from 64 bits).

@@ -60,7 +60,9 @@ int host_prompt_attention(int T, int seqs, long groups, int KV, int ctx) { retur
 
 int host_score_prompt_attention(int T, long groups, int KV, int ctx) { return prompt_attention(T, 1, groups, KV, ctx, true); }
 
-int host_ring_takes(int K, int residual, int lm) { return ring_takes(K, residual != 0, lm != 0); }
+// NB row blocks x K, one row, 256 compute units
+int host_ring_takes_matrix(int K, int NB, int epi) { return ring_takes(K, NB, 256, (Epilogue)epi); }
+int host_ring_takes(int K, int residual, int lm) { return host_ring_takes_matrix(K, 128, residual ? EPI_RES : lm ? EPI_LOGITS : EPI_QKV); }
 
 // the first `terms` bf16 terms of eight floats, added up
 void host_bf16_terms(const float *in, int terms, double *sum) {

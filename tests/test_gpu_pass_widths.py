@@ -60,6 +60,24 @@ def test_tiles_of_two_to_sixteen_blocks():
     e.close()
 
 
+@pytest.mark.parametrize("d,heads,kv,ffn", [(1056, 33, 11, 7200), (1312, 41, 41, 6176), (2176, 34, 17, 8160), (2048, 32, 8, 6144), (864, 27, 9, 8192)])
+def test_one_row_in_uneven_slices(d, heads, kv, ffn):
+    """k_linear_ring where the waves' slices of K differ by a tile, fill their groups partly and end inside an activation vector: 33, 41
+    and 68 k tiles over four and eight waves, down projections of 192 to 256; one position scored (a single key, so that only V is
+    rounded, to 2^-9) and 12 tokens of one row replayed."""
+    import paper_2502_06833_amd as ead
+    shape = si.ModelShape(f"one-{d}", 1, d, heads, kv, ffn, 1040, 1e-5, 1e4)
+    other = si.ModelShape("one-other", 1, 128, 4, 4, 128, 1040, 1e-5, 1e4)
+    W, Wo, om, _ = make_pair(shape, other, gain_std=0.2, lm_sigma=1.5)
+    e = ead.EAD(shape, W, other, Wo, window=5, tau=0.0, d_min=4, max_batch=1, max_seq=32)
+    toks = si.prompt_np(0, "one", 14, shape.vocab)
+    ref = om.forward_dense(toks)
+    check_logits(e.score(0, toks[:1])["logits"], ref[:1], 4e-3)
+    out = e.replay([toks[:2]], toks[None, 2:], np.zeros((1, 12), np.uint8))
+    assert np.abs(out["H"][0] - oracle.entropy_rows(ref[1:13])[0]).max() < TOL_H
+    e.close()
+
+
 @pytest.mark.parametrize("length", [64, 66, 171])
 def test_logits_of_many_pieces_arrive_in_their_place(length):
     """Long logits reach the caller in pieces, by several threads (from 64 rows of this vocabulary on: a multiple of the piece,

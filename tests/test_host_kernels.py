@@ -201,3 +201,25 @@ def test_scoring_keeps_its_attention_kernel(host, G, KV):
                                                  (3072, 0, 1, 1), (4096, 0, 1, 0), (32, 0, 0, 1)])
 def test_ring_kernel_takes_the_matrices_it_is_faster_at(host, K, residual, lm, takes):
     assert host.host_ring_takes(K, residual, lm) == takes
+
+
+QKV, RES, SWIGLU, LOGITS = range(4)
+
+
+@pytest.mark.parametrize("epi,N,K,takes", [
+    (QKV, 1152, 896, 1), (QKV, 4096, 1536, 1), (QKV, 4608, 1536, 0), (QKV, 3072, 2048, 1), (QKV, 4096, 2048, 0), (QKV, 1024, 2080, 0),
+    (SWIGLU, 4096, 1024, 1), (SWIGLU, 8192, 1024, 0), (SWIGLU, 9728, 896, 1), (SWIGLU, 7680, 1280, 0), (SWIGLU, 17920, 1536, 0), (SWIGLU, 15872, 1984, 0), (SWIGLU, 16384, 2048, 1),
+    (LOGITS, 151936, 896, 1), (LOGITS, 151936, 864, 0), (LOGITS, 32768, 640, 1), (LOGITS, 32784, 640, 0), (LOGITS, 16384, 512, 1), (LOGITS, 32000, 512, 0), (LOGITS, 8192, 64, 1),
+    (LOGITS, 16384, 64, 0), (LOGITS, 128256, 1152, 0), (LOGITS, 16000, 1152, 1), (LOGITS, 256000, 1280, 1), (LOGITS, 151936, 3776, 1), (LOGITS, 151936, 3808, 0),
+    (RES, 3072, 8192, 1), (RES, 4096, 8192, 0), (RES, 2048, 6144, 1), (RES, 2048, 6112, 0), (RES, 2048, 8224, 0)])
+def test_ring_kernel_by_row_blocks(host, epi, N, K, takes):
+    """Matrices on both sides of the rule's edges: where k_linear_valu measured faster, one row is its own."""
+    assert host.host_ring_takes_matrix(K, N // 16, epi) == takes
+
+
+def test_ring_kernel_holds_what_it_takes(host):
+    """No rule takes a K whose slices do not fit the instantiation's registers (four, one and two vectors of 256 elements per wave of eight)."""
+    for K in range(32, 15361, 32):
+        for NB in (1, 72, 192, 193, 256, 257, 512, 513, 1024, 2049, 9496, 16000):
+            for epi, most in ((QKV, 2048), (RES, 8192), (SWIGLU, 2048), (LOGITS, 4096)):
+                assert K <= most or not host.host_ring_takes_matrix(K, NB, epi), (K, NB, epi)
