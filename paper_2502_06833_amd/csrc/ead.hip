@@ -604,8 +604,8 @@ bool launch_ls(ead_handle *h, const LinArgs<bf16_t> &a, int grid) {
 // Passes of up to 32 rows, and longer ones through matrices that k_linear_mfma_ls does not serve better: k_linear_mfma, a
 // workgroup of few waves per R row blocks and NT token blocks (narrow_plan in rules.hpp says how many of each, and how many slabs
 // of K).  Two waves a workgroup where row blocks are many, so that the workgroups are many and all resident: gate/up of up to 16
-// rows (28672 x 4096: 44.8 us with four waves and two row blocks, 40.7 with two and two, 40.2 with two and one; 9728 x 896:
-// 7.1 with four and two, 6.3 with two and one; but 16384 x 3072: 18.0 and 18.7), of 17 to 32 rows with four row blocks (51.7 -> 46.9).
+// rows (28672 x 4096: 44.8 us with four waves and two row blocks, 40.7 with two and two, 40.2 with two and one; gate_up_by_one says which;
+// 9728 x 896: 7.1 with four and two, 6.3 with two and one; but 16384 x 3072: 18.0 and 18.7), of 17 to 32 rows with four row blocks (51.7 -> 46.9).
 template <int EPI>
 void launch_narrow(ead_handle *h, LinArgs<bf16_t> &a, int T) {
     const int NB = a.Np / 16, KC = a.K / 32, TB = (T + 15) / 16, n_cu = h->n_cu;
@@ -614,7 +614,11 @@ void launch_narrow(ead_handle *h, LinArgs<bf16_t> &a, int T) {
     if constexpr (EPI == EPI_SWIGLU) {
         const bool many = NB > 4 * n_cu;
         p.KS = 1;
-        if (TB <= 1) { if (many || KC < 96) EAD_LM(2, 1, 1, 8, false); else EAD_LM(4, 2, 1, 4, false); }
+        if (TB <= 1) {
+            if ((many || KC < 96) && gate_up_by_one(NB, n_cu)) EAD_LM(2, 1, 1, 8, false);
+            else if (many) EAD_LM(2, 2, 1, 8, false);
+            else EAD_LM(4, 2, 1, 4, false);
+        }
         else if (TB == 2) { if (many) EAD_LM(2, 4, 2, 4, false); else EAD_LM(4, 2, 2, 4, false); }
         else EAD_LM(4, 2, 4, 4, false);
     } else {

@@ -64,13 +64,18 @@ inline int entropy_row_parts(int rows, int V) {
 // 8.6 (R = 1, NT = 2, 384 workgroups: 10.8); 4096 x 4096 at 64: 13.4 -> 12.0.  Of two R x NT of two, the one with more workgroups; of equally many
 // two row blocks (2048 x 2048 at 64 rows: 5.6 against 5.9), from 128 k tiles on two token blocks (896 x 4864 at 96: 9.7 against 11.0).
 // Eight blocks (3072 x 3072 at 160 rows: 23.4 -> 12.9) and sixteen (at 256: 31.3 -> 17.2) only where that leaves one round of
-// workgroups; a QKV projection of few k tiles takes two rounds of small ones instead (1152 x 896 at 320 rows 9.6 -> 8.3).
+// workgroups; a QKV projection of fewer than 32 k tiles takes up to three rounds of small ones instead (1152 x 896 at 320 rows 9.6 -> 8.3; in four
+// rounds 4096 x 768 at 128 rows 11.2, in tiles of two by four 9.75), of more than one row block per unit only where eight blocks are more than a round,
+// too (7168 x 768 at 64 rows 12.1 against 10.2), and four blocks up to three rounds before sixteen (6144 x 896 at 80 rows 12.3, 13.8).  Up to 16 k tiles
+// the small ones hold out for six rounds, and sixteen blocks never pay (7168 x 384 at 128 rows: 11.7, in eight 10.8, in sixteen 12.1).
 //
 // K is split where units would idle and a slab keeps more than 32 k tiles (896 x 4864 at 16 rows: 8.0 -> 6.4; 2048 x 8192: 128
 // workgroups 11.8, two slabs 9.9, four of two row blocks 10.3).  Long K (256 k tiles and more) of 17 to 64 rows: two row blocks and two token blocks,
 // whose tiles are fetched half as often, and the slabs that fill the chip (2048 x 8192 at 64 rows 14.0, unsplit 15.0; 4096 x
-// 14336 at 32 24.5, unsplit 28.0); of up to 16 rows and more than 3/4 of a row block per unit: two or four row blocks (4096 x 14336: 27.9 -> 21.5, 5120 x
-// 13824: 29.5 -> 26.1).
+// 14336 at 32 24.5, unsplit 28.0), of few row blocks also at more rows (512 x 14336 at 80: 11.4, unsplit 16.8), but not where even eight slabs leave
+// a quarter of the units idle (at 32 rows 768 x 9728 9.3, two row blocks and one token block 8.7; 512 x 11008 9.2, one and one in four slabs 8.1).  Long K of up to 16 rows: two or four row blocks from 3/4 of a row block per unit on (4096 x 14336: 27.9
+// -> 21.5, 5120 x 13824: 29.5 -> 26.1), and from half on where that gives three slabs (2560 x 11008 13.8, unsplit 16.3) or K is very long (3072 x
+// 14336 19.5 against 20.6, but 3072 x 8192 14.0 against 12.7).
 constexpr int kSplitKMax = 8;       // most slabs of K per row-block group
 
 struct NarrowPlan { int R, NT, KS; };
@@ -80,10 +85,12 @@ inline NarrowPlan narrow_plan(int NB, int KC, int TB, int n_cu, bool may_split, 
     const auto fits = [&](const NarrowPlan &p) {       // the slabs' sums and the counters have room
         return (size_t)p.KS * groups(p.R, p.NT) * p.R * p.NT * 256 <= most_floats && groups(p.R, p.NT) <= most_groups;
     };
-    if (may_split && KC >= 256 && TB <= 4) {
+    if (may_split && KC >= 256 && (TB <= 4 || 3 * groups(2, 2) <= n_cu)) {
         NarrowPlan p{0, 0, 1};
-        if (TB >= 2) p = NB > n_cu && TB == 2 ? NarrowPlan{4, 2, 1} : NarrowPlan{2, 2, 1};
+        if (TB >= 2 && 4 * kSplitKMax * groups(2, 2) > 3 * n_cu) p = NB > n_cu && TB == 2 ? NarrowPlan{4, 2, 1} : NarrowPlan{2, 2, 1};
+        else if (TB >= 2) { if (TB == 2 && kSplitKMax * groups(2, 1) > n_cu) p = NarrowPlan{2, 1, 1}; }
         else if (4 * NB > 3 * n_cu) p = NarrowPlan{NB > n_cu ? 4 : 2, 1, 1};
+        else if (2 * NB > n_cu && (3 * groups(2, 1) <= n_cu || KC >= 384)) p = NarrowPlan{2, 1, 1};
         if (p.R) {
             p.KS = std::min<long>(kSplitKMax, n_cu / groups(p.R, p.NT));
             if (p.KS > 1 && fits(p)) return p;
@@ -96,16 +103,22 @@ inline NarrowPlan narrow_plan(int NB, int KC, int TB, int n_cu, bool may_split, 
         const bool toks = rows2 > n_cu || (toks2 <= n_cu && (toks2 > rows2 || (toks2 == rows2 && KC >= 128)));
         p = toks ? NarrowPlan{1, 2, 1} : NarrowPlan{2, 1, 1};
     } else if (groups(2, 2) <= n_cu) p = NarrowPlan{2, 2, 1};
-    else if (!may_split && KC < 32) p = NarrowPlan{1, 2, 1};
-    else if (toks4 <= n_cu || TB == 2) p = NarrowPlan{2, TB > 2 ? 4 : 2, 1};
+    else if (!may_split && KC < 32 && (KC <= 16 ? toks2 <= 6 * n_cu : toks2 <= 3 * n_cu && (NB <= n_cu || toks4 > n_cu))) p = NarrowPlan{1, 2, 1};
+    else if (toks4 <= n_cu || TB == 2 || KC <= 16) p = NarrowPlan{2, TB > 2 ? 4 : 2, 1};
     else if (rows4 <= n_cu) p = NarrowPlan{4, 2, 1};
+    else if (!may_split && KC < 32 && groups(2, 2) <= 3 * n_cu) p = NarrowPlan{2, 2, 1};
     else p = groups(4, 4) <= n_cu ? NarrowPlan{4, 4, 1} : NarrowPlan{2, 4, 1};
-    if (may_split && (p.R == 1 || p.R == 2) && p.NT <= p.R) {
+    if (may_split && p.R == 1 && p.NT == 1) {          // any larger tile was taken because the smaller ones fill the chip
         while (p.KS < kSplitKMax && (p.KS + 1) * groups(p.R, p.NT) <= n_cu && KC / (p.KS + 1) > 32) ++p.KS;
         while (p.KS > 1 && !fits(p)) --p.KS;
     }
     return p;
 }
+
+// Whether gate/up of up to 16 rows goes one row block a workgroup instead of two: where the fullest unit then has fewer blocks to take.  us of two / one:
+// 4096 x 2560 7.8 / 6.2 (one block per unit instead of two), 9728 x 896 7.3 / 6.6 (three instead of four), 28672 x 4096 41.2 / 40.6 (seven, eight); but,
+// as many either way, 6144 x 2048 7.1 / 8.1, 8192 x 2560 9.0 / 9.9, 21504 x 4096 32.1 / 35.4, 32768 x 5120 53.4 / 54.9.
+inline bool gate_up_by_one(int NB, int n_cu) { return (NB + n_cu - 1) / n_cu % 2 == 1; }
 
 // Keys per split of a pass's attention.  A workgroup takes at least 512 keys; more splits only while that helps to fill the
 // chip, never more than max_splits (the last one merges them all), bounded scratch (items: rows x splits).  A decode

@@ -82,4 +82,6 @@ int host_narrow_plan(int NB, int KC, int TB, int split, long floats, int groups)
     return p.R * 100 + p.NT * 10 + p.KS;
 }
 
+int host_gate_up_by_one(int NB) { return gate_up_by_one(NB, 256); }
+
 }  // extern "C"

@@ -223,3 +223,21 @@ def test_ring_kernel_holds_what_it_takes(host):
         for NB in (1, 72, 192, 193, 256, 257, 512, 513, 1024, 2049, 9496, 16000):
             for epi, most in ((QKV, 2048), (RES, 8192), (SWIGLU, 2048), (LOGITS, 4096)):
                 assert K <= most or not host.host_ring_takes_matrix(K, NB, epi), (K, NB, epi)
+
+
+@pytest.mark.parametrize("NB,KC,split,plans", [
+    (448, 24, 0, {3: 241, 4: 241, 5: 221, 8: 441}), (256, 24, 0, {4: 221, 8: 241}), (512, 28, 0, {4: 241, 8: 441}), (288, 16, 0, {4: 121}), (448, 12, 0, {8: 241}), (192, 28, 0, {8: 121}),
+    (160, 344, 1, {1: 213}), (192, 256, 1, {1: 111}), (192, 448, 1, {1: 212}), (136, 256, 1, {1: 213}),
+    (384, 28, 0, {5: 221, 8: 221}),
+    (32, 344, 1, {2: 114, 3: 228, 5: 225, 8: 224}), (48, 448, 1, {2: 215, 6: 223, 8: 121}), (64, 256, 1, {2: 228}), (16, 448, 1, {2: 118, 10: 226}), (384, 16, 1, {6: 241})])
+def test_narrow_passes_of_wide_or_small_matrices(host, NB, KC, split, plans):
+    """Shapes that no model above has: where the smallest tiles take four rounds of workgroups and more, and long K of few row blocks."""
+    for TB, plan in plans.items():
+        assert host.host_narrow_plan(NB, KC, TB, split, C.c_long(8 << 20), 4096) == plan, TB
+
+
+@pytest.mark.parametrize("NB,one", [(1, 1), (256, 1), (257, 0), (512, 0), (513, 1), (608, 1), (768, 1), (1024, 0), (1120, 1), (1344, 0), (1728, 1), (1792, 1), (2048, 0)])
+def test_gate_up_takes_one_row_block_where_the_fullest_unit_has_fewer(host, NB, one):
+    assert host.host_gate_up_by_one(NB) == one
+    by_one, by_two = -(-NB // 256), 2 * -(-(-(-NB // 2)) // 256)
+    assert bool(one) == (by_one < by_two)
