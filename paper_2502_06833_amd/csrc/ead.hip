@@ -779,14 +779,13 @@ void launch_pack(ead_handle *h, int mi, const PackArgs &a) {
         else hipLaunchKernelGGL(k_pack_rows<20>, grid, dim3(256), 0, h->stream, a);
         return;
     }
+#define EAD_PA(V_, NT_) hipLaunchKernelGGL((k_pack_act<V_, NT_>), dim3(rows16), dim3(NT_), 0, h->stream, a); break
     switch ((a.K + 1023) / 1024) {
-        case 1: hipLaunchKernelGGL(k_pack_act<1>, dim3(rows16), dim3(256), 0, h->stream, a); break;
-        case 2: hipLaunchKernelGGL(k_pack_act<2>, dim3(rows16), dim3(256), 0, h->stream, a); break;
-        case 3: hipLaunchKernelGGL(k_pack_act<3>, dim3(rows16), dim3(256), 0, h->stream, a); break;
-        case 4: hipLaunchKernelGGL(k_pack_act<4>, dim3(rows16), dim3(256), 0, h->stream, a); break;
-        case 5: hipLaunchKernelGGL(k_pack_act<5>, dim3(rows16), dim3(256), 0, h->stream, a); break;
-        default: hipLaunchKernelGGL(k_pack_act<kPackVecs>, dim3(rows16), dim3(256), 0, h->stream, a); break;
+        case 1: EAD_PA(1, 256); case 2: EAD_PA(2, 256); case 3: EAD_PA(3, 256); case 4: EAD_PA(4, 256); case 5: EAD_PA(5, 256);
+        case 6: EAD_PA(3, 512); case 7: case 8: EAD_PA(4, 512); case 9: case 10: EAD_PA(5, 512); case 11: case 12: EAD_PA(6, 512);
+        default: EAD_PA(8, 512);             // up to 16384; models are refused above 15360
     }
+#undef EAD_PA
 }
 
 template <typename KT, int HD>

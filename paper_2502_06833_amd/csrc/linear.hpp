@@ -1374,8 +1374,6 @@ struct PackArgs {
     bf16_t *out; int K;
 };
 
-constexpr int kPackVecs = 15;        // most 16-byte pieces of a row per thread of a workgroup: K <= 15 * 4 * 256
-
 // pieces tid, tid + stride, .. (V of them) of row t, normalised, into their tiles; a piece past the row repeats its last one and is dropped
 template <int V>
 __device__ __forceinline__ void pack_load(const PackArgs &a, int t, int tid, int stride, float4 (&v)[V], float4 (&g)[V]) {
@@ -1414,18 +1412,22 @@ __device__ __forceinline__ void pack_store(const PackArgs &a, int t, int tid, in
     }
 }
 
-// A workgroup per row: V pieces per thread, K <= 1024 V.
-template <int V>
-__global__ __launch_bounds__(256) void k_pack_act(PackArgs a) {
-    __shared__ float s_ss[4];
+// A workgroup of NT threads per row: V pieces per thread, K <= 4 NT V.  Rows of more than 5120: eight waves (3 and 1024 rows of 8192, us: 3.1
+// and 18.9; four waves and eight pieces 3.5 and 19.7; the kernel for all lengths 4.9 and 18.8; of 15360: 4.1 and 33.9, 4.5 and 35.5, 6.9 and 34.0).
+template <int V, int NT = 256>
+__global__ __launch_bounds__(NT) void k_pack_act(PackArgs a) {
+    __shared__ float s_ss[NT / 64];
     const int t = blockIdx.x, tid = threadIdx.x;
     float4 v[V], g[V];
-    pack_load<V>(a, min(t, a.rows - 1), tid, 256, v, g);
-    const float ss = wave_sum(pack_squares<V>(a, tid, 256, v));
+    pack_load<V>(a, min(t, a.rows - 1), tid, NT, v, g);
+    const float ss = wave_sum(pack_squares<V>(a, tid, NT, v));
     if ((tid & 63) == 0) s_ss[tid >> 6] = ss;
     __syncthreads();
-    const float inv = 1.0f / sqrtf((s_ss[0] + s_ss[1] + s_ss[2] + s_ss[3]) / (float)a.K + a.eps);
-    pack_store<V>(a, t, tid, 256, inv, v, g);
+    float tot = 0.f;
+#pragma unroll
+    for (int w = 0; w < NT / 64; ++w) tot += s_ss[w];
+    const float inv = 1.0f / sqrtf(tot / (float)a.K + a.eps);
+    pack_store<V>(a, t, tid, NT, inv, v, g);
 }
 
 // Long passes: a wave per row, four rows per workgroup, V pieces per lane, K <= 256 V: nothing to wait for between waves (1024 rows,

@@ -60,6 +60,29 @@ def test_tiles_of_two_to_sixteen_blocks():
     e.close()
 
 
+class WideRow(si.ModelShape):
+    """A model of few heads, so that rows of up to 15360 come with small matrices."""
+    head_dim = 128
+
+
+@pytest.mark.parametrize("d", [5152, 6176, 8192, 9248, 12320, 15360])
+def test_rows_longer_than_the_models(d):
+    """Normalised and packed rows of every length class past 5120 (three to eight pieces a thread, the last ones partly past the row's end):
+    passes of 1, 3, 40 and 128 rows scored, and 300 as a prompt, whose first generated entropy hangs on it."""
+    import paper_2502_06833_amd as ead
+    shape = WideRow(f"row-{d}", 1, d, 4, 2, 64, 528, 1e-5, 1e4)
+    other = si.ModelShape("row-other", 1, 128, 4, 4, 128, 528, 1e-5, 1e4)
+    W, Wo, om, _ = make_pair(shape, other, gain_std=0.2, lm_sigma=1.5)
+    e = ead.EAD(shape, W, other, Wo, window=5, tau=0.0, d_min=4, max_batch=1, max_seq=320)
+    toks = si.prompt_np(0, "row", 301, shape.vocab)
+    ref = om.forward_dense(toks)
+    for T in (1, 3, 40, 128):
+        check_logits(e.score(0, toks[:T])["logits"], ref[:T], TOL_LOGIT)
+    out = e.replay([toks], np.array([[5]], np.int32), np.array([[0]], np.uint8))
+    assert abs(out["H"][0, 0] - oracle.entropy_rows(ref[-1:])[0][0]) < TOL_H
+    e.close()
+
+
 @pytest.mark.parametrize("d,heads,kv,ffn", [(1056, 33, 11, 7200), (1312, 41, 41, 6176), (2176, 34, 17, 8160), (2048, 32, 8, 6144), (864, 27, 9, 8192)])
 def test_one_row_in_uneven_slices(d, heads, kv, ffn):
     """k_linear_ring where the waves' slices of K differ by a tile, fill their groups partly and end inside an activation vector: 33, 41
