@@ -1491,16 +1491,25 @@ ead_status fetch_impl(ead_handle *h, int stride, int32_t *tok, uint8_t *mid, flo
 // ---- long results into the caller's (pageable) memory ---------------------------------------
 // The runtime's own copy into pageable memory takes one core: 61 MB of logits in 6 ms, of which the bus needs 1.2; the
 // rest is copying out of its staging memory and touching the caller's fresh pages.  Here pieces go to pinned slots and a few
-// threads, which live as long as the call, bring them to their place.  A scoring call of 101 rows x 151936, 1.8 ms without its
+// threads, which live as long as the copy of one pass, bring them to their place.  A scoring call of 101 rows x 151936, 1.8 ms without its
 // logits: 7.9 ms before; with 2, 4, 6, 8 and 12 threads 4.8, 3.7, 3.9, 3.9, 3.7 ms; pieces of 0.5, 1, 2 and 4 MB 5.0, 4.1, 3.7, 3.8.  Copies
-// of less than four pieces go the old way.  The HIP calls stay on the calling thread.
+// of less than four pieces go the old way, and so does memory that the runtime can write itself (the same call into
+// pinned memory: 2.9 ms directly, 3.4 by way of the slots).  The HIP calls stay on the
+// calling thread.
 constexpr size_t kCopyPiece = (size_t)2 << 20;
 constexpr int kCopySlots = 8, kCopyThreads = 4;
+
+// Whether the runtime knows the memory at p (pinned, managed): it is copied to directly then
+bool known_to_runtime(const void *p) {
+    hipPointerAttribute_t at{};
+    if (hipPointerGetAttributes(&at, p) != hipSuccess) { (void)hipGetLastError(); return false; }
+    return at.type != hipMemoryTypeUnregistered;
+}
 
 ead_status copy_out(ead_handle *h, void *dst, const void *src, size_t bytes) {
     hipStream_t st = h->stream;
     const int n = (int)((bytes + kCopyPiece - 1) / kCopyPiece);
-    const int want = std::min({kCopyThreads, n / 2, (int)std::thread::hardware_concurrency()});
+    const int want = n < 4 || known_to_runtime(dst) ? 0 : std::min({kCopyThreads, n / 2, (int)std::thread::hardware_concurrency()});
     if (want >= 2 && h->copy_ev.size() < (size_t)kCopySlots) {
         if (!h->h_copy && hipHostMalloc((void **)&h->h_copy, kCopySlots * kCopyPiece, hipHostMallocDefault) != hipSuccess) { h->h_copy = nullptr; (void)hipGetLastError(); }
         hipEvent_t e;

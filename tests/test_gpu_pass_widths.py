@@ -120,6 +120,37 @@ def test_logits_of_many_pieces_arrive_in_their_place(length):
     e.close()
 
 
+def _score_into(e, toks, logits, H):
+    import ctypes as C
+    import paper_2502_06833_amd as ead
+    t = np.ascontiguousarray(toks, np.int32)
+    rc = ead.lib().ead_score(e._h, 0, t.ctypes.data_as(C.POINTER(C.c_int32)), t.size, C.cast(logits, C.POINTER(C.c_float)),
+                             H.ctypes.data_as(C.POINTER(C.c_float)), None)
+    assert rc == 0
+
+
+def test_logits_into_pinned_memory():
+    """A pinned destination, whole or from the middle of the allocation on, gets what a pageable one gets, and nothing beyond it."""
+    import torch
+    import paper_2502_06833_amd as ead
+    shape = si.ModelShape("pinned", 1, 256, 4, 2, 416, 32768, 1e-5, 1e4)
+    other = si.ModelShape("other", 1, 128, 4, 4, 128, 32768, 1e-5, 1e4)
+    Ws, Wl, _, _ = make_pair(shape, other, lm_sigma=1.5)
+    e = ead.EAD(shape, Ws, other, Wl, window=5, tau=0.0, d_min=4, max_batch=1, max_seq=192)
+    for length in (40, 66, 171):
+        toks = si.prompt_np(0, "pinned", length, shape.vocab)
+        want = e.score(0, toks)
+        n = length * shape.vocab
+        for skip in (0, 48):
+            buf = torch.full((n + 96,), -7.0, pin_memory=True)
+            H = np.zeros(length, np.float32)
+            _score_into(e, toks, buf.data_ptr() + 4 * skip, H)
+            got = buf.numpy()
+            assert (got[skip:skip + n].reshape(length, -1) == want["logits"]).all() and (H == want["H"]).all()
+            assert (got[:skip] == -7.0).all() and (got[skip + n:] == -7.0).all()
+    e.close()
+
+
 @pytest.mark.parametrize("batch", [3, 20, 40])
 def test_sampled_choice_of_wide_passes(batch):
     """The sampled token of every row of a pass, where the two best perturbed scores are clearly apart."""
