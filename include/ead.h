@@ -19,7 +19,8 @@
  *    caller's tensors and the library's tiles): about 58 GB for a 0.5 B + 14 B
  *    parameter pair in bf16, half of that afterwards.  Everything else the
  *    library needs (KV caches, gate state, scratch) it allocates in ead_create()
- *    and frees in ead_destroy().
+ *    and frees in ead_destroy(), 16 MB of pinned host memory among it where the
+ *    logits of a scoring pass are long (more than 6 MB).
  *  - Precision of a bf16 model: the matrices of the linear layers are kept as IEEE
  *    half, which holds every bf16 value of magnitude 2^-24 .. 65504 exactly (smaller
  *    ones round to a multiple of 2^-24); passes of three or more rows round their
@@ -187,7 +188,10 @@ ead_status ead_fetch(ead_handle *h, int32_t stride, int32_t *out_tokens, uint8_t
 /* One model over one token sequence: logits, entropy and arg max at every
  * position (position i predicts token i+1).
  *   tokens host [len]; out_logits host [len, vocab] float32 (nullable);
- *   out_entropy host [len] (nullable); out_argmax host [len] (nullable). */
+ *   out_entropy host [len] (nullable); out_argmax host [len] (nullable).
+ * Logits of more than 6 MB a pass (160 positions) that go to pageable memory are brought there by up
+ * to four threads of the library's own, which have ended when the call returns; pinned memory is
+ * written directly. */
 ead_status ead_score(ead_handle *h, int32_t which_model, const int32_t *tokens, int32_t len,
                      float *out_logits, float *out_entropy, int32_t *out_argmax);
 

@@ -249,6 +249,10 @@ struct Model {
     size_t esz() const { return dtype == EAD_BF16 ? 2 : 4; }
 };
 
+// ead_score's logits leave in pieces of this size through this many pinned slots, copied on by at most that many threads, from so many pieces on
+constexpr size_t kCopyPiece = (size_t)2 << 20;
+constexpr int kCopySlots = 8, kCopyThreads = 4, kCopyLeast = 4;
+
 struct HostSeq { int len, kvlen[2], model, c, ngen, done, last_step, goal; };
 
 }  // namespace
@@ -282,7 +286,7 @@ struct ead_handle {
     int *h_model = nullptr, *h_plen = nullptr, *h_status = nullptr;   // pinned: forced ids of a replay; prompt lengths; flags (k_status)
     char *h_fetch = nullptr; int fetch_rows = 0;                       // pinned: results of up to fetch_rows sequences (k_fetch)
     std::vector<int> h_tokens;           // the prompts as they are copied to the device
-    char *h_copy = nullptr; std::vector<hipEvent_t> copy_ev;           // pinned pieces of a long copy (copy_out), from its first use on
+    char *h_copy = nullptr; hipEvent_t copy_ev[kCopySlots] = {}; bool copy_ready = false;      // pinned pieces of a long copy (make_copy_slots, copy_out)
     LaneSet lanes[2]; int cur_lane = 0, two_lanes = 0; hipStream_t lane1_stream = nullptr;
     // fused single-row decode
     float *att_o; float2 *att_ml; unsigned *bar_mem; int *abort_flag; unsigned bar_epoch = 0; int fused_on = 0, fused_grid = 0;
@@ -1496,8 +1500,16 @@ ead_status fetch_impl(ead_handle *h, int stride, int32_t *tok, uint8_t *mid, flo
 // of less than four pieces go the old way, and so does memory that the runtime can write itself (the same call into
 // pinned memory: 2.9 ms directly, 3.4 by way of the slots).  The HIP calls stay on the
 // calling thread.
-constexpr size_t kCopyPiece = (size_t)2 << 20;
-constexpr int kCopySlots = 8, kCopyThreads = 4;
+
+// The slots and their events, at the handle's creation: no later call allocates.  Without them the runtime's copy serves.
+void make_copy_slots(ead_handle *h) {
+    bool ok = hipHostMalloc((void **)&h->h_copy, kCopySlots * kCopyPiece, hipHostMallocDefault) == hipSuccess;
+    if (!ok) h->h_copy = nullptr;
+    for (hipEvent_t &e : h->copy_ev)
+        if (ok && hipEventCreateWithFlags(&e, hipEventDisableTiming) != hipSuccess) { e = nullptr; ok = false; }
+    if (!ok) (void)hipGetLastError();
+    h->copy_ready = ok;
+}
 
 // Whether the runtime knows the memory at p (pinned, managed): it is copied to directly then
 bool known_to_runtime(const void *p) {
@@ -1509,16 +1521,8 @@ bool known_to_runtime(const void *p) {
 ead_status copy_out(ead_handle *h, void *dst, const void *src, size_t bytes) {
     hipStream_t st = h->stream;
     const int n = (int)((bytes + kCopyPiece - 1) / kCopyPiece);
-    const int want = n < 4 || known_to_runtime(dst) ? 0 : std::min({kCopyThreads, n / 2, (int)std::thread::hardware_concurrency()});
-    if (want >= 2 && h->copy_ev.size() < (size_t)kCopySlots) {
-        if (!h->h_copy && hipHostMalloc((void **)&h->h_copy, kCopySlots * kCopyPiece, hipHostMallocDefault) != hipSuccess) { h->h_copy = nullptr; (void)hipGetLastError(); }
-        hipEvent_t e;
-        while (h->h_copy && h->copy_ev.size() < (size_t)kCopySlots) {
-            if (hipEventCreateWithFlags(&e, hipEventDisableTiming) != hipSuccess) { (void)hipGetLastError(); break; }
-            h->copy_ev.push_back(e);
-        }
-    }
-    const bool pieces = want >= 2 && h->copy_ev.size() == (size_t)kCopySlots;      // else the runtime's copy
+    const int want = n < kCopyLeast || known_to_runtime(dst) ? 0 : std::min({kCopyThreads, n / 2, (int)std::thread::hardware_concurrency()});
+    const bool pieces = want >= 2 && h->copy_ready;      // else the runtime's copy
     struct Shared {                                    // pieces 0 .. landed - 1 are in their slots; `taken` of them have a thread; `left` counts a slot's pieces that have left it
         std::mutex m; std::condition_variable cv;
         int landed = 0, taken = 0, left[kCopySlots] = {0}; bool stop = false;
@@ -1745,7 +1749,7 @@ void ead_destroy(ead_handle *h) {
     if (h->h_status) (void)hipHostFree(h->h_status);
     if (h->h_fetch) (void)hipHostFree(h->h_fetch);
     if (h->h_copy) (void)hipHostFree(h->h_copy);
-    for (hipEvent_t e : h->copy_ev) (void)hipEventDestroy(e);
+    for (hipEvent_t e : h->copy_ev) if (e) (void)hipEventDestroy(e);
     prof_collect(h);
     for (hipEvent_t e : h->ev_pool) (void)hipEventDestroy(e);
     delete h;
@@ -1879,6 +1883,7 @@ ead_status ead_create(const ead_model_desc *small_model, const ead_model_desc *l
         // results of a fetch: a row's 14 bytes per token and its count, at most about 4 MB (longer batches take several rounds)
         h->fetch_rows = (int)std::min<long>(MB, std::max<long>(1, (4l << 20) / (14l * MS)));
         HIP_TRY(h, hipHostMalloc((void **)&h->h_fetch, (size_t)h->fetch_rows * (14 * (size_t)MS + sizeof(int)), hipHostMallocDefault));
+        if ((size_t)std::min(h->score_rows, MS) * a.V * sizeof(float) > (kCopyLeast - 1) * kCopyPiece) make_copy_slots(h);
         HIP_TRY(h, hipStreamSynchronize(h->stream));
         HIP_TRY(h, hipGetLastError());
         return EAD_OK;

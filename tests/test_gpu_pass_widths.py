@@ -151,6 +151,30 @@ def test_logits_into_pinned_memory():
     e.close()
 
 
+def test_scoring_allocates_nothing():
+    """Everything a handle needs is allocated when it is created: the first scoring call whose logits leave in pieces maps no
+    further memory of the driver's (device or pinned) and leaves no thread behind."""
+    import os
+    import paper_2502_06833_amd as ead
+    shape = si.ModelShape("maps", 1, 256, 4, 2, 416, 32768, 1e-5, 1e4)
+    other = si.ModelShape("other", 1, 128, 4, 4, 128, 32768, 1e-5, 1e4)
+    Ws, Wl, _, _ = make_pair(shape, other)
+    e = ead.EAD(shape, Ws, other, Wl, window=5, tau=0.0, d_min=4, max_batch=1, max_seq=192)
+    toks = si.prompt_np(0, "maps", 100, shape.vocab)
+    logits, H = np.full(100 * shape.vocab, 1.0, np.float32), np.zeros(100, np.float32)
+
+    def mapped():
+        with open("/proc/self/maps") as f:
+            rows = [ln.split() for ln in f if "/dev/dri" in ln]
+        return sum(int(b, 16) - int(a, 16) for a, b in (r[0].split("-") for r in rows)), len(os.listdir("/proc/self/task"))
+
+    _score_into(e, toks[:40], logits.ctypes.data, H)           # 5 MB: the runtime's copy, whose own staging memory comes with its first use
+    before = mapped()
+    _score_into(e, toks, logits.ctypes.data, H)
+    assert mapped() == before
+    e.close()
+
+
 @pytest.mark.parametrize("batch", [3, 20, 40])
 def test_sampled_choice_of_wide_passes(batch):
     """The sampled token of every row of a pass, where the two best perturbed scores are clearly apart."""
