@@ -542,8 +542,8 @@ int launch_ring(ead_handle *h, const LinArgs<bf16_t> &a, int T) {
 #define EAD_LR(NW_, U_, D_, XV_) hipLaunchKernelGGL((k_linear_ring<NW_, EPI, U_, D_, XV_>), dim3(grid), dim3(NW_ * 64), lds(NW_), h->stream, a)
     if constexpr (EPI == EPI_RES) EAD_LR(8, 8, 1, 4);
     else if (K < 40 * 32) EAD_LR(4, 8, 1, 2);
-    else if (K <= 2048) EAD_LR(8, 4, 2, 1);
-    else EAD_LR(8, 4, 2, 2);
+    else if constexpr (EPI == EPI_LOGITS) { if (K <= 2048) EAD_LR(8, 4, 2, 1); else EAD_LR(8, 4, 2, 2); }
+    else EAD_LR(8, 4, 2, 1);
 #undef EAD_LR
     return grid;
 }
