@@ -28,6 +28,11 @@
  *    saturate) and accumulate in float32; passes of one or two rows keep float32
  *    activations.  K and V are cached in bf16.  Embeddings, gains, the residual
  *    stream, soft-max statistics and the entropy are float32 throughout.
+ *  - Sums are taken in an order that the model's shape and the number of rows of
+ *    the pass fix; for passes of one row also whether the handle was made for one
+ *    sequence (max_batch = 1) or several, and for their LM head whether it samples.
+ *    Results of passes of other widths, and one-row steps of such other handles,
+ *    agree up to rounding.
  *  - Outputs are caller-owned host buffers unless the name ends in _dev.
  *  - A handle serves one call at a time (calls are not re-entrant).  Work is
  *    queued on ead_params.hip_stream and every call returns after its results
