@@ -531,7 +531,7 @@ bool allow_big_lds(const void *kernel, size_t bytes) {
 }
 
 // One row of a bf16 model through k_linear_ring where it takes the matrix (ring_takes in rules.hpp): the workgroups launched, else 0.  Not
-// beside another lane's passes (four rows replayed by two models side by side took 1.3 % longer with it), and not for a sampled LM head, whose
+// on a handle of several sequences, whose two models' passes run side by side (four rows replayed took 1.3 % longer with it), and not for a sampled LM head, whose
 // epilogue calls the generator for every logit, which many workgroups per unit hide and one does not.
 template <int EPI>
 int launch_ring(ead_handle *h, const LinArgs<bf16_t> &a, int T) {
@@ -587,7 +587,7 @@ int launch_valu(ead_handle *h, int mi, LinArgs<WT> &a, int T, int grid) {
 //  * 33 to 128 rows: gate/up, and the QKV and residual projections of large matrices with many or long row blocks, through
 //    k_linear_mfma_ls, 64 to 128 rows per sweep; where that gives fewer workgroups than compute units, K is split over
 //    workgroups and k_sk_merge adds the slabs.  k_linear_mfma_wt is the fallback should the device not grant the LDS
-//    k_linear_mfma_ls asks for.  The others stay with launch_narrow, 64 rows per sweep, the sweeps side by side;
+//    k_linear_mfma_ls asks for.  The others stay with launch_narrow, whose workgroups take one to four token blocks;
 //  * more than 128 rows (prefill, scoring): no split of K but for two sweeps of a long K; one workgroup per (row-block
 //    group, sweep), in 256 x 256 tiles (k_linear_mfma_tile) or 128 x 256 ones (k_linear_mfma_gemm) where those fill the
 //    chip; small matrices other than gate/up go this way from 32 token blocks.
@@ -686,9 +686,10 @@ void launch_mfma(ead_handle *h, int mi, LinArgs<bf16_t> &a, int T) {
     // row blocks are split along K over workgroups; a second kernel adds the slabs in order and
     // runs the epilogue.  Gate/up goes this way from 128 row blocks (9728 x 896 at 64 rows: 8.4 us against 12.3; 16384 x
     // 2048: 18.0 against 24.8 with seven row blocks a workgroup).  Residual and QKV projections of up to 64 rows and
-    // under 40 MB don't: the second launch costs more than it saves (4096 x 4096: 12.0 against 15.3 us; 5120 x 5120: 18.7
-    // against 18.0, 7168 x 5120 with the QKV epilogue: 28 against 23).  Small matrices do from two sweeps
-    // (QKV) or three (3072 x 2048 at 300 rows: 26 us in sweeps of 64, 18 this way at 512).
+    // under 40 MB don't: the second launch costs more than it saves (4096 x 4096: 12.2 against 15.3 us; but 5120 x 5120: 20.9
+    // against 18.4, 7168 x 5120 with the QKV epilogue: 24.7 against 22.2).  Small matrices do from two sweeps
+    // (QKV) or three (3072 x 2048 in launch_narrow's tiles / this way: at 300 rows 17.8 / 17.4 us, at 400 28.4 / 17.8; but 2048 x 8192 at
+    // 200 rows 27.7 / 36.2, 3072 x 2048 at 160 12.5 / 17.0: since the tiles of narrow_plan the line lies low there).
     const bool longpass = TB >= 4 * kWideTok, multi = TB > kWideTok;
     const long tiles = (long)NB * (a.K / 32);
     const bool wide = TB > 2 && (EPI == EPI_SWIGLU ? NB >= 128 : (big && (TB > 4 || tiles >= 40000)) ||

@@ -36,7 +36,8 @@ inline bool entropy_folds(int rows, int chunks, size_t bytes) {
 
 // The same for larger calls: up to 32 MB, at most 600 chunks, eight a row, the second launch still is the longer part (us in one launch
 // against two, float32: 97 x 50264 10.5 / 12.6, 128 x 50264 10.1 / 12.6, 64 x 128256 11.1 / 12.5, 256 x 32000 10.8 / 12.6; bf16: 64 x 128256 10.0 /
-// 12.5, 128 x 50264 10.1 / 12.5; but 776 chunks, 97 x 128256, 13.4 / 12.5).
+// 12.5, 128 x 50264 10.1 / 12.5; but 776 chunks, 97 x 128256, 13.4 / 12.5).  That is a call's time where the host bounds it (the Python binding: 64 x 128256 bf16 10.6 a
+// call, two launches 13.4); to a caller whose host takes less than the kernel, the chain of eight arrivals costs up to 0.9 (9.3 / 8.4), of four nothing.
 inline bool entropy_folds_large(int rows, int chunks, size_t bytes) {
     return bytes <= ((size_t)32 << 20) && (long)rows * chunks <= 600 && chunks <= 8;
 }

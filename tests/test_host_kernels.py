@@ -138,6 +138,7 @@ def test_attention_splits_stay_within_the_scratch(host):
     (192, 96, 1, {1: 111, 2: 211, 4: 221, 8: 241, 10: 421, 16: 441}), (256, 448, 1, {1: 212, 2: 222, 4: 221}),
     (320, 432, 1, {1: 413, 2: 423, 3: 241}), (448, 160, 0, {1: 211, 2: 221, 4: 241})])
 def test_narrow_passes_take_the_measured_best(host, NB, KC, split, plans):
+    """The rule's choice at matrices it was measured at (times in rules.hpp); of other shapes it says nothing."""
     for TB, plan in plans.items():
         assert host.host_narrow_plan(NB, KC, TB, split, C.c_long(8 << 20), 4096) == plan, TB
 
@@ -160,6 +161,7 @@ def test_narrow_plans_are_instantiated_and_stay_within_the_scratch(host):
     (64, 1, 22, 8, 264, 0), (130, 1, 44, 8, 330, 0), (130, 1, 44, 8, 310, 1), (160, 1, 55, 8, 2160, 1), (160, 1, 55, 8, 8160, 0), (500, 1, 168, 8, 8500, 1),
     (64, 64, 64, 8, 1000, 0), (160, 1, 80, 2, 760, 0), (500, 1, 250, 2, 1100, 1)])
 def test_prompt_attention_takes_the_passes_it_is_faster_at(host, T, seqs, groups, KV, ctx, takes):
+    """The rule's choice at passes that were measured (times in rules.hpp)."""
     assert host.host_prompt_attention(T, seqs, C.c_long(groups), KV, ctx) == takes
 
 
@@ -200,6 +202,7 @@ def test_scoring_keeps_its_attention_kernel(host, G, KV):
 @pytest.mark.parametrize("K,residual,lm,takes", [(2048, 0, 0, 1), (3072, 0, 0, 0), (2048, 1, 0, 0), (8192, 1, 0, 1), (14336, 1, 0, 0), (4864, 1, 0, 0),
                                                  (3072, 0, 1, 1), (4096, 0, 1, 0), (32, 0, 0, 1)])
 def test_ring_kernel_takes_the_matrices_it_is_faster_at(host, K, residual, lm, takes):
+    """The rule's choice by K, at 128 row blocks; by row blocks below."""
     assert host.host_ring_takes(K, residual, lm) == takes
 
 
