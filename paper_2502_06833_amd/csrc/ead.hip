@@ -1061,7 +1061,7 @@ void plan_groups(ead_handle *h, int m, int T, int ctx, const std::vector<int> &r
         const int have = h->hs[b].kvlen[m], last = have + rows[b] - 1;
         if (rows[b]) { ++seqs; groups += last / gr - have / gr + 1; small += last / rq - have / rq + 1; }
     }
-    if (prompt_attention(T, seqs, small, md.KV, ctx, h->scoring != 0)) { h->group_rows = gr; h->n_groups = groups; }
+    if (prompt_attention(T, seqs, small, groups, md.KV, md.hd, ctx, h->n_cu, h->scoring != 0)) { h->group_rows = gr; h->n_groups = groups; }
 }
 
 // Host copy of k_plan: which rows the pass will hold.  Returns T; fills n_lm, ctx_max and,

@@ -193,13 +193,24 @@ inline bool per_head_attention(int T, int KV, int splits) { return T <= 2 || (lo
 // 12 sequences (384) 23.7 / 20.5, 4 rows each of 40 (640) 50.6 / 24.6; from 2000: 64 rows 29.7 / 49.5, 160 (440) 55.6 / 52.1, 500 rows (1344) 160.6 / 66.3; from 8000: 160 rows 177 /
 // 183, 500 rows 538 / 221.  Heads of 64, 7 per KV head, 2 KV heads: from 600 160 rows (160) 13.2 / 16.1, 500 rows (500) 27.2 / 21.7.
 //
+// A few rows each of many sequences are where the first has more workgroups than units (`own` per KV head) and the second may still have no more than
+// two each, all resident: that one is faster then (5 rows each of 40 sequences, 480 workgroups against 320, heads of 64 and 128, from key
+// 400: 16.1 / 16.5 and 21.2 / 22.9, 1000: 24.6 / 29.0 and 35.9 / 41.5, 2000: 41.5 / 48.4 and 60.3 / 70.7; but 6 rows each of 33, 528 against 264: 31.6 / 28.4 and 56.3 /
+// 41.3), heads of 64 and up to five rows a sequence also a little past it (5 each of 48, 576: 25.5 / 29.1, 6 each of 40, 640: 31.7 / 29.4; from key 400 5 each of 48 16.7 / 15.8).
+// Where a sequence's rows are one workgroup of the second, too, and their keys and values more than the caches hold, both read the same bytes (32 KV heads of 128, 5
+// rows each of 100 sequences from 600, 1 GB: 193 / 202, of 40 from 1000, 0.66 GB: 130 / 133; of 64 from 300, 0.32 GB: 76 / 75).
+//
 // Scoring stays with k_attn_mfma.  It returns logits, and the two kernels add a row's keys in another order: behind a few layers of half-precision
 // activations that is 9e-4 of the logits' norm (8 layers of the 14B shape, 101 rows; either kernel is 1.4e-3 from 64 bits), where a pass of 101 rows
 // with its logits takes 3.7 ms and the other kernel saves 0.03 of them.
 constexpr int kGroupSeqs = 1024;                        // most sequences of a batch whose passes k_plan lists in groups
-inline bool prompt_attention(int T, int seqs, long groups, int KV, int ctx, bool scoring) {
+inline bool prompt_attention(int T, int seqs, long groups, long own, int KV, int hd, int ctx, int n_cu, bool scoring) {
     if (scoring || T < 17 || T < 4 * seqs || per_head_attention(T, KV, 1)) return false;
-    return ctx <= 160 || groups * KV >= (ctx <= 320 ? 256 : ctx <= 4096 ? 400 : 512);
+    if (ctx <= 160) return true;
+    const long wgs = groups * KV;
+    if (ctx > 320 && own * KV > n_cu && wgs <= (hd <= 64 && ctx > 512 && T <= 5 * seqs ? 600 : 2 * n_cu)) return false;
+    if (groups == seqs && (size_t)seqs * ctx * KV * hd * 4 >= ((size_t)512 << 20)) return false;
+    return wgs >= (ctx <= 320 ? 256 : ctx <= 4096 ? 400 : 512);
 }
 
 }  // namespace ead

@@ -56,9 +56,15 @@ int host_entropy_row_parts(int rows, int V) { return entropy_row_parts(rows, V);
 
 int host_attention_chunk(int T, int KV, int hd, int ctx, int mfma, long items) { return attention_chunk(T, KV, hd, ctx, mfma != 0, 256, 16, items); }
 
-int host_prompt_attention(int T, int seqs, long groups, int KV, int ctx) { return prompt_attention(T, seqs, groups, KV, ctx, false); }
+int host_prompt_attention(int T, int seqs, long groups, int KV, int ctx) { return prompt_attention(T, seqs, groups, 1, KV, 128, ctx, 256, false); }
 
-int host_score_prompt_attention(int T, long groups, int KV, int ctx) { return prompt_attention(T, 1, groups, KV, ctx, true); }
+int host_score_prompt_attention(int T, long groups, int KV, int ctx) { return prompt_attention(T, 1, groups, 1, KV, 128, ctx, 256, true); }
+
+// `rows` rows each of `seqs` sequences behind `have` keys, G query heads per KV head, 256 compute units
+int host_prompt_attention_rows(int seqs, int rows, int have, int G, int KV, int hd) {
+    const int rq = 16 / G, gr = 4 * rq, last = have + rows - 1;
+    return prompt_attention(seqs * rows, seqs, (long)seqs * (last / rq - have / rq + 1), (long)seqs * (last / gr - have / gr + 1), KV, hd, last + 1, 256, false);
+}
 
 // NB row blocks x K, one row, 256 compute units
 int host_ring_takes_matrix(int K, int NB, int epi) { return ring_takes(K, NB, 256, (Epilogue)epi); }

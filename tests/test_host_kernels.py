@@ -165,6 +165,16 @@ def test_prompt_attention_takes_the_passes_it_is_faster_at(host, T, seqs, groups
     assert host.host_prompt_attention(T, seqs, C.c_long(groups), KV, ctx) == takes
 
 
+@pytest.mark.parametrize("seqs,rows,have,G,KV,hd,takes", [
+    (40, 5, 999, 8, 4, 64, 0), (40, 5, 999, 8, 4, 128, 0), (40, 5, 1999, 6, 4, 128, 0), (40, 5, 399, 8, 4, 128, 0),      # 480 workgroups against 320
+    (33, 6, 999, 8, 4, 64, 1), (33, 6, 999, 8, 4, 128, 1), (24, 8, 1999, 8, 4, 64, 1), (64, 5, 999, 7, 4, 64, 1),       # 528 and more; 480 against 192
+    (48, 5, 999, 8, 4, 64, 0), (48, 5, 399, 8, 4, 64, 1), (48, 5, 999, 8, 4, 128, 1), (24, 8, 1999, 4, 8, 64, 1), (40, 6, 999, 7, 4, 64, 1),
+    (100, 5, 599, 1, 32, 128, 0), (100, 7, 599, 1, 32, 128, 0), (40, 5, 299, 1, 32, 128, 1), (100, 5, 599, 2, 16, 128, 1), (100, 5, 599, 4, 8, 64, 1)])
+def test_prompt_attention_of_a_few_rows_of_many_sequences(host, seqs, rows, have, G, KV, hd, takes):
+    """The same for catch-ups, where the kernels' numbers of workgroups and the bytes of the caches decide (times in rules.hpp)."""
+    assert host.host_prompt_attention_rows(seqs, rows, have, G, KV, hd) == takes
+
+
 def test_queries_in_three_terms_lose_nothing(host):
     """k_attn_prompt's queries: three bf16 terms are the float32 value itself (two are within 2^-17 of it, which is seen in its sums)."""
     rng = np.random.default_rng(0)
