@@ -633,7 +633,7 @@ void launch_narrow(ead_handle *h, LinArgs<bf16_t> &a, int T) {
             if (p.KS > 1) {
                 switch (p.R * 10 + p.NT) {
                     case 11: EAD_LM(4, 1, 1, 4, true); break;
-                    case 21: EAD_LM(4, 2, 1, 4, true); break; case 22: EAD_LM(4, 2, 2, 4, true); break;
+                    case 21: EAD_LM(4, 2, 1, 4, true); break; case 22: EAD_LM(4, 2, 2, 4, true); break; case 24: EAD_LM(4, 2, 4, 4, true); break;
                     case 41: EAD_LM(2, 4, 1, 6, true); break; default: EAD_LM(2, 4, 2, 4, true); break;
                 }
                 return;

@@ -73,7 +73,8 @@ inline int entropy_row_parts(int rows, int V) {
 // K is split where units would idle and a slab keeps more than 32 k tiles (896 x 4864 at 16 rows: 8.0 -> 6.4; 2048 x 8192: 128
 // workgroups 11.8, two slabs 9.9, four of two row blocks 10.3).  Long K (256 k tiles and more) of 17 to 64 rows: two row blocks and two token blocks,
 // whose tiles are fetched half as often, and the slabs that fill the chip (2048 x 8192 at 64 rows 14.0, unsplit 15.0; 4096 x
-// 14336 at 32 24.5, unsplit 28.0), of few row blocks also at more rows (512 x 14336 at 80: 11.4, unsplit 16.8), but not where even eight slabs leave
+// 14336 at 32 24.5, unsplit 28.0), three token blocks all in one workgroup from a third of a row block per unit on (a layer's two residual projections, 2048 x 9728 at 40
+// rows: 23.8, in two by two 25.8; 2048 x 8192 21.9, 23.0; 1536 x 11008 24.6, 25.7; but 1024 x 8192 20.6, 18.4); of few row blocks also at more rows (512 x 14336 at 80: 11.4, unsplit 16.8), but not where even eight slabs leave
 // a quarter of the units idle (at 32 rows 768 x 9728 9.3, two row blocks and one token block 8.7; 512 x 11008 9.2, one and one in four slabs 8.1).  Long K of up to 16 rows: two or four row blocks from 3/4 of a row block per unit on (4096 x 14336: 27.9
 // -> 21.5, 5120 x 13824: 29.5 -> 26.1), and from half on where that gives three slabs (2560 x 11008 13.8, unsplit 16.3) or K is very long (3072 x
 // 14336 19.5 against 20.6, but 3072 x 8192 14.0 against 12.7).
@@ -88,7 +89,8 @@ inline NarrowPlan narrow_plan(int NB, int KC, int TB, int n_cu, bool may_split, 
     };
     if (may_split && KC >= 256 && (TB <= 4 || 3 * groups(2, 2) <= n_cu)) {
         NarrowPlan p{0, 0, 1};
-        if (TB >= 2 && 4 * kSplitKMax * groups(2, 2) > 3 * n_cu) p = NB > n_cu && TB == 2 ? NarrowPlan{4, 2, 1} : NarrowPlan{2, 2, 1};
+        if (TB == 3 && 3 * NB > n_cu) p = NarrowPlan{2, 4, 1};
+        else if (TB >= 2 && 4 * kSplitKMax * groups(2, 2) > 3 * n_cu) p = NB > n_cu && TB == 2 ? NarrowPlan{4, 2, 1} : NarrowPlan{2, 2, 1};
         else if (TB >= 2) { if (TB == 2 && kSplitKMax * groups(2, 1) > n_cu) p = NarrowPlan{2, 1, 1}; }
         else if (4 * NB > 3 * n_cu) p = NarrowPlan{NB > n_cu ? 4 : 2, 1, 1};
         else if (2 * NB > n_cu && (3 * groups(2, 1) <= n_cu || KC >= 384)) p = NarrowPlan{2, 1, 1};

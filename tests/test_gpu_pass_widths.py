@@ -83,6 +83,21 @@ def test_rows_longer_than_the_models(d):
     e.close()
 
 
+@pytest.mark.parametrize("d,ffn", [(1408, 8192), (1440, 8224), (2048, 9728)])
+def test_three_token_blocks_split_along_k(d, ffn):
+    """Residual projections of two row blocks and four token blocks a workgroup, in four and five slabs of K, even and uneven: 33 to 48 rows scored."""
+    import paper_2502_06833_amd as ead
+    shape = WideRow(f"three-{d}", 1, d, 4, 2, ffn, 528, 1e-5, 1e4)
+    other = si.ModelShape("three-other", 1, 128, 4, 4, 128, 528, 1e-5, 1e4)
+    W, Wo, om, _ = make_pair(shape, other, gain_std=0.2, lm_sigma=1.5)
+    e = ead.EAD(shape, W, other, Wo, window=5, tau=0.0, d_min=4, max_batch=1, max_seq=64)
+    toks = si.prompt_np(0, "three", 48, shape.vocab)
+    ref = om.forward_dense(toks)
+    for T in (33, 40, 48):
+        check_logits(e.score(0, toks[:T])["logits"], ref[:T], TOL_LOGIT)
+    e.close()
+
+
 @pytest.mark.parametrize("d,heads,kv,ffn", [(1056, 33, 11, 7200), (1312, 41, 41, 6176), (2176, 34, 17, 8160), (2048, 32, 8, 6144), (864, 27, 9, 8192)])
 def test_one_row_in_uneven_slices(d, heads, kv, ffn):
     """k_linear_ring where the waves' slices of K differ by a tile, fill their groups partly and end inside an activation vector: 33, 41

@@ -145,7 +145,7 @@ def test_narrow_passes_take_the_measured_best(host, NB, KC, split, plans):
 
 def test_narrow_plans_are_instantiated_and_stay_within_the_scratch(host):
     plain = {11, 12, 21, 22, 24, 42, 44}                     # R, NT of the kernels launch_narrow knows without a split of K
-    slabs = {11, 21, 22, 41, 42}
+    slabs = {11, 21, 22, 24, 41, 42}
     for NB in (1, 2, 5, 16, 63, 64, 96, 128, 171, 192, 193, 256, 257, 320, 512, 513, 960):
         for KC in (1, 4, 28, 33, 66, 128, 255, 256, 300, 448, 480):
             for TB in (1, 2, 3, 4, 5, 8, 9, 16, 17, 31):
@@ -247,6 +247,12 @@ def test_narrow_passes_of_wide_or_small_matrices(host, NB, KC, split, plans):
     """Shapes that no model above has: where the smallest tiles take four rounds of workgroups and more, and long K of few row blocks."""
     for TB, plan in plans.items():
         assert host.host_narrow_plan(NB, KC, TB, split, C.c_long(8 << 20), 4096) == plan, TB
+
+
+@pytest.mark.parametrize("NB,KC,plan", [(128, 304, 244), (96, 344, 245), (86, 257, 245), (85, 257, 222), (128, 255, 121), (64, 256, 224)])
+def test_three_token_blocks_of_long_k_share_a_workgroup(host, NB, KC, plan):
+    """Residual projections of 33 to 48 rows: from a third of a row block per unit on, the weights are fetched once (times in rules.hpp)."""
+    assert host.host_narrow_plan(NB, KC, 3, 1, C.c_long(8 << 20), 4096) == plan
 
 
 @pytest.mark.parametrize("NB,one", [(1, 1), (256, 1), (257, 0), (512, 0), (513, 1), (608, 1), (768, 1), (1024, 0), (1120, 1), (1344, 0), (1728, 1), (1792, 1), (2048, 0)])
