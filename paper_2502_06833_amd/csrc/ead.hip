@@ -583,7 +583,7 @@ int launch_valu(ead_handle *h, int mi, LinArgs<WT> &a, int T, int grid) {
 }
 
 // T: the host's count of token rows.  The shape of the matrix and ceil(T / 16) pick the kernel:
-//  * up to 32 rows: launch_narrow (k_linear_mfma; see there);
+//  * up to 32 rows: launch_narrow (k_linear_mfma; see there), but for the gate/up matrices that gate_up_streamed names;
 //  * 33 to 128 rows: gate/up, and the QKV and residual projections of large matrices with many or long row blocks, through
 //    k_linear_mfma_ls, 64 to 128 rows per sweep; where that gives fewer workgroups than compute units, K is split over
 //    workgroups and k_sk_merge adds the slabs.  k_linear_mfma_wt is the fallback should the device not grant the LDS
@@ -609,7 +609,8 @@ bool launch_ls(ead_handle *h, const LinArgs<bf16_t> &a, int grid) {
 // workgroup of few waves per R row blocks and NT token blocks (narrow_plan in rules.hpp says how many of each, and how many slabs
 // of K).  Two waves a workgroup where row blocks are many, so that the workgroups are many and all resident: gate/up of up to 16
 // rows (28672 x 4096: 44.8 us with four waves and two row blocks, 40.7 with two and two, 40.2 with two and one; gate_up_by_one says which;
-// 9728 x 896: 7.1 with four and two, 6.3 with two and one; but 16384 x 3072: 18.0 and 18.7), of 17 to 32 rows with four row blocks (51.7 -> 46.9).
+// 9728 x 896: 7.1 with four and two, 6.3 with two and one; but 16384 x 3072: 18.0 and 18.7).  gate_up_streamed says which matrices go to
+// k_linear_mfma_ls instead.
 template <int EPI>
 void launch_narrow(ead_handle *h, LinArgs<bf16_t> &a, int T) {
     const int NB = a.Np / 16, KC = a.K / 32, TB = (T + 15) / 16, n_cu = h->n_cu;
@@ -623,7 +624,7 @@ void launch_narrow(ead_handle *h, LinArgs<bf16_t> &a, int T) {
             else if (many) EAD_LM(2, 2, 1, 8, false);
             else EAD_LM(4, 2, 1, 4, false);
         }
-        else if (TB == 2) { if (many) EAD_LM(2, 4, 2, 4, false); else EAD_LM(4, 2, 2, 4, false); }
+        else if (TB == 2) EAD_LM(4, 2, 2, 4, false);
         else EAD_LM(4, 2, 4, 4, false);
     } else {
         // (the rotary / cache-append epilogue is too heavy to be left to one workgroup per group)
@@ -649,16 +650,15 @@ void launch_narrow(ead_handle *h, LinArgs<bf16_t> &a, int T) {
 #undef EAD_LM
 }
 
-// The LM head: writes one partial per (row, workgroup) and returns their number per row (0: no LDS for k_lm_ls).  Up to 16 rows through
-// k_linear_mfma, two waves and two row blocks per workgroup (128256 x 4096: 212 -> 162 us = 6.5 TB/s, 151936 x 5120:
-// 255 -> 238), at 17 to 32 rows with four row blocks while K is long (203 -> 175); otherwise, and where a row block
-// is so short that filling and draining the pipeline per block counts (K < 1280: 50.9 against 57.3 us at 151936 x 896),
-// through k_lm_ls, 128 rows per sweep (64 rows: 350 -> 257 us at 151936 x 5120, 122 -> 52 at 151936 x 896; 128 rows:
-// 699 -> 300).
+// The LM head: writes one partial per (row, workgroup) and returns their number per row (0: no LDS for k_lm_ls).  Through
+// k_lm_ls, 128 rows per sweep: its fetching waves' non-temporal loads bring 7.2 TB/s (us at 32 rows with the register ring
+// of k_linear_mfma / this way: 128256 x 4096 188 / 166, x 3072 133 / 124; 151936 x 5120 263 / 243; at 12 rows 171 / 167, 249 / 242, 151936 x 1536 85.8 / 79.2,
+// 128256 x 2048 90.9 / 88.3).  But one token block of K between 2048 and 4096 stays with k_linear_mfma (128256 x 3072 at 3 and 12 rows 121.6 and 130.4
+// against 125.6 and 131.8).
 int launch_lm(ead_handle *h, int mi, LinArgs<bf16_t> &a, int T) {
     ProfScope ps(h, PK_MFMA_LOGITS, mi, (double)a.Np * a.K * 2.0);
     const int NB = a.Np / 16, KC = a.K / 32, TB = (T + 15) / 16;
-    if (!((TB == 1 && KC >= 40) || (TB == 2 && KC > 64)) && kLmLdsBytes <= h->lds_per_block) {
+    if (!(TB == 1 && KC > 64 && KC < 128) && kLmLdsBytes <= h->lds_per_block) {
         const int grid = std::min(NB, h->n_cu);
         bool ok = true;
         for (a.tb_base = 0; ok && a.tb_base < TB; a.tb_base += 8) {
@@ -669,11 +669,9 @@ int launch_lm(ead_handle *h, int mi, LinArgs<bf16_t> &a, int T) {
         }
         if (ok) return grid;
     }
-    if (TB > 2) return 0;
-    a.tb_base = 0;
-    const int R = TB == 1 ? 2 : 4, grid = std::min((NB + R - 1) / R, 2 * h->n_cu);
-    if (TB == 1) hipLaunchKernelGGL((k_linear_mfma<2, 2, 1, 8, EPI_LOGITS, false>), dim3(grid), dim3(128), 0, h->stream, a);
-    else hipLaunchKernelGGL((k_linear_mfma<2, 4, 2, 4, EPI_LOGITS, false>), dim3(grid), dim3(128), 0, h->stream, a);
+    if (TB > 1) return 0;
+    const int grid = std::min((NB + 1) / 2, 2 * h->n_cu);
+    hipLaunchKernelGGL((k_linear_mfma<2, 2, 1, 8, EPI_LOGITS, false>), dim3(grid), dim3(128), 0, h->stream, a);
     return grid;
 }
 
@@ -692,12 +690,12 @@ void launch_mfma(ead_handle *h, int mi, LinArgs<bf16_t> &a, int T) {
     // 200 rows 27.7 / 36.2, 3072 x 2048 at 160 12.5 / 17.0: since the tiles of narrow_plan the line lies low there).
     const bool longpass = TB >= 4 * kWideTok, multi = TB > kWideTok;
     const long tiles = (long)NB * (a.K / 32);
-    const bool wide = TB > 2 && (EPI == EPI_SWIGLU ? NB >= 128 : (big && (TB > 4 || tiles >= 40000)) ||
+    const bool wide = (TB > 2 || (EPI == EPI_SWIGLU && gate_up_streamed(NB, a.K / 32, TB, h->n_cu))) && (EPI == EPI_SWIGLU ? NB >= 128 : (big && (TB > 4 || tiles >= 40000)) ||
                                                                  (NB >= 128 && TB > (EPI == EPI_QKV ? 1 : 2) * kWideTok));
     if (wide || longpass) {
-        // token blocks per sweep: four up to 64 rows; the pass's own five to eight for 65-128 rows, one
+        // token blocks per sweep: one or two up to 32 rows, four up to 64; the pass's own five to eight for 65-128 rows, one
         // wave per block; eight for the sweeps of longer passes
-        const int NG = (NB + 7) / 8, nt = TB <= 4 ? 4 : (multi ? kWideTok : TB);
+        const int NG = (NB + 7) / 8, nt = TB <= 2 ? TB : TB <= 4 ? 4 : (multi ? kWideTok : TB);
         const int sw = (TB + nt - 1) / nt, n_cu = h->n_cu;
         // row blocks per workgroup without a split of K: the fewest that still make one round of workgroups over the
         // compute units; of longer passes the cheapest.  Cost of a launch in cycles per k tile: rounds of workgroups over
@@ -756,7 +754,7 @@ void launch_mfma(ead_handle *h, int mi, LinArgs<bf16_t> &a, int T) {
                                        case 6: ok = launch_ls<EPI, false, NW_, 6>(h, a, grid); break; case 7: ok = launch_ls<EPI, false, NW_, 7>(h, a, grid); break; \
                                        default: ok = launch_ls<EPI, false, NW_, 8>(h, a, grid); break; } } while (0)
         if constexpr (EPI == EPI_SWIGLU) {
-            switch (nt) { case 4: EAD_LS(4); break; case 5: EAD_LS(5); break; case 6: EAD_LS(6); break; case 7: EAD_LS(7); break; default: EAD_LS(8); break; }
+            switch (nt) { case 1: EAD_LS(1); break; case 2: EAD_LS(2); break; case 4: EAD_LS(4); break; case 5: EAD_LS(5); break; case 6: EAD_LS(6); break; case 7: EAD_LS(7); break; default: EAD_LS(8); break; }
         } else if (nt == 8) EAD_LS(8);
 #undef EAD_LS
         if (ok) return;

@@ -828,7 +828,7 @@ constexpr int ls_depth(int rg) { return kLsDepth * 8 / ls_slot_tiles(rg); }
 
 template <int EPI, bool SK, int NW, int RG>
 __global__ __launch_bounds__((NW + kLsProducers) * 64) void k_linear_mfma_ls(LinArgs<bf16_t> a) {
-    static_assert(RG >= 3 && RG <= 8 && NW >= 2 && NW <= 8, "two producer waves share a step's four or eight tile slots");
+    static_assert(RG >= 3 && RG <= 8 && NW >= 1 && NW <= 8, "two producer waves share a step's four or eight tile slots");
     constexpr int SLOT = ls_slot_tiles(RG), PL = SLOT / 2, DEPTH = ls_depth(RG);      // tiles per slot, loads per producer wave and step, k steps in the ring
     static_assert(PL * (DEPTH - 1) <= 63, "the load counter holds 63");
     constexpr int DA = 6;                              // ring of activation fragments per multiplying wave
@@ -860,13 +860,15 @@ __global__ __launch_bounds__((NW + kLsProducers) * 64) void k_linear_mfma_ls(Lin
 #pragma unroll
         for (int q = 0; q < PL; ++q)
             wp[q] = a.W + tile_offset(min(g * RG + min(p + 2 * q, RG - 1), NB - 1), kbase, KCfull) + lane * 8;
+        const bool once = SK || a.sweeps <= 1;            // no other workgroup reads these tiles
         auto issue = [&](int j) __attribute__((always_inline)) {      // step j (past the end: the last step again, never read)
             const size_t off = (size_t)kstep(j) * 512;
             bf16_t (*slot)[512] = s_w[j % DEPTH];
 #pragma unroll
-            for (int q = 0; q < PL; ++q)
-                __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(wp[q] + off),
-                                                 (__attribute__((address_space(3))) void *)&slot[p + 2 * q][0], 16, 0, 0);
+            for (int q = 0; q < PL; ++q) {
+                if (once) request_tile_once(wp[q] + off, &slot[p + 2 * q][0]);
+                else request_tile_kept(wp[q] + off, &slot[p + 2 * q][0]);
+            }
         };
         for (int j = 0; j < DEPTH - 1; ++j) issue(j);
         asm volatile("s_waitcnt vmcnt(%0)" ::"n"(PL * (DEPTH - 2)) : "memory");      // step 0 has landed
@@ -1034,9 +1036,7 @@ __global__ __launch_bounds__((NW + kLsProducers) * 64) void k_lm_ls(LinArgs<bf16
         auto issue = [&]() __attribute__((always_inline)) {      // past the range: its last step again, never read
             const size_t off = (size_t)k * 512;
 #pragma unroll
-            for (int q = 0; q < 4; ++q)
-                __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(wp[q] + off),
-                                                 (__attribute__((address_space(3))) void *)&s_w[slot][p + 2 * q][0], 16, 0, 0);
+            for (int q = 0; q < 4; ++q) request_tile_once(wp[q] + off, &s_w[slot][p + 2 * q][0]);
             slot = slot + 1 == kLsDepth ? 0 : slot + 1;
             if (k + 1 < KC) ++k;
             else if (g + 1 < groups) { k = 0; ++g; point(); }

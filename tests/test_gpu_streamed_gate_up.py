@@ -1,0 +1,33 @@
+"""GPU: gate/up matrices and LM heads of passes of one and two token blocks through the fetching-wave kernels, on both sides of their rules
+(gate_up_streamed in rules.hpp, launch_lm): 1028 row blocks (a last group of three in five) x 128 and 129 k tiles from three rows on, 128 row blocks x 96
+from 17, 1024 x 128 that stay with the other kernel up to 16."""
+import numpy as np
+import pytest
+
+import oracle
+import synth_inputs as si
+from gpu_helpers import TOL_H, TOL_LOGIT, check_logits, make_pair
+
+pytestmark = pytest.mark.gpu
+
+
+class FewHeads(si.ModelShape):
+    head_dim = 128
+
+
+@pytest.mark.parametrize("d,ffn", [(4096, 8224), (4128, 8224), (3072, 1024), (4096, 8192)])
+def test_gate_up_of_one_and_two_token_blocks(d, ffn):
+    """Logits within 2e-2 of the row maximum, entropy within 1e-2 nats (the tolerances of all bf16 parity tests)."""
+    import paper_2502_06833_amd as ead
+    shape = FewHeads(f"gu-{d}", 1, d, 4, 2, ffn, 1040, 1e-5, 1e4)
+    other = si.ModelShape("gu-other", 1, 128, 4, 4, 128, 1040, 1e-5, 1e4)
+    W, Wo, om, _ = make_pair(shape, other, gain_std=0.2, lm_sigma=1.5)
+    e = ead.EAD(shape, W, other, Wo, window=5, tau=0.0, d_min=4, max_batch=1, max_seq=64)
+    toks = si.prompt_np(0, "gu", 33, shape.vocab)
+    ref = om.forward_dense(toks)
+    for T in (3, 16, 17, 32, 33):
+        out = e.score(0, toks[:T])
+        check_logits(out["logits"], ref[:T], TOL_LOGIT)
+        assert np.abs(out["H"] - oracle.entropy_rows(ref[:T])[0]).max() < TOL_H
+        assert np.abs(oracle.entropy_rows(out["logits"])[0] - out["H"]).max() < 1e-4      # statistics against the logits they fold
+    e.close()
