@@ -1676,7 +1676,7 @@ void launch_entropy_folded(const void *logits, int rows, int V, EntPartial *part
 }
 
 ead_status entropy_check(const void *const *step_logits, int steps, int dtype, int rows, int vocab) {
-    if (steps < 1 || steps > kGateMaxSteps || (long)steps * rows > kEntMaxRows)
+    if (steps < 1 || steps > kRowsMaxSteps || (long)steps * rows > kEntMaxRows)
         return fail(nullptr, EAD_ERR_INVALID_ARG, "too many steps for one launch");
     for (int z = 0; z < steps; ++z)
         if (!step_logits[z]) return fail(nullptr, EAD_ERR_INVALID_ARG, "null logits pointer");
@@ -1686,6 +1686,11 @@ ead_status entropy_check(const void *const *step_logits, int steps, int dtype, i
     if (vocab % 8) return fail(nullptr, EAD_ERR_SHAPE, "vocab must be a multiple of 8");
     if ((long)vocab > 64L * 2048 * 8) return fail(nullptr, EAD_ERR_SHAPE, "vocab above %ld", 64L * 2048 * 8);
     return EAD_OK;
+}
+
+// Steps one launch takes: bounded by the kernels' arguments and the gate's hand-over buffers.
+int gate_steps_per_launch(int window, int rows) {
+    return std::max(1, std::min(window <= kGateFoldWindow ? kRowsMaxSteps : kGateMaxSteps, kEntMaxRows / rows));
 }
 
 // step_logits: host array of `steps` device pointers (<= kGateMaxSteps), one [rows, vocab] matrix each;
@@ -2180,7 +2185,7 @@ ead_status ead_gate_create(int32_t rows, int32_t window, float tau, int32_t d_mi
     EntDevice *d = nullptr;
     { const ead_status rc = entropy_device(&d); if (rc != EAD_OK) { delete g; return rc; } }
     g->resident = d->resident;
-    const size_t steps_per_launch = std::max(1, std::min(kGateMaxSteps, kEntMaxRows / rows));
+    const size_t steps_per_launch = gate_steps_per_launch(window, rows);
     void *p[8] = {nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr};
     const size_t sz[8] = {(size_t)rows * window * 4, (size_t)rows * 4, (size_t)rows * 4, (size_t)rows * 4,
                           steps_per_launch * rows * kEntMaxChunks * sizeof(EntPartial), steps_per_launch * rows * 4, (size_t)rows * 4, steps_per_launch * rows * 4};
@@ -2261,10 +2266,10 @@ ead_status ead_gate_run_logits(ead_gate *g, const void *const *logits_dev_list, 
     if (unit != EAD_NATS && unit != EAD_BITS) return fail(nullptr, EAD_ERR_INVALID_ARG, "unit must be 0 or 1");
     for (int i = 0; i < n_tensors; ++i) if (!logits_dev_list[i]) return fail(nullptr, EAD_ERR_INVALID_ARG, "null logits pointer");
     // steps per launch, bounded by the gate's hand-over buffers
-    const int S = std::max(1, std::min(kGateMaxSteps, kEntMaxRows / g->rows));
+    const int S = gate_steps_per_launch(g->cfg.w, g->rows);
     for (int s0 = 0; s0 < n_steps; s0 += S) {
         const int ns = std::min(S, n_steps - s0);
-        const void *ptrs[kGateMaxSteps];
+        const void *ptrs[kRowsMaxSteps];
         for (int z = 0; z < ns; ++z) ptrs[z] = logits_dev_list[(s0 + z) % n_tensors];
         const size_t o = (size_t)s0 * g->rows;
         TRY(gate_steps(g, ptrs, ns, dtype, vocab, unit, H_dev ? H_dev + o : nullptr, argmax_dev ? argmax_dev + o : nullptr,

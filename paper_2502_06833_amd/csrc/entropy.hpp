@@ -8,7 +8,11 @@
 namespace ead {
 
 constexpr float kLn2Inv = 1.4426950408889634f;
-constexpr int kGateMaxSteps = 16;       // steps of the gate one launch can take
+constexpr int kGateMaxSteps = 16;       // steps of the gate one launch can take: k_entropy_partial + k_gate_step (a wave per step)
+// The same for k_entropy_rows, whose workgroups take one row after another: with 16 a launch, most of the chip idled at every launch's end and wherever
+// 16 steps of the rows are no multiple of its workgroups (us, 16 a launch -> 64: 64 rows x 151936 bf16, 48 steps 175 -> 170; 33 x 128256, 40 steps
+// 97 -> 71; 17 x 151936, 37 steps 87 -> 49; 50 x 151936 float32, 33 steps 240 -> 187; 7 x 32000, 30 steps 23.6 -> 16.3; 2 x 151936, 40 steps 39 -> 22.5).
+constexpr int kRowsMaxSteps = 64;
 
 // H = ln Z - S/Z in nats, or divided by ln 2 for bits
 __device__ __forceinline__ float entropy_from(const EntStat &s, int unit) {
@@ -85,7 +89,7 @@ struct GateStepArgs {
 
 // A row's window means and switch decisions for the steps of one launch, once their entropies are in
 // s_H[0 .. steps) (LDS): called by a whole workgroup of any size; ends with a workgroup barrier.
-// s_hb: kGateMaxSteps floats, s_ring: at least cfg.w floats of LDS.
+// s_hb: a.steps floats, s_ring: at least cfg.w floats of LDS.
 __device__ __forceinline__ void gate_row_apply(const GateStepArgs &a, int r, const float *s_H, float *s_ring, float *s_hb) {
     // the window lives in LDS while the steps are taken: a store-then-load round trip through
     // device memory per step would dominate
@@ -317,7 +321,7 @@ __global__ __launch_bounds__(256) void k_entropy_partial(EntArgs<T> a) {
 // them, one reduction over the workgroup per row instead of one per chunk and no partials in memory --
 // and leaves the row's entropy and arg max.  The workgroup that does so for the last of a row's steps
 // in this launch (arrival counter per row, left at zero) reads the row's entropies back and takes its
-// window and switch rule through the steps in order.  One launch per up to kGateMaxSteps steps.
+// window and switch rule through the steps in order.  One launch per up to kRowsMaxSteps steps.
 // With few rows a workgroup per (row, step) leaves most of the chip idle (two rows x 3 steps: six workgroups); `parts` > 1
 // gives every piece of a row a workgroup (SPLIT: its indexes and arguments cost whole rows 0.5 us a launch), which leaves a
 // partial, and the last to arrive at the row's step merges them (entropy_row_parts: which rows, and what it measured).
@@ -326,7 +330,7 @@ constexpr int kGateFoldWindow = 64;     // largest window this kernel serves (it
 
 template <typename T>
 struct EntRowArgs {
-    const T *step_logits[kGateMaxSteps];      // one [rows, V] matrix per step of the launch
+    const T *step_logits[kRowsMaxSteps];      // one [rows, V] matrix per step of the launch
     int V, rows, steps, chunks, vec_per_item; // a row is walked in `chunks` pieces of vec_per_item vectors (<= 8 per thread)
     float *pair_H;                            // [steps * rows]: the entropies, handed between workgroups (written through)
     int *row_tickets;                         // [rows] arrival counters, zero between launches
@@ -353,7 +357,7 @@ template <typename T, bool SPLIT>
 __global__ __launch_bounds__(256) void k_entropy_rows(EntRowsArgs<T, SPLIT> a) {
     __shared__ float s_max[4], s_Z[4], s_S[4];
     __shared__ int s_idx[4], s_last_row, s_last_part;
-    __shared__ float s_H[kGateMaxSteps], s_hb[kGateMaxSteps], s_ring[kGateFoldWindow];
+    __shared__ float s_H[kRowsMaxSteps], s_hb[kRowsMaxSteps], s_ring[kGateFoldWindow];
     const int tid = threadIdx.x, pairs = a.steps * a.rows;
     // uniform, kept in scalar registers.  (pair, chunk) walks whole rows; SPLIT: blockIdx.x and its successors number the
     // pieces of all rows
