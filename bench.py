@@ -282,7 +282,7 @@ def bench_entropy_gate(args):
         "config": {"workload": "entropy_gate_b64", "rows": rows, "vocab": V, "window": w, "tau_nats": tau,
                    "d_min": d_min, "pool_tensors": pool_n},
         "large_token_share": float(share.item()), "event_ms_total": ev_ms,
-        "roofline": {"bound": "hbm", "kernel": "entropy_rows (entropy, arg max, window and switch rule; 16 steps per launch)",
+        "roofline": {"bound": "hbm", "kernel": "entropy_rows (entropy, arg max, window and switch rule; up to 64 steps per launch)",
                      "achieved": bytes_step / per_step_us / 1e3, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": bytes_step / per_step_us / 1e3 / HBM_PEAK_GBS, "traffic": None,
                      "avg_launch_us": per_step_us, "bytes_per_launch": bytes_step, "launches": steps},

@@ -132,8 +132,18 @@ def _dtype_code(t) -> int:
 
 
 def _stream_ptr():
-    import torch
-    return C.c_void_p(torch.cuda.current_stream().cuda_stream)
+    """The current device's current stream.  By the accessors that return plain numbers where this torch has them: building a Stream object takes
+    3 us, a third of an `entropy_argmax` call (10.3 -> 7.2 us at 1 x 128256 bf16)."""
+    global _stream_of
+    if _stream_of is None:
+        import torch
+        torch.cuda.current_stream()                # the runtime is set up from here on
+        raw, dev = getattr(torch._C, "_cuda_getCurrentRawStream", None), getattr(torch._C, "_cuda_getDevice", None)
+        _stream_of = (lambda: raw(dev())) if raw and dev else (lambda: torch.cuda.current_stream().cuda_stream)
+    return _stream_of()
+
+
+_stream_of = None
 
 
 def _desc(shape, weights) -> tuple:
