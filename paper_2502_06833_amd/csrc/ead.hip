@@ -595,6 +595,7 @@ int launch_valu(ead_handle *h, int mi, LinArgs<WT> &a, int T, int grid) {
 constexpr float kSmallLaneMin = 0.3f;                  // grouped schedule, two lanes: see decode_grouped
 constexpr int kSplitKGroups = 4096;                     // arrival counters
 constexpr size_t kSplitKFloats = (size_t)8 << 20;      // partial sums: KS slabs of (padded Np) x 128 floats at most
+constexpr size_t kTileSplitFloats = 2 * kSplitKFloats;  // the same of the long passes' tiles: what the buffer holds
 
 template <int EPI, bool SK, int NW, int RG>
 bool launch_ls(ead_handle *h, const LinArgs<bf16_t> &a, int grid) {
@@ -700,7 +701,7 @@ void launch_mfma(ead_handle *h, int mi, LinArgs<bf16_t> &a, int T) {
         // row blocks per workgroup without a split of K: the fewest that still make one round of workgroups over the
         // compute units; of longer passes the cheapest.  Cost of a launch in cycles per k tile: rounds of workgroups over
         // the compute units times the time of a k step (measured: about 260 + 64 rg cycles with rg row blocks x 128
-        // rows, about 1150 for the 128 x 256 tiles and 1750 for the 256 x 256 ones); the tiles win where their groups still fill the chip.
+        // rows, about 1150 for the 128 x 256 tiles; tile_plan for the 256 x 256 ones); the tiles win where their groups still fill the chip.
         // cost_tile: 256 x 256 tiles.  (Gate/up 28672 x 4096 at 300 rows: 113 us in tiles, 126 in sweeps; at 1024: 209 against 260
         // in 128 x 256 tiles = 1150 Tflop/s; 4096 x 14336 at 3584: 365 against 435.  9728 x 896 at 512: 28 against 24 in sweeps.)
         auto cost_of = [&](int r) { return (((long)((NB + r - 1) / r) * sw + n_cu - 1) / n_cu) * (260 + 64 * r); };
@@ -711,13 +712,24 @@ void launch_mfma(ead_handle *h, int mi, LinArgs<bf16_t> &a, int T) {
         // launch pairs per sweep, which stream the matrix once each, are not (4096 x 4096 at 300 rows: 58 against 32)
         const bool split = EPI != EPI_SWIGLU && big && (!multi || (sw == 2 && a.K >= 256 * 32));
         if (multi && !split) {
-            const int sg = (TB + kGemmTok - 1) / kGemmTok, NG16 = (NB + kTileBlocks - 1) / kTileBlocks;
-            const long cost_gemm = (((long)NG * sg + n_cu - 1) / n_cu) * 1150, cost_tile = (((long)NG16 * sg + n_cu - 1) / n_cu) * 1750;
+            const int sg = (TB + kGemmTok - 1) / kGemmTok, NG16 = (NB + kTileBlocks - 1) / kTileBlocks, KC = a.K / 32;
+            const TilePlan tp = tile_plan(NG16, sg, KC, n_cu, EPI != EPI_SWIGLU, kTileSplitFloats);
+            const long cost_gemm = (((long)NG * sg + n_cu - 1) / n_cu) * 1150, cost_tile = tp.cost / KC;
             const void *gemm = (const void *)k_linear_mfma_gemm<EPI>, *tile = (const void *)k_linear_mfma_tile<EPI>;
             if (cost_tile < cost_gemm && cost_tile < cost_of(rg) && kTileLdsBytes <= h->lds_per_block && allow_big_lds(tile, kTileLdsBytes)) {
-                const int bands = (sg + kTileBand - 1) / kTileBand;
-                a.sweeps = (sg + bands - 1) / bands;
-                hipLaunchKernelGGL((k_linear_mfma_tile<EPI>), dim3((NG16 + 7) / 8 * a.sweeps * bands * 8), dim3(512), kTileLdsBytes, h->stream, a);
+                auto spread = [](int n) { const int bands = (n + kTileBand - 1) / kTileBand; return (n + bands - 1) / bands; };
+                a.tb_base = 0; a.tile_sweeps = tp.whole;
+                if (tp.whole) {
+                    a.sweeps = spread(tp.whole);
+                    hipLaunchKernelGGL((k_linear_mfma_tile<EPI>), dim3((NG16 * tp.whole + 7) / 8 * 8), dim3(512), kTileLdsBytes, h->stream, a);
+                }
+                if constexpr (EPI != EPI_SWIGLU) {
+                    if (tp.whole < sg && allow_big_lds((const void *)k_linear_mfma_tile<EPI, true>, kTileLdsBytes)) {
+                        a.tb_base = tp.whole * kTileBlocks; a.tile_sweeps = sg - tp.whole; a.sweeps = spread(a.tile_sweeps); a.KS = tp.KS; a.sk_part = h->sk_part;
+                        hipLaunchKernelGGL((k_linear_mfma_tile<EPI, true>), dim3((NG16 * a.tile_sweeps * tp.KS + 7) / 8 * 8), dim3(512), kTileLdsBytes, h->stream, a);
+                        hipLaunchKernelGGL((k_sk_merge<EPI, 0>), dim3((NB * a.tile_sweeps * kTileBlocks + 3) / 4), dim3(256), 0, h->stream, a, NG16 * kTileBlocks);
+                    }
+                }
                 return;
             }
             if (cost_gemm < cost_of(rg) && kGemmLdsBytes <= h->lds_per_block && allow_big_lds(gemm, kGemmLdsBytes)) {
@@ -1827,7 +1839,7 @@ ead_status ead_create(const ead_model_desc *small_model, const ead_model_desc *l
             HIP_TRY(h, hipMemsetAsync(h->xp_h, 0, T * fmax_ * 2, h->stream));
             TRY(dmalloc(h, &h->part_o, (size_t)h->items_max * qmax)); TRY(dmalloc(h, &h->part_ml, (size_t)h->items_max * std::max(a.H, b.H)));
             TRY(dmalloc(h, &h->tickets, T * std::max(a.H, b.H)));
-            TRY(dmalloc(h, &h->sk_part, kSplitKFloats)); TRY(dmalloc(h, &h->sk_tickets, (size_t)kSplitKGroups));
+            TRY(dmalloc(h, &h->sk_part, kTileSplitFloats)); TRY(dmalloc(h, &h->sk_tickets, (size_t)kSplitKGroups));
             HIP_TRY(h, hipMemsetAsync(h->sk_tickets, 0, kSplitKGroups * sizeof(int), h->stream));
             HIP_TRY(h, hipMemsetAsync(h->tickets, 0, T * std::max(a.H, b.H) * sizeof(int), h->stream));
             TRY(dmalloc(h, &h->lm_part, std::max((size_t)std::max<size_t>(MB, h->score_rows) * h->lm_grid, (size_t)256 * kFusedRbChunk)));

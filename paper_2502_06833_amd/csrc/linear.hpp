@@ -53,6 +53,7 @@ struct LinArgs {
     // MFMA path with K split over KS workgroups per row-block group
     int tb_base;            // k_linear_mfma_wt with split K, k_sk_merge, k_lm_ls: first token block of the sweep this launch takes
     int sweeps;             // without split K: > 1 = one workgroup per (row-block group, sweep of 128 rows; k_linear_mfma_gemm: 256); k_linear_mfma_tile: sweeps of a band
+    int tile_sweeps;        // k_linear_mfma_tile, k_sk_merge<EPI, 0>: sweeps of 256 rows this launch takes, from token block tb_base on
     int KS;
     float *sk_part;         // [KS][groups][R][NT][256] partial sums
     int *sk_tickets;        // [groups] arrival counters, zero between launches
@@ -1242,33 +1243,50 @@ __global__ __launch_bounds__(640) void k_linear_mfma_gemm(LinArgs<bf16_t> a) {
 // Step i: wait until this wave's tiles of step i + 1 have landed, meet the other waves (theirs have, too, and all have
 // read step i - 1), request step i + 4 into the slot of step i - 1, read the fragments of step i + 1, multiply step i.
 // Every output element adds its k tiles in ascending order, as in the other kernels without a split of K.
+//
+// SK: a workgroup takes one of KS slabs of K of a tile and leaves its sums for k_sk_merge.  Serves the sweeps that a whole round of
+// workgroups would serve half empty (tile_plan in rules.hpp).
 // ------------------------------------------------------------------------------------
 constexpr int kTileDepth = 5, kTileBlocks = 16;        // k steps in LDS; row blocks and token blocks per workgroup
 constexpr size_t kTileLdsBytes = (size_t)kTileDepth * 2 * kTileBlocks * 1024;
 constexpr int kTileBand = 6;                           // most sweeps that run side by side, see launch
 
-template <int EPI>
+// Which tile a workgroup takes: group of 16 row blocks, sweep of 256 tokens, slab of K (g < 0: none), of NG x SG x KS in a grid of those rounded up to a multiple of
+// eight.  XCD id % 8 takes an eighth of all tiles, one behind the other: with every eighth group of row blocks instead, 108 groups x 14 sweeps were 196 tiles for
+// the 32 units of one XCD and 182 for those of another, seven rounds where 189 are six.  The sweeps of a band of `bs` run side by side for one group after the
+// other, so that what runs at a time on an XCD shares weights and activations in L2.
+struct TileAt { int g, sweep, ks; };
+__device__ __forceinline__ TileAt tile_at(int id, int NG, int SG, int KS, int bs) {
+    const int total = NG * SG * KS, per = (total + 7) >> 3, unit = (id & 7) * per + (id >> 3);
+    if ((id >> 3) >= per || unit >= total) return TileAt{-1, 0, 0};
+    const int ks = unit % KS, tile = unit / KS;
+    const int band = min(tile / (NG * bs), (SG - 1) / bs), in = tile - band * NG * bs, width = min(bs, SG - band * bs);
+    return TileAt{in / width, band * bs + in % width, ks};
+}
+
+template <int EPI, bool SK = false>
 __global__ __launch_bounds__(512, 2) void k_linear_mfma_tile(LinArgs<bf16_t> a) {
     constexpr int NWV = 8, WB = 4, PL = 4;             // waves; token blocks of a wave; its requests per step
     extern __shared__ __attribute__((aligned(16))) unsigned char ls_smem[];
     bf16_t (*s_w)[2 * kTileBlocks][512] = reinterpret_cast<bf16_t (*)[2 * kTileBlocks][512]>(ls_smem);       // [kTileDepth]: weight tiles, activation tiles
-    const int KC = a.K >> 5, NB = a.Np >> 4, NG = (NB + kTileBlocks - 1) / kTileBlocks;
+    const int KCfull = a.K >> 5, NB = a.Np >> 4, NG = (NB + kTileBlocks - 1) / kTileBlocks;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int T = *a.count;
     const int TB = (T + 15) >> 4;
-    // workgroup id -> (group of row blocks, sweep of tokens): XCD id % 8 takes every eighth group; on it the sweeps of a band run
-    // side by side for one group after the other, so that what runs at a time shares weights and activations in L2
-    const int GX = (NG + 7) >> 3, q = (int)blockIdx.x >> 3, per = GX * a.sweeps, band = q / per, in = q % per;
-    const int g = (in / a.sweeps) * 8 + ((int)blockIdx.x & 7), tb0 = (band * a.sweeps + in % a.sweeps) * kTileBlocks;
-    if (g >= NG || tb0 >= TB) return;
+    const int KS = SK ? a.KS : 1, SG = a.tile_sweeps;
+    const TileAt at = tile_at((int)blockIdx.x, NG, SG, KS, a.sweeps);
+    if (at.g < 0) return;
+    const int g = at.g, ks = at.ks, tb0 = a.tb_base + at.sweep * kTileBlocks;
+    if (tb0 >= TB) return;
+    const int kbase = (ks * KCfull) / KS, KC = ((ks + 1) * KCfull) / KS - kbase;     // this workgroup's k tiles
 
     // this wave's four tiles of a step: weight tiles wave, wave + 8, activation tiles wave, wave + 8
     const bf16_t *src[PL];
 #pragma unroll
     for (int j = 0; j < PL / 2; ++j) {
-        src[j] = a.W + tile_offset(min(g * kTileBlocks + wave + NWV * j, NB - 1), 0, KC);
-        src[PL / 2 + j] = a.xp + act_tile_offset(min(tb0 + wave + NWV * j, TB - 1), 0, TB);
+        src[j] = a.W + tile_offset(min(g * kTileBlocks + wave + NWV * j, NB - 1), kbase, KCfull);
+        src[PL / 2 + j] = a.xp + act_tile_offset(min(tb0 + wave + NWV * j, TB - 1), kbase, TB);
     }
     const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char *)ls_smem + (uint32_t)wave * 1024, voff = (uint32_t)lane * 16;
     const size_t xstep = (size_t)TB * 512;
@@ -1326,6 +1344,25 @@ __global__ __launch_bounds__(512, 2) void k_linear_mfma_tile(LinArgs<bf16_t> a) 
         }
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");    // nothing may land in LDS after the workgroup has gone
+    if constexpr (SK) {
+        // this slab's sums, for k_sk_merge: blocks of 16 x 16 ordered [slab][row block][token block of the launch]
+        const int NT = SG * kTileBlocks;
+#pragma unroll
+        for (int b = 0; b < WB; ++b) {
+            const int tb = tb0 + WB * wt + b;
+            if (tb < TB) {
+#pragma unroll
+                for (int j = 0; j < 8; ++j) {
+                    const int rb = g * kTileBlocks + 8 * wr + j;
+                    if (rb < NB) {
+                        float *dst = a.sk_part + (((size_t)ks * NG * kTileBlocks + rb) * NT + (tb - a.tb_base)) * 256 + lane;
+                        dst[0] = acc[j][b][0]; dst[64] = acc[j][b][1]; dst[128] = acc[j][b][2]; dst[192] = acc[j][b][3];
+                    }
+                }
+            }
+        }
+        return;
+    }
 #pragma unroll
     for (int b = 0; b < WB; ++b) {
         const f32x4_t *v[8] = {&acc[0][b], &acc[1][b], &acc[2][b], &acc[3][b], &acc[4][b], &acc[5][b], &acc[6][b], &acc[7][b]};
@@ -1334,10 +1371,11 @@ __global__ __launch_bounds__(512, 2) void k_linear_mfma_tile(LinArgs<bf16_t> a) 
     }
 }
 
-// Sum of the K slabs that k_linear_mfma_wt<..., SK = true, TPW> left in memory, in slab order, then
-// the epilogue.  One wave per 16 x 16 block; grid = ceil(row blocks * NT / 4) workgroups, NT = 4 TPW.
-template <int EPI, int NT = kWideTok>
+// Sum of the K slabs that k_linear_mfma_wt<..., SK = true, TPW> (k_linear_mfma_tile<EPI, true>: NTB = 0) left in memory, in slab order, then
+// the epilogue.  One wave per 16 x 16 block; grid = ceil(row blocks * NT / 4) workgroups, NT token blocks.
+template <int EPI, int NTB = kWideTok>
 __global__ __launch_bounds__(256) void k_sk_merge(LinArgs<bf16_t> a, int NGR /* row blocks incl. padding */) {
+    const int NT = NTB ? NTB : a.tile_sweeps * kTileBlocks;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int NB = a.Np >> 4, T = *a.count, TB = (T + 15) >> 4, KS = a.KS;
     const int blk = blockIdx.x * 4 + wave, rb = blk / NT, b = blk % NT;

@@ -224,4 +224,27 @@ inline bool gate_up_streamed(int NB, int KC, int TB, int n_cu) {
     return TB == 1 ? KC >= 128 && NB > 4 * n_cu : TB == 2 && KC >= 96 && NB >= 128;
 }
 
+// How 256 x 256 tiles take a pass: NG groups of 16 row blocks x SG sweeps of 256 tokens x KC k tiles.  The first `whole` sweeps in tiles of full depth, the
+// others, which would leave a round of workgroups partly empty, in tiles of one of KS slabs of K, whose sums another launch adds.  Cost in
+// cycles: 1750 per k tile and round, 1950 with the whole chip busy (measured; an eighth of the tiles to each XCD's units), the sums written and read at 5 TB/s, and
+// the two launches more; a split has to promise 8 %.  (ms of a 6-layer pair's prompts, Qwen 0.5B / 14B shapes, before -> now: 2600 positions
+// 13.2 -> 10.6, 3950 15.4 -> 14.4, 5870 27.3 -> 22.2, 10670 43.8 -> 39.2; of that the numbering of the tiles 42.2.)
+struct TilePlan { int whole, KS; long cost; };
+inline TilePlan tile_plan(int NG, int SG, int KC, int n_cu, bool may_split, size_t most_floats) {
+    const auto cost = [&](long tiles, long steps) {
+        const long rounds = ((tiles + 7) / 8 + n_cu / 8 - 1) / (n_cu / 8);
+        return rounds * steps * 1750 + 200 * steps * tiles / n_cu;
+    };
+    TilePlan best{SG, 1, cost((long)NG * SG, KC)};
+    if (!may_split || SG < 4) return best;
+    for (int whole = 0; whole < SG; ++whole)
+        for (int KS = 2; KS <= kSplitKMax && KC / KS >= 32; ++KS) {
+            const long floats = (long)NG * (SG - whole) * 65536 * KS;
+            if ((size_t)floats > most_floats) break;
+            const long c = (cost((long)NG * whole, KC) + cost((long)NG * (SG - whole) * KS, KC / KS + 9) + floats * 8 / 2000 + 12000) * 27 / 25;
+            if (c < best.cost) best = TilePlan{whole, KS, c};
+        }
+    return best;
+}
+
 }  // namespace ead

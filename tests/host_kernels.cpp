@@ -90,4 +90,16 @@ int host_narrow_plan(int NB, int KC, int TB, int split, long floats, int groups)
 
 int host_gate_up_by_one(int NB) { return gate_up_by_one(NB, 256); }
 
+// the tile of workgroup `id` as g * 1000000 + sweep * 1000 + ks; -1: none
+int host_tile_at(int id, int NG, int SG, int KS, int bs) {
+    const TileAt t = tile_at(id, NG, SG, KS, bs);
+    return t.g < 0 ? -1 : t.g * 1000000 + t.sweep * 1000 + t.ks;
+}
+
+// sweeps in whole tiles * 100 + slabs of the others
+int host_tile_plan(int NG, int SG, int KC, int split, long floats) {
+    const TilePlan p = tile_plan(NG, SG, KC, 256, split != 0, (size_t)floats);
+    return p.whole * 100 + p.KS;
+}
+
 }  // extern "C"

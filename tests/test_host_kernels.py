@@ -260,3 +260,31 @@ def test_gate_up_takes_one_row_block_where_the_fullest_unit_has_fewer(host, NB, 
     assert host.host_gate_up_by_one(NB) == one
     by_one, by_two = -(-NB // 256), 2 * -(-(-(-NB // 2)) // 256)
     assert bool(one) == (by_one < by_two)
+
+
+@pytest.mark.parametrize("NG,SG,KS,bs", [(1, 1, 1, 1), (20, 12, 1, 6), (20, 2, 6, 2), (108, 14, 1, 5), (17, 1, 3, 1), (28, 13, 1, 5), (5, 16, 8, 6), (7, 11, 2, 4)])
+def test_tiles_are_taken_once_each(host, NG, SG, KS, bs):
+    grid = (NG * SG * KS + 7) // 8 * 8
+    got = [host.host_tile_at(i, NG, SG, KS, bs) for i in range(grid)]
+    want = sorted(g * 1000000 + s * 1000 + k for g in range(NG) for s in range(SG) for k in range(KS))
+    assert sorted(v for v in got if v >= 0) == want
+    per_xcd = [sum(v >= 0 for v in got[x::8]) for x in range(8)]
+    assert max(per_xcd) <= (len(want) + 7) // 8
+
+
+@pytest.mark.parametrize("NG,SG,KC,plan", [(20, 14, 432, 1206), (20, 14, 160, 1205), (20, 4, 432, 3), (17, 16, 96, 1503), (28, 14, 160, 1401), (20, 8, 160, 801), (20, 3, 432, 301)])
+def test_last_sweeps_are_cut_along_k_where_a_round_would_be_partly_empty(host, NG, SG, KC, plan):
+    host.host_tile_plan.argtypes = [C.c_int] * 4 + [C.c_long]
+    assert host.host_tile_plan(NG, SG, KC, 1, 16 << 20) == plan
+    assert host.host_tile_plan(NG, SG, KC, 0, 16 << 20) == SG * 100 + 1
+
+
+def test_tile_plans_stay_within_the_scratch(host):
+    host.host_tile_plan.argtypes = [C.c_int] * 4 + [C.c_long]
+    for NG in range(1, 70):
+        for SG in range(1, 17):
+            for KC in (32, 64, 160, 257, 480):
+                p = host.host_tile_plan(NG, SG, KC, 1, 16 << 20)
+                whole, KS = p // 100, p % 100
+                assert 0 <= whole <= SG and 1 <= KS <= 8 and (KS == 1) == (whole == SG)
+                assert KS == 1 or (NG * (SG - whole) * 65536 * KS <= 16 << 20 and KC // KS >= 32)
