@@ -597,12 +597,12 @@ constexpr int kSplitKGroups = 4096;                     // arrival counters
 constexpr size_t kSplitKFloats = (size_t)8 << 20;      // partial sums: KS slabs of (padded Np) x 128 floats at most
 constexpr size_t kTileSplitFloats = 2 * kSplitKFloats;  // the same of the long passes' tiles: what the buffer holds
 
-template <int EPI, bool SK, int NW, int RG>
+template <int EPI, bool SK, int NW, int RG, bool ONCE = true>
 bool launch_ls(ead_handle *h, const LinArgs<bf16_t> &a, int grid) {
-    const void *kern = (const void *)k_linear_mfma_ls<EPI, SK, NW, RG>;
+    const void *kern = (const void *)k_linear_mfma_ls<EPI, SK, NW, RG, ONCE>;
     const size_t lds = kLsLdsBytes;
     if (lds > h->lds_per_block || !allow_big_lds(kern, lds)) return false;
-    hipLaunchKernelGGL((k_linear_mfma_ls<EPI, SK, NW, RG>), dim3(grid), dim3((NW + kLsProducers) * 64), lds, h->stream, a);
+    hipLaunchKernelGGL((k_linear_mfma_ls<EPI, SK, NW, RG, ONCE>), dim3(grid), dim3((NW + kLsProducers) * 64), lds, h->stream, a);
     return true;
 }
 
@@ -762,12 +762,14 @@ void launch_mfma(ead_handle *h, int mi, LinArgs<bf16_t> &a, int T) {
         a.sweeps = sw;
         const int grid = sw > 1 ? (ng + 7) / 8 * 8 * sw : ng;
         bool ok = false;
-#define EAD_LS(NW_) do { switch (rg) { case 4: ok = launch_ls<EPI, false, NW_, 4>(h, a, grid); break; case 5: ok = launch_ls<EPI, false, NW_, 5>(h, a, grid); break; \
-                                       case 6: ok = launch_ls<EPI, false, NW_, 6>(h, a, grid); break; case 7: ok = launch_ls<EPI, false, NW_, 7>(h, a, grid); break; \
-                                       default: ok = launch_ls<EPI, false, NW_, 8>(h, a, grid); break; } } while (0)
-        if constexpr (EPI == EPI_SWIGLU) {
-            switch (nt) { case 1: EAD_LS(1); break; case 2: EAD_LS(2); break; case 4: EAD_LS(4); break; case 5: EAD_LS(5); break; case 6: EAD_LS(6); break; case 7: EAD_LS(7); break; default: EAD_LS(8); break; }
-        } else if (nt == 8) EAD_LS(8);
+#define EAD_LS(NW_, ONCE_) do { switch (rg) { case 4: ok = launch_ls<EPI, false, NW_, 4, ONCE_>(h, a, grid); break; case 5: ok = launch_ls<EPI, false, NW_, 5, ONCE_>(h, a, grid); break; \
+                                       case 6: ok = launch_ls<EPI, false, NW_, 6, ONCE_>(h, a, grid); break; case 7: ok = launch_ls<EPI, false, NW_, 7, ONCE_>(h, a, grid); break; \
+                                       default: ok = launch_ls<EPI, false, NW_, 8, ONCE_>(h, a, grid); break; } } while (0)
+        if (sw > 1) EAD_LS(8, false);                  // several sweeps have eight multiplying waves each
+        else if constexpr (EPI == EPI_SWIGLU) {
+            switch (nt) { case 1: EAD_LS(1, true); break; case 2: EAD_LS(2, true); break; case 4: EAD_LS(4, true); break; case 5: EAD_LS(5, true); break;
+                          case 6: EAD_LS(6, true); break; case 7: EAD_LS(7, true); break; default: EAD_LS(8, true); break; }
+        } else if (nt == 8) EAD_LS(8, true);
 #undef EAD_LS
         if (ok) return;
         // the register-ring kernel where LDS does not allow it (eight row blocks a workgroup)

@@ -827,7 +827,9 @@ constexpr size_t kLsLdsBytes = (size_t)kLsDepth * 8 * 1024;
 constexpr int ls_slot_tiles(int rg) { return rg <= 4 ? 4 : 8; }
 constexpr int ls_depth(int rg) { return kLsDepth * 8 / ls_slot_tiles(rg); }
 
-template <int EPI, bool SK, int NW, int RG>
+// ONCE: one sweep, no other workgroup reads this one's weight tiles.  (Compiled in: a fetching wave that chose at every request made passes of several
+// sweeps 7-20 % slower.)
+template <int EPI, bool SK, int NW, int RG, bool ONCE = true>
 __global__ __launch_bounds__((NW + kLsProducers) * 64) void k_linear_mfma_ls(LinArgs<bf16_t> a) {
     static_assert(RG >= 3 && RG <= 8 && NW >= 1 && NW <= 8, "two producer waves share a step's four or eight tile slots");
     constexpr int SLOT = ls_slot_tiles(RG), PL = SLOT / 2, DEPTH = ls_depth(RG);      // tiles per slot, loads per producer wave and step, k steps in the ring
@@ -861,15 +863,11 @@ __global__ __launch_bounds__((NW + kLsProducers) * 64) void k_linear_mfma_ls(Lin
 #pragma unroll
         for (int q = 0; q < PL; ++q)
             wp[q] = a.W + tile_offset(min(g * RG + min(p + 2 * q, RG - 1), NB - 1), kbase, KCfull) + lane * 8;
-        const bool once = SK || a.sweeps <= 1;            // no other workgroup reads these tiles
         auto issue = [&](int j) __attribute__((always_inline)) {      // step j (past the end: the last step again, never read)
             const size_t off = (size_t)kstep(j) * 512;
             bf16_t (*slot)[512] = s_w[j % DEPTH];
 #pragma unroll
-            for (int q = 0; q < PL; ++q) {
-                if (once) request_tile_once(wp[q] + off, &slot[p + 2 * q][0]);
-                else request_tile_kept(wp[q] + off, &slot[p + 2 * q][0]);
-            }
+            for (int q = 0; q < PL; ++q) request_tile_at<ONCE>(wp[q] + off, &slot[p + 2 * q][0]);
         };
         for (int j = 0; j < DEPTH - 1; ++j) issue(j);
         asm volatile("s_waitcnt vmcnt(%0)" ::"n"(PL * (DEPTH - 2)) : "memory");      // step 0 has landed
@@ -1037,7 +1035,7 @@ __global__ __launch_bounds__((NW + kLsProducers) * 64) void k_lm_ls(LinArgs<bf16
         auto issue = [&]() __attribute__((always_inline)) {      // past the range: its last step again, never read
             const size_t off = (size_t)k * 512;
 #pragma unroll
-            for (int q = 0; q < 4; ++q) request_tile_once(wp[q] + off, &s_w[slot][p + 2 * q][0]);
+            for (int q = 0; q < 4; ++q) request_tile_at<true>(wp[q] + off, &s_w[slot][p + 2 * q][0]);
             slot = slot + 1 == kLsDepth ? 0 : slot + 1;
             if (k + 1 < KC) ++k;
             else if (g + 1 < groups) { k = 0; ++g; point(); }
