@@ -564,7 +564,8 @@ def main():
         # entry is timed on the kernel's own model's passes (the other model idle, only this kernel's launches bracketed):
         # while both lanes' queues are busy, event brackets read about 25 us more than the kernel's begin and
         # end stamps in a rocprofv3 trace of the same launches, with one lane they agree to a few microseconds.
-        linear = [r for r in prof if r["name"].startswith("linear_")]
+        # One row: the step as a whole is one kernel, whose bytes are the model's weights and the keys it reads.
+        linear = [r for r in prof if r["name"].startswith(("linear_", "decode_fused"))]
         dom = max(linear or prof, key=lambda r: r["bytes"])["name"]
         which = 1 if dom.endswith("/large") else 0
         d = next(r for r in profiled_run(dom, force=which, grp=False) if r["name"] == dom)

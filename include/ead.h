@@ -294,10 +294,12 @@ ead_status ead_set_sampling(ead_handle *h, float temperature, uint64_t seed);
  * once for many rows.  Outputs per row are the same (up to the rounding differences between
  * passes of different width).  ead_decode(n) then lets every row produce up to n more tokens. */
 ead_status ead_set_schedule(ead_handle *h, int32_t grouped, float start_fraction, float stop_fraction);
-/* Single-row decode steps can run as ONE persistent kernel per step (grid barriers
- * instead of kernel boundaries, weight prefetch across them) instead of the per-layer
- * kernels that wider batches use.  Off by default (on this hardware the per-layer kernels
- * are the faster of the two); on = 1 selects it for the shapes it is built for (the
+/* Single-row decode steps can run as ONE persistent kernel per step (values handed over
+ * through an exchange buffer instead of kernel boundaries, the weight stream running on
+ * across them) instead of the per-layer kernels that wider batches use.  A handle takes it by
+ * itself for runs of one sequence decoded greedily in lock step by a bf16 model where it is
+ * the faster of the two; on = 0 keeps the per-layer kernels always.  on = 1 selects a
+ * persistent kernel for all the shapes one is built for (the
  * per-layer kernels are used regardless for any other shape): for bf16 models the variant
  * whose fetching waves stream the weights through a ring in LDS, for float32 models the
  * one that buffers them in registers; on = 2 selects the register-buffered variant for

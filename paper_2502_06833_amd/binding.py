@@ -285,7 +285,8 @@ class EAD:
 
     def set_fused(self, on):
         """False/0: per-layer kernels; True/1: one persistent kernel per single-row step (the streamed
-        variant where the model has one); 2: the register-buffered persistent kernel even then."""
+        variant where the model has one); 2: the register-buffered persistent kernel even then.  Without a call the
+        streamed kernel is taken where it is the faster."""
         self._check(lib().ead_set_fused(self._h, 2 if on == 2 and on is not True else (1 if on else 0)))
 
     def profile(self, on: bool):

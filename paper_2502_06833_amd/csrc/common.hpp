@@ -153,8 +153,10 @@ constexpr int kWaitLdsReads = 0xC07F;                  // s_waitcnt lgkmcnt(0), 
 // 16 bytes per lane from base + voff (base uniform over the wave) to LDS at lds + 16 lane.  M0 cannot be named as clobbered:
 // the compiler reserves it, keeps no value in it from one instruction to the next and sets it itself right before an
 // instruction of its own that reads it (the kernels that call this have none: LDS reads need no M0 here).
+template <bool ONCE = false>
 __device__ __forceinline__ void request_tile(const bf16_t *base, uint32_t voff, uint32_t lds) {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(voff), "s"(base) : "memory");
+    if constexpr (ONCE) asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt" ::"s"(lds), "v"(voff), "s"(base) : "memory");
+    else asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(voff), "s"(base) : "memory");
 }
 
 // The same through the builtin, from this lane's address; ONCE: a tile that no other workgroup reads is requested non-temporally

@@ -245,7 +245,7 @@ struct Model {
     double weight_bytes_nolm, lm_bytes, kv_bytes_per_pos, n_params;
     void *fused_mats = nullptr, *fused_layers = nullptr; int n_mats = 0; bool fused_ok = false;
     void *arena = nullptr; size_t layer_elems = 0, mat_off[4] = {0, 0, 0, 0};      // packed layer matrices: layer l's j-th at arena + l * layer_elems + mat_off[j]
-    bool stream_ok = false;                                                     // k_decode_stream serves this model
+    bool stream_ok = false; StreamModel stream_model{}; StreamExchange stream_ex{};      // k_decode_stream serves this model: how
     size_t esz() const { return dtype == EAD_BF16 ? 2 : 4; }
 };
 
@@ -289,7 +289,10 @@ struct ead_handle {
     char *h_copy = nullptr; hipEvent_t copy_ev[kCopySlots] = {}; bool copy_ready = false;      // pinned pieces of a long copy (make_copy_slots, copy_out)
     LaneSet lanes[2]; int cur_lane = 0, two_lanes = 0; hipStream_t lane1_stream = nullptr;
     // fused single-row decode
-    float *att_o; float2 *att_ml; unsigned *bar_mem; int *abort_flag; unsigned bar_epoch = 0; int fused_on = 0, fused_grid = 0;
+    float *att_o; float2 *att_ml; unsigned *bar_mem; int *abort_flag; unsigned bar_epoch = 0; int fused_on = -1, fused_grid = 0;      // fused_on: -1 = k_decode_stream where stream_pays, 0 off, 1 on, 2 on with k_decode_fused
+    int device = -1; hipEvent_t turn_ev = nullptr;      // k_decode_stream: see take_turn
+    bool lock_step = false;              // decode_impl's own loop is running (its passes may go to k_decode_stream by themselves)
+    float *exchange = nullptr; int exchange_words = 0, exchange_turn = 0;      // two buffers of exchange_words (k_decode_stream)
     std::vector<void *> allocs;
     std::vector<HostSeq> hs;
     int batch, max_new, began, replay, n_new, force_model, step;
@@ -997,13 +1000,38 @@ void *stream_kernel_for(const Model &m) {
     if (m.hd == 64 && G == 4) return stream_kernel_ptr<64, 4>();
     if (m.hd == 128 && G == 4) return stream_kernel_ptr<128, 4>();
     if (m.hd == 64 && G == 7) return stream_kernel_ptr<64, 7>();
+    if (m.hd == 128 && G == 3) return stream_kernel_ptr<128, 3>();
     if (m.hd == 128 && G == 5) return stream_kernel_ptr<128, 5>();
+    if (m.hd == 128 && G == 6) return stream_kernel_ptr<128, 6>();
     return nullptr;
 }
-size_t stream_lds_bytes(const Model &m) {
-    const size_t kmax = std::max(std::max(m.d, m.F), m.H * m.hd);
-    const size_t attn = (size_t)kFusedWaves * m.hd + 2 * kFusedWaves;
-    return (size_t)kStreamDepth * kStreamSlotBytes + std::max(kmax + 2 * kFusedWaves * 16 + 64, attn) * sizeof(float);
+// columns of activations the streamed kernel's stage holds beside the ring
+size_t stream_stage_cols(const ead_handle *h) {
+    const size_t rest = (size_t)kStreamDepth * kStreamSlotBytes + (2 * kFusedWaves * 16 + 64) * sizeof(float) + 256;
+    return h->lds_per_block > rest ? (h->lds_per_block - rest) / 6 - 8 : 0;      // three half-precision terms a column
+}
+size_t stream_lds_bytes(const StreamModel &sm, const Model &m) {
+    size_t stage = ((size_t)(m.H / m.KV + 1 + kFusedWaves) * m.hd + 2 * kFusedWaves) * sizeof(float);      // the attention phase's
+    for (int j = 0; j < 5; ++j) stage = std::max(stage, ((size_t)sm.m[j].KCs * 32 + 8) * 6);
+    return (size_t)kStreamDepth * kStreamSlotBytes + (2 * kFusedWaves * 16 + 64) * sizeof(float) + ((stage + 15) & ~(size_t)15);
+}
+// The streamed kernel's view of a model and the regions of its exchange; false where a slice does not fit the stage.
+bool stream_model(const ead_handle *h, const Model &m, StreamModel *sm, StreamExchange *ex) {
+    const int NQ = m.H * m.hd, NK = m.KV * m.hd;
+    sm->base = (const bf16_t *)m.arena; sm->layer_stride = m.layer_elems; sm->lm = (const bf16_t *)m.lm_head; sm->L = m.L;
+    const int rows[5] = {NQ + 2 * NK, m.d, 2 * m.F, m.d, m.V}, cols[5] = {m.d, NQ, m.d, m.F, m.d};
+    for (int j = 0; j < 5; ++j) {
+        StreamMat &t = sm->m[j];
+        t.off = j < 4 ? m.mat_off[j] : 0; t.NB = rows[j] / 16; t.KC = cols[j] / 32;
+        const bool cut = j == 0 || j == 1 || j == 3;      // gate/up and the LM head need whole sums
+        const StreamSplit sp = cut ? stream_split(t.NB, t.KC, h->fused_grid, (int)stream_stage_cols(h)) : StreamSplit{1, t.KC};
+        if (!sp.slices || (size_t)sp.tiles * 32 > stream_stage_cols(h) || sp.tiles * 32 > kStreamStage * 4 * kFusedThreads) return false;
+        t.ks_log2 = sp.slices == 4 ? 2 : sp.slices - 1; t.KCs = sp.tiles;
+    }
+    if (std::max(sm->m[2].NB, sm->m[4].NB) < h->fused_grid) return false;      // a workgroup without any unit has nothing to fetch
+    ex->qkv = 0; ex->att = (NQ + 2 * NK) << sm->m[0].ks_log2; ex->ml = ex->att + NQ * kFusedMaxSplits; ex->o = ex->ml + m.H * kFusedMaxSplits * 2;
+    ex->h = ex->o + (m.d << sm->m[1].ks_log2); ex->down = ex->h + m.F; ex->layer_words = ex->down + (m.d << sm->m[3].ks_log2);
+    return true;
 }
 
 size_t fused_lds_bytes(const Model &m) {
@@ -1025,6 +1053,37 @@ FinArgs make_fin(ead_handle *h, int m, bool score) {
     return fa;
 }
 
+// k_decode_stream needs all its workgroups resident, one per compute unit, so two of them must not start side by side: a launch waits for the stream of
+// the handle that launched one last on its device.  (Cooperative launches would see to that as well, but each takes 17 us, and the runtime's queue for them takes
+// one of the few that the streams of two-lane handles are spread over: their passes then ran 9 % slower in a process that had made one.)  Other
+// kernels may hold units for a while, since they end by themselves; another process's k_decode_stream is what the bounded waits are for.  A
+// handle holds the turn only inside ead_decode and its like, which end by waiting for its streams.
+struct StreamTurn { ead_handle *holder; hipStream_t stream; };
+constexpr int kTurnDevices = 64;
+StreamTurn g_turn[kTurnDevices];
+std::mutex g_turn_mutex;
+
+ead_status take_turn(ead_handle *h) {
+    std::lock_guard<std::mutex> lock(g_turn_mutex);
+    StreamTurn &t = g_turn[h->device];
+    if (t.holder && (t.holder != h || t.stream != h->stream)) {
+        HIP_TRY(h, hipEventRecord(h->turn_ev, t.stream));
+        HIP_TRY(h, hipStreamWaitEvent(h->stream, h->turn_ev, 0));
+    }
+    t = StreamTurn{h, h->stream};
+    return EAD_OK;
+}
+// Gives the turn back, once the handle's launches are over.
+void end_turn(ead_handle *h) {
+    if (h->device < 0) return;
+    const auto held = [&] { return g_turn[h->device].holder == h; };
+    { std::lock_guard<std::mutex> lock(g_turn_mutex); if (!held()) return; }
+    (void)hipStreamSynchronize(h->lanes[0].stream);
+    if (h->two_lanes) (void)hipStreamSynchronize(h->lanes[1].stream);
+    std::lock_guard<std::mutex> lock(g_turn_mutex);
+    if (held()) g_turn[h->device] = StreamTurn{};
+}
+
 template <typename WT>
 ead_status fused_step(ead_handle *h, int mi, double keys) {
     Model &m = h->mdl[mi];
@@ -1039,19 +1098,14 @@ ead_status fused_step(ead_handle *h, int mi, double keys) {
     ProfScope ps(h, PK_FUSED, mi, m.weight_bytes_nolm + m.lm_bytes + keys * m.kv_bytes_per_pos);
     if constexpr (std::is_same<WT, bf16_t>::value) {
         if (m.stream_ok && h->fused_on != 2) {
-            StreamModel sm{};
-            const int NQ = m.H * m.hd, NK = m.KV * m.hd;
-            sm.base = (const bf16_t *)m.arena; sm.layer_stride = m.layer_elems; sm.lm = (const bf16_t *)m.lm_head; sm.L = m.L;
-            for (int j = 0; j < 4; ++j) sm.off[j] = m.mat_off[j];
-            sm.NB[0] = (NQ + 2 * NK) / 16; sm.KC[0] = m.d / 32;
-            sm.NB[1] = m.d / 16; sm.KC[1] = NQ / 32;
-            sm.NB[2] = 2 * m.F / 16; sm.KC[2] = m.d / 32;
-            sm.NB[3] = m.d / 16; sm.KC[3] = m.F / 32;
-            sm.NB[4] = m.V / 16; sm.KC[4] = m.d / 32;
-            void *sargs[] = {&a, &sm};
-            HIP_TRY(h, hipLaunchCooperativeKernel(stream_kernel_for(m), dim3(h->fused_grid), dim3(kStreamThreads), sargs,
-                                                  (unsigned)stream_lds_bytes(m), h->stream));
-            h->bar_epoch += 5u * m.L + 1u;
+            StreamExchange ex = m.stream_ex;
+            ex.now = h->exchange + (size_t)h->exchange_turn * h->exchange_words; ex.next = h->exchange + (size_t)(1 - h->exchange_turn) * h->exchange_words;
+            ex.total_words = h->exchange_words;
+            void *sargs[] = {&a, &m.stream_model, &ex};
+            TRY(take_turn(h));
+            HIP_TRY(h, hipLaunchKernel(stream_kernel_for(m), dim3(h->fused_grid), dim3(kStreamThreads), sargs, stream_lds_bytes(m.stream_model, m), h->stream));
+            h->exchange_turn ^= 1;
+            h->bar_epoch += 1u;
             return EAD_OK;
         }
     }
@@ -1216,10 +1270,17 @@ ead_status decode_pass(ead_handle *h, int m, int step, std::vector<char> &emitte
     const int T = host_plan(h, m, h->Tmax, 0, 1, false, step, &n_lm, &ctx_max, &rows, &complete);
     *T_out = T;
     if (T == 0) return EAD_OK;
-    if (T == 1 && n_lm == 1 && h->batch == 1 && h->fused_on && h->mdl[m].fused_ok && !(h->samp_temp > 0.f)) {
+    const Model &md = h->mdl[m];
+    bool fused = T == 1 && n_lm == 1 && h->batch == 1 && !(h->samp_temp > 0.f);
+    if (h->fused_on < 0) fused = fused && h->lock_step && md.stream_ok && stream_pays(md.d, md.KV, md.L, ctx_max);
+    else fused = fused && h->fused_on && ((h->fused_on != 2 && md.stream_ok) || md.fused_ok);
+    if (fused) {
         const double keys = keys_in_pass(h, m, rows);
-        TRY(h->mdl[m].dtype == EAD_BF16 ? fused_step<bf16_t>(h, m, keys) : fused_step<float>(h, m, keys));
-    } else {
+        const ead_status rc = md.dtype == EAD_BF16 ? fused_step<bf16_t>(h, m, keys) : fused_step<float>(h, m, keys);
+        if (rc != EAD_OK && h->fused_on > 0) return rc;
+        if (rc != EAD_OK) { (void)hipGetLastError(); h->fused_on = 0; fused = false; }      // the launch was refused: the kernels per layer
+    }
+    if (!fused) {
         launch_plan(h, m, h->Tmax, 0, 1, false, step, &rows);
         TRY(run_pass(h, m, T, n_lm, ctx_max, false, rows));
         if (n_lm > 0) launch_finalize(h, m, n_lm, false);
@@ -1419,8 +1480,28 @@ ead_status decode_grouped(ead_handle *h, int n_tokens, long budget = -1, int lea
     return EAD_OK;
 }
 
+// The host's mirror as the device has the state, after passes that did nothing.
+ead_status mirror_from_device(ead_handle *h) {
+    const int MB = h->s.max_batch;
+    std::vector<int> v((size_t)2 * MB);
+    const auto take = [&](const int *src, size_t n, auto put) -> ead_status {
+        HIP_TRY(h, hipMemcpy(v.data(), src, n * sizeof(int), hipMemcpyDeviceToHost));
+        for (int b = 0; b < h->batch; ++b) put(h->hs[b], b);
+        return EAD_OK;
+    };
+    TRY(take(h->s.len, MB, [&](HostSeq &q, int b) { q.len = v[b]; }));
+    TRY(take(h->s.kvlen, (size_t)2 * MB, [&](HostSeq &q, int b) { q.kvlen[0] = v[b]; q.kvlen[1] = v[MB + b]; }));
+    TRY(take(h->s.model, MB, [&](HostSeq &q, int b) { q.model = v[b]; }));
+    TRY(take(h->s.c, MB, [&](HostSeq &q, int b) { q.c = v[b]; }));
+    TRY(take(h->s.ngen, MB, [&](HostSeq &q, int b) { q.ngen = v[b]; }));
+    TRY(take(h->s.done, MB, [&](HostSeq &q, int b) { q.done = v[b]; }));
+    return take(h->s.last_step, MB, [&](HostSeq &q, int b) { q.last_step = v[b]; });
+}
+
 ead_status decode_impl(ead_handle *h, int n_steps, long budget = -1, int lead = 0) {
     if (!h->began) return fail(h, EAD_ERR_STATE, "ead_decode before ead_begin");
+    const int steps_asked = n_steps, ngen_before = h->hs[0].ngen;
+    struct Leave { ead_handle *h; ~Leave() { h->lock_step = false; end_turn(h); } } leave{h};      // however the call ends
     use_lane(h, 0);
     hipStream_t st = h->stream;
     std::vector<char> emitted(h->batch);
@@ -1429,6 +1510,7 @@ ead_status decode_impl(ead_handle *h, int n_steps, long budget = -1, int lead = 
         n_steps = 0;
     }
     bool used_prev[2] = {false, false};
+    h->lock_step = true;
     for (int it = 0; it < n_steps; ++it) {
         const int step = h->step;
         std::fill(emitted.begin(), emitted.end(), 0);
@@ -1467,11 +1549,16 @@ ead_status decode_impl(ead_handle *h, int n_steps, long budget = -1, int lead = 
     HIP_TRY(h, hipStreamSynchronize(st));
     const int err = h->h_status[0], aborted = h->h_status[1];
     if (aborted) {
-        // a grid barrier gave up: drop the fused path for this handle and start its counters afresh
-        h->fused_on = 0; h->bar_epoch = 0; h->began = 0;
+        // a wait inside a persistent kernel was given up (its workgroups were not all resident): drop the fused path for this handle and start its counters afresh
+        const bool asked = h->fused_on > 0;
+        h->fused_on = 0; h->bar_epoch = 0;
         HIP_TRY(h, hipMemset(h->bar_mem, 0, (kBarGroups * 32 + 32) * sizeof(unsigned)));
         HIP_TRY(h, hipMemset(h->abort_flag, 0, sizeof(int)));
-        return fail(h, EAD_ERR_DEVICE, "fused decode kernel abandoned a grid barrier; fused path disabled, run again");
+        if (h->exchange) HIP_TRY(h, hipMemset(h->exchange, 0xFF, (size_t)2 * h->exchange_words * sizeof(float)));
+        if (asked) { h->began = 0; return fail(h, EAD_ERR_DEVICE, "fused decode kernel abandoned a grid barrier; fused path disabled, run again"); }
+        // taken by itself: the launches since then have left the state alone, the kernels per layer go on from there
+        TRY(mirror_from_device(h));
+        return decode_impl(h, steps_asked - (h->hs[0].ngen - ngen_before));
     }
     if (err) return fail(h, EAD_ERR_NONFINITE, "a non-finite entropy was produced (non-finite logits)");
     return EAD_OK;
@@ -1768,6 +1855,7 @@ void ead_destroy(ead_handle *h) {
     if (h->h_fetch) (void)hipHostFree(h->h_fetch);
     if (h->h_copy) (void)hipHostFree(h->h_copy);
     for (hipEvent_t e : h->copy_ev) if (e) (void)hipEventDestroy(e);
+    if (h->turn_ev) (void)hipEventDestroy(h->turn_ev);
     prof_collect(h);
     for (hipEvent_t e : h->ev_pool) (void)hipEventDestroy(e);
     delete h;
@@ -1876,6 +1964,7 @@ ead_status ead_create(const ead_model_desc *small_model, const ead_model_desc *l
             HIP_TRY(h, hipMemsetAsync(h->abort_flag, 0, sizeof(int), h->stream));
             int dev = 0; hipDeviceProp_t prop;
             HIP_TRY(h, hipGetDevice(&dev)); HIP_TRY(h, hipGetDeviceProperties(&prop, dev));
+            if (dev < kTurnDevices) { h->device = dev; HIP_TRY(h, hipEventCreateWithFlags(&h->turn_ev, hipEventDisableTiming)); }
             h->fused_grid = std::min(256, prop.multiProcessorCount);
             h->n_cu = prop.multiProcessorCount;
             h->lds_per_block = std::max<size_t>(prop.sharedMemPerBlock, prop.sharedMemPerBlockOptin);
@@ -1889,10 +1978,17 @@ ead_status ead_create(const ead_model_desc *small_model, const ead_model_desc *l
                               per_cu >= 1 && md.KV * kFusedMaxSplits <= h->fused_grid;
                 void *sfn = stream_kernel_for(md);
                 per_cu = 0;
-                md.stream_ok = md.fused_ok && sfn && stream_lds_bytes(md) <= h->lds_per_block &&
-                               hipFuncSetAttribute(sfn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)stream_lds_bytes(md)) == hipSuccess &&
-                               hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, sfn, kStreamThreads, stream_lds_bytes(md)) == hipSuccess &&
-                               per_cu >= 1;
+                md.stream_ok = sfn && h->turn_ev && md.d <= kStreamMaxWidth && md.KV * kFusedMaxSplits <= h->fused_grid &&
+                               stream_model(h, md, &md.stream_model, &md.stream_ex);
+                const size_t slds = md.stream_ok ? stream_lds_bytes(md.stream_model, md) : 0;
+                md.stream_ok = md.stream_ok && slds <= h->lds_per_block &&
+                               hipFuncSetAttribute(sfn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)slds) == hipSuccess &&
+                               hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, sfn, kStreamThreads, slds) == hipSuccess && per_cu >= 1;
+                if (md.stream_ok) h->exchange_words = std::max(h->exchange_words, md.stream_ex.layer_words * md.L);
+            }
+            if (h->exchange_words) {
+                TRY(dmalloc(h, &h->exchange, (size_t)2 * h->exchange_words));
+                HIP_TRY(h, hipMemsetAsync(h->exchange, 0xFF, (size_t)2 * h->exchange_words * sizeof(float), h->stream));
             }
         }
         HIP_TRY(h, hipHostMalloc((void **)&h->h_model, std::max<size_t>((size_t)MB * MS, 64) * sizeof(int), hipHostMallocDefault));

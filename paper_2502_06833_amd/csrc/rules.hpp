@@ -247,4 +247,30 @@ inline TilePlan tile_plan(int NG, int SG, int KC, int n_cu, bool may_split, size
     return best;
 }
 
+// How k_decode_stream cuts a matrix of NB row blocks x KC tiles into units of one row block x one of `slices` parts of K for G workgroups:
+// the fewest slots of eight tiles for the workgroup that has most (a slot is 0.33 us at the stream's rate), where a slice more
+// is one more vector of sums for every workgroup to read (0.2 us).  `most`: columns of a slice that fit the stage.
+struct StreamSplit { int slices, tiles; };      // slices of K, tiles of each but a shorter last
+inline StreamSplit stream_split(int NB, int KC, int G, int most) {
+    StreamSplit best{0, 0};
+    float cost = 0.f;
+    for (int s = 1; s <= 4; s *= 2) {
+        if (G % s || KC < 8 * s) continue;
+        const int tiles = s == 1 ? KC : ((KC + s - 1) / s + 7) / 8 * 8;
+        if (tiles * (s - 1) >= KC || tiles * 32 > most) continue;
+        const int rounds = (NB + G / s - 1) / (G / s);
+        const float c = 0.33f * (float)(rounds * ((tiles + 7) / 8)) + 0.2f * (float)s;
+        if (best.slices == 0 || c < cost) { best = StreamSplit{s, tiles}; cost = c; }
+    }
+    return best;
+}
+
+// Whether a step of one row goes to k_decode_stream: what a layer gains has to pay for the way in and the barrier at the end, 3-18 us a step.
+// Measured, us a layer at 330 keys with the kernels per layer / this way: d 896 28.0 / 24.8, 1536 44.0 / 35.9, 2048 42.3 / 35.6, 3072 56.1 / 47.2, 4096 90.9 / 83.5, 5120 114.4 /
+// 100.0; at 1200 keys, which eight workgroups per KV head share, 28.9 / 28.2 and 44.3 / 42.9 (two KV heads), 43.9 / 37.6, 58.1 / 50.9, 93.7 / 87.6, 117.1 / 106.1 (eight).
+inline bool stream_pays(int d, int KV, int layers, int keys) {
+    const float gain = (d <= 1024 ? 2.5f : 6.f) - (KV >= 8 ? 0.0015f : 0.006f) * (float)std::max(0, keys - 330);
+    return keys <= 2048 && gain * (float)layers > 20.f;
+}
+
 }  // namespace ead

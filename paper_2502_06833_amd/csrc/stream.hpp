@@ -1,67 +1,89 @@
 // One decode step of one model for a single token row as ONE persistent kernel whose weight
-// stream never stops: the bf16 variant of the fused step for the large shapes.
+// stream never stops: bf16 models.
 //
 // A workgroup is eight consuming waves and two fetching waves.  The fetching waves walk, in
 // order, every weight tile their workgroup will need during the whole step (all layers, then
 // the LM head) and load it straight from global memory into a ring of 8 KB slots in LDS
 // (global_load_lds, 16 bytes per lane); they hold no data in registers and never look at
-// LDS, so nothing but the ring's capacity ever stops them.  While the consuming waves sit in a
-// grid barrier, stage the next phase's activations or run the attention phase, the ring fills
-// with the next matrix (about 4 us of stream at the chip's full rate), and the first row
-// block of a phase is multiplied out of LDS the moment its activations are staged.
+// LDS, so nothing but the ring's capacity ever stops them.  While the consuming waves wait for
+// the other workgroups or run the attention phase, the ring fills with the next matrix, and the first
+// units of a phase are multiplied out of LDS the moment their activations are there.
 //
 // A slot is 8 consecutive tiles of one 16-row block (one per consuming wave: wave w of slot t
 // multiplies tile 8 t + w).  Hand-over is ONE hardware barrier per slot: the fetching waves
 // arrive when slot i has landed, the consuming waves when they have read slot i - 1; behind it
 // the consumers read slot i and the fetchers refill the ring position of slot i - 1.  The
-// consuming waves also meet at the hardware barrier for their own reasons (staging, reductions,
-// grid barriers); the fetching waves cannot look at LDS without stalling their loads (measured: a
+// consuming waves also meet at the hardware barrier for their own reasons (staging, reductions);
+// the fetching waves cannot look at LDS without stalling their loads (measured: a
 // fetching wave that polls a counter in LDS between its loads streams at 3.8 instead of 6.3 TB/s over
 // the chip), so they learn nothing from memory: they replay the fixed sequence of those meetings
 // and arrive at each.  Should the consuming waves
-// leave early (an abandoned grid barrier), the hardware barrier counts only the surviving waves
+// leave early (a wait that was given up), the hardware barrier counts only the surviving waves
 // and the fetching waves run their list to its end.
 //
-// Work split inside a phase is the same as in k_decode_fused: a workgroup owns 16-row blocks
-// wg, wg+G, ... and its waves split K (interleaved by tile); partial sums meet in LDS and one
-// wave, taking turns, finishes the row block after the next slot's barrier.
+// Work split of a phase: units of one 16-row block x one of KS slices of K (stream_split), unit by unit over the
+// workgroups; a workgroup's units are all of one slice, so it stages that slice of the activations only.  A unit's
+// sums leave as they are; whoever stages the next phase adds the slices in order, and the residual stream, which all
+// workgroups add up alike, never leaves their registers.
+//
+// What one workgroup hands to another goes through an exchange buffer that holds a pattern no published value has
+// (kEmptyWord) until the value is there: a reader asks for the words themselves until none of them is empty.  That is one
+// trip to memory and one back, 2.0 us for 2048 words read by each of 256 workgroups and 2.9 for 8192, where a grid barrier
+// and the reads behind it take 3.2 and 4.6.  Every word is written once per launch; two buffers take turns, and a launch
+// empties the one that the next will use.
+//
+// What bounds it (Llama 1B shape, 330 keys, us of a 36 us layer; 19 of weights at 6.4 TB/s): gate/up and down run at the stream's rate (8.5 and 4.5 of what the ring
+// does not hold yet); a hand-over takes 2.3-3.4 of which the ring absorbs the part that it is not full; attention 5 and the hand-overs around it, during which the
+// ring is full and nothing streams, are the rest.  Before, per layer: grid barriers, staging behind them and FMAs 43 us; the kernels per layer 42.
+// Steps that led there, us a layer: exchange 43, fetching waves' position in scalar registers 37.5, non-temporal tiles and matrix-core products 37.8 (the
+// LM head 525 MB 78 -> 72), lane-move reductions 35.6.
 #pragma once
 #include "fused.hpp"
 
 namespace ead {
 
-constexpr int kStreamDepth = 12;                 // ring slots
+constexpr int kStreamDepth = 14;                 // ring slots
 constexpr int kStreamSlotBytes = 8192;           // 8 tiles of 1 KB
 constexpr int kStreamProducers = 2;
 constexpr int kStreamLoads = kFusedWaves / kStreamProducers;   // tile loads per fetching wave and slot
 constexpr int kStreamThreads = (kFusedWaves + kStreamProducers) * 64;
 static_assert(kStreamLoads * (kStreamDepth - 1) <= 63, "outstanding loads must fit the vector memory counter");
+constexpr int kStreamPieces = 3;                 // float4 pieces of the residual stream per thread
+constexpr int kStreamMaxWidth = kStreamPieces * 4 * kFusedThreads;      // d_model this kernel serves
+constexpr int kStreamMaxSlices = 4;              // slices of K a matrix may be cut into
+constexpr int kStreamStage = 8;                  // float4 pieces of any other vector a thread stages at once
 
-// Where a model's packed weights are: matrix j (0 QKV, 1 output projection, 2 gate/up, 3 down)
-// of layer l starts at base + l * layer_stride + off[j] (elements); index 4 is the LM head.
+// How a matrix is split: row blocks, tiles of a row block, slices of K (a power of two) and tiles of a slice (the last may be shorter).
+struct StreamMat { size_t off; int NB, KC, ks_log2, KCs; };
+// Where a model's packed weights are: matrix j (0 QKV, 1 output projection, 2 gate/up, 3 down) of layer l starts at
+// base + l * layer_stride + m[j].off (elements); m[4] is the LM head, at lm.
 struct StreamModel {
-    const bf16_t *base; size_t layer_stride; size_t off[4];
-    const bf16_t *lm;
-    int NB[5], KC[5];
+    const bf16_t *base, *lm; size_t layer_stride;
+    StreamMat m[5];
     int L;
 };
 
-// Slots the workgroup `wg` of `G` takes during a step: both sides of the ring count the same.
-__device__ __forceinline__ long stream_steps(const StreamModel &sm, int wg, int G) {
-    long n = 0;
-#pragma unroll
-    for (int j = 0; j < 5; ++j) {
-        if (wg >= sm.NB[j]) continue;
-        const long blocks = (sm.NB[j] - wg + G - 1) / G, nt = (sm.KC[j] + 7) >> 3;
-        n += blocks * nt * (j < 4 ? sm.L : 1);
-    }
-    return n;
+// The exchange buffer of a launch and the one to be emptied for the next: regions of a layer, in words.
+struct StreamExchange {
+    float *now, *next;
+    int layer_words, total_words;            // of this model's layers; of both buffers as a whole
+    int qkv, att, ml, o, h, down;            // region offsets inside a layer
+};
+
+// A workgroup's share of a matrix: which slice, how many row blocks, from which one on, how far apart; the slice's tiles.
+struct StreamShare { int slice, rb0, step, n, kc0, kcn; };
+__device__ __forceinline__ StreamShare stream_share(const StreamMat &m, int wg, int G) {
+    StreamShare s;
+    s.step = G >> m.ks_log2; s.slice = wg & ((1 << m.ks_log2) - 1); s.rb0 = wg >> m.ks_log2;
+    s.n = s.rb0 < min(s.step, m.NB) ? (m.NB - s.rb0 + s.step - 1) / s.step : 0;
+    s.kc0 = s.slice * m.KCs; s.kcn = min(m.KCs, m.KC - s.kc0);
+    return s;
 }
 
-// The fetching waves' position in the list of slots of their workgroup: matrix (layer l, kind j),
-// row block, slot.  Every member is the same in all lanes and lives in scalar registers: the
-// description is copied out of the kernel arguments once, so that the loop around the loads
-// touches no memory but the weights.
+// The fetching waves' position in the list of slots of their workgroup.  Everything is the same in all lanes and
+// lives in scalar registers; the matrices' descriptions come from the kernel arguments by scalar loads, so that the loop
+// around the tile loads touches no vector memory but the weights.  (An array of descriptions that the compiler put into
+// scratch memory cost a wait for all outstanding loads at every matrix.)
 __device__ __forceinline__ int uni(int v) { return __builtin_amdgcn_readfirstlane(v); }
 __device__ __forceinline__ size_t uni(size_t v) {
     const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)v);
@@ -69,315 +91,573 @@ __device__ __forceinline__ size_t uni(size_t v) {
     return ((size_t)hi << 32) | (size_t)lo;
 }
 struct StreamList {
-    // the model
-    size_t base, lm, stride, off0, off1, off2, off3;        // addresses in bytes
-    int nb0, nb1, nb2, nb3, nb4, kc0, kc1, kc2, kc3, kc4, L, wg, G;
-    // the position
-    int l, j, rb, t, NB, KC, nt;
-    size_t W;                                               // current matrix, byte address
-    bool done;
-    __device__ __forceinline__ explicit StreamList(const StreamModel &sm) {
-        base = uni((size_t)sm.base); lm = uni((size_t)sm.lm); stride = uni(sm.layer_stride * sizeof(bf16_t));
-        off0 = uni(sm.off[0] * sizeof(bf16_t)); off1 = uni(sm.off[1] * sizeof(bf16_t));
-        off2 = uni(sm.off[2] * sizeof(bf16_t)); off3 = uni(sm.off[3] * sizeof(bf16_t));
-        nb0 = uni(sm.NB[0]); nb1 = uni(sm.NB[1]); nb2 = uni(sm.NB[2]); nb3 = uni(sm.NB[3]); nb4 = uni(sm.NB[4]);
-        kc0 = uni(sm.KC[0]); kc1 = uni(sm.KC[1]); kc2 = uni(sm.KC[2]); kc3 = uni(sm.KC[3]); kc4 = uni(sm.KC[4]);
-        L = uni(sm.L); wg = uni((int)blockIdx.x); G = uni((int)gridDim.x);
-        l = 0; j = 0; rb = 0; t = 0; NB = 0; KC = 1; nt = 1; W = 0; done = false;
-    }
-    __device__ __forceinline__ int nb_of(int jj) const { return jj == 0 ? nb0 : jj == 1 ? nb1 : jj == 2 ? nb2 : jj == 3 ? nb3 : nb4; }
-    __device__ __forceinline__ int kc_of(int jj) const { return jj == 0 ? kc0 : jj == 1 ? kc1 : jj == 2 ? kc2 : jj == 3 ? kc3 : kc4; }
-    // first matrix from (ll, jj) on in which this workgroup owns a row block; false if none is left
-    __device__ __forceinline__ bool find(int &ll, int &jj) const {
-        for (;;) {
-            if (wg < nb_of(jj)) return true;
-            if (jj == 4) return false;
-            if (++jj == 4) { jj = 0; if (++ll == L) jj = 4; }
+    int l, j, units;                 // layer, matrix, units of it still to come (this one included)
+    int left, kcn;                   // tiles of this unit from the current slot on; of a whole unit
+    size_t cur, unit, step;          // byte addresses: the slot's first tile, the unit's; distance of two units
+    // to the first unit of matrix jj of layer ll or, where the workgroup has none there, of the next one that has
+    __device__ __forceinline__ void enter(const StreamModel &sm, int ll, int jj, int wg, int G) {
+        for (;; ++jj) {
+            if (jj == 4 && ll < sm.L - 1) { jj = 0; ++ll; }
+            if (jj > 4) { left = 0x7FFFFFFF; units = 1; return; }           // past the end: the position stays on the last slot
+            const StreamShare s = stream_share(sm.m[jj], wg, G);
+            if (s.n == 0) continue;
+            l = ll; j = jj; units = s.n; left = kcn = s.kcn;
+            const size_t first = (size_t)(jj == 4 ? sm.lm : sm.base + (size_t)ll * sm.layer_stride + sm.m[jj].off);
+            unit = cur = uni(first + ((size_t)s.rb0 * sm.m[jj].KC + s.kc0) * 1024);
+            step = (size_t)s.step * sm.m[jj].KC * 1024;
+            return;
         }
     }
-    __device__ __forceinline__ void enter(int ll, int jj) {
-        l = ll; j = jj; NB = nb_of(jj); KC = kc_of(jj); nt = (KC + 7) >> 3; rb = wg; t = 0;
-        const size_t off = jj == 0 ? off0 : jj == 1 ? off1 : jj == 2 ? off2 : off3;
-        W = jj == 4 ? lm : base + (size_t)ll * stride + off;
-    }
-    __device__ __forceinline__ void open() { int ll = 0, jj = 0; if (find(ll, jj)) enter(ll, jj); else done = true; }
-    // to the next slot; past the end of the list the position stays on the last slot
-    __device__ __forceinline__ void next() {
-        if (done) return;
-        if (t + 1 < nt) { ++t; return; }
-        if (rb + G < NB) { rb += G; t = 0; return; }
-        if (j == 4) { done = true; return; }
-        int ll = l, jj = j;
-        if (++jj == 4) { jj = 0; if (++ll == L) jj = 4; }
-        if (find(ll, jj)) enter(ll, jj); else done = true;
+    __device__ __forceinline__ void next(const StreamModel &sm, int wg, int G) {
+        if (left == 0x7FFFFFFF) return;
+        left -= kFusedWaves;
+        if (left > 0) { cur += kStreamSlotBytes; return; }
+        if (--units > 0) { unit += step; cur = unit; left = kcn; return; }
+        enter(sm, l, j + 1, wg, G);
     }
 };
 
 typedef u32x4_t StreamRing[kFusedWaves][64];
 
-// Request this fetching wave's tiles of the slot at the list position into `slot`, then move on.
-// Tiles past the end of a row block re-read its last tile (they meet zeros in the multiply), so
-// that every slot is the same number of loads and the wait counts stay fixed.
-__device__ __forceinline__ void stream_issue(StreamList &pos, StreamRing &slot, int p, int lane) {
-    const size_t row = pos.W + ((size_t)pos.rb * (size_t)pos.KC) * 1024 + (size_t)lane * 16;
+// Request this fetching wave's tiles of the slot at the list position into the ring slot at LDS address `lds`.  Tiles past the
+// end of a unit re-read its last tile (they meet zeros in the multiply), so that every slot is the same number of loads and the
+// wait counts stay fixed.
+__device__ __forceinline__ void stream_issue(const StreamList &pos, uint32_t lds, int p, int lane) {
+    const bf16_t *base = reinterpret_cast<const bf16_t *>(uni(pos.cur));
+    const int last = min(uni(pos.left), kFusedWaves) - 1;
 #pragma unroll
     for (int q = 0; q < kStreamLoads; ++q) {
         const int tile = p + kStreamProducers * q;
-        const int kc = min(pos.t * kFusedWaves + tile, pos.KC - 1);
-        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(row + (size_t)kc * 1024),
-                                         (__attribute__((address_space(3))) void *)&slot[tile][0], 16, 0, 0);
+        request_tile<true>(base, (uint32_t)(min(tile, last) * 1024 + lane * 16), (uint32_t)uni((int)(lds + tile * 1024)));
     }
-    pos.next();
 }
 
 // ---- hardware barriers ---------------------------------------------------------------------------
 // Every barrier of the workgroup is the hardware barrier and takes all ten waves.  The consuming
-// waves meet at it for their own reasons too (staging, reductions, grid barriers): the number of
+// waves meet at it for their own reasons too (staging, reductions): the number of
 // such meetings per phase is fixed by the code below (kSync*), and the fetching waves, which have
 // nothing to do there, simply arrive as many times (follow).
-constexpr int kSyncGridBarrier = 2;      // bar_arrive + bar_wait
-constexpr int kSyncStageNorm = 2;        // stage_norm_v / stage_norm_embed
-constexpr int kSyncStageCopy = 1;        // stage_copy_v
-constexpr int kSyncStageAttn = 1;        // stage_attn_v
-constexpr int kSyncAttention = 1;        // fused_attention (or the lone barrier of a workgroup without a share)
-constexpr int kSyncRowsEnd = 1;          // stream_rows, when the workgroup owned a row block
+constexpr int kSyncStage = 2;            // any of the staging routines
+constexpr int kSyncAttention = 3;        // stream_attention, or as many lone barriers of a workgroup without a share
+constexpr int kSyncRowsEnd = 1;          // stream_rows, when the workgroup owned a unit
+constexpr int kSyncGridBarrier = 2;      // bar_arrive + bar_wait, once, at the end
 
 __device__ __forceinline__ void follow(int n) {
     for (int i = 0; i < n; ++i) asm volatile("s_barrier" ::: "memory");
 }
 
-// ---- device-coherent vector loads ---------------------------------------------------------------
-// What other workgroups wrote during this kernel is read around the caches (see ld_coherent); these
-// fetch 16 or 8 bytes per lane.  The loads are issued through asm, so the compiler does not know
-// when their results arrive: the caller passes every result through coherent_wait before using it.
-__device__ __forceinline__ f32x4e_t ld_coherent4_issue(const float *p) {
-    f32x4e_t v;
-    asm volatile("global_load_dwordx4 %0, %1, off sc1" : "=v"(v) : "v"(p) : "memory");
-    return v;
-}
-typedef float f32x2e_t __attribute__((ext_vector_type(2)));
-__device__ __forceinline__ f32x2e_t ld_coherent2_issue(const float2 *p) {
-    f32x2e_t v;
-    asm volatile("global_load_dwordx2 %0, %1, off sc1" : "=v"(v) : "v"(p) : "memory");
-    return v;
-}
-template <int N>
-__device__ __forceinline__ void coherent_wait(f32x4e_t (&v)[N]) {
-    static_assert(N == 8, "one wait statement names all its registers");
-    asm volatile("s_waitcnt vmcnt(0)"
-                 : "+v"(v[0]), "+v"(v[1]), "+v"(v[2]), "+v"(v[3]), "+v"(v[4]), "+v"(v[5]), "+v"(v[6]), "+v"(v[7])
-                 :: "memory");
+// ---- the exchange ----------------------------------------------------------------------------------
+constexpr uint32_t kEmptyWord = 0xFFFFFFFFu;      // a NaN: a published NaN of this pattern goes out as another one
+
+__device__ __forceinline__ void publish(float *p, float v) {
+    const uint32_t w = __float_as_uint(v);
+    __hip_atomic_store(reinterpret_cast<uint32_t *>(p), w == kEmptyWord ? 0x7FC00000u : w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-constexpr int kStageVecs = 8;            // 16-byte pieces per thread: K <= 8 * 4 * 512
-
-// The staging routines run once per phase inside the kernel's long loop over phases, on the same
-// buffers every time.  Passing a pointer through this keeps the per-thread addresses derived from it
-// inside the phase (computed where they are used) instead of alive, in registers or spilled, across
-// the whole loop.
-template <typename T> __device__ __forceinline__ const T *fresh(const T *p) {
-    int zero = 0;
-    asm volatile("" : "+v"(zero));      // opaque: the sum below cannot be computed ahead of the phase
-    return p + zero;
+constexpr int kCoherentLoad = 16 | (int)0x80000000;      // cache policy of the buffer loads: served past the XCD's L2 (sc1), volatile
+typedef __amdgpu_buffer_rsrc_t StreamRsrc;
+__device__ __forceinline__ StreamRsrc exchange_rsrc(float *base, int words) {
+    return __builtin_amdgcn_make_buffer_rsrc((void *)base, 0, words * 4, 0x00020000);
 }
 
-// RMSNorm of a vector other workgroups wrote, into LDS (K a multiple of 4)
-__device__ __forceinline__ void stage_norm_v(float *xs, float *s_red, const float *src, int K, const float *gain, float eps) {
-    const int tid = threadIdx.x;
-    src = fresh(src); gain = fresh(gain);
-    f32x4e_t v[kStageVecs], gn[kStageVecs];
+// Waits until the pieces of 16 bytes at byte offsets voff[i] (those that `present` names; a lane that needs none passes an offset another lane
+// reads) of the region at `soff` are all published, and returns them.  False: given up, and nothing may be done with the values.
+template <int N, typename Present>
+__device__ __forceinline__ bool collect(StreamRsrc rsrc, int soff, const int (&voff)[N], Present present, u32x4_t (&v)[N], const int *abort_flag) {
+    for (int spins = 0;; ++spins) {
 #pragma unroll
-    for (int i = 0; i < kStageVecs; ++i) {
-        const int k = (tid + i * kFusedThreads) * 4;
-        // unconditional (a piece past the end re-reads the last one and is zeroed after the wait): nothing
-        // but the wait may touch a result register before its load has landed
-        v[i] = ld_coherent4_issue(src + min(k, K - 4));
-        gn[i] = *(gptr<f32x4e_t>)(gain + min(k, K - 4));
+        for (int i = 0; i < N; ++i)
+            if (present(i)) v[i] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, voff[i], soff, kCoherentLoad);
+        bool full = true;
+#pragma unroll
+        for (int i = 0; i < N; ++i)
+            if (present(i)) full = full && v[i].x != kEmptyWord && v[i].y != kEmptyWord && v[i].z != kEmptyWord && v[i].w != kEmptyWord;
+        if (__all(full)) return true;
+        if ((spins & 1023) == 1023 && (spins >= (int)kFusedSpinLimit || ld_coherent(abort_flag))) return false;
+        asm volatile("" ::: "memory");
     }
-    coherent_wait(v);
+}
+
+__device__ __forceinline__ f32x4e_t as_floats(u32x4_t w) { return __builtin_bit_cast(f32x4e_t, w); }
+
+// ---- reductions by lane moves inside a row of sixteen (no trip through LDS, which every phase would wait for several times) ----
+template <int CTRL> __device__ __forceinline__ float moved(float v) { return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, true)); }
+constexpr int kXor1 = 0xB1, kXor2 = 0x4E, kMirror8 = 0x141, kMirror16 = 0x140;
+// the sum over groups of N neighbouring lanes, in all of them
+template <int N> __device__ __forceinline__ float lanes_sum(float v) {
+    static_assert(N == 4 || N == 8 || N == 16, "a row of sixteen lanes at most");
+    v += moved<kXor1>(v); v += moved<kXor2>(v);
+    if constexpr (N >= 8) v += moved<kMirror8>(v);
+    if constexpr (N >= 16) v += moved<kMirror16>(v);
+    return v;
+}
+__device__ __forceinline__ float lane_value(float v, int l) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l)); }
+__device__ __forceinline__ float rows_sum(float v) {
+    v = lanes_sum<16>(v);
+    return (lane_value(v, 0) + lane_value(v, 16)) + (lane_value(v, 32) + lane_value(v, 48));
+}
+__device__ __forceinline__ float rows_max(float v) {
+    v = fmaxf(v, moved<kXor1>(v)); v = fmaxf(v, moved<kXor2>(v)); v = fmaxf(v, moved<kMirror8>(v)); v = fmaxf(v, moved<kMirror16>(v));
+    return fmaxf(fmaxf(lane_value(v, 0), lane_value(v, 16)), fmaxf(lane_value(v, 32), lane_value(v, 48)));
+}
+
+// ---- staging -----------------------------------------------------------------------------------------
+// The work-item's number, opaque: what these routines derive from it is computed where it is used and not kept, in
+// registers or spilled, across the loop over the layers that calls them on the same regions every time.
+__device__ __forceinline__ int fresh_tid() {
+    int t = threadIdx.x;
+    asm volatile("" : "+v"(t));
+    return t;
+}
+// Thread t of the consuming waves keeps elements (t + i * 512) * 4 .. + 3 of the residual stream in x[i].
+
+// x += the KS slices' sums of `n` rows that lie one behind the other at word `off`
+__device__ __forceinline__ bool add_sums(f32x4e_t (&x)[kStreamPieces], StreamRsrc rsrc, int off, int n, int KS, const int *abort_flag) {
+    constexpr int NS = kStreamMaxSlices;
+    const int tid = fresh_tid();
+    int voff[kStreamPieces * NS];
+    u32x4_t v[kStreamPieces * NS];
 #pragma unroll
-    for (int i = 0; i < kStageVecs; ++i)
-        if ((tid + i * kFusedThreads) * 4 >= K) v[i] = f32x4e_t{0.f, 0.f, 0.f, 0.f};
-    float ss = 0.f;
+    for (int i = 0; i < kStreamPieces; ++i)
 #pragma unroll
-    for (int i = 0; i < kStageVecs; ++i) ss += v[i].x * v[i].x + v[i].y * v[i].y + v[i].z * v[i].z + v[i].w * v[i].w;
-    ss = wave_sum(ss);
-    if ((tid & 63) == 0) s_red[tid >> 6] = ss;
+        for (int s = 0; s < NS; ++s) voff[i * NS + s] = (s * n + min((tid + i * kFusedThreads) * 4, n - 4)) * 4;
+    if (!collect(rsrc, off * 4, voff, [&](int j) { return j % NS < KS && j / NS * 4 * kFusedThreads < n; }, v, abort_flag)) return false;
+#pragma unroll
+    for (int i = 0; i < kStreamPieces; ++i)
+#pragma unroll
+        for (int s = 0; s < NS; ++s)
+            if (s < KS && (tid + i * kFusedThreads) * 4 < n) x[i] += as_floats(v[i * NS + s]);
+    return true;
+}
+
+// ---- activations as half-precision terms ---------------------------------------------------------------
+// The products run on the matrix cores, whose sixteen columns a single row leaves idle: three of them take the activations'
+// terms, v = hi + mid / 2^11 + lo / 2^22 with halves hi, mid, lo of 11 bits each, which hold a float32's 24 bits.  The vector is
+// first scaled by the power of two that brings its largest magnitude to 2^14 .. 2^15, so that no term overflows
+// and elements 2^-29 of the largest still keep all their bits.  (With FMAs on float32 activations a slot cost 300 ns, of which half was
+// arithmetic and a third reading the activations.)
+struct StreamScale { float up, down; };
+__device__ __forceinline__ StreamScale scale_for(float largest) {
+    int e = (int)((__float_as_uint(largest) >> 23) & 255u);
+    e = e == 255 ? 141 : max(e, 15);                       // not finite: as it is; tiny or zero: by 2^126
+    return StreamScale{__uint_as_float((uint32_t)(268 - e) << 23), __uint_as_float((uint32_t)(e - 14) << 23)};
+}
+__device__ __forceinline__ float largest_of(f32x4e_t v) { return fmaxf(fmaxf(fabsf(v.x), fabsf(v.y)), fmaxf(fabsf(v.z), fabsf(v.w))); }
+
+// Where the terms of a slice lie in LDS: term m of column k at xt[m * stride + k].
+struct StreamTerms { uint16_t *xt; int stride; };
+__device__ __forceinline__ void put_terms(const StreamTerms &x, int k, f32x4e_t v) {
+    typedef _Float16 f16x4_t __attribute__((ext_vector_type(4)));
+    const f16x4_t hi = __builtin_convertvector(v, f16x4_t);
+    const f32x4e_t r = (v - __builtin_convertvector(hi, f32x4e_t)) * 2048.f;
+    const f16x4_t mid = __builtin_convertvector(r, f16x4_t);
+    const f16x4_t lo = __builtin_convertvector((r - __builtin_convertvector(mid, f32x4e_t)) * 2048.f, f16x4_t);
+    *reinterpret_cast<f16x4_t *>(x.xt + k) = hi;
+    *reinterpret_cast<f16x4_t *>(x.xt + x.stride + k) = mid;
+    *reinterpret_cast<f16x4_t *>(x.xt + 2 * x.stride + k) = lo;
+}
+
+// The largest of the threads' values over the consuming waves (one of the two meetings of a staging routine)
+__device__ __forceinline__ float block_largest(float v, float *s_max) {
+    const int tid = threadIdx.x;
+    v = rows_max(v);
+    if ((tid & 63) == 0) s_max[tid >> 6] = v;
     __syncthreads();
+    float r = 0.f;
+#pragma unroll
+    for (int w = 0; w < kFusedWaves; ++w) r = fmaxf(r, s_max[w]);
+    return r;
+}
+
+// The terms of x * gain, of the columns [c0, c0 + cn) of this workgroup's slice; returns the factor (1 / rms, scale taken back) for the sums to come
+__device__ __forceinline__ float stage_norm_x(const StreamTerms &xt, float *s_red, float *s_max, const f32x4e_t (&x)[kStreamPieces], const f32x4e_t (&gn)[kStreamPieces],
+                                              int n, int c0, int cn, float eps) {
+    const int tid = fresh_tid();
+    float ss = 0.f, big = 0.f;
+#pragma unroll
+    for (int i = 0; i < kStreamPieces; ++i) {
+        if ((tid + i * kFusedThreads) * 4 < n) {
+            ss += x[i].x * x[i].x + x[i].y * x[i].y + x[i].z * x[i].z + x[i].w * x[i].w;
+            big = fmaxf(big, largest_of(x[i] * gn[i]));
+        }
+    }
+    ss = rows_sum(ss);
+    if ((tid & 63) == 0) s_red[tid >> 6] = ss;
+    const StreamScale sc = scale_for(block_largest(big, s_max));
     float tot = 0.f;
 #pragma unroll
     for (int w = 0; w < kFusedWaves; ++w) tot += s_red[w];
-    const float inv = 1.0f / sqrtf(tot / (float)K + eps);
 #pragma unroll
-    for (int i = 0; i < kStageVecs; ++i) {
+    for (int i = 0; i < kStreamPieces; ++i) {
         const int k = (tid + i * kFusedThreads) * 4;
-        if (k < K) *reinterpret_cast<f32x4e_t *>(xs + k) = v[i] * (gn[i] * inv);
+        if (k < n && k >= c0 && k < c0 + cn) put_terms(xt, k - c0, x[i] * gn[i] * sc.up);
     }
     __syncthreads();
+    return sc.down / sqrtf(tot / (float)n + eps);
 }
 
-__device__ __forceinline__ void stage_copy_v(float *xs, const float *src, int K) {
-    const int tid = threadIdx.x;
-    src = fresh(src);
-    f32x4e_t v[kStageVecs];
+__device__ __forceinline__ void load_gain(f32x4e_t (&gn)[kStreamPieces], const float *gain, int n) {
+    const int tid = fresh_tid();
 #pragma unroll
-    for (int i = 0; i < kStageVecs; ++i) {
-        const int k = (tid + i * kFusedThreads) * 4;
-        v[i] = ld_coherent4_issue(src + min(k, K - 4));     // unconditional, see stage_norm_v
-    }
-    coherent_wait(v);
+    for (int i = 0; i < kStreamPieces; ++i) gn[i] = *(gptr<f32x4e_t>)(gain + min((tid + i * kFusedThreads) * 4, n - 4));
+}
+
+// The terms of the words [c0, c0 + cn) of the region at word `off`; *factor: what takes the scale back from the sums
+__device__ __forceinline__ bool stage_words(const StreamTerms &xt, float *s_max, StreamRsrc rsrc, int off, int c0, int cn, const int *abort_flag, float *factor) {
+    const int tid = fresh_tid();
+    int voff[kStreamStage];
+    u32x4_t v[kStreamStage];
 #pragma unroll
-    for (int i = 0; i < kStageVecs; ++i) {
+    for (int i = 0; i < kStreamStage; ++i) voff[i] = (c0 + min((tid + i * kFusedThreads) * 4, cn - 4)) * 4;
+    if (!collect(rsrc, off * 4, voff, [&](int i) { return i * 4 * kFusedThreads < cn; }, v, abort_flag)) return false;
+    float big = 0.f;
+#pragma unroll
+    for (int i = 0; i < kStreamStage; ++i)
+        if (i * 4 * kFusedThreads < cn) big = fmaxf(big, largest_of(as_floats(v[i])));
+    const StreamScale sc = scale_for(block_largest(big, s_max));
+#pragma unroll
+    for (int i = 0; i < kStreamStage; ++i) {
         const int k = (tid + i * kFusedThreads) * 4;
-        if (k < K) *reinterpret_cast<f32x4e_t *>(xs + k) = v[i];
+        if (k < cn) put_terms(xt, k, as_floats(v[i]) * sc.up);
     }
     __syncthreads();
+    *factor = sc.down;
+    return true;
 }
 
-// attention output = merge of the per-split partial results (S <= kFusedMaxSplits): a thread takes
-// four neighbouring dimensions of a head at a time
+// The terms of columns [c0, c0 + cn) of the attention output: the merge of its S splits' un-normalised results.  A thread takes
+// four neighbouring dimensions of a head at a time.
 template <int HD>
-__device__ __forceinline__ void stage_attn_v(float *xs, const float *att_o, const float2 *att_ml, int H, int S) {
-    att_o = fresh(att_o); att_ml = fresh(att_ml);
-    for (int k = threadIdx.x * 4; k < H * HD; k += kFusedThreads * 4) {
-        const int h = k / HD, dd = k % HD;
-        f32x4e_t o[kFusedMaxSplits];
-        f32x2e_t ml[kFusedMaxSplits];
+__device__ __forceinline__ bool stage_attention(const StreamTerms &xt, float *s_max, StreamRsrc rsrc, int att, int ml, int c0, int cn, int S, const int *abort_flag,
+                                                float *factor) {
+    const int tid = fresh_tid();
+    f32x4e_t r[kStreamPieces];
+    float big = 0.f;
 #pragma unroll
-        for (int s = 0; s < kFusedMaxSplits; ++s) {
-            const int sc = s < S ? s : 0;          // unconditional, see stage_norm_v: a split that does not exist re-reads split 0 ...
-            o[s] = ld_coherent4_issue(att_o + ((size_t)h * kFusedMaxSplits + sc) * HD + dd);
-            ml[s] = ld_coherent2_issue(att_ml + h * kFusedMaxSplits + sc);
-        }
-        static_assert(kFusedMaxSplits == 8, "the wait below names eight results");
-        coherent_wait(o);
-        asm volatile("" : "+v"(ml[0]), "+v"(ml[1]), "+v"(ml[2]), "+v"(ml[3]), "+v"(ml[4]), "+v"(ml[5]), "+v"(ml[6]), "+v"(ml[7]));
+    for (int i = 0; i < kStreamPieces; ++i) {
+        r[i] = f32x4e_t{0.f, 0.f, 0.f, 0.f};
+        if (i * 4 * kFusedThreads >= cn) continue;
+        const int kk = c0 + min((tid + i * kFusedThreads) * 4, cn - 4), h = kk / HD, dd = kk % HD;
+        // pieces 0 .. 7: the splits' results; 8 .. 11: their maxima and sums, two splits to a piece
+        constexpr int NS = kFusedMaxSplits;
+        int voff[NS + NS / 2];
+        u32x4_t v[NS + NS / 2];
 #pragma unroll
-        for (int s = 0; s < kFusedMaxSplits; ++s)
-            if (s >= S) ml[s] = f32x2e_t{kNegBig, 0.f};       // ... and gets weight zero
+        for (int s = 0; s < NS; ++s) voff[s] = (att + (h * NS + s) * HD + dd) * 4;
+#pragma unroll
+        for (int s = 0; s < NS / 2; ++s) voff[NS + s] = (ml + (h * NS + 2 * s) * 2) * 4;
+        if (!collect(rsrc, 0, voff, [&](int j) { return j < NS ? j < S : 2 * (j - NS) < S; }, v, abort_flag)) return false;
+        const u32x4_t *m4 = v + NS;
         float M = kNegBig;
 #pragma unroll
-        for (int s = 0; s < kFusedMaxSplits; ++s) M = fmaxf(M, ml[s].x);
+        for (int s = 0; s < NS; ++s)
+            if (s < S) M = fmaxf(M, __uint_as_float(s & 1 ? m4[s >> 1].z : m4[s >> 1].x));
         float L = 0.f;
         f32x4e_t acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int s = 0; s < kFusedMaxSplits; ++s) {
-            const float c = __expf(ml[s].x - M);
-            L += ml[s].y * c;
-            acc += o[s] * c;
-        }
-        *reinterpret_cast<f32x4e_t *>(xs + k) = acc * (1.0f / L);
+        for (int s = 0; s < NS; ++s)
+            if (s < S) {
+                const float c = __expf(__uint_as_float(s & 1 ? m4[s >> 1].z : m4[s >> 1].x) - M);
+                L += __uint_as_float(s & 1 ? m4[s >> 1].w : m4[s >> 1].y) * c;
+                acc += as_floats(v[s]) * c;
+            }
+        r[i] = acc * (1.0f / L);
+        big = fmaxf(big, largest_of(r[i]));
+    }
+    const StreamScale sc = scale_for(block_largest(big, s_max));
+#pragma unroll
+    for (int i = 0; i < kStreamPieces; ++i) {
+        const int k = (tid + i * kFusedThreads) * 4;
+        if (k < cn) put_terms(xt, k, r[i] * sc.up);
     }
     __syncthreads();
+    *factor = sc.down;
+    return true;
 }
 
-struct StreamPos { int ri; int nblk; };   // ring position of the next slot; row blocks taken so far (whose turn, which buffer)
+struct StreamPos { int ri; int nblk; };   // ring position of the next slot; units taken so far (whose turn, which buffer)
 
-// The consuming side of one matrix: NB row blocks of KC tiles, activations staged in xs.
+// The consuming side of one matrix: this workgroup's units, the activations' terms of its slice in LDS, sums scaled by `scale`.
+// SWIGLU publishes the products, LOGITS folds the logits into the entropy statistics, the others publish the sums.
 template <int EPI>
-__device__ __forceinline__ void stream_rows(const LinArgs<bf16_t> &a, const StreamRing *ring, const float *xs, const float *xzero,
-                                            float *red, int NB, int KC, StreamPos &sp, EntStat &st) {
+__device__ __forceinline__ void stream_rows(const LinArgs<bf16_t> &a, float *out, const StreamRing *ring, const StreamTerms &xt, const uint16_t *xzero,
+                                            float *red, const StreamShare &sh, float scale, StreamPos &sp, EntStat &st) {
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int nt = (KC + 7) >> 3;
-    const float *xq = xs + (lane >> 4) * 8;
+    const int nt = (sh.kcn + 7) >> 3, col = lane & 15;
+    const uint16_t *xq = col < 3 ? xt.xt + col * xt.stride + (lane >> 4) * 8 : xzero;
+    const int xstep = col < 3 ? kFusedWaves * 32 : 0;            // from a wave's tile to its next
+    const float weight = col == 0 ? scale : col == 1 ? scale * (1.f / 2048.f) : col == 2 ? scale * (1.f / 4194304.f) : 0.f;
     int pend = -1, pend_wave = 0, pend_par = 0;
-    EpiPre pend_pre{};
-    auto finish = [&]() {          // the row block `pend`: add the waves' partial sums, run the epilogue
+    auto finish = [&]() {          // the row block `pend`: add the waves' partial sums and pass them on
         if (wave == pend_wave && lane < 16) {
             float v = 0.f;
 #pragma unroll
             for (int w = 0; w < kFusedWaves; ++w) v += red[(pend_par * kFusedWaves + w) * 16 + lane];
-            epilogue<bf16_t, EPI, true>(a, pend * 16 + lane, 0, v, true, st, pend_pre);
+            const int p = pend * 16 + lane;
+            if constexpr (EPI == EPI_SWIGLU) {
+                const float other = __shfl_xor(v, 1, kWave);       // even lane: gate, odd lane: up
+                if (!(lane & 1)) publish(out + (p >> 1), v / (1.f + __expf(-v)) * other);
+            } else if constexpr (EPI == EPI_LOGITS) {
+                epilogue<bf16_t, EPI_LOGITS>(a, p, 0, v, true, st, EpiPre{});
+            } else {
+                publish(out + (size_t)sh.slice * a.Np + p, v);
+            }
         }
     };
-    for (int rb = blockIdx.x; rb < NB; rb += gridDim.x) {
+    for (int u = 0, rb = sh.rb0; u < sh.n; ++u, rb += sh.step) {
         const int my_wave = sp.nblk & (kFusedWaves - 1), par = sp.nblk & 1;
-        // what this row block's epilogue reads is requested now and arrives during its k loop
-        const EpiPre pre = epi_prefetch<bf16_t, EPI, true>(a, rb * 16 + (lane & 15), 0, wave == my_wave && lane < 16);
         // A slot's tile and activations are read right behind its barrier and multiplied behind the NEXT
-        // one, while the next slot's reads are in flight: the step is then as long as an LDS read, not a
-        // read plus a chain of sixteen multiply-adds.  Two sums keep that chain short.
-        float acc0 = 0.f, acc1 = 0.f;
-        u32x4_t w{};
-        float4 x0 = make_float4(0.f, 0.f, 0.f, 0.f), x1 = x0;
-        auto multiply = [&]() {
-            Vec8<bf16_t> t8; t8.raw = w;
-            float wf[8];
-            t8.unpack_w(wf);
-            acc0 += wf[0] * x0.x + wf[1] * x0.y + wf[2] * x0.z + wf[3] * x0.w;
-            acc1 += wf[4] * x1.x + wf[5] * x1.y + wf[6] * x1.z + wf[7] * x1.w;
-        };
+        // one, while the next slot's reads are in flight.
+        f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
+        u32x4_t w{}, x{};
+        const uint16_t *xp = xq + (col < 3 ? wave * 32 : 0);
         for (int t = 0; t < nt; ++t) {
             asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
             const u32x4_t wn = ring[sp.ri][wave][lane];
             sp.ri = sp.ri + 1 == kStreamDepth ? 0 : sp.ri + 1;
-            const int kc = t * kFusedWaves + wave;
-            const float *xp = kc < KC ? xq + kc * 32 : xzero;
-            const float4 xn0 = *reinterpret_cast<const float4 *>(xp);
-            const float4 xn1 = *reinterpret_cast<const float4 *>(xp + 4);
+            const u32x4_t xn = *reinterpret_cast<const u32x4_t *>(t * kFusedWaves + wave < sh.kcn ? xp : xzero);
+            xp += xstep;
             if (t == 0 && pend >= 0) finish();
-            if (t > 0) multiply();
-            w = wn; x0 = xn0; x1 = xn1;
+            if (t > 0) acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8_t, w), __builtin_bit_cast(f16x8_t, x), acc, 0, 0, 0);
+            w = wn; x = xn;
         }
-        multiply();
-        float acc = acc0 + acc1;
-        acc += __shfl_xor(acc, 16, kWave);
-        acc += __shfl_xor(acc, 32, kWave);
-        if (lane < 16) red[(par * kFusedWaves + wave) * 16 + lane] = acc;
-        pend = rb; pend_wave = my_wave; pend_par = par; pend_pre = pre;
+        acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8_t, w), __builtin_bit_cast(f16x8_t, x), acc, 0, 0, 0);
+        f32x4e_t sum;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            float v = acc[i] * weight;
+            sum[i] = lanes_sum<4>(v);
+        }
+        if (col == 0) *reinterpret_cast<f32x4e_t *>(red + (par * kFusedWaves + wave) * 16 + (lane >> 4) * 4) = sum;
+        pend = rb; pend_wave = my_wave; pend_par = par;
         ++sp.nblk;
     }
     if (pend >= 0) { __syncthreads(); finish(); }     // kSyncRowsEnd
 }
 
+// ---- attention of the row, split over (KV head, key split) ---------------------------------------------
+// A wave serves one of the G query heads that share the KV head on one slice of the split's keys (wave w: head w % G, slice
+// w / G), so the per-lane state is one head's worth.  The first keys and values are requested before the row's query is there, the
+// next ones one round ahead.  The newest position's key and value come with the query through the exchange; the workgroup whose
+// split holds that position appends them to the caches.
 template <int HD, int G>
-__global__ __launch_bounds__(kStreamThreads) void k_decode_stream(FusedArgs<bf16_t> a, StreamModel sm) {
+__device__ __forceinline__ bool stream_attention(const FusedArgs<bf16_t> &a, const FusedLayer<bf16_t> &ly, StreamRsrc rsrc, float *now,
+                                                 const StreamExchange &ex, int layer, int KS, int seq, int pos, int S, float *lds) {
+    typedef bf16_t KT;
+    constexpr int LPK = HD / 8, KPI = 64 / LPK, NI = 4, CH = NI * KPI;
+    constexpr int NS = kFusedWaves / G;            // key slices per workgroup
+    const int kvh = blockIdx.x / S, split = blockIdx.x % S;
+    const int nkeys = pos + 1, per = (nkeys + S - 1) / S;
+    const int key0 = split * per, key1 = min(key0 + per, nkeys);
+    const int tid = fresh_tid(), lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int slot = lane / LPK, dl = lane % LPK;
+    const int g = wave % G, slice = wave / G;
+    const bool active = slice < NS, own = pos >= key0 && pos < key1;
+    // LDS: the G scaled queries, the new key and value as the caches hold them, then the waves' results
+    float *qs = lds;
+    bf16_t *kn = reinterpret_cast<bf16_t *>(qs + G * HD), *vn = kn + HD;
+    float *wo = qs + (G + 1) * HD, *wm = wo + kFusedWaves * HD, *wl = wm + kFusedWaves;
+    const size_t base = ((size_t)seq * a.KV + kvh) * (size_t)a.fin.s.max_seq * HD;
+    const KT *kb = ly.kcache + base + dl * 8, *vb = ly.vcache + base + dl * 8;
+    Vec8<KT> kx[2][NI], vx[2][NI];
+    auto request = [&](Vec8<KT> (&k)[NI], Vec8<KT> (&v)[NI], int c0) {
+#pragma unroll
+        for (int i = 0; i < NI; ++i) {
+            const int kk = min(c0 + i * KPI + slot, key1 - 1);
+            k[i].load(kb + (size_t)max(kk, 0) * HD); v[i].load(vb + (size_t)max(kk, 0) * HD);
+        }
+    };
+    const int c00 = key0 + slice * CH;
+    if (active) { request(kx[0], vx[0], c00); request(kx[1], vx[1], c00 + NS * CH); }
+    // the G query heads, and for the newest position its key and value: four packed rows a thread
+    {
+        const int NQ = a.H * HD, NK = a.KV * HD, nq4 = G * HD / 4, n4 = own ? nq4 + HD / 2 : nq4;
+        const int i4 = min(tid, n4 - 1), part = i4 < nq4 ? 0 : i4 < nq4 + HD / 4 ? 1 : 2;      // query, key, value
+        const int r4 = part == 0 ? i4 : part == 1 ? i4 - nq4 : i4 - nq4 - HD / 4;
+        const int row = (part == 0 ? kvh * G * HD : part == 1 ? NQ + kvh * HD : NQ + NK + kvh * HD) + r4 * 4;
+        const int r = (r4 * 4) % HD, i = r >> 1;       // packed rows (2i, 2i + 1) of a head are its dimensions (i, i + HD / 2)
+        const f32x4e_t cs = *(gptr<f32x4e_t>)(reinterpret_cast<const float *>(a.rope + (size_t)pos * (HD / 2) + i));
+        int voff[kStreamMaxSlices];
+        u32x4_t w[kStreamMaxSlices];
+#pragma unroll
+        for (int s = 0; s < kStreamMaxSlices; ++s) voff[s] = (s * (NQ + 2 * NK) + row) * 4;
+        if (!collect(rsrc, (layer * ex.layer_words + ex.qkv) * 4, voff, [&](int s) { return s < KS; }, w, a.bar.abort_flag)) return false;
+        f32x4e_t v = as_floats(w[0]);
+#pragma unroll
+        for (int s = 1; s < kStreamMaxSlices; ++s)
+            if (s < KS) v += as_floats(w[s]);
+        if (tid < n4) {
+            if (part < 2) v = f32x4e_t{v.x * cs.x - v.y * cs.y, v.x * cs.y + v.y * cs.x, v.z * cs.z - v.w * cs.w, v.z * cs.w + v.w * cs.z};
+            if (part == 0) {
+                const float scale = 1.0f / sqrtf((float)HD);
+                float *q = qs + (r4 * 4) / HD * HD + i;
+                q[0] = v.x * scale; q[1] = v.z * scale; q[HD / 2] = v.y * scale; q[HD / 2 + 1] = v.w * scale;
+            } else if (part == 1) {
+                const KT b0 = from_f32<KT>(v.x), b1 = from_f32<KT>(v.z), b2 = from_f32<KT>(v.y), b3 = from_f32<KT>(v.w);
+                KT *d = ly.kcache + base + (size_t)pos * HD + i;
+                kn[i] = b0; kn[i + 1] = b1; kn[i + HD / 2] = b2; kn[i + HD / 2 + 1] = b3;
+                d[0] = b0; d[1] = b1; d[HD / 2] = b2; d[HD / 2 + 1] = b3;
+            } else {
+                const size_t tb = ((size_t)seq * a.KV + kvh) * HD * (size_t)a.fin.s.max_seq;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {       // rows of V are not permuted
+                    const KT b = from_f32<KT>(e == 0 ? v.x : e == 1 ? v.y : e == 2 ? v.z : v.w);
+                    vn[r + e] = b;
+                    ly.vcache[base + (size_t)pos * HD + r + e] = b;
+                    if (ly.vtcache) ly.vtcache[tb + vt_offset(r + e, pos, a.fin.s.max_seq)] = b;
+                }
+            }
+        }
+    }
+    __syncthreads();
+    float o[8], m = kNegBig, l = 0.f;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) o[e] = 0.f;
+    auto round = [&](Vec8<KT> (&k)[NI], Vec8<KT> (&v)[NI], const float (&qv)[8], int c0) {
+        float s[NI];
+#pragma unroll
+        for (int i = 0; i < NI; ++i) {
+            const int kk = c0 + i * KPI + slot;
+            if (kk == pos) {
+                k[i].raw = *reinterpret_cast<const u32x4_t *>(kn + dl * 8);
+                v[i].raw = *reinterpret_cast<const u32x4_t *>(vn + dl * 8);
+            }
+            float kf[8];
+            k[i].unpack(kf);
+            float d = 0.f;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) d += qv[e] * kf[e];
+            d = lanes_sum<LPK>(d);
+            s[i] = kk < key1 ? d : kNegBig;
+        }
+        float mc = s[0];
+#pragma unroll
+        for (int i = 1; i < NI; ++i) mc = fmaxf(mc, s[i]);
+        const float mn = fmaxf(m, mc);
+        const float corr = __expf(m - mn);
+        l *= corr;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) o[e] *= corr;
+        m = mn;
+#pragma unroll
+        for (int i = 0; i < NI; ++i) {
+            const bool in = c0 + i * KPI + slot < key1;      // past the split's end the value may be anything
+            const float p = in ? __expf(s[i] - mn) : 0.f;
+            l += p;
+            float vf[8];
+            v[i].unpack(vf);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) o[e] += in ? p * vf[e] : 0.f;
+        }
+    };
+    if (active) {
+        float qv[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) qv[e] = qs[g * HD + dl * 8 + e];
+        for (int c0 = c00; c0 < key1; c0 += 2 * NS * CH) {
+            round(kx[0], vx[0], qv, c0);
+            if (c0 + 2 * NS * CH < key1) request(kx[0], vx[0], c0 + 2 * NS * CH);
+            if (c0 + NS * CH < key1) {
+                round(kx[1], vx[1], qv, c0 + NS * CH);
+                if (c0 + 3 * NS * CH < key1) request(kx[1], vx[1], c0 + 3 * NS * CH);
+            }
+        }
+    }
+    // merge the key slots of the wave
+#pragma unroll
+    for (int off = LPK; off < 64; off <<= 1) {
+        const float m2 = __shfl_xor(m, off, kWave), l2 = __shfl_xor(l, off, kWave);
+        const float M = fmaxf(m, m2);
+        const float ca = __expf(m - M), cb = __expf(m2 - M);
+        l = l * ca + l2 * cb;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const float o2 = __shfl_xor(o[e], off, kWave);
+            o[e] = o[e] * ca + o2 * cb;
+        }
+        m = M;
+    }
+    // waves meet in LDS: wo[wave][HD], wm[wave], wl[wave]
+    if (slot == 0) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) wo[wave * HD + dl * 8 + e] = o[e];
+        if (dl == 0) { wm[wave] = active ? m : kNegBig; wl[wave] = active ? l : 0.f; }
+    }
+    __syncthreads();
+    float *att = now + (size_t)layer * ex.layer_words + ex.att, *ml = now + (size_t)layer * ex.layer_words + ex.ml;
+    for (int e = tid; e < G * HD; e += kFusedThreads) {
+        const int gg = e / HD, dd = e % HD, h = kvh * G + gg;
+        float M = kNegBig;
+#pragma unroll
+        for (int sl = 0; sl < NS; ++sl) M = fmaxf(M, wm[sl * G + gg]);
+        float L = 0.f, acc = 0.f;
+#pragma unroll
+        for (int sl = 0; sl < NS; ++sl) {
+            const float c = __expf(wm[sl * G + gg] - M);
+            L += wl[sl * G + gg] * c;
+            acc += wo[(sl * G + gg) * HD + dd] * c;
+        }
+        publish(att + ((size_t)h * kFusedMaxSplits + split) * HD + dd, acc);
+        if (dd == 0) {
+            float *q = ml + ((size_t)h * kFusedMaxSplits + split) * 2;
+            publish(q, M); publish(q + 1, L);
+            // a reader takes two splits at a time: the one past the last is never written by anybody else
+            if (split == S - 1 && (S & 1)) { publish(q + 2, kNegBig); publish(q + 3, 0.f); }
+        }
+    }
+    __syncthreads();
+    return true;
+}
+
+template <int HD, int G>
+__global__ __launch_bounds__(kStreamThreads) void k_decode_stream(FusedArgs<bf16_t> a, StreamModel sm, StreamExchange ex) {
     typedef bf16_t WT;
     extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
     StreamRing *ring = reinterpret_cast<StreamRing *>(smem_raw);
     float *smem = reinterpret_cast<float *>(smem_raw + (size_t)kStreamDepth * kStreamSlotBytes);
-    __shared__ int s_plan[4];        // seq, pos, token, T(=1)
+    __shared__ int s_plan[4];        // seq, pos, token
     __shared__ int s_ok;
-    __shared__ float s_red[kFusedWaves];
-    const int Kmax = max(max(a.d, a.F), a.H * HD);
-    float *xs = smem, *red = smem + Kmax, *xzero = red + 2 * kFusedWaves * 16;       // xzero: 64 zeros
+    __shared__ float s_red[kFusedWaves], s_max[kFusedWaves];
+    float *red = smem, *zeros = red + 2 * kFusedWaves * 16, *xs = zeros + 64;       // 64 zeros
+    const uint16_t *xzero = reinterpret_cast<const uint16_t *>(zeros);
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const long n_steps = stream_steps(sm, blockIdx.x, gridDim.x);
+    if (uni(ld_coherent(a.bar.abort_flag))) return;      // an earlier launch was given up: its exchange is in no defined state
 
     if (wave >= kFusedWaves) {
         // ---- fetching waves ------------------------------------------------------------------
-        const int p = wave - kFusedWaves;
-        if (n_steps == 0) { __syncthreads(); return; }
-        StreamList pos(sm);
-        pos.open();                         // n_steps > 0: there is a first matrix
+        const int p = wave - kFusedWaves, wg = blockIdx.x, G_ = gridDim.x;
+        const uint32_t ring0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char *)smem_raw;
+        StreamList pos;
+        pos.enter(sm, 0, 0, wg, G_);        // a workgroup owns a unit of some matrix: the launch has at most as many as the LM head has row blocks
         int ri = 0;
-        for (int s = 0; s < kStreamDepth - 1; ++s) { stream_issue(pos, ring[ri], p, lane); ri = ri + 1 == kStreamDepth ? 0 : ri + 1; }
+        for (int s = 0; s < kStreamDepth - 1; ++s) {
+            stream_issue(pos, ring0 + ri * kStreamSlotBytes, p, lane);
+            pos.next(sm, wg, G_);
+            ri = ri + 1 == kStreamDepth ? 0 : ri + 1;
+        }
         __syncthreads();                    // the consuming waves have set up their constants
         // the consuming waves' phases, one by one: arrive where they meet, hand over a slot where they read one
-        const int n_phases = 5 * pos.L + 1;
-        for (int ph = 0; ph < n_phases; ++ph) {
-            const int kind = ph < 5 * pos.L ? ph % 5 : 5;
-            if (ph > 0) follow(kSyncGridBarrier);
-            if (kind == 1) { follow(kSyncAttention); continue; }
-            follow(kind == 2 ? kSyncStageAttn : kind == 4 ? kSyncStageCopy : kSyncStageNorm);
-            const int j = kind == 0 ? 0 : kind == 5 ? 4 : kind - 1;
-            const int NB = pos.nb_of(j);
-            if (pos.wg >= NB) continue;
-            const long n = (long)((NB - pos.wg + pos.G - 1) / pos.G) * ((pos.kc_of(j) + 7) >> 3);
-            for (long i = 0; i < n; ++i) {
-                asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(kStreamLoads * (kStreamDepth - 2)) : "memory");
-                stream_issue(pos, ring[ri], p, lane);
-                ri = ri + 1 == kStreamDepth ? 0 : ri + 1;
+        for (int l = 0; l <= sm.L; ++l)
+            for (int kind = l < sm.L ? 0 : 5; kind < (l < sm.L ? 5 : 6); ++kind) {
+                if (kind == 1) { follow(kSyncAttention); continue; }
+                follow(kSyncStage);
+                const StreamShare sh = stream_share(sm.m[kind == 0 ? 0 : kind - 1], wg, G_);
+                const int n = sh.n * ((sh.kcn + 7) >> 3);
+                for (int i = 0; i < n; ++i) {
+                    asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(kStreamLoads * (kStreamDepth - 2)) : "memory");
+                    stream_issue(pos, ring0 + ri * kStreamSlotBytes, p, lane);
+                    pos.next(sm, wg, G_);
+                    ri = ri + 1 == kStreamDepth ? 0 : ri + 1;
+                }
+                if (n > 0) follow(kSyncRowsEnd);
             }
-            follow(kSyncRowsEnd);
-        }
         follow(kSyncGridBarrier);
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         return;
     }
 
     // ---- consuming waves -----------------------------------------------------------------------
-    if (tid < 64) xzero[tid] = 0.f;
+    if (tid < 64) zeros[tid] = 0.f;
     const int m = a.fin.model_id, MB = a.fin.s.max_batch;
     // the one sequence this model serves in this step, and its newest position
     if (tid == 0) {
@@ -385,63 +665,91 @@ __global__ __launch_bounds__(kStreamThreads) void k_decode_stream(FusedArgs<bf16
         for (int b = 0; b < a.batch; ++b)
             if (!a.fin.s.done[b] && a.fin.s.model[b] == m && a.fin.s.last_step[b] != a.fin.step) { seq = b; break; }
         const int pos = a.fin.s.kvlen[m * MB + seq];
-        s_plan[0] = seq; s_plan[1] = pos; s_plan[2] = a.fin.s.tokens[(size_t)seq * a.fin.s.max_seq + pos]; s_plan[3] = 1;
+        s_plan[0] = seq; s_plan[1] = pos; s_plan[2] = a.fin.s.tokens[(size_t)seq * a.fin.s.max_seq + pos];
     }
     __syncthreads();
     BlockSync sync;
     StreamPos sp{0, 0};
-    const int seq = s_plan[0], pos = s_plan[1];
+    const int seq = uni(s_plan[0]), pos = uni(s_plan[1]);
     const WT *emb = a.embed + (size_t)s_plan[2] * a.d;
-    const int NQ = a.H * HD, NK = a.KV * HD;
+    const int NQ = a.H * HD, NK = a.KV * HD, G_ = gridDim.x, wg = blockIdx.x;
     // key splits of the attention phase: 64 keys or more each, as many workgroups as that gives
     const int S = min(kFusedMaxSplits, max(1, (pos + 1 + 63) / 64));
+    const StreamRsrc rsrc = exchange_rsrc(ex.now, ex.layer_words * a.L);
     GridBar bar = a.bar;
     EntStat st; st.init();
+    f32x4e_t x[kStreamPieces], gn[kStreamPieces];
+#pragma unroll
+    for (int i = 0; i < kStreamPieces; ++i) {       // the residual stream starts as the embedding row
+        const int k = (tid + i * kFusedThreads) * 4;
+        x[i] = f32x4e_t{0.f, 0.f, 0.f, 0.f};
+        if (k < a.d) x[i] = f32x4e_t{to_f32(emb[k]), to_f32(emb[k + 1]), to_f32(emb[k + 2]), to_f32(emb[k + 3])};
+    }
 
     // phases: per layer QKV, attention, output projection, gate/up, down; then the LM head.
     // Every workgroup-wide meeting below is counted in the kSync* constants the fetching waves follow.
-    const int n_phases = 5 * a.L + 1;
-    for (int ph = 0; ph < n_phases; ++ph) {
-        const int kind = ph < 5 * a.L ? ph % 5 : 5, l = ph / 5;
-        if (ph > 0) {
-            bar_arrive(bar, sync);
-            if (!bar_wait(bar, &s_ok, sync)) return;
-        }
-        if (kind == 1) {
-            const FusedLayer<WT> ly = a.layers[l];
-            if ((int)blockIdx.x < a.KV * S) fused_attention<WT, HD, G>(a, ly.kcache, ly.vcache, seq, pos, S, smem, sync);
-            else __syncthreads();
-            continue;
-        }
+    const int *ab = a.bar.abort_flag;
+    const int clear_per = (ex.total_words / 4 + a.L * G_ - 1) / (a.L * G_);      // float4 pieces of the other buffer a workgroup empties per layer
+    // the terms' rows start 16 bytes apart from a multiple of the banks
+    auto terms = [&](const StreamShare &sh) { return StreamTerms{reinterpret_cast<uint16_t *>(xs), sh.kcn * 32 + 8}; };
+    auto share = [&](int j) { return stream_share(sm.m[j], wg, G_); };
+    for (int l = 0; l < a.L; ++l) {
+        const FusedLayer<WT> ly = a.layers[l];
+        const int lo = l * ex.layer_words;
+        float *now = ex.now + (size_t)lo;
         LinArgs<WT> p{};
-        if (kind == 0) {                        // RMSNorm + QKV + rotary + KV append
-            const FusedLayer<WT> ly = a.layers[l];
-            if (l == 0) stage_norm_embed<WT>(xs, s_red, emb, a.d, ly.g_attn, a.eps, sync);
-            else stage_norm_v(xs, s_red, a.x, a.d, ly.g_attn, a.eps);
-            p.Np = NQ + 2 * NK; p.K = a.d; p.out = a.q; p.ldo = NQ; p.kcache = ly.kcache; p.vcache = ly.vcache; p.vtcache = ly.vtcache;
-            p.row_seq = &s_plan[0]; p.row_pos = &s_plan[1]; p.rope = a.rope; p.n_heads = a.H; p.n_kv_heads = a.KV;
-            p.hd = HD; p.max_seq = a.fin.s.max_seq;
-            stream_rows<EPI_QKV>(p, ring, xs, xzero, red, sm.NB[0], sm.KC[0], sp, st);
-        } else if (kind == 2) {                 // output projection + residual
-            stage_attn_v<HD>(xs, a.att_o, a.att_ml, a.H, S);
-            p.Np = a.d; p.K = NQ; p.out = a.x; p.ldo = a.d; p.res_embed = l == 0 ? emb : nullptr;
-            stream_rows<EPI_RES>(p, ring, xs, xzero, red, sm.NB[1], sm.KC[1], sp, st);
-        } else if (kind == 3) {                 // RMSNorm + gate/up + SwiGLU
-            stage_norm_v(xs, s_red, a.x, a.d, a.layers[l].g_ffn, a.eps);
-            p.Np = 2 * a.F; p.K = a.d; p.out = a.hbuf; p.ldo = a.F;
-            stream_rows<EPI_SWIGLU>(p, ring, xs, xzero, red, sm.NB[2], sm.KC[2], sp, st);
-        } else if (kind == 4) {                 // down projection + residual
-            stage_copy_v(xs, a.hbuf, a.F);
-            p.Np = a.d; p.K = a.F; p.out = a.x; p.ldo = a.d;
-            stream_rows<EPI_RES>(p, ring, xs, xzero, red, sm.NB[3], sm.KC[3], sp, st);
-        } else {                                // final RMSNorm + LM head, entropy statistics folded in
-            stage_norm_v(xs, s_red, a.x, a.d, a.g_final, a.eps);
-            p.Np = a.V; p.K = a.d;
-            stream_rows<EPI_LOGITS>(p, ring, xs, xzero, red, sm.NB[4], sm.KC[4], sp, st);
-            if (lane < 16) {                    // one partial per (workgroup, wave)
-                p.partials = a.lm_part + (size_t)wave * gridDim.x;
-                logits_flush<WT, true>(p, 0, true, st);
+        {                                       // RMSNorm + QKV
+            const StreamShare sh = share(0);
+            load_gain(gn, ly.g_attn, a.d);
+            if (l > 0 && !add_sums(x, rsrc, lo - ex.layer_words + ex.down, a.d, 1 << sm.m[3].ks_log2, ab)) { st_coherent(a.bar.abort_flag, 1); return; }
+            const float inv = stage_norm_x(terms(sh), s_red, s_max, x, gn, a.d, sh.kc0 * 32, sh.kcn * 32, a.eps);
+            p.Np = NQ + 2 * NK;
+            stream_rows<EPI_QKV>(p, now + ex.qkv, ring, terms(sh), xzero, red, sh, inv, sp, st);
+        }
+        // rotary + KV append + attention
+        if (wg < a.KV * S) {
+            if (!stream_attention<HD, G>(a, ly, rsrc, ex.now, ex, l, 1 << sm.m[0].ks_log2, seq, pos, S, xs)) { st_coherent(a.bar.abort_flag, 1); return; }
+        } else follow(kSyncAttention);
+        {                                       // output projection
+            const StreamShare sh = share(1);
+            float f = 1.f;
+            if (sh.n == 0) follow(kSyncStage);
+            else if (!stage_attention<HD>(terms(sh), s_max, rsrc, lo + ex.att, lo + ex.ml, sh.kc0 * 32, sh.kcn * 32, S, ab, &f)) { st_coherent(a.bar.abort_flag, 1); return; }
+            p.Np = a.d;
+            stream_rows<EPI_RES>(p, now + ex.o, ring, terms(sh), xzero, red, sh, f, sp, st);
+        }
+        {                                       // residual, RMSNorm + gate/up + SwiGLU
+            const StreamShare sh = share(2);
+            load_gain(gn, ly.g_ffn, a.d);
+            if (!add_sums(x, rsrc, lo + ex.o, a.d, 1 << sm.m[1].ks_log2, ab)) { st_coherent(a.bar.abort_flag, 1); return; }
+            const float inv = stage_norm_x(terms(sh), s_red, s_max, x, gn, a.d, sh.kc0 * 32, sh.kcn * 32, a.eps);
+            for (int i = tid; i < clear_per; i += kFusedThreads) {
+                const int c = (l * G_ + wg) * clear_per + i;
+                if (c * 4 < ex.total_words) reinterpret_cast<u32x4_t *>(ex.next)[c] = u32x4_t{kEmptyWord, kEmptyWord, kEmptyWord, kEmptyWord};
             }
+            p.Np = 2 * a.F;
+            stream_rows<EPI_SWIGLU>(p, now + ex.h, ring, terms(sh), xzero, red, sh, inv, sp, st);
+        }
+        {                                       // down projection
+            const StreamShare sh = share(3);
+            float f = 1.f;
+            if (sh.n == 0) follow(kSyncStage);
+            else if (!stage_words(terms(sh), s_max, rsrc, lo + ex.h, sh.kc0 * 32, sh.kcn * 32, ab, &f)) { st_coherent(a.bar.abort_flag, 1); return; }
+            p.Np = a.d;
+            stream_rows<EPI_RES>(p, now + ex.down, ring, terms(sh), xzero, red, sh, f, sp, st);
+        }
+    }
+    {                                           // residual, final RMSNorm + LM head, entropy statistics folded in
+        const StreamShare sh = share(4);
+        load_gain(gn, a.g_final, a.d);
+        if (!add_sums(x, rsrc, (a.L - 1) * ex.layer_words + ex.down, a.d, 1 << sm.m[3].ks_log2, ab)) { st_coherent(a.bar.abort_flag, 1); return; }
+        const float inv = stage_norm_x(terms(sh), s_red, s_max, x, gn, a.d, 0, a.d, a.eps);
+        LinArgs<WT> p{};
+        p.Np = a.V;
+        stream_rows<EPI_LOGITS>(p, nullptr, ring, terms(sh), xzero, red, sh, inv, sp, st);
+        if (lane < 16) {                        // one partial per (workgroup, wave)
+            p.partials = a.lm_part + (size_t)wave * gridDim.x;
+            logits_flush<WT, true>(p, 0, true, st);
         }
     }
     bar_arrive(bar, sync);

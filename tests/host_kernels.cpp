@@ -102,4 +102,11 @@ int host_tile_plan(int NG, int SG, int KC, int split, long floats) {
     return p.whole * 100 + p.KS;
 }
 
+// slices of K * 1000 + tiles of a slice; 0: no slice fits
+int host_stream_split(int NB, int KC, int most) {
+    const StreamSplit p = stream_split(NB, KC, 256, most);
+    return p.slices * 1000 + p.tiles;
+}
+int host_stream_pays(int d, int KV, int layers, int keys) { return stream_pays(d, KV, layers, keys); }
+
 }  // extern "C"

@@ -1,0 +1,96 @@
+"""GPU: single-row decode steps through the persistent streaming kernel (k_decode_stream), asked for and taken by itself, against the per-layer kernels."""
+import threading
+
+import numpy as np
+import pytest
+
+import oracle
+import synth_inputs as si
+from gpu_helpers import TOL_H, make_pair
+
+pytestmark = pytest.mark.gpu
+
+# heads x head_dim x query heads per KV head of every instantiation; row blocks and k tiles that leave remainders in the units and slots (33 to 161 k
+# tiles, 2 to 4 slices of K); a vocabulary of 257 row blocks
+CASES = [("g4", 2, 2048, 32, 8, 5152), ("g7", 3, 896, 14, 2, 4864), ("g3", 2, 3072, 24, 8, 2080), ("g5", 1, 5120, 40, 8, 2048),
+         ("g6", 2, 1536, 12, 2, 8960), ("g4-128", 1, 4096, 32, 8, 4192)]
+
+
+@pytest.mark.parametrize("name,layers,d,heads,kv,ffn", CASES, ids=[c[0] for c in CASES])
+def test_replay_matches_the_oracle_and_the_per_layer_kernels(name, layers, d, heads, kv, ffn):
+    """Entropies along a trajectory within 1e-2 nats of the oracle, from the first key on and across 64-key splits, and within 2e-3 of the per-layer kernels: both keep
+    float32 activations, but another order of sums moves a cached key or value to its other bf16 neighbour (2^-8 of it), and what two kernel families differ by
+    for that reason is bounded by 7e-3 of the row maximum in the logits, 2e-3 nats."""
+    import paper_2502_06833_amd as ead
+    shape = si.ModelShape("stream-" + name, layers, d, heads, kv, ffn, 4112, 1e-5, 1e4)
+    other = si.ModelShape("stream-other", 1, 128, 4, 4, 128, 4112, 1e-5, 1e4)
+    W, Wo, om, _ = make_pair(shape, other, gain_std=0.2, lm_sigma=1.5)
+    e = ead.EAD(shape, W, other, Wo, window=5, tau=0.0, d_min=4, max_batch=1, max_seq=160)
+    for P, n in ((1, 6), (60, 8), (125, 10)):
+        toks = si.prompt_np(0, f"s{P}", P + n, shape.vocab)
+        got = {}
+        for mode in (0, 1):
+            e.set_fused(mode)
+            got[mode] = e.replay([toks[:P]], toks[None, P:], np.zeros((1, n), np.uint8))["H"][0]
+        ref = oracle.entropy_rows(om.forward_dense(toks)[P - 1:P + n - 1])[0]
+        assert np.abs(got[1] - ref).max() < TOL_H
+        assert np.abs(got[1] - got[0]).max() < 2e-3
+    e.close()
+
+
+DEEP = si.ModelShape("stream-deep", 20, 2048, 32, 8, 512, 4112, 1e-5, 1e4)
+FLAT = si.ModelShape("stream-flat", 20, 1536, 12, 2, 512, 4112, 1e-5, 1e4)
+
+
+def _pair():
+    return [si.model_weights_torch(s, 0, "cuda", lm_std=1.5 / np.sqrt(s.d_model)) for s in (DEEP, FLAT)]
+
+
+def test_taken_by_itself_and_switched_off():
+    """A run of both models, switching: the default takes the kernel, as the profile says, set_fused(False) does not; two default runs agree bit for bit, and the
+    entropies before the first token that differs (two logits may be close) are within 2e-3 (see above)."""
+    import paper_2502_06833_amd as ead
+    Ws, Wl = _pair()
+    e = ead.EAD(DEEP, Ws, FLAT, Wl, window=3, tau=7.2, d_min=2, max_batch=1, max_seq=96)
+    prompt = si.prompt_np(0, "auto", 40, DEEP.vocab)
+    e.profile(True)
+    runs = [e.generate([prompt], 24)]
+    names = {p["name"] for p in e.profile_read() if p["launches"]}
+    e.profile(False)
+    assert any("decode_fused" in n for n in names)
+    runs.append(e.generate([prompt], 24))
+    e.set_fused(False)
+    runs.append(e.generate([prompt], 24))
+    assert (runs[0]["H"] == runs[1]["H"]).all() and (runs[0]["tokens"] == runs[1]["tokens"]).all()
+    same = (runs[2]["tokens"] == runs[0]["tokens"])[0].cumprod().astype(bool) & (runs[2]["model_id"] == runs[0]["model_id"])[0].cumprod().astype(bool)
+    assert same[:4].all() and np.abs(runs[2]["H"] - runs[0]["H"])[0][same].max() < 2e-3
+    e.close()
+
+
+def test_two_handles_in_two_threads():
+    """Persistent kernels of two handles on streams of their own: one starts after the other's has ended, and both finish with the tokens of a run alone."""
+    import torch
+    import paper_2502_06833_amd as ead
+    Ws, Wl = _pair()
+    prompts = [si.prompt_np(0, f"thread{i}", 30 + i, DEEP.vocab) for i in range(2)]
+    handles, streams = [], [torch.cuda.Stream() for _ in range(2)]
+    for i in range(2):
+        with torch.cuda.stream(streams[i]):
+            handles.append(ead.EAD(DEEP, Ws, FLAT, Wl, window=3, tau=7.2, d_min=2, max_batch=1, max_seq=96))
+    want = [handles[i].generate([prompts[i]], 32) for i in range(2)]
+    got = [[], []]
+
+    def work(i):
+        for _ in range(4):
+            got[i].append(handles[i].generate([prompts[i]], 32))
+
+    threads = [threading.Thread(target=work, args=(i,)) for i in range(2)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    for i in range(2):
+        assert len(got[i]) == 4
+        for r in got[i]:
+            assert (r["tokens"] == want[i]["tokens"]).all() and (r["H"] == want[i]["H"]).all()
+        handles[i].close()

@@ -288,3 +288,22 @@ def test_tile_plans_stay_within_the_scratch(host):
                 whole, KS = p // 100, p % 100
                 assert 0 <= whole <= SG and 1 <= KS <= 8 and (KS == 1) == (whole == SG)
                 assert KS == 1 or (NG * (SG - whole) * 65536 * KS <= 16 << 20 and KC // KS >= 32)
+
+
+def test_stream_splits_cover_k_and_fit_the_stage(host):
+    for NB in (8, 56, 128, 192, 256, 320, 384, 448, 960):
+        for KC in range(8, 481):
+            for most in (512, 1024, 7680):
+                p = host.host_stream_split(NB, KC, most)
+                slices, tiles = p // 1000, p % 1000
+                if slices == 0:
+                    assert KC * 32 > most
+                    continue
+                assert slices in (1, 2, 4) and tiles * 32 <= most
+                assert tiles * (slices - 1) < KC <= tiles * slices and (slices == 1 or tiles % 8 == 0)
+
+
+@pytest.mark.parametrize("d,KV,layers,keys,pays", [(2048, 8, 16, 330, 1), (896, 2, 24, 330, 1), (4096, 8, 8, 1200, 1), (5120, 8, 48, 2048, 1), (1536, 2, 28, 330, 1),
+                                                   (896, 2, 24, 1200, 0), (2048, 8, 1, 330, 0), (896, 2, 6, 330, 0), (2048, 8, 16, 4096, 0)])
+def test_one_row_streams_where_that_is_faster(host, d, KV, layers, keys, pays):
+    assert host.host_stream_pays(d, KV, layers, keys) == pays
