@@ -21,10 +21,7 @@
 
 namespace ead {
 
-constexpr int kFusedWaves = 8;
-constexpr int kFusedThreads = kFusedWaves * 64;
 constexpr long kFusedSpinLimit = 1L << 21;
-constexpr int kFusedMaxSplits = 8;
 constexpr int kBarGroups = 8;
 constexpr int kFusedRbChunk = 8;     // row blocks between two workgroup synchronisations
 constexpr int kFusedMaxMats = 200;   // 4 per layer + LM head

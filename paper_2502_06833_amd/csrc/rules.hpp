@@ -7,6 +7,9 @@ namespace ead {
 
 enum Epilogue { EPI_QKV = 0, EPI_RES = 1, EPI_SWIGLU = 2, EPI_LOGITS = 3 };      // what becomes of a linear layer's sums
 
+// the persistent kernels of one row: waves (of the streamed one: that multiply) and threads of a workgroup, most splits of a KV head's keys
+constexpr int kFusedWaves = 8, kFusedThreads = kFusedWaves * 64, kFusedMaxSplits = 8;
+
 constexpr int kEntMaxChunks = 64;                       // most pieces a row of logits is cut into
 
 // The split of a row into work items depends on (rows, V) alone, so a step's result does not depend on

@@ -39,96 +39,21 @@
 // LM head 525 MB 78 -> 72), lane-move reductions 35.6.
 #pragma once
 #include "fused.hpp"
+#include "stream_list.hpp"
 
 namespace ead {
-
-constexpr int kStreamDepth = 14;                 // ring slots
-constexpr int kStreamSlotBytes = 8192;           // 8 tiles of 1 KB
-constexpr int kStreamProducers = 2;
-constexpr int kStreamLoads = kFusedWaves / kStreamProducers;   // tile loads per fetching wave and slot
-constexpr int kStreamThreads = (kFusedWaves + kStreamProducers) * 64;
-static_assert(kStreamLoads * (kStreamDepth - 1) <= 63, "outstanding loads must fit the vector memory counter");
-constexpr int kStreamPieces = 3;                 // float4 pieces of the residual stream per thread
-constexpr int kStreamMaxWidth = kStreamPieces * 4 * kFusedThreads;      // d_model this kernel serves
-constexpr int kStreamMaxSlices = 4;              // slices of K a matrix may be cut into
-constexpr int kStreamStage = 8;                  // float4 pieces of any other vector a thread stages at once
-
-// How a matrix is split: row blocks, tiles of a row block, slices of K (a power of two) and tiles of a slice (the last may be shorter).
-struct StreamMat { size_t off; int NB, KC, ks_log2, KCs; };
-// Where a model's packed weights are: matrix j (0 QKV, 1 output projection, 2 gate/up, 3 down) of layer l starts at
-// base + l * layer_stride + m[j].off (elements); m[4] is the LM head, at lm.
-struct StreamModel {
-    const bf16_t *base, *lm; size_t layer_stride;
-    StreamMat m[5];
-    int L;
-};
-
-// The exchange buffer of a launch and the one to be emptied for the next: regions of a layer, in words.
-struct StreamExchange {
-    float *now, *next;
-    int layer_words, total_words;            // of this model's layers; of both buffers as a whole
-    int qkv, att, ml, o, h, down;            // region offsets inside a layer
-};
-
-// A workgroup's share of a matrix: which slice, how many row blocks, from which one on, how far apart; the slice's tiles.
-struct StreamShare { int slice, rb0, step, n, kc0, kcn; };
-__device__ __forceinline__ StreamShare stream_share(const StreamMat &m, int wg, int G) {
-    StreamShare s;
-    s.step = G >> m.ks_log2; s.slice = wg & ((1 << m.ks_log2) - 1); s.rb0 = wg >> m.ks_log2;
-    s.n = s.rb0 < min(s.step, m.NB) ? (m.NB - s.rb0 + s.step - 1) / s.step : 0;
-    s.kc0 = s.slice * m.KCs; s.kcn = min(m.KCs, m.KC - s.kc0);
-    return s;
-}
-
-// The fetching waves' position in the list of slots of their workgroup.  Everything is the same in all lanes and
-// lives in scalar registers; the matrices' descriptions come from the kernel arguments by scalar loads, so that the loop
-// around the tile loads touches no vector memory but the weights.  (An array of descriptions that the compiler put into
-// scratch memory cost a wait for all outstanding loads at every matrix.)
-__device__ __forceinline__ int uni(int v) { return __builtin_amdgcn_readfirstlane(v); }
-__device__ __forceinline__ size_t uni(size_t v) {
-    const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)v);
-    const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(v >> 32));
-    return ((size_t)hi << 32) | (size_t)lo;
-}
-struct StreamList {
-    int l, j, units;                 // layer, matrix, units of it still to come (this one included)
-    int left, kcn;                   // tiles of this unit from the current slot on; of a whole unit
-    size_t cur, unit, step;          // byte addresses: the slot's first tile, the unit's; distance of two units
-    // to the first unit of matrix jj of layer ll or, where the workgroup has none there, of the next one that has
-    __device__ __forceinline__ void enter(const StreamModel &sm, int ll, int jj, int wg, int G) {
-        for (;; ++jj) {
-            if (jj == 4 && ll < sm.L - 1) { jj = 0; ++ll; }
-            if (jj > 4) { left = 0x7FFFFFFF; units = 1; return; }           // past the end: the position stays on the last slot
-            const StreamShare s = stream_share(sm.m[jj], wg, G);
-            if (s.n == 0) continue;
-            l = ll; j = jj; units = s.n; left = kcn = s.kcn;
-            const size_t first = (size_t)(jj == 4 ? sm.lm : sm.base + (size_t)ll * sm.layer_stride + sm.m[jj].off);
-            unit = cur = uni(first + ((size_t)s.rb0 * sm.m[jj].KC + s.kc0) * 1024);
-            step = (size_t)s.step * sm.m[jj].KC * 1024;
-            return;
-        }
-    }
-    __device__ __forceinline__ void next(const StreamModel &sm, int wg, int G) {
-        if (left == 0x7FFFFFFF) return;
-        left -= kFusedWaves;
-        if (left > 0) { cur += kStreamSlotBytes; return; }
-        if (--units > 0) { unit += step; cur = unit; left = kcn; return; }
-        enter(sm, l, j + 1, wg, G);
-    }
-};
 
 typedef u32x4_t StreamRing[kFusedWaves][64];
 
 // Request this fetching wave's tiles of the slot at the list position into the ring slot at LDS address `lds`.  Tiles past the
 // end of a unit re-read its last tile (they meet zeros in the multiply), so that every slot is the same number of loads and the
-// wait counts stay fixed.
+// wait counts stay fixed; so do the slots requested past the end of the list.
 __device__ __forceinline__ void stream_issue(const StreamList &pos, uint32_t lds, int p, int lane) {
     const bf16_t *base = reinterpret_cast<const bf16_t *>(uni(pos.cur));
-    const int last = min(uni(pos.left), kFusedWaves) - 1;
 #pragma unroll
     for (int q = 0; q < kStreamLoads; ++q) {
         const int tile = p + kStreamProducers * q;
-        request_tile<true>(base, (uint32_t)(min(tile, last) * 1024 + lane * 16), (uint32_t)uni((int)(lds + tile * 1024)));
+        request_tile<true>(base, (uint32_t)(pos.request(tile) * 1024 + lane * 16), (uint32_t)uni((int)(lds + tile * 1024)));
     }
 }
 

@@ -8,6 +8,7 @@
 #define HOST_SHARED static
 #include "rules.hpp"
 #include "state.hpp"
+#include "stream_list.hpp"
 
 using namespace ead;
 
@@ -108,5 +109,49 @@ int host_stream_split(int NB, int KC, int most) {
     return p.slices * 1000 + p.tiles;
 }
 int host_stream_pays(int d, int KV, int layers, int keys) { return stream_pays(d, KV, layers, keys); }
+
+// The fetching waves' list of every workgroup of a model whose matrices lie apart from each other: slots it begins (layers x phases, then the
+// ones requested past the end of the list), each of them the slot the multiplying waves read there and every byte inside the unit.  Returns the
+// bytes requested outside, or -1 where a slot is another one than is read.
+long host_stream_list(int L, const int *NB, const int *KC, const int *ks_log2, const int *KCs, int G) {
+    StreamModel sm{};
+    sm.L = L;
+    size_t at = 0;
+    for (int j = 0; j < 4; ++j) {
+        sm.m[j] = StreamMat{at, NB[j], KC[j], ks_log2[j], KCs[j]};
+        at += (size_t)NB[j] * KC[j] * 512 + 8192;
+    }
+    sm.layer_stride = at;
+    sm.base = (const bf16_t *)0x10000000;
+    sm.m[4] = StreamMat{0, NB[4], KC[4], ks_log2[4], KCs[4]};
+    sm.lm = sm.base + at * L;
+    long outside = 0;
+    for (int wg = 0; wg < G; ++wg) {
+        StreamList pos;
+        pos.enter(sm, 0, 0, wg, G);
+        size_t end = 0;
+        auto take = [&]() {
+            for (int tile = 0; tile < kFusedWaves; ++tile) {
+                const size_t last = pos.cur + (size_t)pos.request(tile) * 1024 + 1024;
+                if (last > end) outside += (long)(last - end);
+            }
+            pos.next(sm, wg, G);
+        };
+        for (int l = 0; l < L; ++l)
+            for (int j = 0; j < (l + 1 < L ? 4 : 5); ++j) {
+                const StreamShare s = stream_share(sm.m[j], wg, G);
+                for (int u = 0; u < s.n; ++u)
+                    for (int t = 0; t < s.kcn; t += kFusedWaves) {
+                        const size_t tiles = (size_t)(s.rb0 + u * s.step) * sm.m[j].KC + s.kc0;
+                        const size_t first = (size_t)(j == 4 ? sm.lm : sm.base + l * sm.layer_stride + sm.m[j].off) + tiles * 1024;
+                        if (pos.cur != first + (size_t)t * 1024) return -1;
+                        end = first + (size_t)s.kcn * 1024;
+                        take();
+                    }
+            }
+        for (int i = 0; i < kStreamDepth - 1; ++i) take();      // the ring is filled to the end
+    }
+    return outside;
+}
 
 }  // extern "C"

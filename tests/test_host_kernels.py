@@ -307,3 +307,17 @@ def test_stream_splits_cover_k_and_fit_the_stage(host):
                                                    (896, 2, 24, 1200, 0), (2048, 8, 1, 330, 0), (896, 2, 6, 330, 0), (2048, 8, 16, 4096, 0)])
 def test_one_row_streams_where_that_is_faster(host, d, KV, layers, keys, pays):
     assert host.host_stream_pays(d, KV, layers, keys) == pays
+
+
+@pytest.mark.parametrize("KC", [1, 7, 8, 9, 28, 31, 33, 34, 35, 37, 38, 64, 161])
+@pytest.mark.parametrize("G,NB", [(256, (72, 56, 608, 56, 8192)), (256, (160, 128, 256, 128, 257)), (8, (3, 2, 9, 8, 8)), (8, (24, 17, 31, 1, 9))])
+def test_stream_requests_stay_inside_the_matrices(host, KC, G, NB):
+    """Every matrix of KC k tiles, whole or in two or four slices; the list ends inside the LM head or, for workgroups without a unit of it, before."""
+    host.host_stream_list.restype = C.c_long
+    ints = lambda v: (C.c_int * 5)(*v)
+    for ks in range(3):
+        tiles = KC if ks == 0 else (KC + (8 << ks) - 1) // (8 << ks) * 8
+        if tiles * ((1 << ks) - 1) >= KC:
+            continue
+        cut = [ks, ks, 0, ks, 0]
+        assert host.host_stream_list(2, ints(NB), ints([KC] * 5), ints(cut), ints([tiles if c else KC for c in cut]), G) == 0
