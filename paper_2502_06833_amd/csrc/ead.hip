@@ -1005,32 +1005,16 @@ void *stream_kernel_for(const Model &m) {
     if (m.hd == 128 && G == 6) return stream_kernel_ptr<128, 6>();
     return nullptr;
 }
-// columns of activations the streamed kernel's stage holds beside the ring
-size_t stream_stage_cols(const ead_handle *h) {
-    const size_t rest = (size_t)kStreamDepth * kStreamSlotBytes + (2 * kFusedWaves * 16 + 64) * sizeof(float) + 256;
-    return h->lds_per_block > rest ? (h->lds_per_block - rest) / 6 - 8 : 0;      // three half-precision terms a column
-}
 size_t stream_lds_bytes(const StreamModel &sm, const Model &m) {
     size_t stage = ((size_t)(m.H / m.KV + 1 + kFusedWaves) * m.hd + 2 * kFusedWaves) * sizeof(float);      // the attention phase's
     for (int j = 0; j < 5; ++j) stage = std::max(stage, ((size_t)sm.m[j].KCs * 32 + 8) * 6);
     return (size_t)kStreamDepth * kStreamSlotBytes + (2 * kFusedWaves * 16 + 64) * sizeof(float) + ((stage + 15) & ~(size_t)15);
 }
-// The streamed kernel's view of a model and the regions of its exchange; false where a slice does not fit the stage.
+// The streamed kernel's view of a model and the regions of its exchange; false where it does not serve the model.
 bool stream_model(const ead_handle *h, const Model &m, StreamModel *sm, StreamExchange *ex) {
-    const int NQ = m.H * m.hd, NK = m.KV * m.hd;
-    sm->base = (const bf16_t *)m.arena; sm->layer_stride = m.layer_elems; sm->lm = (const bf16_t *)m.lm_head; sm->L = m.L;
-    const int rows[5] = {NQ + 2 * NK, m.d, 2 * m.F, m.d, m.V}, cols[5] = {m.d, NQ, m.d, m.F, m.d};
-    for (int j = 0; j < 5; ++j) {
-        StreamMat &t = sm->m[j];
-        t.off = j < 4 ? m.mat_off[j] : 0; t.NB = rows[j] / 16; t.KC = cols[j] / 32;
-        const bool cut = j == 0 || j == 1 || j == 3;      // gate/up and the LM head need whole sums
-        const StreamSplit sp = cut ? stream_split(t.NB, t.KC, h->fused_grid, (int)stream_stage_cols(h)) : StreamSplit{1, t.KC};
-        if (!sp.slices || (size_t)sp.tiles * 32 > stream_stage_cols(h) || sp.tiles * 32 > kStreamStage * 4 * kFusedThreads) return false;
-        t.ks_log2 = sp.slices == 4 ? 2 : sp.slices - 1; t.KCs = sp.tiles;
-    }
-    if (std::max(sm->m[2].NB, sm->m[4].NB) < h->fused_grid) return false;      // a workgroup without any unit has nothing to fetch
-    ex->qkv = 0; ex->att = (NQ + 2 * NK) << sm->m[0].ks_log2; ex->ml = ex->att + NQ * kFusedMaxSplits; ex->o = ex->ml + m.H * kFusedMaxSplits * 2;
-    ex->h = ex->o + (m.d << sm->m[1].ks_log2); ex->down = ex->h + m.F; ex->layer_words = ex->down + (m.d << sm->m[3].ks_log2);
+    if (!stream_plan(StreamDims{m.d, m.H, m.KV, m.hd, m.F, m.V, m.L}, h->fused_grid, h->lds_per_block, sm, ex)) return false;
+    sm->base = (const bf16_t *)m.arena; sm->layer_stride = m.layer_elems; sm->lm = (const bf16_t *)m.lm_head;
+    for (int j = 0; j < 4; ++j) sm->m[j].off = m.mat_off[j];
     return true;
 }
 
@@ -1978,8 +1962,7 @@ ead_status ead_create(const ead_model_desc *small_model, const ead_model_desc *l
                               per_cu >= 1 && md.KV * kFusedMaxSplits <= h->fused_grid;
                 void *sfn = stream_kernel_for(md);
                 per_cu = 0;
-                md.stream_ok = sfn && h->turn_ev && md.d <= kStreamMaxWidth && md.KV * kFusedMaxSplits <= h->fused_grid &&
-                               stream_model(h, md, &md.stream_model, &md.stream_ex);
+                md.stream_ok = sfn && h->turn_ev && stream_model(h, md, &md.stream_model, &md.stream_ex);
                 const size_t slds = md.stream_ok ? stream_lds_bytes(md.stream_model, md) : 0;
                 md.stream_ok = md.stream_ok && slds <= h->lds_per_block &&
                                hipFuncSetAttribute(sfn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)slds) == hipSuccess &&

@@ -15,7 +15,10 @@ static_assert(kStreamLoads * (kStreamDepth - 1) <= 63, "outstanding loads must f
 constexpr int kStreamPieces = 3;                 // float4 pieces of the residual stream per thread
 constexpr int kStreamMaxWidth = kStreamPieces * 4 * kFusedThreads;      // d_model this kernel serves
 constexpr int kStreamMaxSlices = 4;              // slices of K a matrix may be cut into
-constexpr int kStreamStage = 8;                  // float4 pieces of any other vector a thread stages at once
+constexpr int kStreamStage = 8;                  // float4 pieces of the SwiGLU products a thread stages at once
+// columns of a slice of matrix j (StreamModel) that the routine staging its activations holds in registers: the attention output comes in as many
+// pieces as the residual stream
+constexpr int stream_stage_most(int j) { return 4 * kFusedThreads * (j == 3 ? kStreamStage : kStreamPieces); }
 
 // How a matrix is split: row blocks, tiles of a row block, slices of K (a power of two) and tiles of a slice (the last may be shorter).
 struct StreamMat { size_t off; int NB, KC, ks_log2, KCs; };
@@ -33,6 +36,37 @@ struct StreamExchange {
     int layer_words, total_words;            // of this model's layers; of both buffers as a whole
     int qkv, att, ml, o, h, down;            // region offsets inside a layer
 };
+
+// columns of activations the stage holds beside the ring (three half-precision terms a column), of `lds` bytes a workgroup may have
+inline int stream_stage_cols(size_t lds) {
+    const size_t rest = (size_t)kStreamDepth * kStreamSlotBytes + (2 * kFusedWaves * 16 + 64) * sizeof(float) + 256;
+    return lds > rest ? std::max(0, (int)((lds - rest) / 6) - 8) : 0;
+}
+
+struct StreamDims { int d, H, KV, hd, F, V, L; };
+
+// How k_decode_stream takes a model on `grid` workgroups of `lds` bytes (all but where the weights are), and the regions of its exchange; false
+// where it does not serve it: the key splits of all KV heads need workgroups of their own, a slice of K has to fit the stage and the
+// registers of the routine that stages it, and every workgroup needs a unit of some matrix.
+inline bool stream_plan(const StreamDims &q, int grid, size_t lds, StreamModel *sm, StreamExchange *ex) {
+    const int NQ = q.H * q.hd, NK = q.KV * q.hd, stage = stream_stage_cols(lds);
+    if (q.d > kStreamMaxWidth || q.KV * kFusedMaxSplits > grid) return false;
+    sm->L = q.L;
+    const int rows[5] = {NQ + 2 * NK, q.d, 2 * q.F, q.d, q.V}, cols[5] = {q.d, NQ, q.d, q.F, q.d};
+    for (int j = 0; j < 5; ++j) {
+        StreamMat &t = sm->m[j];
+        t.off = 0; t.NB = rows[j] / 16; t.KC = cols[j] / 32;
+        const int most = std::min(stage, stream_stage_most(j));
+        const bool cut = j == 0 || j == 1 || j == 3;      // gate/up and the LM head need whole sums
+        const StreamSplit sp = cut ? stream_split(t.NB, t.KC, grid, most) : StreamSplit{1, t.KC};
+        if (!sp.slices || sp.tiles * 32 > most) return false;
+        t.ks_log2 = sp.slices == 4 ? 2 : sp.slices - 1; t.KCs = sp.tiles;
+    }
+    if (std::max(sm->m[2].NB, sm->m[4].NB) < grid) return false;      // a workgroup without any unit has nothing to fetch
+    ex->qkv = 0; ex->att = (NQ + 2 * NK) << sm->m[0].ks_log2; ex->ml = ex->att + NQ * kFusedMaxSplits; ex->o = ex->ml + q.H * kFusedMaxSplits * 2;
+    ex->h = ex->o + (q.d << sm->m[1].ks_log2); ex->down = ex->h + q.F; ex->layer_words = ex->down + (q.d << sm->m[3].ks_log2);
+    return true;
+}
 
 // A workgroup's share of a matrix: which slice, how many row blocks, from which one on, how far apart; the slice's tiles.
 struct StreamShare { int slice, rb0, step, n, kc0, kcn; };

@@ -154,4 +154,10 @@ long host_stream_list(int L, const int *NB, const int *KC, const int *ks_log2, c
     return outside;
 }
 
+// 160 KB of LDS, 256 workgroups: a slice's columns of matrix j, 0 where the model is not taken
+int host_stream_slice(int d, int H, int KV, int hd, int F, int j) {
+    StreamModel sm{}; StreamExchange ex{};
+    return stream_plan(StreamDims{d, H, KV, hd, F, 128256, 16}, 256, (size_t)160 << 10, &sm, &ex) ? sm.m[j].KCs * 32 : 0;
+}
+
 }  // extern "C"

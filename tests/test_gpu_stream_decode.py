@@ -21,11 +21,29 @@ def test_replay_matches_the_oracle_and_the_per_layer_kernels(name, layers, d, he
     """Entropies along a trajectory within 1e-2 nats of the oracle, from the first key on and across 64-key splits, and within 2e-3 of the per-layer kernels: both keep
     float32 activations, but another order of sums moves a cached key or value to its other bf16 neighbour (2^-8 of it), and what two kernel families differ by
     for that reason is bounded by 7e-3 of the row maximum in the logits, 2e-3 nats."""
+    _check_replay(si.ModelShape("stream-" + name, layers, d, heads, kv, ffn, 4112, 1e-5, 1e4))
+
+
+class Head128(si.ModelShape):
+    head_dim = 128
+
+
+@pytest.mark.parametrize("d,heads,kv", [(4096, 56, 14), (2048, 100, 25)])
+def test_attention_output_of_more_columns_than_a_workgroup_stages_at_once(d, heads, kv):
+    """7168 and 12800 columns, in two slices of the output projection's K and in four."""
+    _check_replay(Head128(f"stream-wide-{heads}", 1, d, heads, kv, 1056, 4112, 1e-5, 1e4))
+
+
+def _check_replay(shape):
     import paper_2502_06833_amd as ead
-    shape = si.ModelShape("stream-" + name, layers, d, heads, kv, ffn, 4112, 1e-5, 1e4)
     other = si.ModelShape("stream-other", 1, 128, 4, 4, 128, 4112, 1e-5, 1e4)
     W, Wo, om, _ = make_pair(shape, other, gain_std=0.2, lm_sigma=1.5)
     e = ead.EAD(shape, W, other, Wo, window=5, tau=0.0, d_min=4, max_batch=1, max_seq=160)
+    e.set_fused(1)
+    e.profile(True)
+    e.replay([si.prompt_np(0, "taken", 1, shape.vocab)], np.zeros((1, 2), np.int32), np.zeros((1, 2), np.uint8))
+    assert any("decode_fused" in p["name"] for p in e.profile_read())      # the kernel serves this shape
+    e.profile(False)
     for P, n in ((1, 6), (60, 8), (125, 10)):
         toks = si.prompt_np(0, f"s{P}", P + n, shape.vocab)
         got = {}

@@ -321,3 +321,20 @@ def test_stream_requests_stay_inside_the_matrices(host, KC, G, NB):
             continue
         cut = [ks, ks, 0, ks, 0]
         assert host.host_stream_list(2, ints(NB), ints([KC] * 5), ints(cut), ints([tiles if c else KC for c in cut]), G) == 0
+
+
+def test_stream_stages_whole_slices(host):
+    """A thread of the 512 that stage holds 3 x 4 columns of the residual stream and of the attention output, 8 x 4 of the SwiGLU products; every
+    width of attention output the kernel is built for (heads x head_dim up to 15360), whatever d_model is."""
+    taken = 0
+    for hd, G in ((64, 4), (128, 4), (64, 7), (128, 3), (128, 5), (128, 6)):
+        for KV in range(1, 33):
+            if G * KV * hd > 15360:
+                continue
+            for d in list(range(256, 6145, 448)) + [2048, 3584, 4096, 6144]:
+                for F in (1024, 14336, 15360):
+                    cols = [host.host_stream_slice(d, G * KV, KV, hd, F, j) for j in range(5)]
+                    taken += cols[0] > 0
+                    assert max(cols[0], cols[1], cols[2], cols[4]) <= 3 * 4 * 512 and cols[3] <= 8 * 4 * 512, (hd, G, KV, d, F)
+    assert taken > 1000
+    assert host.host_stream_slice(4096, 56, 14, 128, 1024, 1) == 3584        # two slices where one of 7168 would fit the stage
