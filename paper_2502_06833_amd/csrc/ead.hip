@@ -28,6 +28,7 @@
 #include "state.hpp"
 #include "fused.hpp"
 #include "stream.hpp"
+#include "turn.hpp"
 
 using namespace ead;
 
@@ -290,7 +291,7 @@ struct ead_handle {
     LaneSet lanes[2]; int cur_lane = 0, two_lanes = 0; hipStream_t lane1_stream = nullptr;
     // fused single-row decode
     float *att_o; float2 *att_ml; unsigned *bar_mem; int *abort_flag; unsigned bar_epoch = 0; int fused_on = -1, fused_grid = 0;      // fused_on: -1 = k_decode_stream where stream_pays, 0 off, 1 on, 2 on with k_decode_fused
-    int device = -1; hipEvent_t turn_ev = nullptr;      // k_decode_stream: see take_turn
+    int device = -1; hipEvent_t turn_ev = nullptr;      // persistent kernels: see launch_in_turn
     bool lock_step = false;              // decode_impl's own loop is running (its passes may go to k_decode_stream by themselves)
     float *exchange = nullptr; int exchange_words = 0, exchange_turn = 0;      // two buffers of exchange_words (k_decode_stream)
     std::vector<void *> allocs;
@@ -1037,35 +1038,30 @@ FinArgs make_fin(ead_handle *h, int m, bool score) {
     return fa;
 }
 
-// k_decode_stream needs all its workgroups resident, one per compute unit, so two of them must not start side by side: a launch waits for the stream of
-// the handle that launched one last on its device.  (Cooperative launches would see to that as well, but each takes 17 us, and the runtime's queue for them takes
-// one of the few that the streams of two-lane handles are spread over: their passes then ran 9 % slower in a process that had made one.)  Other
-// kernels may hold units for a while, since they end by themselves; another process's k_decode_stream is what the bounded waits are for.  A
-// handle holds the turn only inside ead_decode and its like, which end by waiting for its streams.
-struct StreamTurn { ead_handle *holder; hipStream_t stream; };
+// The persistent kernels need all their workgroups resident, one per compute unit: see LaunchTurns.  (Cooperative launches would see to that for k_decode_stream as
+// well, but each takes 17 us, and the runtime's queue for them takes one of the few that the streams of two-lane handles are spread over: their passes then ran
+// 9 % slower in a process that had made one.)  Other kernels may hold units for a while, since they end by themselves; another process's persistent kernel is what
+// the bounded waits are for.  A handle holds the turn only inside ead_decode and its like, which end by waiting for its streams.
 constexpr int kTurnDevices = 64;
-StreamTurn g_turn[kTurnDevices];
-std::mutex g_turn_mutex;
+LaunchTurns<hipStream_t, kTurnDevices> g_turns;
 
-ead_status take_turn(ead_handle *h) {
-    std::lock_guard<std::mutex> lock(g_turn_mutex);
-    StreamTurn &t = g_turn[h->device];
-    if (t.holder && (t.holder != h || t.stream != h->stream)) {
-        HIP_TRY(h, hipEventRecord(h->turn_ev, t.stream));
+// launch() on the current lane's stream, when the turn has come to this handle
+template <typename Launch>
+ead_status launch_in_turn(ead_handle *h, Launch launch) {
+    if (h->device < 0) return launch();
+    return g_turns.launch(h->device, h, h->stream, [h](hipStream_t last) -> ead_status {
+        HIP_TRY(h, hipEventRecord(h->turn_ev, last));
         HIP_TRY(h, hipStreamWaitEvent(h->stream, h->turn_ev, 0));
-    }
-    t = StreamTurn{h, h->stream};
-    return EAD_OK;
+        return EAD_OK;
+    }, launch);
 }
 // Gives the turn back, once the handle's launches are over.
 void end_turn(ead_handle *h) {
     if (h->device < 0) return;
-    const auto held = [&] { return g_turn[h->device].holder == h; };
-    { std::lock_guard<std::mutex> lock(g_turn_mutex); if (!held()) return; }
-    (void)hipStreamSynchronize(h->lanes[0].stream);
-    if (h->two_lanes) (void)hipStreamSynchronize(h->lanes[1].stream);
-    std::lock_guard<std::mutex> lock(g_turn_mutex);
-    if (held()) g_turn[h->device] = StreamTurn{};
+    g_turns.end(h->device, h, [h] {
+        (void)hipStreamSynchronize(h->lanes[0].stream);
+        if (h->two_lanes) (void)hipStreamSynchronize(h->lanes[1].stream);
+    });
 }
 
 template <typename WT>
@@ -1086,16 +1082,21 @@ ead_status fused_step(ead_handle *h, int mi, double keys) {
             ex.now = h->exchange + (size_t)h->exchange_turn * h->exchange_words; ex.next = h->exchange + (size_t)(1 - h->exchange_turn) * h->exchange_words;
             ex.total_words = h->exchange_words;
             void *sargs[] = {&a, &m.stream_model, &ex};
-            TRY(take_turn(h));
-            HIP_TRY(h, hipLaunchKernel(stream_kernel_for(m), dim3(h->fused_grid), dim3(kStreamThreads), sargs, stream_lds_bytes(m.stream_model, m), h->stream));
+            TRY(launch_in_turn(h, [&]() -> ead_status {
+                HIP_TRY(h, hipLaunchKernel(stream_kernel_for(m), dim3(h->fused_grid), dim3(kStreamThreads), sargs, stream_lds_bytes(m.stream_model, m), h->stream));
+                return EAD_OK;
+            }));
             h->exchange_turn ^= 1;
             h->bar_epoch += 1u;
             return EAD_OK;
         }
     }
     void *args[] = {&a};
-    HIP_TRY(h, hipLaunchCooperativeKernel(fused_kernel_for(m), dim3(h->fused_grid), dim3(kFusedThreads), args,
-                                          (unsigned)fused_lds_bytes(m), h->stream));
+    TRY(launch_in_turn(h, [&]() -> ead_status {
+        HIP_TRY(h, hipLaunchCooperativeKernel(fused_kernel_for(m), dim3(h->fused_grid), dim3(kFusedThreads), args,
+                                              (unsigned)fused_lds_bytes(m), h->stream));
+        return EAD_OK;
+    }));
     h->bar_epoch += 5u * m.L + 1u;
     return EAD_OK;
 }

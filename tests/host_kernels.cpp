@@ -9,6 +9,9 @@
 #include "rules.hpp"
 #include "state.hpp"
 #include "stream_list.hpp"
+#include "turn.hpp"
+#include <atomic>
+#include <chrono>
 
 using namespace ead;
 
@@ -158,6 +161,43 @@ long host_stream_list(int L, const int *NB, const int *KC, const int *ks_log2, c
 int host_stream_slice(int d, int H, int KV, int hd, int F, int j) {
     StreamModel sm{}; StreamExchange ex{};
     return stream_plan(StreamDims{d, H, KV, hd, F, 128256, 16}, 256, (size_t)160 << 10, &sm, &ex) ? sm.m[j].KCs * 32 : 0;
+}
+
+// `n` handles in threads of their own, each launching `times` on its stream: launches that another handle's stream was queued after without having
+// waited for them, + 1000000 per launch that the last holder had not ended with.
+int host_turns(int n, int times) {
+    LaunchTurns<int, 2> turns;
+    std::vector<std::atomic<int>> queued(n), seen(n);      // launches on a stream; how many of the last one's the stream that waited last has seen
+    std::atomic<int> last{-1}, bad{0};
+    std::vector<std::thread> pool;
+    for (int i = 0; i < n; ++i)
+        pool.emplace_back([&, i] {
+            for (int k = 0; k < times; ++k) {
+                const int rc = turns.launch(1, &queued[i], i, [&](int on) { seen[i] = on * 10000 + queued[on]; return 0; }, [&] {
+                    std::this_thread::sleep_for(std::chrono::microseconds(300));       // a launch takes a while before it is queued
+                    const int before = last;
+                    if (before >= 0 && before != i && seen[i] != before * 10000 + queued[before]) ++bad;
+                    ++queued[i]; last = i;
+                    return 0;
+                });
+                if (rc) ++bad;
+            }
+        });
+    for (auto &t : pool) t.join();
+    for (int i = 0; i < n; ++i) turns.end(1, &queued[i], [&] { if (last != i) bad += 1000000; last = -1; });
+    return bad;
+}
+
+// a refused launch leaves the turn where it was, so that the next handle waits for the launch that did run
+int host_turn_refused() {
+    LaunchTurns<int, 1> turns;
+    int a, b, c, waited = -1;
+    const auto wait = [&](int on) { waited = on; return 0; };
+    turns.launch(0, &a, 7, wait, [] { return 0; });
+    if (waited != -1 || turns.launch(0, &b, 8, wait, [] { return 5; }) != 5 || waited != 7) return -1;
+    waited = -1;
+    turns.launch(0, &c, 9, wait, [] { return 0; });
+    return waited;
 }
 
 }  // extern "C"

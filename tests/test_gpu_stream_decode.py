@@ -85,7 +85,8 @@ def test_taken_by_itself_and_switched_off():
     e.close()
 
 
-def test_two_handles_in_two_threads():
+@pytest.mark.parametrize("other", ["streamed", "register-buffered"])
+def test_two_handles_in_two_threads(other):
     """Persistent kernels of two handles on streams of their own: one starts after the other's has ended, and both finish with the tokens of a run alone."""
     import torch
     import paper_2502_06833_amd as ead
@@ -95,6 +96,8 @@ def test_two_handles_in_two_threads():
     for i in range(2):
         with torch.cuda.stream(streams[i]):
             handles.append(ead.EAD(DEEP, Ws, FLAT, Wl, window=3, tau=7.2, d_min=2, max_batch=1, max_seq=96))
+    if other == "register-buffered":
+        handles[1].set_fused(2)
     want = [handles[i].generate([prompts[i]], 32) for i in range(2)]
     got = [[], []]
 

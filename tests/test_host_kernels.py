@@ -338,3 +338,10 @@ def test_stream_stages_whole_slices(host):
                     assert max(cols[0], cols[1], cols[2], cols[4]) <= 3 * 4 * 512 and cols[3] <= 8 * 4 * 512, (hd, G, KV, d, F)
     assert taken > 1000
     assert host.host_stream_slice(4096, 56, 14, 128, 1024, 1) == 3584        # two slices where one of 7168 would fit the stage
+
+
+@pytest.mark.parametrize("handles", [1, 2, 3, 8])
+def test_persistent_launches_wait_for_each_other(host, handles):
+    """A launch is queued behind all earlier ones on the device, whichever handle made them."""
+    assert host.host_turns(handles, 60) == 0
+    assert host.host_turn_refused() == 7
