@@ -717,7 +717,10 @@ void launch_mfma(ead_handle *h, int mi, LinArgs<bf16_t> &a, int T) {
         const bool split = EPI != EPI_SWIGLU && big && (!multi || (sw == 2 && a.K >= 256 * 32));
         if (multi && !split) {
             const int sg = (TB + kGemmTok - 1) / kGemmTok, NG16 = (NB + kTileBlocks - 1) / kTileBlocks, KC = a.K / 32;
-            const TilePlan tp = tile_plan(NG16, sg, KC, n_cu, EPI != EPI_SWIGLU, kTileSplitFloats);
+            // where the kernel of the slabs is refused its LDS, the other takes all sweeps (the plan decides which launches there are)
+            bool may_split = false;
+            if constexpr (EPI != EPI_SWIGLU) may_split = kTileLdsBytes <= h->lds_per_block && allow_big_lds((const void *)k_linear_mfma_tile<EPI, true>, kTileLdsBytes);
+            const TilePlan tp = tile_plan(NG16, sg, KC, n_cu, may_split, kTileSplitFloats);
             const long cost_gemm = (((long)NG * sg + n_cu - 1) / n_cu) * 1150, cost_tile = tp.cost / KC;
             const void *gemm = (const void *)k_linear_mfma_gemm<EPI>, *tile = (const void *)k_linear_mfma_tile<EPI>;
             if (cost_tile < cost_gemm && cost_tile < cost_of(rg) && kTileLdsBytes <= h->lds_per_block && allow_big_lds(tile, kTileLdsBytes)) {
@@ -728,7 +731,7 @@ void launch_mfma(ead_handle *h, int mi, LinArgs<bf16_t> &a, int T) {
                     hipLaunchKernelGGL((k_linear_mfma_tile<EPI>), dim3((NG16 * tp.whole + 7) / 8 * 8), dim3(512), kTileLdsBytes, h->stream, a);
                 }
                 if constexpr (EPI != EPI_SWIGLU) {
-                    if (tp.whole < sg && allow_big_lds((const void *)k_linear_mfma_tile<EPI, true>, kTileLdsBytes)) {
+                    if (tp.whole < sg) {
                         a.tb_base = tp.whole * kTileBlocks; a.tile_sweeps = sg - tp.whole; a.sweeps = spread(a.tile_sweeps); a.KS = tp.KS; a.sk_part = h->sk_part;
                         hipLaunchKernelGGL((k_linear_mfma_tile<EPI, true>), dim3((NG16 * a.tile_sweeps * tp.KS + 7) / 8 * 8), dim3(512), kTileLdsBytes, h->stream, a);
                         hipLaunchKernelGGL((k_sk_merge<EPI, 0>), dim3((NB * a.tile_sweeps * kTileBlocks + 3) / 4), dim3(256), 0, h->stream, a, NG16 * kTileBlocks);
