@@ -655,7 +655,7 @@ void launch_narrow(ead_handle *h, LinArgs<bf16_t> &a, int T) {
 #undef EAD_LM
 }
 
-// The LM head: writes one partial per (row, workgroup) and returns their number per row (0: no LDS for k_lm_ls).  Through
+// The LM head: writes one partial per (row, workgroup) and returns their number per row.  Through
 // k_lm_ls, 128 rows per sweep: its fetching waves' non-temporal loads bring 7.2 TB/s (us at 32 rows with the register ring
 // of k_linear_mfma / this way: 128256 x 4096 188 / 166, x 3072 133 / 124; 151936 x 5120 263 / 243; at 12 rows 171 / 167, 249 / 242, 151936 x 1536 85.8 / 79.2,
 // 128256 x 2048 90.9 / 88.3).  But one token block of K between 2048 and 4096 stays with k_linear_mfma (128256 x 3072 at 3 and 12 rows 121.6 and 130.4
@@ -674,7 +674,7 @@ int launch_lm(ead_handle *h, int mi, LinArgs<bf16_t> &a, int T) {
         }
         if (ok) return grid;
     }
-    if (TB > 1) return 0;
+    // (also what serves, a token block after the other, where k_lm_ls is refused its LDS)
     const int grid = std::min((NB + 1) / 2, 2 * h->n_cu);
     hipLaunchKernelGGL((k_linear_mfma<2, 2, 1, 8, EPI_LOGITS, false>), dim3(grid), dim3(128), 0, h->stream, a);
     return grid;
@@ -937,7 +937,6 @@ ead_status forward_pass(ead_handle *h, int mi, int T, int n_lm, int ctx_max, boo
                 launch_pack(h, mi, PackArgs{h->x, d, n_lm, h->plan.lm_row, m.g_final, m.eps, h->xp_a, d});
                 g.xp = h->xp_a;
                 h->lm_n_part = launch_lm(h, mi, g, n_lm);
-                if (!h->lm_n_part) return fail(h, EAD_ERR_DEVICE, "the device does not grant %zu bytes of LDS to a workgroup", kLmLdsBytes);
             }
         } else {
             g.x = h->x; g.ldx = d; g.gain = m.g_final; g.eps = m.eps;
