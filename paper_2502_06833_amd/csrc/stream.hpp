@@ -540,13 +540,12 @@ __global__ __launch_bounds__(kStreamThreads) void k_decode_stream(FusedArgs<bf16
     extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
     StreamRing *ring = reinterpret_cast<StreamRing *>(smem_raw);
     float *smem = reinterpret_cast<float *>(smem_raw + (size_t)kStreamDepth * kStreamSlotBytes);
-    __shared__ int s_plan[4];        // seq, pos, token
+    __shared__ int s_plan[4];        // seq, pos, token, whether to go on
     __shared__ int s_ok;
     __shared__ float s_red[kFusedWaves], s_max[kFusedWaves];
     float *red = smem, *zeros = red + 2 * kFusedWaves * 16, *xs = zeros + 64;       // 64 zeros
     const uint16_t *xzero = reinterpret_cast<const uint16_t *>(zeros);
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    if (uni(ld_coherent(a.bar.abort_flag))) return;      // an earlier launch was given up: its exchange is in no defined state
 
     if (wave >= kFusedWaves) {
         // ---- fetching waves ------------------------------------------------------------------
@@ -561,6 +560,7 @@ __global__ __launch_bounds__(kStreamThreads) void k_decode_stream(FusedArgs<bf16
             ri = ri + 1 == kStreamDepth ? 0 : ri + 1;
         }
         __syncthreads();                    // the consuming waves have set up their constants
+        if (!uni(s_plan[3])) { wait_stores(); return; }      // (nothing may land in LDS after the workgroup has gone)
         // the consuming waves' phases, one by one: arrive where they meet, hand over a slot where they read one
         for (int l = 0; l <= sm.L; ++l)
             for (int kind = l < sm.L ? 0 : 5; kind < (l < sm.L ? 5 : 6); ++kind) {
@@ -586,13 +586,18 @@ __global__ __launch_bounds__(kStreamThreads) void k_decode_stream(FusedArgs<bf16
     const int m = a.fin.model_id, MB = a.fin.s.max_batch;
     // the one sequence this model serves in this step, and its newest position
     if (tid == 0) {
+        // Given up, in an earlier launch (the exchange is in no defined state then) or in this one while this workgroup was starting?  One
+        // thread looks, for all waves: where each looks by itself, some can leave and others go on with a plan that nobody has written.
+        const int given_up = ld_coherent(a.bar.abort_flag);
         int seq = 0;
         for (int b = 0; b < a.batch; ++b)
             if (!a.fin.s.done[b] && a.fin.s.model[b] == m && a.fin.s.last_step[b] != a.fin.step) { seq = b; break; }
         const int pos = a.fin.s.kvlen[m * MB + seq];
         s_plan[0] = seq; s_plan[1] = pos; s_plan[2] = a.fin.s.tokens[(size_t)seq * a.fin.s.max_seq + pos];
+        s_plan[3] = !given_up;
     }
     __syncthreads();
+    if (!uni(s_plan[3])) return;
     BlockSync sync;
     StreamPos sp{0, 0};
     const int seq = uni(s_plan[0]), pos = uni(s_plan[1]);
