@@ -290,7 +290,7 @@ struct ead_handle {
     char *h_copy = nullptr; hipEvent_t copy_ev[kCopySlots] = {}; bool copy_ready = false;      // pinned pieces of a long copy (make_copy_slots, copy_out)
     LaneSet lanes[2]; int cur_lane = 0, two_lanes = 0; hipStream_t lane1_stream = nullptr;
     // fused single-row decode
-    float *att_o; float2 *att_ml; unsigned *bar_mem; int *abort_flag; unsigned bar_epoch = 0; int fused_on = -1, fused_grid = 0;      // fused_on: -1 = k_decode_stream where stream_pays, 0 off, 1 on, 2 on with k_decode_fused
+    float *att_o; float2 *att_ml; unsigned *bar_mem; int *abort_flag; unsigned bar_epoch = 0; int fused_on = -1, fused_grid = 0, spin_limit = kFusedSpinLimit;      // fused_on: -1 = k_decode_stream where stream_pays, 0 off, 1 on, 2 on with k_decode_fused
     int device = -1; hipEvent_t turn_ev = nullptr;      // persistent kernels: see launch_in_turn
     bool lock_step = false;              // decode_impl's own loop is running (its passes may go to k_decode_stream by themselves)
     float *exchange = nullptr; int exchange_words = 0, exchange_turn = 0;      // two buffers of exchange_words (k_decode_stream)
@@ -1074,7 +1074,7 @@ ead_status fused_step(ead_handle *h, int mi, double keys) {
     a.mats = (const FusedMat<WT> *)m.fused_mats; a.layers = (const FusedLayer<WT> *)m.fused_layers; a.n_mats = m.n_mats;
     a.embed = (const WT *)m.embed; a.g_final = m.g_final; a.rope = m.rope;
     a.x = h->x; a.q = h->q; a.hbuf = h->hbuf; a.att_o = h->att_o; a.att_ml = h->att_ml; a.lm_part = h->lm_part;
-    a.bar = GridBar{h->bar_mem, h->bar_mem + kBarGroups * 32, h->abort_flag, h->bar_epoch};
+    a.bar = GridBar{h->bar_mem, h->bar_mem + kBarGroups * 32, h->abort_flag, h->bar_epoch, h->spin_limit};
     a.fin = make_fin(h, mi, false);
     a.batch = h->batch;
     ProfScope ps(h, PK_FUSED, mi, m.weight_bytes_nolm + m.lm_bytes + keys * m.kv_bytes_per_pos);
@@ -2220,6 +2220,13 @@ ead_status ead_profile_read(ead_handle *h, ead_kernel_profile *out, int32_t capa
         ++n;
     }
     *n_out = n;
+    return EAD_OK;
+}
+
+// For the tests alone, in no header: polls after which the persistent kernels give up a wait, and with it the launch.
+ead_status ead_test_spin_limit(ead_handle *h, int32_t polls) {
+    if (!h) return EAD_ERR_INVALID_ARG;
+    h->spin_limit = polls < 0 ? kFusedSpinLimit : polls;
     return EAD_OK;
 }
 

@@ -21,7 +21,7 @@
 
 namespace ead {
 
-constexpr long kFusedSpinLimit = 1L << 21;
+constexpr int kFusedSpinLimit = 1 << 21;
 constexpr int kBarGroups = 8;
 constexpr int kFusedRbChunk = 8;     // row blocks between two workgroup synchronisations
 constexpr int kFusedMaxMats = 200;   // 4 per layer + LM head
@@ -39,7 +39,14 @@ constexpr int kFusedMaxMats = 200;   // 4 per layer + LM head
 // ld_coherent, so a barrier only has to wait until the stores have completed.  Weights
 // and gains are immutable and K/V lines are never read before they are written, so those
 // keep using ordinary cached / streaming loads.
-struct GridBar { unsigned *grp, *glob; int *abort_flag; unsigned epoch; };
+// spin_limit: polls a wait makes before it is given up (kFusedSpinLimit, about two seconds).
+struct GridBar { unsigned *grp, *glob; int *abort_flag; unsigned epoch; int spin_limit; };
+
+// The wait is over without what it waited for: what follows in the launch, and the launches after it, must not change a sequence's state.
+__device__ __forceinline__ void give_up(const GridBar &b) {
+    st_coherent(b.abort_flag, 1);
+    wait_stores();
+}
 
 // How the threads that run the phases of a step meet inside their workgroup.  Here: all of them, at
 // the hardware barrier.  The streamed kernel passes a policy of its own, because there the
@@ -64,11 +71,10 @@ template <typename Sync>
 __device__ __forceinline__ bool bar_wait(GridBar &b, int *s_ok, Sync &sync) {
     if (threadIdx.x == 0) {
         const unsigned target = b.epoch * kBarGroups;
-        long spins = 0;
-        int ok = 1;
+        int spins = 0, ok = 1;
         while ((int)(__hip_atomic_load(b.glob, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) - target) < 0) {
-            if (++spins > kFusedSpinLimit || __hip_atomic_load(b.abort_flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) {
-                __hip_atomic_store(b.abort_flag, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (++spins > b.spin_limit || ld_coherent(b.abort_flag)) {
+                give_up(b);
                 ok = 0;
                 break;
             }

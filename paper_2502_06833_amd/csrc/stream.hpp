@@ -88,7 +88,7 @@ __device__ __forceinline__ StreamRsrc exchange_rsrc(float *base, int words) {
 // Waits until the pieces of 16 bytes at byte offsets voff[i] (those that `present` names; a lane that needs none passes an offset another lane
 // reads) of the region at `soff` are all published, and returns them.  False: given up, and nothing may be done with the values.
 template <int N, typename Present>
-__device__ __forceinline__ bool collect(StreamRsrc rsrc, int soff, const int (&voff)[N], Present present, u32x4_t (&v)[N], const int *abort_flag) {
+__device__ __forceinline__ bool collect(StreamRsrc rsrc, int soff, const int (&voff)[N], Present present, u32x4_t (&v)[N], const GridBar &bar) {
     for (int spins = 0;; ++spins) {
 #pragma unroll
         for (int i = 0; i < N; ++i)
@@ -98,7 +98,7 @@ __device__ __forceinline__ bool collect(StreamRsrc rsrc, int soff, const int (&v
         for (int i = 0; i < N; ++i)
             if (present(i)) full = full && v[i].x != kEmptyWord && v[i].y != kEmptyWord && v[i].z != kEmptyWord && v[i].w != kEmptyWord;
         if (__all(full)) return true;
-        if ((spins & 1023) == 1023 && (spins >= (int)kFusedSpinLimit || ld_coherent(abort_flag))) return false;
+        if (spins >= bar.spin_limit || ((spins & 1023) == 1023 && ld_coherent(bar.abort_flag))) return false;
         asm volatile("" ::: "memory");
     }
 }
@@ -137,7 +137,7 @@ __device__ __forceinline__ int fresh_tid() {
 // Thread t of the consuming waves keeps elements (t + i * 512) * 4 .. + 3 of the residual stream in x[i].
 
 // x += the KS slices' sums of `n` rows that lie one behind the other at word `off`
-__device__ __forceinline__ bool add_sums(f32x4e_t (&x)[kStreamPieces], StreamRsrc rsrc, int off, int n, int KS, const int *abort_flag) {
+__device__ __forceinline__ bool add_sums(f32x4e_t (&x)[kStreamPieces], StreamRsrc rsrc, int off, int n, int KS, const GridBar &bar) {
     constexpr int NS = kStreamMaxSlices;
     const int tid = fresh_tid();
     int voff[kStreamPieces * NS];
@@ -146,7 +146,7 @@ __device__ __forceinline__ bool add_sums(f32x4e_t (&x)[kStreamPieces], StreamRsr
     for (int i = 0; i < kStreamPieces; ++i)
 #pragma unroll
         for (int s = 0; s < NS; ++s) voff[i * NS + s] = (s * n + min((tid + i * kFusedThreads) * 4, n - 4)) * 4;
-    if (!collect(rsrc, off * 4, voff, [&](int j) { return j % NS < KS && j / NS * 4 * kFusedThreads < n; }, v, abort_flag)) return false;
+    if (!collect(rsrc, off * 4, voff, [&](int j) { return j % NS < KS && j / NS * 4 * kFusedThreads < n; }, v, bar)) return false;
 #pragma unroll
     for (int i = 0; i < kStreamPieces; ++i)
 #pragma unroll
@@ -228,13 +228,13 @@ __device__ __forceinline__ void load_gain(f32x4e_t (&gn)[kStreamPieces], const f
 }
 
 // The terms of the words [c0, c0 + cn) of the region at word `off`; *factor: what takes the scale back from the sums
-__device__ __forceinline__ bool stage_words(const StreamTerms &xt, float *s_max, StreamRsrc rsrc, int off, int c0, int cn, const int *abort_flag, float *factor) {
+__device__ __forceinline__ bool stage_words(const StreamTerms &xt, float *s_max, StreamRsrc rsrc, int off, int c0, int cn, const GridBar &bar, float *factor) {
     const int tid = fresh_tid();
     int voff[kStreamStage];
     u32x4_t v[kStreamStage];
 #pragma unroll
     for (int i = 0; i < kStreamStage; ++i) voff[i] = (c0 + min((tid + i * kFusedThreads) * 4, cn - 4)) * 4;
-    if (!collect(rsrc, off * 4, voff, [&](int i) { return i * 4 * kFusedThreads < cn; }, v, abort_flag)) return false;
+    if (!collect(rsrc, off * 4, voff, [&](int i) { return i * 4 * kFusedThreads < cn; }, v, bar)) return false;
     float big = 0.f;
 #pragma unroll
     for (int i = 0; i < kStreamStage; ++i)
@@ -253,7 +253,7 @@ __device__ __forceinline__ bool stage_words(const StreamTerms &xt, float *s_max,
 // The terms of columns [c0, c0 + cn) of the attention output: the merge of its S splits' un-normalised results.  A thread takes
 // four neighbouring dimensions of a head at a time.
 template <int HD>
-__device__ __forceinline__ bool stage_attention(const StreamTerms &xt, float *s_max, StreamRsrc rsrc, int att, int ml, int c0, int cn, int S, const int *abort_flag,
+__device__ __forceinline__ bool stage_attention(const StreamTerms &xt, float *s_max, StreamRsrc rsrc, int att, int ml, int c0, int cn, int S, const GridBar &bar,
                                                 float *factor) {
     const int tid = fresh_tid();
     f32x4e_t r[kStreamPieces];
@@ -271,7 +271,7 @@ __device__ __forceinline__ bool stage_attention(const StreamTerms &xt, float *s_
         for (int s = 0; s < NS; ++s) voff[s] = (att + (h * NS + s) * HD + dd) * 4;
 #pragma unroll
         for (int s = 0; s < NS / 2; ++s) voff[NS + s] = (ml + (h * NS + 2 * s) * 2) * 4;
-        if (!collect(rsrc, 0, voff, [&](int j) { return j < NS ? j < S : 2 * (j - NS) < S; }, v, abort_flag)) return false;
+        if (!collect(rsrc, 0, voff, [&](int j) { return j < NS ? j < S : 2 * (j - NS) < S; }, v, bar)) return false;
         const u32x4_t *m4 = v + NS;
         float M = kNegBig;
 #pragma unroll
@@ -406,7 +406,7 @@ __device__ __forceinline__ bool stream_attention(const FusedArgs<bf16_t> &a, con
         u32x4_t w[kStreamMaxSlices];
 #pragma unroll
         for (int s = 0; s < kStreamMaxSlices; ++s) voff[s] = (s * (NQ + 2 * NK) + row) * 4;
-        if (!collect(rsrc, (layer * ex.layer_words + ex.qkv) * 4, voff, [&](int s) { return s < KS; }, w, a.bar.abort_flag)) return false;
+        if (!collect(rsrc, (layer * ex.layer_words + ex.qkv) * 4, voff, [&](int s) { return s < KS; }, w, a.bar)) return false;
         f32x4e_t v = as_floats(w[0]);
 #pragma unroll
         for (int s = 1; s < kStreamMaxSlices; ++s)
@@ -618,7 +618,6 @@ __global__ __launch_bounds__(kStreamThreads) void k_decode_stream(FusedArgs<bf16
 
     // phases: per layer QKV, attention, output projection, gate/up, down; then the LM head.
     // Every workgroup-wide meeting below is counted in the kSync* constants the fetching waves follow.
-    const int *ab = a.bar.abort_flag;
     const int clear_per = (ex.total_words / 4 + a.L * G_ - 1) / (a.L * G_);      // float4 pieces of the other buffer a workgroup empties per layer
     // the terms' rows start 16 bytes apart from a multiple of the banks
     auto terms = [&](const StreamShare &sh) { return StreamTerms{reinterpret_cast<uint16_t *>(xs), sh.kcn * 32 + 8}; };
@@ -631,27 +630,27 @@ __global__ __launch_bounds__(kStreamThreads) void k_decode_stream(FusedArgs<bf16
         {                                       // RMSNorm + QKV
             const StreamShare sh = share(0);
             load_gain(gn, ly.g_attn, a.d);
-            if (l > 0 && !add_sums(x, rsrc, lo - ex.layer_words + ex.down, a.d, 1 << sm.m[3].ks_log2, ab)) { st_coherent(a.bar.abort_flag, 1); return; }
+            if (l > 0 && !add_sums(x, rsrc, lo - ex.layer_words + ex.down, a.d, 1 << sm.m[3].ks_log2, a.bar)) { give_up(a.bar); return; }
             const float inv = stage_norm_x(terms(sh), s_red, s_max, x, gn, a.d, sh.kc0 * 32, sh.kcn * 32, a.eps);
             p.Np = NQ + 2 * NK;
             stream_rows<EPI_QKV>(p, now + ex.qkv, ring, terms(sh), xzero, red, sh, inv, sp, st);
         }
         // rotary + KV append + attention
         if (wg < a.KV * S) {
-            if (!stream_attention<HD, G>(a, ly, rsrc, ex.now, ex, l, 1 << sm.m[0].ks_log2, seq, pos, S, xs)) { st_coherent(a.bar.abort_flag, 1); return; }
+            if (!stream_attention<HD, G>(a, ly, rsrc, ex.now, ex, l, 1 << sm.m[0].ks_log2, seq, pos, S, xs)) { give_up(a.bar); return; }
         } else follow(kSyncAttention);
         {                                       // output projection
             const StreamShare sh = share(1);
             float f = 1.f;
             if (sh.n == 0) follow(kSyncStage);
-            else if (!stage_attention<HD>(terms(sh), s_max, rsrc, lo + ex.att, lo + ex.ml, sh.kc0 * 32, sh.kcn * 32, S, ab, &f)) { st_coherent(a.bar.abort_flag, 1); return; }
+            else if (!stage_attention<HD>(terms(sh), s_max, rsrc, lo + ex.att, lo + ex.ml, sh.kc0 * 32, sh.kcn * 32, S, a.bar, &f)) { give_up(a.bar); return; }
             p.Np = a.d;
             stream_rows<EPI_RES>(p, now + ex.o, ring, terms(sh), xzero, red, sh, f, sp, st);
         }
         {                                       // residual, RMSNorm + gate/up + SwiGLU
             const StreamShare sh = share(2);
             load_gain(gn, ly.g_ffn, a.d);
-            if (!add_sums(x, rsrc, lo + ex.o, a.d, 1 << sm.m[1].ks_log2, ab)) { st_coherent(a.bar.abort_flag, 1); return; }
+            if (!add_sums(x, rsrc, lo + ex.o, a.d, 1 << sm.m[1].ks_log2, a.bar)) { give_up(a.bar); return; }
             const float inv = stage_norm_x(terms(sh), s_red, s_max, x, gn, a.d, sh.kc0 * 32, sh.kcn * 32, a.eps);
             for (int i = tid; i < clear_per; i += kFusedThreads) {
                 const int c = (l * G_ + wg) * clear_per + i;
@@ -664,7 +663,7 @@ __global__ __launch_bounds__(kStreamThreads) void k_decode_stream(FusedArgs<bf16
             const StreamShare sh = share(3);
             float f = 1.f;
             if (sh.n == 0) follow(kSyncStage);
-            else if (!stage_words(terms(sh), s_max, rsrc, lo + ex.h, sh.kc0 * 32, sh.kcn * 32, ab, &f)) { st_coherent(a.bar.abort_flag, 1); return; }
+            else if (!stage_words(terms(sh), s_max, rsrc, lo + ex.h, sh.kc0 * 32, sh.kcn * 32, a.bar, &f)) { give_up(a.bar); return; }
             p.Np = a.d;
             stream_rows<EPI_RES>(p, now + ex.down, ring, terms(sh), xzero, red, sh, f, sp, st);
         }
@@ -672,7 +671,7 @@ __global__ __launch_bounds__(kStreamThreads) void k_decode_stream(FusedArgs<bf16
     {                                           // residual, final RMSNorm + LM head, entropy statistics folded in
         const StreamShare sh = share(4);
         load_gain(gn, a.g_final, a.d);
-        if (!add_sums(x, rsrc, (a.L - 1) * ex.layer_words + ex.down, a.d, 1 << sm.m[3].ks_log2, ab)) { st_coherent(a.bar.abort_flag, 1); return; }
+        if (!add_sums(x, rsrc, (a.L - 1) * ex.layer_words + ex.down, a.d, 1 << sm.m[3].ks_log2, a.bar)) { give_up(a.bar); return; }
         const float inv = stage_norm_x(terms(sh), s_red, s_max, x, gn, a.d, 0, a.d, a.eps);
         LinArgs<WT> p{};
         p.Np = a.V;
@@ -684,7 +683,9 @@ __global__ __launch_bounds__(kStreamThreads) void k_decode_stream(FusedArgs<bf16
     }
     bar_arrive(bar, sync);
     if (!bar_wait(bar, &s_ok, sync)) return;
-    if (blockIdx.x == 0 && wave == 0) {
+    // A wave that gives up leaves alone: the rest of its workgroup goes on, with what that wave would have staged missing, and may arrive here in full
+    // number.  The flag was in memory before the wave was gone, and so before its workgroup could arrive without it.
+    if (blockIdx.x == 0 && wave == 0 && !ld_coherent(a.bar.abort_flag)) {
         EntStat r; r.init();
         for (int i = lane; i < (int)gridDim.x * kFusedWaves; i += 64) {
             EntStat q;

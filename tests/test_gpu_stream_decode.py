@@ -1,4 +1,5 @@
 """GPU: single-row decode steps through the persistent streaming kernel (k_decode_stream), asked for and taken by itself, against the per-layer kernels."""
+import ctypes as C
 import threading
 
 import numpy as np
@@ -83,6 +84,40 @@ def test_taken_by_itself_and_switched_off():
     same = (runs[2]["tokens"] == runs[0]["tokens"])[0].cumprod().astype(bool) & (runs[2]["model_id"] == runs[0]["model_id"])[0].cumprod().astype(bool)
     assert same[:4].all() and np.abs(runs[2]["H"] - runs[0]["H"])[0][same].max() < 2e-3
     e.close()
+
+
+def _spin_limit(e, polls):
+    """Polls after which a wait inside the kernel is given up (negative: as many as ever); every kernel ends normally."""
+    import paper_2502_06833_amd as ead
+    fn = ead.lib().ead_test_spin_limit
+    fn.argtypes = [C.c_void_p, C.c_int32]
+    assert fn(e._h, polls) == 0
+
+
+@pytest.mark.parametrize("polls", [0, 1, 2, 4])
+def test_a_launch_given_up_leaves_no_token(polls):
+    """Waves that give up leave one by one while the rest of their workgroups go on, at other places for every limit and run: the kernels per layer finish the
+    run from the last token that was whole.  Entropies within 2e-3 of those kernels' own run, as long as the tokens are the same (two logits may be close)."""
+    import paper_2502_06833_amd as ead
+    Ws, Wl = _pair()
+    e = ead.EAD(DEEP, Ws, FLAT, Wl, window=3, tau=7.2, d_min=2, max_batch=1, max_seq=96)
+    e.force_model(0)
+    prompt = si.prompt_np(0, "given-up", 40, DEEP.vocab)
+    e.set_fused(False)
+    want = e.generate([prompt], 24)
+    e.close()
+    for _ in range(4):
+        e = ead.EAD(DEEP, Ws, FLAT, Wl, window=3, tau=7.2, d_min=2, max_batch=1, max_seq=96)
+        e.force_model(0)
+        e.begin([prompt], 24)
+        e.decode(3)
+        _spin_limit(e, polls)
+        e.decode(21)
+        got = e.fetch()
+        assert got["lens"][0] == 24
+        same = (got["tokens"] == want["tokens"])[0].cumprod().astype(bool)
+        assert same[:4].all() and np.abs(got["H"] - want["H"])[0][same].max() < 2e-3
+        e.close()
 
 
 @pytest.mark.parametrize("other", ["streamed", "register-buffered"])
