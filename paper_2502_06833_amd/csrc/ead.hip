@@ -254,6 +254,8 @@ struct Model {
 constexpr size_t kCopyPiece = (size_t)2 << 20;
 constexpr int kCopySlots = 8, kCopyThreads = 4, kCopyLeast = 4;
 
+constexpr int kGaveUp = 2;       // ead_handle::h_status: set by a persistent kernel that gives up a wait
+
 struct HostSeq { int len, kvlen[2], model, c, ngen, done, last_step, goal; };
 
 }  // namespace
@@ -284,7 +286,7 @@ struct ead_handle {
     float *x, *q, *o, *hbuf; bf16_t *xp_a, *xp_o, *xp_h;
     float *sk_part; int *sk_tickets;     // split-K partial sums of the MFMA path
     float *part_o; float2 *part_ml; int *tickets; EntPartial *lm_part; float *logits_dump; float *sc_H; int *sc_arg;
-    int *h_model = nullptr, *h_plen = nullptr, *h_status = nullptr;   // pinned: forced ids of a replay; prompt lengths; flags (k_status)
+    int *h_model = nullptr, *h_plen = nullptr, *h_status = nullptr;   // pinned: forced ids of a replay; prompt lengths; flags (k_status; kGaveUp: a kernel's own)
     char *h_fetch = nullptr; int fetch_rows = 0;                       // pinned: results of up to fetch_rows sequences (k_fetch)
     std::vector<int> h_tokens;           // the prompts as they are copied to the device
     char *h_copy = nullptr; hipEvent_t copy_ev[kCopySlots] = {}; bool copy_ready = false;      // pinned pieces of a long copy (make_copy_slots, copy_out)
@@ -292,6 +294,10 @@ struct ead_handle {
     // fused single-row decode
     float *att_o; float2 *att_ml; unsigned *bar_mem; int *abort_flag; unsigned bar_epoch = 0; int fused_on = -1, fused_grid = 0, spin_limit = kFusedSpinLimit;      // fused_on: -1 = k_decode_stream where stream_pays, 0 off, 1 on, 2 on with k_decode_fused
     int device = -1; hipEvent_t turn_ev = nullptr;      // persistent kernels: see launch_in_turn
+    // launches of persistent kernels that may yet turn out to have been given up: the run's statistics before each, and the tokens it had then
+    struct Unsettled { ead_stats stats; int ngen; };
+    std::vector<Unsettled> unsettled;
+    bool gave_up = false;                // one has (settle)
     bool lock_step = false;              // decode_impl's own loop is running (its passes may go to k_decode_stream by themselves)
     float *exchange = nullptr; int exchange_words = 0, exchange_turn = 0;      // two buffers of exchange_words (k_decode_stream)
     std::vector<void *> allocs;
@@ -1074,7 +1080,7 @@ ead_status fused_step(ead_handle *h, int mi, double keys) {
     a.mats = (const FusedMat<WT> *)m.fused_mats; a.layers = (const FusedLayer<WT> *)m.fused_layers; a.n_mats = m.n_mats;
     a.embed = (const WT *)m.embed; a.g_final = m.g_final; a.rope = m.rope;
     a.x = h->x; a.q = h->q; a.hbuf = h->hbuf; a.att_o = h->att_o; a.att_ml = h->att_ml; a.lm_part = h->lm_part;
-    a.bar = GridBar{h->bar_mem, h->bar_mem + kBarGroups * 32, h->abort_flag, h->bar_epoch, h->spin_limit};
+    a.bar = GridBar{h->bar_mem, h->bar_mem + kBarGroups * 32, h->abort_flag, h->h_status + kGaveUp, h->bar_epoch, h->spin_limit};
     a.fin = make_fin(h, mi, false);
     a.batch = h->batch;
     ProfScope ps(h, PK_FUSED, mi, m.weight_bytes_nolm + m.lm_bytes + keys * m.kv_bytes_per_pos);
@@ -1247,6 +1253,14 @@ ead_status begin_impl(ead_handle *h, const int32_t *toks, const int32_t *lens, i
     return EAD_OK;
 }
 
+// Once the streams are at rest: whether one of the persistent kernels launched since the last look has been given up (h->gave_up).  The device
+// then is behind what the host counts, and nothing but k_decode_stream, which looks for itself, may be launched on top.
+void settle(ead_handle *h) {
+    if (h->unsettled.empty()) return;
+    if (*(volatile int *)&h->h_status[kGaveUp]) h->gave_up = true;
+    else h->unsettled.clear();
+}
+
 // One forward pass of model m over the rows the plan gives it, with the host's copy of
 // the per-sequence state advanced for the rows that produced a token.  Returns the number of
 // token rows through *T_out (0: nothing to do).  `step` gates rows that already produced a
@@ -1255,8 +1269,8 @@ ead_status decode_pass(ead_handle *h, int m, int step, std::vector<char> &emitte
     std::vector<int> rows; std::vector<char> complete;
     int n_lm, ctx_max;
     const int T = host_plan(h, m, h->Tmax, 0, 1, false, step, &n_lm, &ctx_max, &rows, &complete);
-    *T_out = T;
-    if (T == 0) return EAD_OK;
+    *T_out = h->gave_up ? 0 : T;
+    if (T == 0 || h->gave_up) return EAD_OK;
     const Model &md = h->mdl[m];
     bool fused = T == 1 && n_lm == 1 && h->batch == 1 && !(h->samp_temp > 0.f);
     if (h->fused_on < 0) fused = fused && h->lock_step && md.stream_ok && stream_pays(md.d, md.KV, md.L, ctx_max);
@@ -1266,6 +1280,14 @@ ead_status decode_pass(ead_handle *h, int m, int step, std::vector<char> &emitte
         const ead_status rc = md.dtype == EAD_BF16 ? fused_step<bf16_t>(h, m, keys) : fused_step<float>(h, m, keys);
         if (rc != EAD_OK && h->fused_on > 0) return rc;
         if (rc != EAD_OK) { (void)hipGetLastError(); h->fused_on = 0; fused = false; }      // the launch was refused: the kernels per layer
+        else h->unsettled.push_back({h->stats, h->hs[0].ngen});
+    }
+    if (!fused && !h->unsettled.empty()) {
+        // the kernels per layer are launched for the rows the host counts, so the device has to have got as far
+        HIP_TRY(h, hipStreamSynchronize(h->lanes[0].stream));
+        if (h->two_lanes) HIP_TRY(h, hipStreamSynchronize(h->lanes[1].stream));
+        settle(h);
+        if (h->gave_up) { *T_out = 0; return EAD_OK; }
     }
     if (!fused) {
         launch_plan(h, m, h->Tmax, 0, 1, false, step, &rows);
@@ -1318,6 +1340,8 @@ ead_status after_tokens(ead_handle *h, const std::vector<char> &emitted, bool al
         if (all_lanes && h->two_lanes) HIP_TRY(h, hipStreamSynchronize(h->lanes[1 - h->cur_lane].stream));
         HIP_TRY(h, hipStreamSynchronize(st));      // the pass's last kernel wrote rb_model / rb_done (pinned) itself
         h->stats.host_syncs++;
+        settle(h);
+        if (h->gave_up) return EAD_OK;
         for (int b = 0; b < h->batch; ++b) {
             HostSeq &s = h->hs[b];
             if (!emitted[b]) continue;              // entries of rows in flight on the other lane are not at rest
@@ -1327,6 +1351,8 @@ ead_status after_tokens(ead_handle *h, const std::vector<char> &emitted, bool al
     } else if (need_sync) {
         if (all_lanes && h->two_lanes) HIP_TRY(h, hipStreamSynchronize(h->lanes[1 - h->cur_lane].stream));
         HIP_TRY(h, hipStreamSynchronize(st));
+        settle(h);
+        if (h->gave_up) return EAD_OK;
         for (int b = 0; b < h->batch; ++b) if (emitted[b] && rb_done[b]) h->hs[b].done = 1;
     }
     return EAD_OK;
@@ -1392,8 +1418,10 @@ ead_status decode_grouped(ead_handle *h, int n_tokens, long budget = -1, int lea
             std::fill(emitted.begin(), emitted.end(), 0);
             int T = 0;
             TRY(decode_pass(h, m, -1, emitted, &T));
+            if (h->gave_up) return EAD_OK;          // the caller sees to it
             if (T == 0) return fail(h, EAD_ERR_STATE, "scheduler found no work for model %d", m);
             TRY(after_tokens(h, emitted, false));
+            if (h->gave_up) return EAD_OK;
             h->step++;
         }
     } else {
@@ -1431,6 +1459,7 @@ ead_status decode_grouped(ead_handle *h, int n_tokens, long budget = -1, int lea
                 std::fill(em[m].begin(), em[m].end(), 0);
                 int T = 0;
                 TRY(decode_pass(h, m, -1, em[m], &T));
+                if (h->gave_up) return EAD_OK;
                 if (T == 0) return fail(h, EAD_ERR_STATE, "scheduler found no work for model %d", m);
                 HIP_TRY(h, hipEventRecord(h->lanes[m].done_ev, h->lanes[m].stream));
                 busy[m] = true;
@@ -1453,6 +1482,7 @@ ead_status decode_grouped(ead_handle *h, int n_tokens, long budget = -1, int lea
             }
             use_lane(h, fin);
             TRY(after_tokens(h, em[fin], false));
+            if (h->gave_up) return EAD_OK;
             busy[fin] = false;
             h->step++;
         }
@@ -1492,8 +1522,10 @@ ead_status decode_impl(ead_handle *h, int n_steps, long budget = -1, int lead = 
     use_lane(h, 0);
     hipStream_t st = h->stream;
     std::vector<char> emitted(h->batch);
+    h->unsettled.clear(); h->gave_up = false;
     if (h->sched_grouped || budget >= 0) {
         TRY(decode_grouped(h, n_steps, budget, lead));
+        use_lane(h, 0);
         n_steps = 0;
     }
     bool used_prev[2] = {false, false};
@@ -1526,8 +1558,9 @@ ead_status decode_impl(ead_handle *h, int n_steps, long budget = -1, int lead = 
                 if (used[m]) HIP_TRY(h, hipEventRecord(h->lanes[m].done_ev, h->lanes[m].stream));
         used_prev[0] = used[0]; used_prev[1] = used[1];
         use_lane(h, 0);
-        if (!any) break;
+        if (!any || h->gave_up) break;
         TRY(after_tokens(h, emitted, true));
+        if (h->gave_up) break;
         h->step++;
     }
     if (h->two_lanes) HIP_TRY(h, hipStreamSynchronize(h->lanes[1].stream));
@@ -1538,12 +1571,13 @@ ead_status decode_impl(ead_handle *h, int n_steps, long budget = -1, int lead = 
     if (aborted) {
         // a wait inside a persistent kernel was given up (its workgroups were not all resident): drop the fused path for this handle and start its counters afresh
         const bool asked = h->fused_on > 0;
-        h->fused_on = 0; h->bar_epoch = 0;
+        h->fused_on = 0; h->bar_epoch = 0; h->h_status[kGaveUp] = 0;
+        h->step++;                       // the step it happened in may have been finished
         HIP_TRY(h, hipMemset(h->bar_mem, 0, (kBarGroups * 32 + 32) * sizeof(unsigned)));
         HIP_TRY(h, hipMemset(h->abort_flag, 0, sizeof(int)));
         if (h->exchange) HIP_TRY(h, hipMemset(h->exchange, 0xFF, (size_t)2 * h->exchange_words * sizeof(float)));
         if (asked) { h->began = 0; return fail(h, EAD_ERR_DEVICE, "fused decode kernel abandoned a grid barrier; fused path disabled, run again"); }
-        // taken by itself: the launches since then have left the state alone, the kernels per layer go on from there
+        // taken by itself: the launches since then have left the state alone (nothing else followed them: settle), the kernels per layer go on from there
         TRY(mirror_from_device(h));
         return decode_impl(h, steps_asked - (h->hs[0].ngen - ngen_before));
     }
@@ -1980,6 +2014,7 @@ ead_status ead_create(const ead_model_desc *small_model, const ead_model_desc *l
         HIP_TRY(h, hipHostMalloc((void **)&h->h_model, std::max<size_t>((size_t)MB * MS, 64) * sizeof(int), hipHostMallocDefault));
         HIP_TRY(h, hipHostMalloc((void **)&h->h_plen, std::max<size_t>(MB, 64) * sizeof(int), hipHostMallocDefault));
         HIP_TRY(h, hipHostMalloc((void **)&h->h_status, 64 * sizeof(int), hipHostMallocDefault));
+        h->h_status[kGaveUp] = 0;
         // results of a fetch: a row's 14 bytes per token and its count, at most about 4 MB (longer batches take several rounds)
         h->fetch_rows = (int)std::min<long>(MB, std::max<long>(1, (4l << 20) / (14l * MS)));
         HIP_TRY(h, hipHostMalloc((void **)&h->h_fetch, (size_t)h->fetch_rows * (14 * (size_t)MS + sizeof(int)), hipHostMallocDefault));

@@ -40,11 +40,13 @@ constexpr int kFusedMaxMats = 200;   // 4 per layer + LM head
 // and gains are immutable and K/V lines are never read before they are written, so those
 // keep using ordinary cached / streaming loads.
 // spin_limit: polls a wait makes before it is given up (kFusedSpinLimit, about two seconds).
-struct GridBar { unsigned *grp, *glob; int *abort_flag; unsigned epoch; int spin_limit; };
+// host_flag: abort_flag's copy in pinned memory.
+struct GridBar { unsigned *grp, *glob; int *abort_flag, *host_flag; unsigned epoch; int spin_limit; };
 
 // The wait is over without what it waited for: what follows in the launch, and the launches after it, must not change a sequence's state.
 __device__ __forceinline__ void give_up(const GridBar &b) {
     st_coherent(b.abort_flag, 1);
+    __hip_atomic_store(b.host_flag, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     wait_stores();
 }
 

@@ -120,6 +120,61 @@ def test_a_launch_given_up_leaves_no_token(polls):
         e.close()
 
 
+@pytest.mark.parametrize("polls", [0, 2])
+@pytest.mark.parametrize("max_batch", [1, 2], ids=["one-lane", "two-lanes"])
+def test_switches_after_a_launch_given_up(polls, max_batch):
+    """Passes of the kernels per layer that follow a launch that was given up (the other model's catch-up after a switch, here dictated by a trajectory and by
+    the window) find the device where the host counts it.  Without a single poll no launch gets through: bit for bit the run of the kernels per layer."""
+    import paper_2502_06833_amd as ead
+    Ws, Wl = _pair()
+    args = dict(window=3, tau=7.2, d_min=2, max_batch=max_batch, max_seq=96)
+    prompt, forced = si.prompt_np(0, "given-up", 30, DEEP.vocab), si.prompt_np(0, "forced", 24, DEEP.vocab)
+    for mid in (np.arange(24) // 5 % 2, 1 - np.arange(24) // 3 % 2):
+        got = {}
+        for limit in (None, polls):
+            e = ead.EAD(DEEP, Ws, FLAT, Wl, **args)
+            if limit is None:
+                e.set_fused(False)
+            else:
+                _spin_limit(e, limit)
+            got[limit] = e.replay([prompt], forced[None], mid[None].astype(np.uint8))
+            e.close()
+        assert np.abs(got[polls]["H"] - got[None]["H"]).max() < (1e-9 if polls == 0 else 2e-3)
+    got = {}
+    for limit in (None, polls):
+        e = ead.EAD(DEEP, Ws, FLAT, Wl, **args)
+        if limit is None:
+            e.set_fused(False)
+        else:
+            _spin_limit(e, limit)
+        got[limit] = e.generate([prompt], 24)
+        if limit is not None:
+            assert (e.generate([prompt], 24)["lens"] == 24).all()        # the handle goes on with the kernels per layer
+        e.close()
+    assert len(set(got[None]["model_id"][0])) == 2 and got[polls]["lens"][0] == 24
+    if polls == 0:
+        assert all((got[0][k] == got[None][k]).all() for k in ("tokens", "model_id", "H", "Hbar"))
+
+
+def test_a_kernel_asked_for_that_gives_up_is_an_error():
+    import paper_2502_06833_amd as ead
+    Ws, Wl = _pair()
+    prompt = si.prompt_np(0, "given-up", 30, DEEP.vocab)
+    for mode, grouped in ((1, False), (2, False), (1, True)):
+        e = ead.EAD(DEEP, Ws, FLAT, Wl, window=3, tau=7.2, d_min=2, max_batch=2, max_seq=96)
+        e.set_schedule(grouped)
+        e.set_fused(False)
+        want = e.generate([prompt], 24)
+        e.set_fused(mode)
+        _spin_limit(e, 0)
+        with pytest.raises(ead.EadError) as err:
+            e.generate([prompt], 24)
+        assert err.value.status == 7                                   # EAD_ERR_DEVICE
+        got = e.generate([prompt], 24)                                 # the kernels per layer from then on
+        assert all((got[k] == want[k]).all() for k in ("tokens", "model_id", "H"))
+        e.close()
+
+
 @pytest.mark.parametrize("other", ["streamed", "register-buffered"])
 def test_two_handles_in_two_threads(other):
     """Persistent kernels of two handles on streams of their own: one starts after the other's has ended, and both finish with the tokens of a run alone."""
