@@ -1578,7 +1578,15 @@ ead_status decode_impl(ead_handle *h, int n_steps, long budget = -1, int lead = 
         if (h->exchange) HIP_TRY(h, hipMemset(h->exchange, 0xFF, (size_t)2 * h->exchange_words * sizeof(float)));
         if (asked) { h->began = 0; return fail(h, EAD_ERR_DEVICE, "fused decode kernel abandoned a grid barrier; fused path disabled, run again"); }
         // taken by itself: the launches since then have left the state alone (nothing else followed them: settle), the kernels per layer go on from there
+        const HostSeq counted = h->hs[0];
         TRY(mirror_from_device(h));
+        if (h->hs[0].ngen == counted.ngen && h->hs[0].model != counted.model) h->stats.switches++;      // all tokens are there, the last one's switch not yet seen
+        for (const ead_handle::Unsettled &u : h->unsettled)
+            if (u.ngen == h->hs[0].ngen) {              // the first of the launches that did nothing: their tokens have been counted
+                const int64_t syncs = h->stats.host_syncs;
+                h->stats = u.stats; h->stats.host_syncs = syncs;
+                break;
+            }
         return decode_impl(h, steps_asked - (h->hs[0].ngen - ngen_before));
     }
     if (err) return fail(h, EAD_ERR_NONFINITE, "a non-finite entropy was produced (non-finite logits)");

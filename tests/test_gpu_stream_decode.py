@@ -130,7 +130,7 @@ def test_switches_after_a_launch_given_up(polls, max_batch):
     args = dict(window=3, tau=7.2, d_min=2, max_batch=max_batch, max_seq=96)
     prompt, forced = si.prompt_np(0, "given-up", 30, DEEP.vocab), si.prompt_np(0, "forced", 24, DEEP.vocab)
     for mid in (np.arange(24) // 5 % 2, 1 - np.arange(24) // 3 % 2):
-        got = {}
+        got, stats = {}, {}
         for limit in (None, polls):
             e = ead.EAD(DEEP, Ws, FLAT, Wl, **args)
             if limit is None:
@@ -138,7 +138,9 @@ def test_switches_after_a_launch_given_up(polls, max_batch):
             else:
                 _spin_limit(e, limit)
             got[limit] = e.replay([prompt], forced[None], mid[None].astype(np.uint8))
+            stats[limit] = e.stats()
             e.close()
+        assert _counts(stats[polls]) == _counts(stats[None])
         assert np.abs(got[polls]["H"] - got[None]["H"]).max() < (1e-9 if polls == 0 else 2e-3)
     got = {}
     for limit in (None, polls):
@@ -148,12 +150,20 @@ def test_switches_after_a_launch_given_up(polls, max_batch):
         else:
             _spin_limit(e, limit)
         got[limit] = e.generate([prompt], 24)
+        stats[limit] = e.stats()
+        assert stats[limit]["tokens_small"] + stats[limit]["tokens_large"] == 24
         if limit is not None:
             assert (e.generate([prompt], 24)["lens"] == 24).all()        # the handle goes on with the kernels per layer
         e.close()
     assert len(set(got[None]["model_id"][0])) == 2 and got[polls]["lens"][0] == 24
     if polls == 0:
         assert all((got[0][k] == got[None][k]).all() for k in ("tokens", "model_id", "H", "Hbar"))
+        assert _counts(stats[0]) == _counts(stats[None])
+
+
+def _counts(stats):
+    """What a run's statistics say of its tokens, not of how often the host waited."""
+    return {k: v for k, v in stats.items() if k != "host_syncs"}
 
 
 def test_a_kernel_asked_for_that_gives_up_is_an_error():
