@@ -1075,6 +1075,7 @@ void end_turn(ead_handle *h) {
 template <typename WT>
 ead_status fused_step(ead_handle *h, int mi, double keys) {
     Model &m = h->mdl[mi];
+    if (h->spin_limit < 0) return fail(h, EAD_ERR_DEVICE, "a test refuses the launch");
     FusedArgs<WT> a{};
     a.L = m.L; a.d = m.d; a.H = m.H; a.KV = m.KV; a.hd = m.hd; a.F = m.F; a.V = m.V; a.eps = m.eps;
     a.mats = (const FusedMat<WT> *)m.fused_mats; a.layers = (const FusedLayer<WT> *)m.fused_layers; a.n_mats = m.n_mats;
@@ -1573,9 +1574,11 @@ ead_status decode_impl(ead_handle *h, int n_steps, long budget = -1, int lead = 
         const bool asked = h->fused_on > 0;
         h->fused_on = 0; h->bar_epoch = 0; h->h_status[kGaveUp] = 0;
         h->step++;                       // the step it happened in may have been finished
-        HIP_TRY(h, hipMemset(h->bar_mem, 0, (kBarGroups * 32 + 32) * sizeof(unsigned)));
-        HIP_TRY(h, hipMemset(h->abort_flag, 0, sizeof(int)));
-        if (h->exchange) HIP_TRY(h, hipMemset(h->exchange, 0xFF, (size_t)2 * h->exchange_words * sizeof(float)));
+        // on the stream the next launches go to: it need not wait for the null stream
+        HIP_TRY(h, hipMemsetAsync(h->bar_mem, 0, (kBarGroups * 32 + 32) * sizeof(unsigned), st));
+        HIP_TRY(h, hipMemsetAsync(h->abort_flag, 0, sizeof(int), st));
+        if (h->exchange) HIP_TRY(h, hipMemsetAsync(h->exchange, 0xFF, (size_t)2 * h->exchange_words * sizeof(float), st));
+        HIP_TRY(h, hipStreamSynchronize(st));      // lane 1's stream too
         if (asked) { h->began = 0; return fail(h, EAD_ERR_DEVICE, "fused decode kernel abandoned a grid barrier; fused path disabled, run again"); }
         // taken by itself: the launches since then have left the state alone (nothing else followed them: settle), the kernels per layer go on from there
         const HostSeq counted = h->hs[0];
@@ -2266,10 +2269,11 @@ ead_status ead_profile_read(ead_handle *h, ead_kernel_profile *out, int32_t capa
     return EAD_OK;
 }
 
-// For the tests alone, in no header: polls after which the persistent kernels give up a wait, and with it the launch.
+// For the tests alone, in no header: polls after which the persistent kernels give up a wait, and with it the launch; -1: as many as ever; -2: launches of
+// them are refused.
 ead_status ead_test_spin_limit(ead_handle *h, int32_t polls) {
     if (!h) return EAD_ERR_INVALID_ARG;
-    h->spin_limit = polls < 0 ? kFusedSpinLimit : polls;
+    h->spin_limit = polls == -1 ? kFusedSpinLimit : polls;
     return EAD_OK;
 }
 

@@ -87,7 +87,7 @@ def test_taken_by_itself_and_switched_off():
 
 
 def _spin_limit(e, polls):
-    """Polls after which a wait inside the kernel is given up (negative: as many as ever); every kernel ends normally."""
+    """Polls after which a wait inside the kernel is given up (-1: as many as ever; -2: its launches are refused); every kernel ends normally."""
     import paper_2502_06833_amd as ead
     fn = ead.lib().ead_test_spin_limit
     fn.argtypes = [C.c_void_p, C.c_int32]
@@ -166,6 +166,28 @@ def _counts(stats):
     return {k: v for k, v in stats.items() if k != "host_syncs"}
 
 
+def test_a_launch_refused_leaves_the_run_to_the_kernels_per_layer():
+    import paper_2502_06833_amd as ead
+    Ws, Wl = _pair()
+    prompt = si.prompt_np(0, "given-up", 30, DEEP.vocab)
+    e = ead.EAD(DEEP, Ws, FLAT, Wl, window=3, tau=7.2, d_min=2, max_batch=1, max_seq=96)
+    runs = [e.generate([prompt], 24)]
+    _spin_limit(e, -2)
+    runs.append(e.generate([prompt], 24))
+    _spin_limit(e, -1)
+    e.set_fused(False)
+    runs.append(e.generate([prompt], 24))
+    assert all((runs[1][k] == runs[2][k]).all() for k in ("tokens", "model_id", "H", "Hbar"))
+    e.set_fused(1)
+    _spin_limit(e, -2)
+    with pytest.raises(ead.EadError):                                  # asked for: an error
+        e.generate([prompt], 24)
+    _spin_limit(e, -1)
+    again = e.generate([prompt], 24)
+    assert all((again[k] == runs[0][k]).all() for k in ("tokens", "model_id", "H", "Hbar"))
+    e.close()
+
+
 def test_a_kernel_asked_for_that_gives_up_is_an_error():
     import paper_2502_06833_amd as ead
     Ws, Wl = _pair()
@@ -182,6 +204,11 @@ def test_a_kernel_asked_for_that_gives_up_is_an_error():
         assert err.value.status == 7                                   # EAD_ERR_DEVICE
         got = e.generate([prompt], 24)                                 # the kernels per layer from then on
         assert all((got[k] == want[k]).all() for k in ("tokens", "model_id", "H"))
+        _spin_limit(e, -1)
+        e.set_fused(mode)                                              # asked for once more: its buffers are as at the start
+        again = e.generate([prompt], 24)
+        same = (again["tokens"] == want["tokens"])[0].cumprod().astype(bool) & (again["model_id"] == want["model_id"])[0].cumprod().astype(bool)
+        assert same[:4].all() and np.abs(again["H"] - want["H"])[0][same].max() < 2e-3
         e.close()
 
 
