@@ -303,7 +303,8 @@ ead_status ead_set_schedule(ead_handle *h, int32_t grouped, float start_fraction
  * per-layer kernels are used regardless for any other shape): for bf16 models the variant
  * whose fetching waves stream the weights through a ring in LDS, for float32 models the
  * one that buffers them in registers; on = 2 selects the register-buffered variant for
- * bf16 models as well.  All paths compute the same thing; tests compare them. */
+ * bf16 models as well; on = -1 is the choice a new handle makes.  All paths compute the same
+ * thing; tests compare them. */
 ead_status ead_set_fused(ead_handle *h, int32_t on);
 
 /* Per-kernel timing for roofline reports.  While enabled, every kernel launch of the

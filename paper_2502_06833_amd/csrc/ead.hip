@@ -2225,7 +2225,7 @@ ead_status ead_set_sampling(ead_handle *h, float temperature, uint64_t seed) {
 
 ead_status ead_set_fused(ead_handle *h, int32_t on) {
     if (!h) return EAD_ERR_INVALID_ARG;
-    h->fused_on = on == 2 ? 2 : (on ? 1 : 0);     // 2: the register-buffered kernel even where the streamed one is available
+    h->fused_on = on == 2 || on == -1 ? on : (on ? 1 : 0);     // 2: the register-buffered kernel even where the streamed one is available
     return EAD_OK;
 }
 

@@ -80,6 +80,9 @@ def test_taken_by_itself_and_switched_off():
     runs.append(e.generate([prompt], 24))
     e.set_fused(False)
     runs.append(e.generate([prompt], 24))
+    e.set_fused(-1)                                     # the default again
+    runs.append(e.generate([prompt], 24))
+    assert (runs[3]["H"] == runs[0]["H"]).all() and (runs[3]["tokens"] == runs[0]["tokens"]).all()
     assert (runs[0]["H"] == runs[1]["H"]).all() and (runs[0]["tokens"] == runs[1]["tokens"]).all()
     same = (runs[2]["tokens"] == runs[0]["tokens"])[0].cumprod().astype(bool) & (runs[2]["model_id"] == runs[0]["model_id"])[0].cumprod().astype(bool)
     assert same[:4].all() and np.abs(runs[2]["H"] - runs[0]["H"])[0][same].max() < 2e-3
