@@ -30,9 +30,13 @@
  *    stream, soft-max statistics and the entropy are float32 throughout.
  *  - Sums are taken in an order that the model's shape and the number of rows of
  *    the pass fix; for passes of one row also whether the handle was made for one
- *    sequence (max_batch = 1) or several, and for their LM head whether it samples.
- *    Results of passes of other widths, and one-row steps of such other handles,
- *    agree up to rounding.
+ *    sequence (max_batch = 1) or several, for their LM head whether it samples, and
+ *    whether the step runs as one persistent kernel (ead_set_fused).  A bf16 model's
+ *    step does by default in a run of one sequence, greedy and in lock step, where
+ *    the shape and the keys the step reads make it the faster way (never past 2048
+ *    keys); after a wait of that kernel has been given up, the handle keeps to the
+ *    per-layer kernels.  Results of passes of other widths, and one-row steps that
+ *    run in another way, agree up to rounding.
  *  - Outputs are caller-owned host buffers unless the name ends in _dev.
  *  - A handle serves one call at a time (calls are not re-entrant).  Work is
  *    queued on ead_params.hip_stream and every call returns after its results
@@ -303,7 +307,13 @@ ead_status ead_set_schedule(ead_handle *h, int32_t grouped, float start_fraction
  * per-layer kernels are used regardless for any other shape): for bf16 models the variant
  * whose fetching waves stream the weights through a ring in LDS, for float32 models the
  * one that buffers them in registers; on = 2 selects the register-buffered variant for
- * bf16 models as well; on = -1 is the choice a new handle makes.  All paths compute the same
+ * bf16 models as well.  A persistent kernel needs the whole device: kernels of other handles
+ * of this process are kept apart from it, those of another process cannot be.  Two processes
+ * that decode one sequence each on one GPU at a time may keep each other's workgroups out; the
+ * wait is given up after about two seconds, and the handle continues with the per-layer kernels
+ * from the last whole token (where on = 1 or 2 asked for the kernel, the call fails with
+ * EAD_ERR_DEVICE instead, and the next one runs).  Programs that share a GPU that way set
+ * on = 0.  on = -1 is the choice a new handle makes.  All paths compute the same
  * thing; tests compare them. */
 ead_status ead_set_fused(ead_handle *h, int32_t on);
 
