@@ -620,8 +620,11 @@ bool launch_ls(ead_handle *h, const LinArgs<bf16_t> &a, int grid) {
 // workgroup of few waves per R row blocks and NT token blocks (narrow_plan in rules.hpp says how many of each, and how many slabs
 // of K).  Two waves a workgroup where row blocks are many, so that the workgroups are many and all resident: gate/up of up to 16
 // rows (28672 x 4096: 44.8 us with four waves and two row blocks, 40.7 with two and two, 40.2 with two and one; gate_up_by_one says which;
-// 9728 x 896: 7.1 with four and two, 6.3 with two and one; but 16384 x 3072: 18.0 and 18.7).  gate_up_streamed says which matrices go to
-// k_linear_mfma_ls instead.
+// 9728 x 896: 7.1 with four and two, 6.3 with two and one; but 16384 x 3072: 18.0 and 18.7).  Two token blocks and more than six row blocks per
+// compute unit: two waves and four row blocks (us at 17 and 32 rows with four waves and two / this way: 27648 x 896 18.0 18.3 / 15.9 16.4, x 1536 23.8 23.1 / 21.6
+// 22.1, x 2560 34.8 35.0 / 31.9 32.6, 30720 x 2944 41.2 / 37.1 37.5; but 24576 x 896 15.3 15.4 / 15.5 15.9, x 2560 28.7 28.8 / 31.0 31.6, 17920 x 1536 16.2 / 16.4, 19456 x 2048
+// 20.8 / 25.3), unless row blocks lie a multiple of 64 KB apart, where four at once gain nothing (27648 x 2048 27.5 27.0 / 27.6 28.4).  gate_up_streamed says which
+// matrices go to k_linear_mfma_ls instead.
 template <int EPI>
 void launch_narrow(ead_handle *h, LinArgs<bf16_t> &a, int T) {
     const int NB = a.Np / 16, KC = a.K / 32, TB = (T + 15) / 16, n_cu = h->n_cu;
@@ -635,7 +638,7 @@ void launch_narrow(ead_handle *h, LinArgs<bf16_t> &a, int T) {
             else if (many) EAD_LM(2, 2, 1, 8, false);
             else EAD_LM(4, 2, 1, 4, false);
         }
-        else if (TB == 2) EAD_LM(4, 2, 2, 4, false);
+        else if (TB == 2) { if (gate_up_by_four(NB, KC, n_cu)) EAD_LM(2, 4, 2, 4, false); else EAD_LM(4, 2, 2, 4, false); }
         else EAD_LM(4, 2, 4, 4, false);
     } else {
         // (the rotary / cache-append epilogue is too heavy to be left to one workgroup per group)

@@ -218,6 +218,9 @@ inline bool prompt_attention(int T, int seqs, long groups, long own, int KV, int
     return wgs >= (ctx <= 320 ? 256 : ctx <= 4096 ? 400 : 512);
 }
 
+// Whether a gate/up matrix in a pass of two token blocks goes four row blocks to a workgroup of two waves (launch_narrow: what both ways measured).
+inline bool gate_up_by_four(int NB, int KC, int n_cu) { return NB > 6 * n_cu && KC % 64 != 0; }
+
 // Gate/up matrices whose passes of one or two token blocks stream through k_linear_mfma_ls (us in launch_narrow's workgroups / this way).  One
 // block: long K and more than four row blocks per compute unit (28672 x 4096 41.5 / 40.0, 27648 x 5120 50.6 / 46.9; but 16384 x 3072 18.1 / 21.1, 16384 x 2048
 // 14.5 / 16.9, 9728 x 896 7.4 / 8.4).  Two: K of 3072 and more (28672 x 4096 48.3 / 40.2, 27648 x 5120 55.6 / 47.2, 16384 x 3072 21.8 / 20.4).  Shorter ones gain alone

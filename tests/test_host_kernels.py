@@ -345,3 +345,8 @@ def test_persistent_launches_wait_for_each_other(host, handles):
     """A launch is queued behind all earlier ones on the device, whichever handle made them."""
     assert host.host_turns(handles, 60) == 0
     assert host.host_turn_refused() == 7
+
+
+@pytest.mark.parametrize("N,K,four", [(27648, 896, 1), (27648, 2560, 1), (30720, 2944, 1), (24576, 896, 0), (24576, 2560, 0), (17920, 1536, 0), (27648, 2048, 0)])
+def test_gate_up_of_two_token_blocks_where_four_row_blocks_are_faster(host, N, K, four):
+    assert host.host_gate_up_by_four(N // 16, K // 32) == four
