@@ -32,9 +32,9 @@
  *    the pass fix; for passes of one row also whether the handle was made for one
  *    sequence (max_batch = 1) or several, for their LM head whether it samples, and
  *    whether the step runs as one persistent kernel (ead_set_fused).  A bf16 model's
- *    step does by default in a run of one sequence, greedy and in lock step, where
- *    the shape and the keys the step reads make it the faster way (never past 2048
- *    keys); after a wait of that kernel has been given up, the handle keeps to the
+ *    step does by default in a run of one sequence, greedy and in lock step, begun
+ *    while no handle on another stream was there, where the shape and the keys the
+ *    step reads make it the faster way (never past 2048 keys); after a wait of that kernel has been given up, the handle keeps to the
  *    per-layer kernels.  Results of passes of other widths, and one-row steps that
  *    run in another way, agree up to rounding.
  *  - Outputs are caller-owned host buffers unless the name ends in _dev.
@@ -302,13 +302,14 @@ ead_status ead_set_schedule(ead_handle *h, int32_t grouped, float start_fraction
  * through an exchange buffer instead of kernel boundaries, the weight stream running on
  * across them) instead of the per-layer kernels that wider batches use.  A handle takes it by
  * itself for runs of one sequence decoded greedily in lock step by a bf16 model where it is
- * the faster of the two; on = 0 keeps the per-layer kernels always.  on = 1 selects a
+ * the faster of the two, unless another handle on the same device has another stream when the
+ * run begins (side by side the per-layer kernels of several handles are faster); on = 0 keeps the per-layer kernels always.  on = 1 selects a
  * persistent kernel for all the shapes one is built for (the
  * per-layer kernels are used regardless for any other shape): for bf16 models the variant
  * whose fetching waves stream the weights through a ring in LDS, for float32 models the
  * one that buffers them in registers; on = 2 selects the register-buffered variant for
- * bf16 models as well.  A persistent kernel needs the whole device: kernels of other handles
- * of this process are kept apart from it, those of another process cannot be.  Two processes
+ * bf16 models as well.  A persistent kernel needs the whole device: those of one process are kept
+ * apart, those of another process cannot be.  Two processes
  * that decode one sequence each on one GPU at a time may keep each other's workgroups out; the
  * wait is given up after about two seconds, and the handle continues with the per-layer kernels
  * from the last whole token (where on = 1 or 2 asked for the kernel, the call fails with

@@ -286,7 +286,7 @@ class EAD:
     def set_fused(self, on):
         """False/0: per-layer kernels; True/1: one persistent kernel per single-row step (the streamed
         variant where the model has one); 2: the register-buffered persistent kernel even then.  -1, as without a call:
-        the streamed kernel where it is the faster."""
+        the streamed kernel where it is the faster, in runs begun while no handle on another stream is there."""
         self._check(lib().ead_set_fused(self._h, on if on in (2, -1) else (1 if on else 0)))
 
     def profile(self, on: bool):

@@ -226,8 +226,8 @@ def test_two_handles_in_two_threads(other):
     for i in range(2):
         with torch.cuda.stream(streams[i]):
             handles.append(ead.EAD(DEEP, Ws, FLAT, Wl, window=3, tau=7.2, d_min=2, max_batch=1, max_seq=96))
-    if other == "register-buffered":
-        handles[1].set_fused(2)
+    for i in range(2):
+        handles[i].set_fused(2 if other == "register-buffered" and i else 1)      # not taken by itself with two streams
     want = [handles[i].generate([prompts[i]], 32) for i in range(2)]
     got = [[], []]
 
@@ -245,3 +245,39 @@ def test_two_handles_in_two_threads(other):
         for r in got[i]:
             assert (r["tokens"] == want[i]["tokens"]).all() and (r["H"] == want[i]["H"]).all()
         handles[i].close()
+
+
+def test_not_taken_by_itself_beside_a_handle_on_another_stream():
+    """The kernel takes the whole chip, so runs of handles on streams of their own keep to the per-layer kernels, which share it; on one stream they take it."""
+    import torch
+    import paper_2502_06833_amd as ead
+    Ws, Wl = _pair()
+    prompt = si.prompt_np(0, "beside", 40, DEEP.vocab)
+
+    def handle(stream):
+        with torch.cuda.stream(stream):
+            return ead.EAD(DEEP, Ws, FLAT, Wl, window=3, tau=7.2, d_min=2, max_batch=1, max_seq=96)
+
+    def run(e):
+        e.profile(True)
+        out = e.generate([prompt], 16)
+        names = {p["name"] for p in e.profile_read() if p["launches"]}
+        e.profile(False)
+        return out, any("decode_fused" in n for n in names)
+
+    one, two = torch.cuda.Stream(), torch.cuda.Stream()
+    a, same = handle(one), handle(one)
+    alone, taken = run(a)
+    assert taken and run(same)[1]
+    b = handle(two)
+    beside, taken = run(a)
+    assert not taken and not run(b)[1]
+    a.set_fused(False)
+    layers, _ = run(a)
+    assert all((beside[k] == layers[k]).all() for k in ("tokens", "model_id", "H"))
+    a.set_fused(-1)
+    b.close()
+    again, taken = run(a)
+    assert taken and all((again[k] == alone[k]).all() for k in ("tokens", "model_id", "H"))
+    a.close()
+    same.close()
