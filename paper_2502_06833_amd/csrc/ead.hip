@@ -1294,7 +1294,7 @@ ead_status decode_pass(ead_handle *h, int m, int step, std::vector<char> &emitte
     if (T == 0 || h->gave_up) return EAD_OK;
     const Model &md = h->mdl[m];
     bool fused = T == 1 && n_lm == 1 && h->batch == 1 && !(h->samp_temp > 0.f);
-    if (h->fused_on < 0) fused = fused && h->lock_step && h->alone && md.stream_ok && stream_pays(md.d, md.KV, md.L, ctx_max);
+    if (h->fused_on < 0) fused = fused && h->lock_step && h->alone && md.stream_ok && stream_pays(md.d, md.F, md.KV, md.L, ctx_max);
     else fused = fused && h->fused_on && ((h->fused_on != 2 && md.stream_ok) || md.fused_ok);
     if (fused) {
         const double keys = keys_in_pass(h, m, rows);

@@ -274,8 +274,14 @@ inline StreamSplit stream_split(int NB, int KC, int G, int most) {
 // Whether a step of one row goes to k_decode_stream: what a layer gains has to pay for the way in and the barrier at the end, 3-18 us a step.
 // Measured, us a layer at 330 keys with the kernels per layer / this way: d 896 28.0 / 24.8, 1536 44.0 / 35.9, 2048 42.3 / 35.6, 3072 56.1 / 47.2, 4096 90.9 / 83.5, 5120 114.4 /
 // 100.0; at 1200 keys, which eight workgroups per KV head share, 28.9 / 28.2 and 44.3 / 42.9 (two KV heads), 43.9 / 37.6, 58.1 / 50.9, 93.7 / 87.6, 117.1 / 106.1 (eight).
-inline bool stream_pays(int d, int KV, int layers, int keys) {
-    const float gain = (d <= 1024 ? 2.5f : 6.f) - (KV >= 8 ? 0.0015f : 0.006f) * (float)std::max(0, keys - 330);
+// Those have an FFN of 2.7 to 5.8 d.  The hand-overs cost the same whatever streams between them, so short FFNs gain less or lose (us a step of 12 layers and a vocabulary of
+// 8192, per layer / this way, at d_ffn 512, 1024, 2048, 3072, 4864: d 896 278 285 297 322 - / 300 299 300 309 -; 1024 279 287 302 333 365 / 292 292 293 299 318; 1536 330
+// 339 357 378 432 / 339 345 350 367 391; 2048 with four KV heads 327 336 368 398 447 / 339 342 342 365 404, with eight 332 346 371 398 447 / 332 333 332 356 396; 3072 432
+// 440 473 510 582 / 388 397 402 444 496; 4096 492 506 548 592 681 / 490 492 525 577 657).
+inline bool stream_pays(int d, int F, int KV, int layers, int keys) {
+    const float f = (float)F, at330 = d <= 1024 ? std::min(2.5f, 0.00093f * f - 1.3f) : d < 2048 ? std::min(6.f, 0.00088f * f - 0.8f) :
+                    std::min(6.f, (d <= 3072 ? 0.0016f * f + 0.3f + 0.0035f * (float)(d - 2048) : 0.0004f * f + 1.f) - (KV >= 8 ? 0.f : 1.2f));
+    const float gain = at330 - (KV >= 8 ? 0.0015f : 0.006f) * (float)std::max(0, keys - 330);
     return keys <= 2048 && gain * (float)layers > 20.f;
 }
 

@@ -112,7 +112,8 @@ int host_stream_split(int NB, int KC, int most) {
     const StreamSplit p = stream_split(NB, KC, 256, most);
     return p.slices * 1000 + p.tiles;
 }
-int host_stream_pays(int d, int KV, int layers, int keys) { return stream_pays(d, KV, layers, keys); }
+int host_stream_pays_ffn(int d, int F, int KV, int layers, int keys) { return stream_pays(d, F, KV, layers, keys); }
+int host_stream_pays(int d, int KV, int layers, int keys) { return stream_pays(d, 4 * d, KV, layers, keys); }
 
 // The fetching waves' list of every workgroup of a model whose matrices lie apart from each other: slots it begins (layers x phases, then the
 // ones requested past the end of the list), each of them the slot the multiplying waves read there and every byte inside the unit.  Returns the

@@ -174,7 +174,9 @@ def test_a_launch_refused_leaves_the_run_to_the_kernels_per_layer():
     Ws, Wl = _pair()
     prompt = si.prompt_np(0, "given-up", 30, DEEP.vocab)
     e = ead.EAD(DEEP, Ws, FLAT, Wl, window=3, tau=7.2, d_min=2, max_batch=1, max_seq=96)
+    e.set_fused(1)
     runs = [e.generate([prompt], 24)]
+    e.set_fused(-1)
     _spin_limit(e, -2)
     runs.append(e.generate([prompt], 24))
     _spin_limit(e, -1)

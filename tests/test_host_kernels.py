@@ -350,3 +350,11 @@ def test_persistent_launches_wait_for_each_other(host, handles):
 @pytest.mark.parametrize("N,K,four", [(27648, 896, 1), (27648, 2560, 1), (30720, 2944, 1), (24576, 896, 0), (24576, 2560, 0), (17920, 1536, 0), (27648, 2048, 0)])
 def test_gate_up_of_two_token_blocks_where_four_row_blocks_are_faster(host, N, K, four):
     assert host.host_gate_up_by_four(N // 16, K // 32) == four
+
+
+@pytest.mark.parametrize("d,F,KV,layers,keys,pays", [
+    (896, 4864, 2, 24, 330, 1), (896, 1024, 2, 24, 330, 0), (896, 2048, 2, 24, 330, 0), (1024, 1024, 4, 40, 330, 0), (1024, 4864, 4, 24, 330, 1), (768, 512, 3, 24, 40, 0),
+    (1536, 8960, 2, 28, 1200, 1), (1536, 4864, 2, 28, 1200, 0), (1536, 1024, 2, 28, 330, 0), (2048, 512, 4, 40, 330, 0), (2048, 8192, 8, 16, 2048, 1), (3072, 8192, 8, 28, 2048, 1), (3072, 512, 8, 24, 1200, 1),
+    (4096, 512, 8, 40, 1200, 0), (4096, 14336, 8, 32, 2048, 1), (5120, 13824, 8, 48, 2048, 1)])
+def test_one_row_does_not_stream_where_the_ffn_is_short(host, d, F, KV, layers, keys, pays):
+    assert host.host_stream_pays_ffn(d, F, KV, layers, keys) == pays
