@@ -1,6 +1,7 @@
 """GPU: prompt passes long enough for the tiled kernels (128-row sweeps, 128 x 256 and 256 x 256 tiles, several bands of
 sweeps), with row-block counts and row counts that leave partly empty tiles, against teacher-forced scoring of the
-same prompts in passes of at most 160 rows."""
+same prompts in passes of at most 160 rows.  (Of a model of one layer the prompt's first entropy sees the QKV projections' sums alone; the
+residual projections of these shapes are compared with the oracle in test_gpu_wide_batches.py.)"""
 import numpy as np
 import pytest
 

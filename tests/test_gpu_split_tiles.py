@@ -1,6 +1,7 @@
 """GPU: long passes whose last sweeps are cut along K (tile_plan in rules.hpp), against teacher-forced scoring of the same prompts in passes of at most 160
 rows: residual projections of 17 groups of row blocks, 15 sweeps whole and a partly filled one in 3 and 4 slabs; all sweeps in 8 slabs, the last token block
-partly filled; row blocks that fill their groups partly, uneven slabs of 257 k tiles; QKV projections, 10 sweeps whole and two in slabs."""
+partly filled; row blocks that fill their groups partly, uneven slabs of 257 k tiles; QKV projections, 10 sweeps whole and two in slabs.  In models of one layer the first
+entropy after a prompt follows the QKV projections' sums alone; test_gpu_wide_batches.py compares all of them, row by row, with the oracle."""
 import numpy as np
 import pytest
 
