@@ -606,7 +606,9 @@ int launch_valu(ead_handle *h, int mi, LinArgs<WT> &a, int T, int grid) {
 constexpr float kSmallLaneMin = 0.3f;                  // grouped schedule, two lanes: see decode_grouped
 constexpr int kSplitKGroups = 4096;                     // arrival counters
 constexpr size_t kSplitKFloats = (size_t)8 << 20;      // partial sums: KS slabs of (padded Np) x 128 floats at most
-constexpr size_t kTileSplitFloats = 2 * kSplitKFloats;  // the same of the long passes' tiles: what the buffer holds
+// The same of the long passes' tiles: what the buffer holds.  Lane 1's too: its passes of up to 1024 rows and more are four sweeps and more (17 groups x 4 sweeps x 256 k
+// tiles are cut in three with it, by the rule's cost 264 thousand cycles, and not at all with half of it, 462).
+constexpr size_t kTileSplitFloats = 2 * kSplitKFloats;
 
 template <int EPI, bool SK, int NW, int RG, bool ONCE = true>
 bool launch_ls(ead_handle *h, const LinArgs<bf16_t> &a, int grid) {
@@ -1006,7 +1008,8 @@ void *fused_kernel_for(const Model &m) {
     return nullptr;
 }
 
-// the streamed variant: bf16 only
+// The streamed variant: bf16 only.  Head layouts are compiled in, one kernel each; these are the ones it has been measured for (stream_pays).  Any
+// other, as groups of 1, 2 and 8 heads, keeps the kernels per layer, for the rule knows nothing of its attention phase.
 template <int HD, int G>
 void *stream_kernel_ptr() { return (void *)k_decode_stream<HD, G>; }
 void *stream_kernel_for(const Model &m) {
