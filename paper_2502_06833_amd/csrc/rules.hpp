@@ -223,12 +223,14 @@ inline bool gate_up_by_four(int NB, int KC, int n_cu) { return NB > 6 * n_cu && 
 
 // Gate/up matrices whose passes of one or two token blocks stream through k_linear_mfma_ls (us in launch_narrow's workgroups / this way).  One
 // block: long K and more than four row blocks per compute unit (28672 x 4096 41.5 / 40.0, 27648 x 5120 50.6 / 46.9; but 16384 x 3072 18.1 / 21.1, 16384 x 2048
-// 14.5 / 16.9, 9728 x 896 7.4 / 8.4).  Two: K of 3072 and more (28672 x 4096 48.3 / 40.2, 27648 x 5120 55.6 / 47.2, 16384 x 3072 21.8 / 20.4).  Shorter ones gain alone
+// 14.5 / 16.9, 9728 x 896 7.4 / 8.4).  Two: K of 3072 and more (28672 x 4096 48.3 / 40.2, 27648 x 5120 55.6 / 47.2, 16384 x 3072 21.8 / 20.4) and more than two row
+// blocks per unit, since up to there launch_narrow's workgroups are one round (8192 x 3072 12.8 / 15.8, x 5120 18.2 / 23.6, 2048 x 4096 12.9 / 17.7; 8320 x 3072 17.5 / 15.2,
+// 9728 x 5120 29.0 / 23.5).  Shorter ones gain alone
 // (17920 x 1536 17.5 / 14.6, 24576 x 1536 18.8 / 16.5, 9728 x 896 9.5 / 8.3; not 16384 x 2048, 16.1 / 16.5) but belong to small models, whose passes run beside the large
 // model's: a workgroup of 112 KB of LDS keeps that one's out of its unit (64 rows grouped, 0.5B / 14B shapes: 64.5 ms with them, 63.4 without).  Runs of one
 // lane, where nothing runs beside them, go without that gain: the rule does not know the lane.
 inline bool gate_up_streamed(int NB, int KC, int TB, int n_cu) {
-    return TB == 1 ? KC >= 128 && NB > 4 * n_cu : TB == 2 && KC >= 96 && NB >= 128;
+    return TB == 1 ? KC >= 128 && NB > 4 * n_cu : TB == 2 && KC >= 96 && NB > 2 * n_cu;
 }
 
 // How 256 x 256 tiles take a pass: NG groups of 16 row blocks x SG sweeps of 256 tokens x KC k tiles.  The first `whole` sweeps in tiles of full depth, the

@@ -358,3 +358,8 @@ def test_gate_up_of_two_token_blocks_where_four_row_blocks_are_faster(host, N, K
     (4096, 512, 8, 40, 1200, 0), (4096, 14336, 8, 32, 2048, 1), (5120, 13824, 8, 48, 2048, 1)])
 def test_one_row_does_not_stream_where_the_ffn_is_short(host, d, F, KV, layers, keys, pays):
     assert host.host_stream_pays_ffn(d, F, KV, layers, keys) == pays
+
+
+@pytest.mark.parametrize("N,K,rows,streamed", [(8192, 3072, 32, 0), (8208, 3072, 32, 1), (2048, 4096, 24, 0), (9728, 5120, 24, 1), (28672, 4096, 3, 1), (16384, 4096, 3, 0), (17920, 1536, 24, 0)])
+def test_gate_up_of_few_rows_streams_where_that_is_faster(host, N, K, rows, streamed):
+    assert host.host_gate_up_streamed(N // 16, K // 32, (rows + 15) // 16) == streamed
