@@ -670,14 +670,12 @@ void launch_narrow(ead_handle *h, LinArgs<bf16_t> &a, int T) {
 // The LM head: writes one partial per (row, workgroup) and returns their number per row.  Through
 // k_lm_ls, 128 rows per sweep: its fetching waves' non-temporal loads bring 7.2 TB/s (us at 32 rows with the register ring
 // of k_linear_mfma / this way: 128256 x 4096 188 / 166, x 3072 133 / 124; 151936 x 5120 263 / 243; at 12 rows 171 / 167, 249 / 242, 151936 x 1536 85.8 / 79.2,
-// 128256 x 2048 90.9 / 88.3).  But one token block of K between 2048 and 4096 stays with
-// k_linear_mfma where K is a multiple of 512, whole turns of the two waves' ring: the two are level there, and with few rows that sample k_linear_mfma is up to 4 % the faster
-// (128256 x 3072 at 3 and 12 rows greedy 126 127 / 127 128, sampling 131 141 / 132 133; 151936 x 3584 171 172 / 172 172 and 176 188 / 180 180).  Other K: 128256 x 2304 105 105 / 91 93, x 2816
-// 125 126 / 113 113, 151936 x 3328 170 171 / 163 161.
+// 128256 x 2048 90.9 / 88.3, x 2304 105 / 93).  lm_by_rings says which heads of up to 32 rows stay with k_linear_mfma.
 int launch_lm(ead_handle *h, int mi, LinArgs<bf16_t> &a, int T) {
     ProfScope ps(h, PK_MFMA_LOGITS, mi, (double)a.Np * a.K * 2.0);
     const int NB = a.Np / 16, KC = a.K / 32, TB = (T + 15) / 16;
-    if (!(TB == 1 && KC > 64 && KC < 128 && KC % 16 == 0) && kLmLdsBytes <= h->lds_per_block) {
+    const bool rings = lm_by_rings(NB, KC, TB, h->n_cu);
+    if (!rings && kLmLdsBytes <= h->lds_per_block) {
         const int grid = std::min(NB, h->n_cu);
         bool ok = true;
         for (a.tb_base = 0; ok && a.tb_base < TB; a.tb_base += 8) {
@@ -687,6 +685,11 @@ int launch_lm(ead_handle *h, int mi, LinArgs<bf16_t> &a, int T) {
 #undef EAD_LL
         }
         if (ok) return grid;
+    }
+    if (rings && TB == 2) {
+        const int grid = std::min((NB + 3) / 4, 2 * h->n_cu);
+        hipLaunchKernelGGL((k_linear_mfma<2, 4, 2, 4, EPI_LOGITS, false>), dim3(grid), dim3(128), 0, h->stream, a);
+        return grid;
     }
     // (also what serves, a token block after the other, where k_lm_ls is refused its LDS)
     const int grid = std::min((NB + 1) / 2, 2 * h->n_cu);

@@ -233,6 +233,21 @@ inline bool gate_up_streamed(int NB, int KC, int TB, int n_cu) {
     return TB == 1 ? KC >= 128 && NB > 4 * n_cu : TB == 2 && KC >= 96 && NB > 2 * n_cu;
 }
 
+// LM heads of one and two token blocks that stay with k_linear_mfma's register rings (us with them / through k_lm_ls).  A workgroup of k_lm_ls walks its NB / n_cu
+// row blocks eight at a time, and slots past their end cost what the others do: rings where that leaves half a group and more empty on every unit
+// (8192 x 4096 at 3 rows 15.6 / 31.5, 16384 x 5120 30.3 / 38.7, 40000 x 4096 53 / 73, 100000 x 4096 131 / 151, at 24 rows 40000 x 5120 77 / 94;
+// but 24000 x 4096 at 12 rows 36.6 / 35.0, 65536 x 3328 72 / 67, 50256 x 4096 at 24 rows 90 / 77).  Where K is no multiple of 512 the rings' last turn is partly empty and
+// more has to be (81920 x 2304 at 12 rows 66 / 65, 114688 x 1792 at 3 rows 72 / 70; 100000 x 3328 111 / 121).  K below 1280, with two blocks to 2048: never.  One block of
+// K between 2048 and 4096, whole turns: the two are level, and with few rows that sample the rings are up to 4 % the faster (128256 x 3072 at 3 and 12 rows greedy
+// 126 127 / 127 128, sampling 131 141 / 132 133).  (180 shapes at 3 to 32 rows; the one taken is at most 7 % the slower, 1 % in the mean.)
+inline bool lm_by_rings(int NB, int KC, int TB, int n_cu) {
+    if (TB > 2 || KC < 40 || (TB == 2 && KC <= 64)) return false;
+    const long walked = (long)((NB + 8 * n_cu - 1) / (8 * n_cu)) * 8 * n_cu, empty = walked - NB;
+    const bool whole = KC % 16 == 0;
+    if (TB == 1 && whole && KC > 64 && KC < 128) return true;
+    return 2 * empty >= (TB == 1 ? 7 : 8) * n_cu && (whole || 8 * NB <= 5 * walked || (TB == 1 && KC > 64 && empty >= 6 * n_cu));
+}
+
 // How 256 x 256 tiles take a pass: NG groups of 16 row blocks x SG sweeps of 256 tokens x KC k tiles.  The first `whole` sweeps in tiles of full depth, the
 // others, which would leave a round of workgroups partly empty, in tiles of one of KS slabs of K, whose sums another launch adds.  Cost in
 // cycles: 1750 per k tile and round, 1950 with the whole chip busy (measured; an eighth of the tiles to each XCD's units), the sums written and read at 5 TB/s, and

@@ -360,6 +360,16 @@ def test_one_row_does_not_stream_where_the_ffn_is_short(host, d, F, KV, layers, 
     assert host.host_stream_pays_ffn(d, F, KV, layers, keys) == pays
 
 
+@pytest.mark.parametrize("N,K,rows,rings", [
+    (8192, 4096, 3, 1), (8192, 2304, 16, 1), (8192, 4096, 32, 1), (8192, 2048, 32, 0), (8192, 896, 3, 0), (16384, 5120, 24, 1), (16384, 5120, 64, 0),
+    (24000, 1024, 64, 0), (24000, 4096, 12, 0), (32000, 768, 3, 0), (32000, 4096, 16, 0), (40000, 2048, 3, 1), (40000, 5120, 24, 1), (50256, 4096, 24, 0),
+    (65536, 2048, 24, 0), (81920, 2304, 12, 0), (100000, 4096, 3, 1), (100000, 3328, 12, 1), (128256, 2048, 3, 0), (128256, 2304, 3, 0), (128256, 3072, 3, 1),
+    (128256, 3072, 32, 0), (128256, 4096, 16, 0), (151936, 896, 3, 0), (151936, 1536, 3, 0), (151936, 5120, 32, 0), (151936, 5120, 64, 0)])
+def test_lm_heads_take_the_kernel_measured_faster(host, N, K, rows, rings):
+    TB = (rows + 15) // 16
+    assert host.host_lm_by_rings(N // 16, K // 32, TB) == rings
+
+
 @pytest.mark.parametrize("N,K,rows,streamed", [(8192, 3072, 32, 0), (8208, 3072, 32, 1), (2048, 4096, 24, 0), (9728, 5120, 24, 1), (28672, 4096, 3, 1), (16384, 4096, 3, 0), (17920, 1536, 24, 0)])
 def test_gate_up_of_few_rows_streams_where_that_is_faster(host, N, K, rows, streamed):
     assert host.host_gate_up_streamed(N // 16, K // 32, (rows + 15) // 16) == streamed
