@@ -159,8 +159,8 @@ __device__ __forceinline__ void request_tile(const bf16_t *base, uint32_t voff, 
     else asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(voff), "s"(base) : "memory");
 }
 
-// The same through the builtin, from this lane's address; ONCE: a tile that no other workgroup reads is requested non-temporally
-// (the fetching-wave kernels' streams: 6.2-6.4 -> 7.2 TB/s).
+// The same through the builtin, from this lane's address; ONCE: non-temporally, for tiles that no other workgroup reads
+// (the fetching-wave kernels' long streams: 6.2-6.4 -> 7.2 TB/s; tiles_once and lm_once in rules.hpp say which).
 template <bool ONCE>
 __device__ __forceinline__ void request_tile_at(const bf16_t *src, bf16_t *lds) {
     __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)src, (__attribute__((address_space(3))) void *)lds, 16, 0, ONCE ? 2 : 0);

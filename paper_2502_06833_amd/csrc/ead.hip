@@ -610,12 +610,12 @@ constexpr size_t kSplitKFloats = (size_t)8 << 20;      // partial sums: KS slabs
 // tiles are cut in three with it, by the rule's cost 264 thousand cycles, and not at all with half of it, 462).
 constexpr size_t kTileSplitFloats = 2 * kSplitKFloats;
 
-template <int EPI, bool SK, int NW, int RG, bool ONCE = true>
+template <int EPI, bool SK, int NW, int RG>
 bool launch_ls(ead_handle *h, const LinArgs<bf16_t> &a, int grid) {
-    const void *kern = (const void *)k_linear_mfma_ls<EPI, SK, NW, RG, ONCE>;
+    const void *kern = (const void *)k_linear_mfma_ls<EPI, SK, NW, RG>;
     const size_t lds = kLsLdsBytes;
     if (lds > h->lds_per_block || !allow_big_lds(kern, lds)) return false;
-    hipLaunchKernelGGL((k_linear_mfma_ls<EPI, SK, NW, RG, ONCE>), dim3(grid), dim3((NW + kLsProducers) * 64), lds, h->stream, a);
+    hipLaunchKernelGGL((k_linear_mfma_ls<EPI, SK, NW, RG>), dim3(grid), dim3((NW + kLsProducers) * 64), lds, h->stream, a);
     return true;
 }
 
@@ -675,6 +675,7 @@ int launch_lm(ead_handle *h, int mi, LinArgs<bf16_t> &a, int T) {
     ProfScope ps(h, PK_MFMA_LOGITS, mi, (double)a.Np * a.K * 2.0);
     const int NB = a.Np / 16, KC = a.K / 32, TB = (T + 15) / 16;
     const bool rings = lm_by_rings(NB, KC, TB, h->n_cu);
+    a.once = lm_once(NB, KC, h->n_cu);
     if (!rings && kLmLdsBytes <= h->lds_per_block) {
         const int grid = std::min(NB, h->n_cu);
         bool ok = true;
@@ -767,7 +768,7 @@ void launch_mfma(ead_handle *h, int mi, LinArgs<bf16_t> &a, int T) {
         while (KS > 1 && (a.K / 32) / KS < 16) --KS;
         if (KS > 1 && (size_t)KS * NG * 8 * nt * 256 <= kSplitKFloats) {
             if constexpr (EPI != EPI_SWIGLU) {
-                a.KS = KS; a.sk_part = h->sk_part;
+                a.KS = KS; a.sk_part = h->sk_part; a.once = tiles_once(tiles, 8, true);
 #define EAD_SK(TPW_, NW_) do { if (TPW_ != 1 || !launch_ls<EPI, true, NW_, 8>(h, a, NG * KS)) \
                                    hipLaunchKernelGGL((k_linear_mfma_wt<6, EPI, true, TPW_, 8, NW_>), dim3(NG * KS), dim3(NW_ * 64), 0, h->stream, a); \
                                hipLaunchKernelGGL((k_sk_merge<EPI, TPW_ * NW_>), dim3((NB * TPW_ * NW_ + 3) / 4), dim3(256), 0, h->stream, a, NG * 8); } while (0)
@@ -786,14 +787,14 @@ void launch_mfma(ead_handle *h, int mi, LinArgs<bf16_t> &a, int T) {
         a.sweeps = sw;
         const int grid = sw > 1 ? (ng + 7) / 8 * 8 * sw : ng;
         bool ok = false;
-#define EAD_LS(NW_, ONCE_) do { switch (rg) { case 4: ok = launch_ls<EPI, false, NW_, 4, ONCE_>(h, a, grid); break; case 5: ok = launch_ls<EPI, false, NW_, 5, ONCE_>(h, a, grid); break; \
-                                       case 6: ok = launch_ls<EPI, false, NW_, 6, ONCE_>(h, a, grid); break; case 7: ok = launch_ls<EPI, false, NW_, 7, ONCE_>(h, a, grid); break; \
-                                       default: ok = launch_ls<EPI, false, NW_, 8, ONCE_>(h, a, grid); break; } } while (0)
-        if (sw > 1) EAD_LS(8, false);                  // several sweeps have eight multiplying waves each
+#define EAD_LS(NW_) do { switch (rg) { case 4: ok = launch_ls<EPI, false, NW_, 4>(h, a, grid); break; case 5: ok = launch_ls<EPI, false, NW_, 5>(h, a, grid); break; \
+                                       case 6: ok = launch_ls<EPI, false, NW_, 6>(h, a, grid); break; case 7: ok = launch_ls<EPI, false, NW_, 7>(h, a, grid); break; \
+                                       default: ok = launch_ls<EPI, false, NW_, 8>(h, a, grid); break; } } while (0)
+        a.once = sw == 1 && tiles_once(tiles, rg, false);
+        if (nt == 8) EAD_LS(8);                        // several sweeps have eight multiplying waves each
         else if constexpr (EPI == EPI_SWIGLU) {
-            switch (nt) { case 1: EAD_LS(1, true); break; case 2: EAD_LS(2, true); break; case 4: EAD_LS(4, true); break; case 5: EAD_LS(5, true); break;
-                          case 6: EAD_LS(6, true); break; case 7: EAD_LS(7, true); break; default: EAD_LS(8, true); break; }
-        } else if (nt == 8) EAD_LS(8, true);
+            switch (nt) { case 1: EAD_LS(1); break; case 2: EAD_LS(2); break; case 4: EAD_LS(4); break; case 5: EAD_LS(5); break; case 6: EAD_LS(6); break; default: EAD_LS(7); break; }
+        }
 #undef EAD_LS
         if (ok) return;
         // the register-ring kernel where LDS does not allow it (eight row blocks a workgroup)

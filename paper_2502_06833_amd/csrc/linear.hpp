@@ -55,6 +55,7 @@ struct LinArgs {
     int sweeps;             // without split K: > 1 = one workgroup per (row-block group, sweep of 128 rows; k_linear_mfma_gemm: 256); k_linear_mfma_tile: sweeps of a band
     int tile_sweeps;        // k_linear_mfma_tile, k_sk_merge<EPI, 0>: sweeps of 256 rows this launch takes, from token block tb_base on
     int KS;
+    int once;               // k_linear_mfma_ls, k_lm_ls: weight tiles are requested non-temporally (tiles_once, lm_once)
     float *sk_part;         // [KS][groups][R][NT][256] partial sums
     int *sk_tickets;        // [groups] arrival counters, zero between launches
 };
@@ -827,9 +828,8 @@ constexpr size_t kLsLdsBytes = (size_t)kLsDepth * 8 * 1024;
 constexpr int ls_slot_tiles(int rg) { return rg <= 4 ? 4 : 8; }
 constexpr int ls_depth(int rg) { return kLsDepth * 8 / ls_slot_tiles(rg); }
 
-// ONCE: one sweep, no other workgroup reads this one's weight tiles.  (Compiled in: a fetching wave that chose at every request made passes of several
-// sweeps 7-20 % slower.)
-template <int EPI, bool SK, int NW, int RG, bool ONCE = true>
+// a.once picks one of two fetching loops.  (A fetching wave that chose at every request made passes of several sweeps 7-20 % slower.)
+template <int EPI, bool SK, int NW, int RG>
 __global__ __launch_bounds__((NW + kLsProducers) * 64) void k_linear_mfma_ls(LinArgs<bf16_t> a) {
     static_assert(RG >= 3 && RG <= 8 && NW >= 1 && NW <= 8, "two producer waves share a step's four or eight tile slots");
     constexpr int SLOT = ls_slot_tiles(RG), PL = SLOT / 2, DEPTH = ls_depth(RG);      // tiles per slot, loads per producer wave and step, k steps in the ring
@@ -863,22 +863,25 @@ __global__ __launch_bounds__((NW + kLsProducers) * 64) void k_linear_mfma_ls(Lin
 #pragma unroll
         for (int q = 0; q < PL; ++q)
             wp[q] = a.W + tile_offset(min(g * RG + min(p + 2 * q, RG - 1), NB - 1), kbase, KCfull) + lane * 8;
-        auto issue = [&](int j) __attribute__((always_inline)) {      // step j (past the end: the last step again, never read)
-            const size_t off = (size_t)kstep(j) * 512;
-            bf16_t (*slot)[512] = s_w[j % DEPTH];
+        auto fetch = [&](auto once) __attribute__((always_inline)) {
+            auto issue = [&](int j) __attribute__((always_inline)) {      // step j (past the end: the last step again, never read)
+                const size_t off = (size_t)kstep(j) * 512;
+                bf16_t (*slot)[512] = s_w[j % DEPTH];
 #pragma unroll
-            for (int q = 0; q < PL; ++q) request_tile_at<ONCE>(wp[q] + off, &slot[p + 2 * q][0]);
+                for (int q = 0; q < PL; ++q) request_tile_at<decltype(once)::value>(wp[q] + off, &slot[p + 2 * q][0]);
+            };
+            for (int j = 0; j < DEPTH - 1; ++j) issue(j);
+            asm volatile("s_waitcnt vmcnt(%0)" ::"n"(PL * (DEPTH - 2)) : "memory");      // step 0 has landed
+            __builtin_amdgcn_s_barrier();                 // the bare barrier: this wave has nothing else to wait for
+            for (int i = 0; i < KC; ++i) {
+                // the multiplying waves read a step's tiles one step ahead of using them: step i + 1 has to
+                // have landed; steps i + 2 .. i + DEPTH - 2 may still be on their way
+                asm volatile("s_waitcnt vmcnt(%0)" ::"n"(PL * (DEPTH - 3)) : "memory");
+                __builtin_amdgcn_s_barrier();
+                issue(i + DEPTH - 1);                  // into the slot of step i - 1, which every wave has read by now
+            }
         };
-        for (int j = 0; j < DEPTH - 1; ++j) issue(j);
-        asm volatile("s_waitcnt vmcnt(%0)" ::"n"(PL * (DEPTH - 2)) : "memory");      // step 0 has landed
-        __builtin_amdgcn_s_barrier();                 // the bare barrier: this wave has nothing else to wait for
-        for (int i = 0; i < KC; ++i) {
-            // the multiplying waves read a step's tiles one step ahead of using them: step i + 1 has to
-            // have landed; steps i + 2 .. i + DEPTH - 2 may still be on their way
-            asm volatile("s_waitcnt vmcnt(%0)" ::"n"(PL * (DEPTH - 3)) : "memory");
-            __builtin_amdgcn_s_barrier();
-            issue(i + DEPTH - 1);                  // into the slot of step i - 1, which every wave has read by now
-        }
+        if (a.once) fetch(std::true_type{}); else fetch(std::false_type{});
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");    // nothing may land in LDS after the workgroup has gone
         return;
     }
@@ -1032,22 +1035,25 @@ __global__ __launch_bounds__((NW + kLsProducers) * 64) void k_lm_ls(LinArgs<bf16
             for (int q = 0; q < 4; ++q) wp[q] = a.W + tile_offset(min(rb0 + g * kLmRows + p + 2 * q, rb1 - 1), 0, KC) + lane * 8;
         };
         point();
-        auto issue = [&]() __attribute__((always_inline)) {      // past the range: its last step again, never read
-            const size_t off = (size_t)k * 512;
+        auto fetch = [&](auto once) __attribute__((always_inline)) {
+            auto issue = [&]() __attribute__((always_inline)) {      // past the range: its last step again, never read
+                const size_t off = (size_t)k * 512;
 #pragma unroll
-            for (int q = 0; q < 4; ++q) request_tile_at<true>(wp[q] + off, &s_w[slot][p + 2 * q][0]);
-            slot = slot + 1 == kLsDepth ? 0 : slot + 1;
-            if (k + 1 < KC) ++k;
-            else if (g + 1 < groups) { k = 0; ++g; point(); }
-        };
-        for (int j = 0; j < kLsDepth - 1; ++j) issue();
-        asm volatile("s_waitcnt vmcnt(%0)" ::"n"(4 * (kLsDepth - 2)) : "memory");      // step 0 has landed
-        __builtin_amdgcn_s_barrier();
-        for (int i = 0; i < total; ++i) {
-            asm volatile("s_waitcnt vmcnt(%0)" ::"n"(4 * (kLsDepth - 3)) : "memory");  // step i + 1 has landed
+                for (int q = 0; q < 4; ++q) request_tile_at<decltype(once)::value>(wp[q] + off, &s_w[slot][p + 2 * q][0]);
+                slot = slot + 1 == kLsDepth ? 0 : slot + 1;
+                if (k + 1 < KC) ++k;
+                else if (g + 1 < groups) { k = 0; ++g; point(); }
+            };
+            for (int j = 0; j < kLsDepth - 1; ++j) issue();
+            asm volatile("s_waitcnt vmcnt(%0)" ::"n"(4 * (kLsDepth - 2)) : "memory");      // step 0 has landed
             __builtin_amdgcn_s_barrier();
-            issue();                                   // into the slot of step i - 1, which every wave has read by now
-        }
+            for (int i = 0; i < total; ++i) {
+                asm volatile("s_waitcnt vmcnt(%0)" ::"n"(4 * (kLsDepth - 3)) : "memory");  // step i + 1 has landed
+                __builtin_amdgcn_s_barrier();
+                issue();                               // into the slot of step i - 1, which every wave has read by now
+            }
+        };
+        if (a.once) fetch(std::true_type{}); else fetch(std::false_type{});
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");    // nothing may land in LDS after the workgroup has gone
         return;
     }

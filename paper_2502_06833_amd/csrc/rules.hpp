@@ -233,6 +233,15 @@ inline bool gate_up_streamed(int NB, int KC, int TB, int n_cu) {
     return TB == 1 ? KC >= 128 && NB > 4 * n_cu : TB == 2 && KC >= 96 && NB > 2 * n_cu;
 }
 
+// Whether k_linear_mfma_ls requests a matrix of `tiles` k tiles (KB) non-temporally, rg row blocks to a workgroup, in slabs of K or not.  A long stream from memory
+// gains by it (us with plain requests / this way: 27648 x 5120 at 64 rows 50.3 / 48.0, 5120 x 13824 in slabs 31.7 / 26.9), a shorter one is not bound by memory and
+// loses (16384 x 896 at 128 rows 13.1 / 15.0, 4096 x 2048 11.2 / 13.2, 12288 x 1536 in slabs 13.3 / 14.8), and so does a group of five row blocks, whose
+// slot repeats three tiles that the vector cache no longer holds (19456 x 5120 37.6 / 42.8), up to some size one of six (20672 x 3328 23.7 / 27.6).  236 gate/up
+// shapes at 16 to 128 rows, 22 of slabs.
+inline bool tiles_once(long tiles, int rg, bool slabs) {
+    return slabs ? tiles >= 80000 : rg != 5 && tiles >= (rg == 6 ? 140000 : 96000);
+}
+
 // LM heads of one and two token blocks that stay with k_linear_mfma's register rings (us with them / through k_lm_ls).  A workgroup of k_lm_ls walks its NB / n_cu
 // row blocks eight at a time, and slots past their end cost what the others do: rings where that leaves half a group and more empty on every unit
 // (8192 x 4096 at 3 rows 15.6 / 31.5, 16384 x 5120 30.3 / 38.7, 40000 x 4096 53 / 73, 100000 x 4096 131 / 151, at 24 rows 40000 x 5120 77 / 94;
@@ -246,6 +255,16 @@ inline bool lm_by_rings(int NB, int KC, int TB, int n_cu) {
     const bool whole = KC % 16 == 0;
     if (TB == 1 && whole && KC > 64 && KC < 128) return true;
     return 2 * empty >= (TB == 1 ? 7 : 8) * n_cu && (whole || 8 * NB <= 5 * walked || (TB == 1 && KC > 64 && empty >= 6 * n_cu));
+}
+
+// Whether k_lm_ls requests its tiles non-temporally.  Where its groups of eight row blocks are mostly full it does: the kernel alone then is faster from some 300 MB on (us with
+// plain requests / this way: 128256 x 4096 at 32 rows 178 / 159, 32000 x 4096 at 64 rows 51 / 45) and up to 10 % slower below (32000 x 2048 at 3 rows 25.1 / 27.6), but the head
+// leaves the caches to the layers' weights, K and V, which gains more (us a step of small models, LM head of 32000 x 1536, 48, 64, 100 and 128 rows: 304 310 361 377 / 288 297 342 363;
+// 32000 x 768: 454 486 608 643 / 440 479 603 640).  Where slots past the row blocks' end repeat the last one, which the vector cache then no longer holds, only
+// long streams do (8192 x 4096 at 64 rows 28 / 31, 16384 x 5120 34 / 43; 40000 x 4096 at 3 rows 77 / 73).
+inline bool lm_once(int NB, int KC, int n_cu) {
+    const long walked = (long)((NB + 8 * n_cu - 1) / (8 * n_cu)) * 8 * n_cu;
+    return 4 * NB >= 3 * walked || (long)NB * KC >= (KC >= 96 ? 190000 : 290000);
 }
 
 // How 256 x 256 tiles take a pass: NG groups of 16 row blocks x SG sweeps of 256 tokens x KC k tiles.  The first `whole` sweeps in tiles of full depth, the

@@ -95,6 +95,8 @@ int host_narrow_plan(int NB, int KC, int TB, int split, long floats, int groups)
 int host_gate_up_by_one(int NB) { return gate_up_by_one(NB, 256); }
 int host_gate_up_streamed(int NB, int KC, int TB) { return gate_up_streamed(NB, KC, TB, 256); }
 int host_lm_by_rings(int NB, int KC, int TB) { return lm_by_rings(NB, KC, TB, 256); }
+int host_lm_once(int NB, int KC) { return lm_once(NB, KC, 256); }
+int host_tiles_once(int NB, int KC, int rg, int slabs) { return tiles_once((long)NB * KC, rg, slabs != 0); }
 int host_gate_up_by_four(int NB, int KC) { return gate_up_by_four(NB, KC, 256); }
 
 // the tile of workgroup `id` as g * 1000000 + sweep * 1000 + ks; -1: none

@@ -1,5 +1,5 @@
 """GPU: gate/up matrices and LM heads of passes of one and two token blocks through the fetching-wave kernels and the register rings, on both sides of their rules
-(gate_up_streamed and lm_by_rings in rules.hpp): 1028 row blocks (a last group of three in five) x 128 and 129 k tiles from three rows on, 1024 x 128 and
+(gate_up_streamed, lm_by_rings, tiles_once and lm_once in rules.hpp): 1028 row blocks (a last group of three in five) x 128 and 129 k tiles from three rows on, 1024 x 128 and
 544 x 96 from 17, 128 x 96 that stay with the other kernel; 1540 row blocks x 29, two waves to four of them from 17 to 32; LM heads of 1000 to 2000 row blocks."""
 import numpy as np
 import pytest
@@ -23,7 +23,7 @@ def test_gate_up_of_one_and_two_token_blocks(d, ffn):
 
 @pytest.mark.parametrize("vocab,d", [(24000, 4096), (32000, 1280), (23984, 1280), (16400, 2336), (16368, 2336), (16384, 2560)])
 def test_lm_heads_of_one_and_two_token_blocks(vocab, d):
-    """1500 row blocks x 128, 2000 and 1499 x 40 through k_lm_ls; 1025 x 73 through the rings up to 16 rows, 1023 x 73 (whose last workgroup has three row
+    """1500 row blocks x 128 and 2000 x 40 non-temporally, 1499 x 40 plainly through k_lm_ls; 1025 x 73 through the rings up to 16 rows, 1023 x 73 (whose last workgroup has three row
     blocks of four) and 1024 x 80 up to 32."""
     _check_scores(FewHeads(f"lm-{vocab}", 1, d, 4, 2, 256, vocab, 1e-5, 1e4))
 

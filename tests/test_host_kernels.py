@@ -360,14 +360,20 @@ def test_one_row_does_not_stream_where_the_ffn_is_short(host, d, F, KV, layers, 
     assert host.host_stream_pays_ffn(d, F, KV, layers, keys) == pays
 
 
-@pytest.mark.parametrize("N,K,rows,rings", [
-    (8192, 4096, 3, 1), (8192, 2304, 16, 1), (8192, 4096, 32, 1), (8192, 2048, 32, 0), (8192, 896, 3, 0), (16384, 5120, 24, 1), (16384, 5120, 64, 0),
-    (24000, 1024, 64, 0), (24000, 4096, 12, 0), (32000, 768, 3, 0), (32000, 4096, 16, 0), (40000, 2048, 3, 1), (40000, 5120, 24, 1), (50256, 4096, 24, 0),
-    (65536, 2048, 24, 0), (81920, 2304, 12, 0), (100000, 4096, 3, 1), (100000, 3328, 12, 1), (128256, 2048, 3, 0), (128256, 2304, 3, 0), (128256, 3072, 3, 1),
-    (128256, 3072, 32, 0), (128256, 4096, 16, 0), (151936, 896, 3, 0), (151936, 1536, 3, 0), (151936, 5120, 32, 0), (151936, 5120, 64, 0)])
-def test_lm_heads_take_the_kernel_measured_faster(host, N, K, rows, rings):
+@pytest.mark.parametrize("N,K,rows,rings,once", [
+    (8192, 4096, 3, 1, 0), (8192, 2304, 16, 1, 0), (8192, 4096, 32, 1, 0), (8192, 2048, 32, 0, 0), (8192, 896, 3, 0, 0), (16384, 5120, 24, 1, 0), (16384, 5120, 64, 0, 0),
+    (24000, 1024, 64, 0, 0), (24000, 4096, 12, 0, 1), (32000, 768, 3, 0, 1), (32000, 4096, 16, 0, 1), (40000, 2048, 3, 1, 0), (40000, 5120, 24, 1, 1), (50256, 4096, 24, 0, 1),
+    (65536, 2048, 24, 0, 1), (81920, 2304, 12, 0, 1), (100000, 4096, 3, 1, 1), (100000, 3328, 12, 1, 1), (128256, 2048, 3, 0, 1), (128256, 2304, 3, 0, 1), (128256, 3072, 3, 1, 1),
+    (128256, 3072, 32, 0, 1), (128256, 4096, 16, 0, 1), (151936, 896, 3, 0, 1), (151936, 1536, 3, 0, 1), (151936, 5120, 32, 0, 1), (151936, 5120, 64, 0, 1)])
+def test_lm_heads_take_the_kernel_and_the_requests_measured_faster(host, N, K, rows, rings, once):
     TB = (rows + 15) // 16
-    assert host.host_lm_by_rings(N // 16, K // 32, TB) == rings
+    assert host.host_lm_by_rings(N // 16, K // 32, TB) == rings and host.host_lm_once(N // 16, K // 32) == once
+
+
+@pytest.mark.parametrize("N,K,rg,slabs,once", [(27648, 5120, 7, 0, 1), (28672, 4096, 7, 0, 1), (16384, 896, 4, 0, 0), (4096, 2048, 4, 0, 0), (19456, 5120, 5, 0, 0), (20672, 3328, 6, 0, 0),
+                                               (24576, 5120, 6, 0, 1), (5120, 13824, 8, 1, 1), (12288, 1536, 8, 1, 0), (7168, 5120, 8, 1, 0)])
+def test_tiles_are_requested_as_measured_faster(host, N, K, rg, slabs, once):
+    assert host.host_tiles_once(N // 16, K // 32, rg, slabs) == once
 
 
 @pytest.mark.parametrize("N,K,rows,streamed", [(8192, 3072, 32, 0), (8208, 3072, 32, 1), (2048, 4096, 24, 0), (9728, 5120, 24, 1), (28672, 4096, 3, 1), (16384, 4096, 3, 0), (17920, 1536, 24, 0)])
